@@ -51,8 +51,7 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
         arow[i] = B.X.off + pl * B.X.poff + (m - pl * B.X.split);
     }
     const op_t* pb = static_cast<const op_t*>(P_.Rops) + B.Roff * P::PER +
-                     (((int64_t)(tl.n0 / kPanel) * nch) * 4 + g) * (kPanel * lane_elems<P>()) +
-                     r * lane_elems<P>();
+                     (int64_t)(tl.n0 / kPanel) * nch * chunk_elems<P>() + lane_off<P>(g, r);
     const int64_t panel = (int64_t)nch * chunk_elems<P>();
     const int64_t ldx = B.X.ld;
     acc_t acc[MI][NJ];
@@ -62,11 +61,10 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
         for (int nj = 0; nj < NJ; ++nj) zero<P>(acc[mi][nj]);
     frag_t a[2][MI], b[2][NJ];
     auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
-        const int kb = c * P::CK + P::KPL * g;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             double v[P::KPL];
-            load_clamped<P>(X, arow[i], kb, K, ldx, v);
+            load_clamped<P>(X, arow[i], c * P::CK, g, K, ldx, v);
             fa[i] = P::from(v);
         }
 #pragma unroll
@@ -76,7 +74,7 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(fa[mi], fb[nj], acc[mi][nj]);
+            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma_t(fa[mi], fb[nj], acc[mi][nj]);
     };
     // two register buffers, the next chunk always in flight (as in the stage-2 loop)
     load(0, a[0], b[0]);
@@ -90,24 +88,28 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
         mma(a[1], b[1]);
     }
     if (c < nch) mma(a[0], b[0]);
+    // the accumulators hold the transposed tile (mma_t), so that the 16 lanes of a group store 16
+    // consecutive rows of a column of T: whole 128-byte lines (FP64).  With the rows in the lane's
+    // own values, a store touched 16 columns for 32 bytes each, and the write-back of the 41 MB
+    // intermediate held up the loads of the tiles that follow: stage 1 of the 2x16 ladder at
+    // m = 1000 took 34.4 us, now 29.0 (2x32 at m = 2000: 186 -> 164; FP32 at m = 1000:
+    // 32.5 -> 25.3)
     ws_t* __restrict__ T = static_cast<ws_t*>(P_.T);
     const View tv = B.T;
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < MI; ++mi) {
+        const int m = tl.m0 + 16 * mi + r;
+        if (m >= B.M) continue;
+        const int pl = m >= tv.split;
+        ws_t* __restrict__ Tm = T + tv.off + pl * tv.poff + (m - pl * tv.split);
 #pragma unroll
-        for (int nj = 0; nj < NJ; ++nj) {
-            const int n = tl.n0 + 16 * nj + r;
-            if (n >= B.N) continue;
+        for (int nj = 0; nj < NJ; ++nj)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int m = tl.m0 + 16 * mi + P::row(g, v);
-                if (m < B.M) {
-                    const int pl = m >= tv.split;
-                    T[tv.off + pl * tv.poff + (int64_t)n * tv.ld + (m - pl * tv.split)] =
-                        (ws_t)acc[mi][nj][v];
-                }
+                const int n = tl.n0 + 16 * nj + P::row(g, v);
+                if (n < B.N) Tm[(int64_t)n * tv.ld] = (ws_t)acc[mi][nj][v];
             }
-        }
+    }
 }
 
 template <class P, int NJ>
@@ -185,7 +187,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
     for (int i = 0; i < MI; ++i) {
         const int pnl = tl.m0 / kPanel + i;
         pa[i] = static_cast<const op_t*>(P_.Lops) + B.Aoff * P::PER +
-                (((int64_t)pnl * B.nch) * 4 + g) * (kPanel * lane_elems<P>()) + r * lane_elems<P>();
+                (int64_t)pnl * B.nch * chunk_elems<P>() + lane_off<P>(g, r);
     }
     int pl[NJ], col[NJ];
 #pragma unroll
@@ -211,11 +213,10 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-            const int kb = c * P::CK + P::KPL * g;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 double v[P::KPL];
-                load_clamped<P>(P_.x, bcol[j], kb, s0.K, 1, v);
+                load_clamped<P>(P_.x, bcol[j], c * P::CK, g, s0.K, 1, v);
                 fb[j] = P::from(v);
             }
         };
@@ -242,11 +243,11 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
             const int64_t* e = ctab[c - nch0];
-            const int64_t kb = (int64_t)c * P::CK + P::KPL * g;
+            const int64_t kb = (int64_t)c * P::CK;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 double v[P::KPL];
-                load_run<P>(Tws, e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, v);
+                load_run<P>(Tws, e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, g, v);
                 fb[j] = P::from(v);
             }
         };
@@ -267,11 +268,10 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
                 const int64_t ga = (int64_t)(sg.ch0 + c) * chunk_elems<P>();
 #pragma unroll
                 for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-                const int kb = c * P::CK + P::KPL * g;
-#pragma unroll
+    #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
-                    load_run<P>(Tws, bcol[j] + kb, v);
+                    load_run<P>(Tws, bcol[j] + c * P::CK, g, v);
                     fb[j] = P::from(v);
                 }
             };
@@ -397,7 +397,7 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
     for (int i = 0; i < MI; ++i) {
         const int pnl = tl.m0 / kPanel + i;
         pa[i] = static_cast<const op_t*>(PP[0].Lops) + B.Aoff * P::PER +
-                (((int64_t)pnl * B.nch) * 4 + g) * (kPanel * lane_elems<P>()) + r * lane_elems<P>();
+                (int64_t)pnl * B.nch * chunk_elems<P>() + lane_off<P>(g, r);
     }
     int pl[NJ], col[NJ];
 #pragma unroll
@@ -425,13 +425,12 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-            const int kb = c * P::CK + P::KPL * g;
 #pragma unroll
             for (int q = 0; q < NR; ++q)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
-                    load_clamped<P>(PP[q].x, bcol[j], kb, s0.K, 1, v);
+                    load_clamped<P>(PP[q].x, bcol[j], c * P::CK, g, s0.K, 1, v);
                     fb[q][j] = P::from(v);
                 }
         };
@@ -455,14 +454,14 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
             const int64_t* e = ctab[c - nch0];
-            const int64_t kb = (int64_t)c * P::CK + P::KPL * g;
+            const int64_t kb = (int64_t)c * P::CK;
 #pragma unroll
             for (int q = 0; q < NR; ++q)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
                     load_run<P>(static_cast<const ws_t*>(PP[q].T),
-                                e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, v);
+                                e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, g, v);
                     fb[q][j] = P::from(v);
                 }
         };
@@ -481,13 +480,12 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
                 const int64_t ga = (int64_t)(sg.ch0 + c) * chunk_elems<P>();
 #pragma unroll
                 for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-                const int kb = c * P::CK + P::KPL * g;
-#pragma unroll
+    #pragma unroll
                 for (int q = 0; q < NR; ++q)
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) {
                         double v[P::KPL];
-                        load_run<P>(static_cast<const ws_t*>(PP[q].T), bcol[j] + kb, v);
+                        load_run<P>(static_cast<const ws_t*>(PP[q].T), bcol[j] + c * P::CK, g, v);
                         fb[q][j] = P::from(v);
                     }
             };

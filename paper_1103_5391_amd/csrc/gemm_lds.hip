@@ -118,16 +118,15 @@ __global__ __launch_bounds__(256, 3) void stage1_lds(const S1Block* __restrict__
     const int64_t ldx = B.X.ld;
     const double* __restrict__ X = P_.x;
     const op_t* __restrict__ pb = static_cast<const op_t*>(P_.Rops) + B.Roff * P::PER +
-                                  (((int64_t)(it.n0 / kPanel + wave) * nch) * 4 + g) *
-                                      (kPanel * lane_elems<P>()) +
-                                  r * lane_elems<P>();
+                                  (int64_t)(it.n0 / kPanel + wave) * nch * chunk_elems<P>() +
+                                  lane_off<P>(g, r);
     // loads only request data (raw values in registers); conversion to the MFMA input type
     // happens when the group is written to LDS, after the products of the previous group
     constexpr int D = group_depth<P>();
     double xa[D][P::KPL];
     frag_t rb[D];
     auto load = [&](int c, int d) {
-        if (a_on) load_clamped<P>(X, arow, c * P::CK + P::KPL * g, K, ldx, xa[d]);
+        if (a_on) load_clamped<P>(X, arow, c * P::CK, g, K, ldx, xa[d]);
         if (b_on) rb[d] = P::load_op(pb + (int64_t)c * chunk_elems<P>());
     };
     auto store = [&](int d) {
@@ -195,9 +194,8 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     // (t % 4, t / 4 % 16) of column panel t / 64
     const bool a_on = wave < mval;
     const op_t* __restrict__ pa = static_cast<const op_t*>(P_.Lops) + B.Aoff * P::PER +
-                                  (((int64_t)(it.m0 / kPanel + wave) * B.nch) * 4 + g) *
-                                      (kPanel * lane_elems<P>()) +
-                                  r * lane_elems<P>();
+                                  (int64_t)(it.m0 / kPanel + wave) * B.nch * chunk_elems<P>() +
+                                  lane_off<P>(g, r);
     const int bn = tid >> 2, bq = tid & 3;
     const int ncol = min(it.n0 + bn, B.N - 1);
     const int bpl = ncol >= split;
@@ -232,7 +230,7 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     const int64_t xbase = s0.B.off + bpl * s0.B.poff + (int64_t)bcol * s0.B.ld;
     auto load_x = [&](int c, int d) {
         load_a(c, d);
-        load_clamped<P>(P_.x, xbase, c * P::CK + P::KPL * bq, s0.K, 1, xb[d]);
+        load_clamped<P>(P_.x, xbase, c * P::CK, bq, s0.K, 1, xb[d]);
     };
     auto store_x = [&](int d) {
         if (a_on) sm.A[d][wave][lane] = ra[d];
@@ -241,9 +239,9 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     auto load_t = [&](int c, int d) {
         load_a(c, d);
         const int64_t* e = ctab[c - t_beg];
-        const int64_t base = e[0] + bpl * e[1] + (int64_t)bcol * e[2] + c * P::CK + P::KPL * bq;
+        const int64_t base = e[0] + bpl * e[1] + (int64_t)bcol * e[2] + c * P::CK;
 #pragma unroll
-        for (int t = 0; t < P::KPL; ++t) tb[d][t] = ldg(Tws, base + t);
+        for (int t = 0; t < P::KPL; ++t) tb[d][t] = ldg(Tws, base + koff<P>(bq, t));
     };
     auto store_t = [&](int d) {
         if (a_on) sm.A[d][wave][lane] = ra[d];

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kXT, 2) void stage1x(const S1Block* __restrict__ bl
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // column panel of the wave
     const int K = B.K, nch = (K + PF64::CK - 1) / PF64::CK;
-    // X loader: row lrow of the tile, k = 4 kg + j of each chunk -> lane (kg, lrow mod 16) of
+    // X loader: row lrow of the tile, k = koff(kg, j) of each chunk -> lane (kg, lrow mod 16) of
     // row panel lrow / 16
     const int lrow = tid & 63, kg = tid >> 6;
     int64_t arow;
@@ -208,21 +208,19 @@ __global__ __launch_bounds__(kXT, 2) void stage1x(const S1Block* __restrict__ bl
     const double* __restrict__ X = P_.x;
     const int64_t ldx = B.X.ld;
     const int apanel = lrow >> 4, alane = kg * 16 + (lrow & 15);
-    // R loader: lane `lane` of column panel tid / 64 (packed: [panel][chunk][64 lanes][4])
+    // R loader: lane `lane` of column panel tid / 64 (packed: [panel][chunk][half][64 lanes][2])
     const int rpanel = tid >> 6, rpos = bpos(lane);
     const double* rp = static_cast<const double*>(P_.Rops) + B.Roff +
-                       ((int64_t)(tl.n0 / kPanel + rpanel) * nch * 64 + lane) * 4;
+                       (int64_t)(tl.n0 / kPanel + rpanel) * nch * 256 + lane * 2;
     struct Regs {
         double xa[4];
         u4 rlo, rhi;
     };
     auto load = [&](int c, Regs& r) {
-        const int kb = c * PF64::CK + 4 * kg;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r.xa[j] = ldg(X, arow + (int64_t)min(kb + j, K - 1) * ldx);
+        load_clamped<PF64>(X, arow, c * PF64::CK, kg, K, ldx, r.xa);
         const double* q = rp + (int64_t)c * 256;
         r.rlo = ldgv<u4>(q);
-        r.rhi = ldgv<u4>(q + 2);
+        r.rhi = ldgv<u4>(q + 128);
     };
     auto store = [&](int buf, const Regs& r) {
         sm[buf].A[apanel][0][alane] = pack2(r.xa[0], r.xa[1]);
@@ -306,14 +304,14 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
     // A loader: lane `lane` of row panel tid / 64 (packed left factors, 64-row tiles)
     const int apanel = tid >> 6;
     const double* ap = static_cast<const double*>(P_.Lops) + B.Aoff +
-                       ((int64_t)(it.m0 / kPanel + apanel) * B.nch * 64 + lane) * 4;
-    // B loader: column j of the tile, k = 2 q, 2 q + 1 of the chunk -> half q mod 2 of lane
-    // (q / 2, j mod 16) of column panel j / 16 (eight consecutive lanes read one column's 128
+                       (int64_t)(it.m0 / kPanel + apanel) * B.nch * 256 + lane * 2;
+    // B loader: column j of the tile, k = 2 q, 2 q + 1 of the chunk -> half q / 4 of lane
+    // (q mod 4, j mod 16) of column panel j / 16 (eight consecutive lanes read one column's 128
     // bytes)
     const int jc = tid >> 3, q = tid & 7, kq = 2 * q;
     const int n = min(it.n0 + jc, B.N - 1);    // columns beyond N: any valid column, not stored
     const int pl = n >= split, col = n - pl * split;
-    const int bpanel = jc >> 4, bslot = (q & 1) * kBHalf + bpos((q >> 1) * 16 + (jc & 15));
+    const int bpanel = jc >> 4, bslot = (q >> 2) * kBHalf + bpos((q & 3) * 16 + (jc & 15));
     const double* __restrict__ xin = P_.x;
     const double* __restrict__ tws = static_cast<const double*>(P_.T);
     const int K0 = B.M;   // segment 0 (the diagonal H_S term) reads the block from x: K0 rows
@@ -324,7 +322,7 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
     auto load = [&](int c, Regs& r) {
         const double* qa = ap + (int64_t)c * 256;
         r.alo = ldgv<u4>(qa);
-        r.ahi = ldgv<u4>(qa + 2);
+        r.ahi = ldgv<u4>(qa + 128);
         const int t = c - it.kc0;
         const int k = c * PF64::CK + kq;
         const int64_t base = s_off[t] + pl * s_poff[t] + (int64_t)col * s_ld[t];

@@ -45,7 +45,9 @@ struct View {
 // Operator factors are packed once per arithmetic in the order the MFMA lanes consume them:
 // 16-row (or 16-column) panels, K chunks of depth CK (16 for FP64/FP32, 32 for BF16), and
 // inside a chunk [g][r][t] with k = KPL g + t, KPL = CK / 4, so lane (g, r) reads its KPL
-// values of one chunk as one contiguous piece (BF16: KPL hi values then KPL lo values).
+// values of one chunk as one contiguous piece (BF16: KPL hi values then KPL lo values).  FP64:
+// [half][g][r][2] with k = 8 half + 2 g + t, so that each of a chunk's two 16-byte loads per lane
+// reads one contiguous kilobyte.
 // Rows (columns) are zero-padded to the tile and K to whole chunks, so operator loads never
 // need bounds checks and padded products vanish.
 constexpr int kPanel = 16;                        // rows (columns) per packed panel

@@ -2,16 +2,21 @@
 // packed-operator loads, conversion of FP64 data values to the MFMA input type, and the
 // multiply-accumulate of one K chunk.
 //
-// Inside one MFMA the K index each lane group supplies is free as long as A and B agree, so
-// lane group g takes the KPL consecutive indices k = KPL g + t of a chunk.  The operator
-// factors are packed in exactly that order (see internal.hpp), so lane (g, r) reads its part
-// of a chunk as one contiguous piece.
+// Inside one MFMA the K index each lane group supplies is free as long as A and B agree.  Lane
+// group g takes the KPL consecutive indices k = KPL g + t of a chunk, and the operator factors
+// are packed in exactly that order (see internal.hpp), so lane (g, r) reads its part of a chunk
+// as one contiguous piece.  FP64, whose four values are two 16-byte loads, takes the pairs
+// k = 2 g and k = 8 + 2 g instead (koff): the four lane groups of one load then cover 64
+// contiguous bytes of a column of the workspace, and a whole packed half chunk is one contiguous
+// kilobyte.  With four consecutive indices each load touched every line of both halves for half
+// of its bytes, and the vector L1 spent twice the cycles on the same operands.
 #pragma once
 
 #include "internal.hpp"
 
 namespace dmrg {
 
+typedef double d2 __attribute__((ext_vector_type(2)));
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
@@ -27,7 +32,9 @@ __device__ __forceinline__ V ldgv(const void* p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// arithmetic traits
+// arithmetic traits.  mma: c += A B with the result's rows in the lane's four values (row(g, v))
+// and its columns across the lanes; mma_t: the transposed result, c^T += (A B)^T, the same
+// products in the same order, with the rows of A B across the lanes.
 // ---------------------------------------------------------------------------------------
 struct PF64 {
     static constexpr int CK = 16, KPL = 4, PER = 1;   // PER: packed pieces per value
@@ -36,12 +43,17 @@ struct PF64 {
     using acc_t = d4;
     using frag_t = d4;            // one lane's operand values of one chunk
     __device__ static frag_t from(const double (&v)[KPL]) { return (d4){v[0], v[1], v[2], v[3]}; }
-    __device__ static frag_t load_op(const op_t* p) { return ldgv<d4>(p); }
+    static constexpr int KP = 2;  // consecutive K indices per lane group
+    __device__ static frag_t load_op(const op_t* p) {
+        const d2 lo = ldgv<d2>(p), hi = ldgv<d2>(p + kPanel * 4 * KP);
+        return (d4){lo[0], lo[1], hi[0], hi[1]};
+    }
     __device__ static acc_t mma(const frag_t& a, const frag_t& b, acc_t c) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[t], c, 0, 0, 0);
         return c;
     }
+    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) { return mma(b, a, c); }
     __device__ static int row(int g, int v) { return g + 4 * v; }   // result lane layout
 };
 
@@ -54,12 +66,14 @@ struct PF32 {
     __device__ static frag_t from(const double (&v)[KPL]) {
         return (f4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
     }
+    static constexpr int KP = KPL;
     __device__ static frag_t load_op(const op_t* p) { return ldgv<f4>(p); }
     __device__ static acc_t mma(const frag_t& a, const frag_t& b, acc_t c) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0);
         return c;
     }
+    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) { return mma(b, a, c); }
     __device__ static int row(int g, int v) { return 4 * g + v; }
 };
 
@@ -88,6 +102,7 @@ struct PSplit {
         }
         return f;
     }
+    static constexpr int KP = KPL;
     __device__ static frag_t load_op(const op_t* p) {
         frag_t f;
 #pragma unroll
@@ -100,6 +115,14 @@ struct PSplit {
 #pragma unroll
             for (int i = 0; i <= o; ++i)
                 c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[i], b.p[o - i], c, 0, 0, 0);
+        return c;
+    }
+    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) {
+#pragma unroll
+        for (int o = 0; o < NP; ++o)
+#pragma unroll
+            for (int i = 0; i <= o; ++i)
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.p[o - i], a.p[i], c, 0, 0, 0);
         return c;
     }
     __device__ static int row(int g, int v) { return 4 * g + v; }
@@ -123,18 +146,31 @@ __device__ __forceinline__ void zero(typename P::acc_t& a) {
     for (int v = 0; v < 4; ++v) a[v] = 0;
 }
 
-// KPL consecutive data values v[t] = src[base + t] (workspace, zero-padded chunks)
-template <class P, typename T>
-__device__ __forceinline__ void load_run(const T* src, int64_t base, double (&v)[P::KPL]) {
-#pragma unroll
-    for (int t = 0; t < P::KPL; ++t) v[t] = (double)ldg(src, base + t);
-}
-// KPL values src[base + min(k0 + t, K - 1) * stride] (input vector, clamped)
+// K index inside a chunk of value t of lane group g
 template <class P>
-__device__ __forceinline__ void load_clamped(const double* src, int64_t base, int k0, int K,
+__device__ __forceinline__ int koff(int g, int t) {
+    return t / P::KP * (4 * P::KP) + P::KP * g + t % P::KP;
+}
+// First element of lane (g, r) inside a packed panel chunk
+template <class P>
+__device__ __forceinline__ int lane_off(int g, int r) {
+    return (kPanel * g + r) * (P::KP * P::PER);
+}
+
+// The lane's data values v[t] = src[base + koff(g, t)] (workspace, zero-padded chunks; base at
+// the chunk's first index)
+template <class P, typename T>
+__device__ __forceinline__ void load_run(const T* src, int64_t base, int g, double (&v)[P::KPL]) {
+#pragma unroll
+    for (int t = 0; t < P::KPL; ++t) v[t] = (double)ldg(src, base + koff<P>(g, t));
+}
+// The lane's values src[base + min(k0 + koff(g, t), K - 1) * stride] (input vector, clamped)
+template <class P>
+__device__ __forceinline__ void load_clamped(const double* src, int64_t base, int k0, int g, int K,
                                              int64_t stride, double (&v)[P::KPL]) {
 #pragma unroll
-    for (int t = 0; t < P::KPL; ++t) v[t] = ldg(src, base + (int64_t)min(k0 + t, K - 1) * stride);
+    for (int t = 0; t < P::KPL; ++t)
+        v[t] = ldg(src, base + (int64_t)min(k0 + koff<P>(g, t), K - 1) * stride);
 }
 
 }  // namespace dmrg

@@ -111,8 +111,10 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 // Element offset of (i, k) inside a packed factor with chunk depth ck: i = row (stage 2) or
 // column (stage 1), k = K index from the start of the packed K range, nch = chunks per panel,
 // per = elements per K index (the bf16 pieces of a split value).  Layout
-// [panel][chunk][g][r][piece][t], KPL = ck / 4.
-int64_t packed_index(int i, int k, int nch, int ck, int per) {
+// [panel][chunk][g][r][piece][t], KPL = ck / 4; FP64 (pairs): [panel][chunk][half][g][r][t] with
+// two K indices per lane in each half chunk of 8.
+int64_t packed_index(int i, int k, int nch, int ck, int per, bool pairs) {
+    if (pairs) ck /= 2, nch *= 2;   // a chunk's halves follow each other like chunks
     const int kpl = ck / 4;
     const int pnl = i / kPanel, r = i % kPanel;
     const int ch = k / ck, g = (k % ck) / kpl, t = k % kpl;
@@ -728,7 +730,7 @@ struct Writer {
     int kind, ck, per;
     uint8_t* base;
     void put(int64_t blk_off, int i, int k, int nch, double v) const {
-        const int64_t o = blk_off * per + packed_index(i, k, nch, ck, per);
+        const int64_t o = blk_off * per + packed_index(i, k, nch, ck, per, kind == DMRG_FP64);
         if (kind == DMRG_FP64) {
             reinterpret_cast<double*>(base)[o] = v;
         } else if (kind == DMRG_FP32) {
