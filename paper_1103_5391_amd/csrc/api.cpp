@@ -1564,9 +1564,9 @@ int dmrg_matvec_noalloc(dmrg_handle h, const double* x, double* y, int32_t nvec)
     if (nvec == 0) return DMRG_OK;
     // the part of the intermediate the handle's block-product family uses (the K-split
     // family pads it further)
-    const int64_t tn = (h->lists.variant & DMRG_GEMM_K) && h->lists.nkt2 > 0
-                           ? h->plan.kf.T_size
-                           : h->plan.T_base;
+    const bool kfam = (h->lists.variant & DMRG_GEMM_K) && h->lists.nkt2 > 0;
+    const int64_t tn = kfam ? h->plan.kf.T_size : h->plan.T_need;
+    const int64_t tb = kfam ? tn : h->plan.T_base;
     if ((size_t)tn * sizeof(double) > kNoAllocScratchBytes)
         return fail(h, DMRG_EINVAL, "the stage-1 intermediate takes " +
                                         std::to_string((size_t)tn * sizeof(double)) +
@@ -1575,10 +1575,17 @@ int dmrg_matvec_noalloc(dmrg_handle h, const double* x, double* y, int32_t nvec)
                                         " bytes of the allocation-free scratch");
     double* T = nullptr;
     HIP_TRY(h, noalloc_scratch(&T));
-    // the array holds whatever the last call on this GPU left: the intermediate's padding rows
-    // meet zero factors and must be finite, so the used region starts from zeros (a fill
-    // kernel, so that a captured call clears it on every replay)
-    HIP_TRY(h, launch_zero(T, tn, h->stream));
+    if ((size_t)tb * sizeof(double) > kNoAllocScratchBytes) {
+        // its column panels round a problem near the limit above it: the handle's own array
+        T = h->ws[0].dT.as<double>();
+    } else if (kfam || h->precision >= DMRG_BF16X3 ||
+               (h->lists.variant & (DMRG_GEMM_STAGE1_LDS | DMRG_GEMM_X))) {
+        // the array holds whatever the last call on this GPU left: the intermediate's padding
+        // rows meet zero factors and must be finite, so the used region starts from zeros (a fill
+        // kernel, so that a captured call clears it on every replay).  The register-tiled stage 1
+        // with 16-deep chunks writes every row that is read.
+        HIP_TRY(h, launch_zero(T, tb, h->stream));
+    }
     const int64_t vs = 2 * h->plan.n;
     for (int v = 0; v < nvec; ++v) {
         ProbPtrs pp = make_ptrs(h, h->precision, x + v * vs, y + v * vs, nullptr);

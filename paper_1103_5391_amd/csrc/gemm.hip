@@ -19,19 +19,51 @@
 // waves; the four partial tiles are summed in LDS in a fixed order (deterministic, no atomics).
 //
 // The operator factors are packed in MFMA lane order (mfma.hpp) and zero-padded so no operator
-// load needs a bounds check.  The data operands are read in place: rows (stage 1) or columns
-// (stage 2) are contiguous in K.  The stage-1 workspace is zero-padded to whole chunks; for the
-// input vector out-of-range K indices are clamped to a valid element, whose product with the
-// padded zeros vanishes.
+// load needs a bounds check.  The input vector is read in place, out-of-range K indices clamped to
+// a valid element, whose product with the padded zeros vanishes.  Stage 1 writes its intermediate
+// in the order stage 2's lanes read it (S1Block::T, zero-padded to whole chunks): a load of 16
+// lanes is then 256 contiguous bytes.  From a column-major intermediate each lane of such a load
+// was in a line of its own, which costs the L1 64 cycles instead of 14, and its tiles stored
+// pieces of 32 bytes, whose write-back held up the loads of the tiles that follow.  Stage 1 / 2
+// of the 2x16 ladder at m = 1000: 34.4 / 36.4 us column-major, 29.8 / 32.2 in units; 2x32 at
+// m = 2000: 186 / 187 -> 161 / 166; BF16x3 at m = 1000: 21.8 / 26.7 -> 21.6 / 23.4.
 #include "mfma.hpp"
 
 namespace dmrg {
 
 // ---------------------------------------------------------------------------------------
-// stage 1: one 16 MI x 16 NJ tile (MI = 2, or 1 for a half-height tile; NJ = 4 wide, 2 narrow)
-// per single-wavefront work group
+// stage 1: one tile of 16 rows of both planes x 16 NJ columns (NJ = 4 wide, 2 narrow) per
+// single-wavefront work group
 // ---------------------------------------------------------------------------------------
-template <class P, int MI, int NJ>
+// One 16 x 16 fragment of T (rows row(g, v), column r of the lane) into a chunk of the workspace:
+// contiguous kilobytes of 16-byte units.  FP32 results hold a unit per lane already; in FP64 lane
+// groups 2 h and 2 h + 1 hold the two rows of a unit, and swapping rows of 16 lanes between the
+// accumulators of two row groups brings each pair to one lane.
+__device__ __forceinline__ void store_frag(double* t, const d4& c, int g, int r) {
+    // after the swap: lane groups 0..3 hold the rows of units 0, 2, 1, 3
+    const int unit = ((g & 1) << 1) | (g >> 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        union {
+            double d[2];
+            unsigned u[4];
+        } p;
+        p.d[0] = c[2 * h];
+        p.d[1] = c[2 * h + 1];
+        const auto lo = __builtin_amdgcn_permlane16_swap(p.u[0], p.u[2], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(p.u[1], p.u[3], false, false);
+        p.u[0] = lo[0];
+        p.u[2] = lo[1];
+        p.u[1] = hi[0];
+        p.u[3] = hi[1];
+        stgv(t + 128 * h + 32 * unit + 2 * r, (d2){p.d[0], p.d[1]});
+    }
+}
+__device__ __forceinline__ void store_frag(float* t, const f4& c, int g, int r) {
+    stgv(t + 64 * g + 4 * r, c);
+}
+
+template <class P, int NJ>
 __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, const ProbPtrs& P_) {
     using op_t = typename P::op_t;
     using ws_t = typename P::ws_t;
@@ -43,26 +75,23 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
     const int K = B.K;
     const int nch = (K + P::CK - 1) / P::CK;
 
-    int64_t arow[MI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        const int m = min(tl.m0 + 16 * i + r, B.M - 1);
-        const int pl = m >= B.X.split;
-        arow[i] = B.X.off + pl * B.X.poff + (m - pl * B.X.split);
-    }
+    // the lane's row of either plane (rows past the block: its last one, in padding rows of T)
+    int64_t arow[2];
+    arow[0] = B.X.off + min(tl.m0 + r, B.X.split - 1);
+    arow[1] = arow[0] + B.X.poff;
     const op_t* pb = static_cast<const op_t*>(P_.Rops) + B.Roff * P::PER +
                      (int64_t)(tl.n0 / kPanel) * nch * chunk_elems<P>() + lane_off<P>(g, r);
     const int64_t panel = (int64_t)nch * chunk_elems<P>();
     const int64_t ldx = B.X.ld;
-    acc_t acc[MI][NJ];
+    acc_t acc[2][NJ];
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
         for (int nj = 0; nj < NJ; ++nj) zero<P>(acc[mi][nj]);
-    frag_t a[2][MI], b[2][NJ];
-    auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
+    frag_t a[2][2], b[2][NJ];
+    auto load = [&](int c, frag_t (&fa)[2], frag_t (&fb)[NJ]) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
+        for (int i = 0; i < 2; ++i) {
             double v[P::KPL];
             load_clamped<P>(X, arow[i], c * P::CK, g, K, ldx, v);
             fa[i] = P::from(v);
@@ -70,11 +99,11 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
 #pragma unroll
         for (int j = 0; j < NJ; ++j) fb[j] = P::load_op(pb + j * panel + (int64_t)c * chunk_elems<P>());
     };
-    auto mma = [&](const frag_t (&fa)[MI], const frag_t (&fb)[NJ]) {
+    auto mma = [&](const frag_t (&fa)[2], const frag_t (&fb)[NJ]) {
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma_t(fa[mi], fb[nj], acc[mi][nj]);
+            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(fa[mi], fb[nj], acc[mi][nj]);
     };
     // two register buffers, the next chunk always in flight (as in the stage-2 loop)
     load(0, a[0], b[0]);
@@ -88,28 +117,21 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
         mma(a[1], b[1]);
     }
     if (c < nch) mma(a[0], b[0]);
-    // the accumulators hold the transposed tile (mma_t), so that the 16 lanes of a group store 16
-    // consecutive rows of a column of T: whole 128-byte lines (FP64).  With the rows in the lane's
-    // own values, a store touched 16 columns for 32 bytes each, and the write-back of the 41 MB
-    // intermediate held up the loads of the tiles that follow: stage 1 of the 2x16 ladder at
-    // m = 1000 took 34.4 us, now 29.0 (2x32 at m = 2000: 186 -> 164; FP32 at m = 1000:
-    // 32.5 -> 25.3)
-    ws_t* __restrict__ T = static_cast<ws_t*>(P_.T);
-    const View tv = B.T;
+    // whole fragments, padding columns (never read) and rows (zero) included
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-        const int m = tl.m0 + 16 * mi + r;
-        if (m >= B.M) continue;
-        const int pl = m >= tv.split;
-        ws_t* __restrict__ Tm = T + tv.off + pl * tv.poff + (m - pl * tv.split);
+    for (int v = 0; v < 4; ++v)
+        if (tl.m0 + P::row(g, v) >= B.X.split)
 #pragma unroll
-        for (int nj = 0; nj < NJ; ++nj)
+            for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int n = tl.n0 + 16 * nj + P::row(g, v);
-                if (n < B.N) Tm[(int64_t)n * tv.ld] = (ws_t)acc[mi][nj][v];
-            }
-    }
+                for (int nj = 0; nj < NJ; ++nj) acc[mi][nj][v] = 0;
+    ws_t* __restrict__ T = static_cast<ws_t*>(P_.T) + B.T.off + tpos<ws_t>(B.T.ld, tl.n0, tl.m0);
+#pragma unroll
+    for (int nj = 0; nj < NJ; ++nj)
+        if (tl.n0 + 16 * nj < B.N)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+                store_frag(T + mi * B.T.poff + (int64_t)nj * B.T.ld, acc[mi][nj], g, r);
 }
 
 template <class P, int NJ>
@@ -124,10 +146,7 @@ __global__ __launch_bounds__(64, 3) void stage1(const S1Block* __restrict__ blks
     const S1Block B = blks[tl.blk];
     const ProbPtrs P_ = probs ? probs[B.prob] : single;
     if (P_.skip && *P_.skip) return;
-    if (tl.half)
-        stage1_tile<P, 1, NJ>(tl, B, P_);
-    else
-        stage1_tile<P, 2, NJ>(tl, B, P_);
+    stage1_tile<P, NJ>(tl, B, P_);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -233,9 +252,9 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
             int si = 1;
             Segment sg = segs[B.seg0 + 1];
             while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-            ctab[t][0] = sg.B.off - (int64_t)sg.ch0 * P::CK;
+            ctab[t][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
             ctab[t][1] = sg.B.poff;
-            ctab[t][2] = sg.B.ld;
+            ctab[t][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
         }
         __syncthreads();
         auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
@@ -243,11 +262,11 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
             const int64_t* e = ctab[c - nch0];
-            const int64_t kb = (int64_t)c * P::CK;
+            const int ld = (int)e[2], col0 = (int)(e[2] >> 32);
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 double v[P::KPL];
-                load_run<P>(Tws, e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, g, v);
+                load_run<P>(Tws, e[0] + (pl[j] ? e[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g, v);
                 fb[j] = P::from(v);
             }
         };
@@ -261,7 +280,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
             int64_t bcol[NJ];
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                bcol[j] = sg.B.off + pl[j] * sg.B.poff + (int64_t)col[j] * sg.B.ld;
+                bcol[j] = sg.B.off + pl[j] * sg.B.poff + tpos<ws_t>(sg.B.ld, sg.col0 + col[j], 0);
             const int nch = (sg.K + P::CK - 1) / P::CK;
             const int c0 = ((wave - sg.ch0) % NW + NW) % NW;
             auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
@@ -271,7 +290,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
     #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
-                    load_run<P>(Tws, bcol[j] + c * P::CK, g, v);
+                    load_run<P>(Tws, bcol[j] + (int64_t)c * (16 * P::CK), g, v);
                     fb[j] = P::from(v);
                 }
             };
@@ -301,7 +320,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
             for (int w = 1; w < NW; ++w) v += red[w][n][m];
             const int p = gn >= split;
             const int c = gn - p * split;
-            const double init = (double)Tws[t0.off + p * t0.poff + (int64_t)c * t0.ld + gm];
+            const double init = (double)Tws[t0.off + p * t0.poff + tpos<ws_t>(t0.ld, c, gm)];
             Y[yv.off + p * yv.poff + (int64_t)c * yv.ld + gm] = init + v;
         }
     }
@@ -444,9 +463,9 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
             int si = 1;
             Segment sg = segs[B.seg0 + 1];
             while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-            ctab[t][0] = sg.B.off - (int64_t)sg.ch0 * P::CK;
+            ctab[t][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
             ctab[t][1] = sg.B.poff;
-            ctab[t][2] = sg.B.ld;
+            ctab[t][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
         }
         __syncthreads();
         auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NR][NJ]) {
@@ -454,14 +473,14 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
             const int64_t* e = ctab[c - nch0];
-            const int64_t kb = (int64_t)c * P::CK;
+            const int ld = (int)e[2], col0 = (int)(e[2] >> 32);
 #pragma unroll
             for (int q = 0; q < NR; ++q)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
                     load_run<P>(static_cast<const ws_t*>(PP[q].T),
-                                e[0] + pl[j] * e[1] + (int64_t)col[j] * e[2] + kb, g, v);
+                                e[0] + (pl[j] ? e[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g, v);
                     fb[q][j] = P::from(v);
                 }
         };
@@ -473,7 +492,7 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
             int64_t bcol[NJ];
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                bcol[j] = sg.B.off + pl[j] * sg.B.poff + (int64_t)col[j] * sg.B.ld;
+                bcol[j] = sg.B.off + pl[j] * sg.B.poff + tpos<ws_t>(sg.B.ld, sg.col0 + col[j], 0);
             const int nch = (sg.K + P::CK - 1) / P::CK;
             const int c0 = ((wave - sg.ch0) % NW + NW) % NW;
             auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NR][NJ]) {
@@ -485,7 +504,7 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) {
                         double v[P::KPL];
-                        load_run<P>(static_cast<const ws_t*>(PP[q].T), bcol[j] + c * P::CK, g, v);
+                        load_run<P>(static_cast<const ws_t*>(PP[q].T), bcol[j] + (int64_t)c * (16 * P::CK), g, v);
                         fb[q][j] = P::from(v);
                     }
             };
@@ -519,7 +538,7 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
                 for (int w = 1; w < NW; ++w) v += red[w][n][m];
                 const int p = gn >= split;
                 const int c = gn - p * split;
-                const double init = (double)Tws[t0.off + p * t0.poff + (int64_t)c * t0.ld + gm];
+                const double init = (double)Tws[t0.off + p * t0.poff + tpos<ws_t>(t0.ld, c, gm)];
                 Y[yv.off + p * yv.poff + (int64_t)c * yv.ld + gm] = init + v;
             }
         }

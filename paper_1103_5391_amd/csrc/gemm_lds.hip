@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, 3) void stage1_lds(const S1Block* __restrict__
                 const int m = it.m0 + 32 * wm + 16 * mi + P::row(g, v);
                 if (m < B.M) {
                     const int pl = m >= tv.split;
-                    T[tv.off + pl * tv.poff + (int64_t)n * tv.ld + (m - pl * tv.split)] =
+                    T[tv.off + pl * tv.poff + tpos<ws_t>(tv.ld, n, m - pl * tv.split)] =
                         (ws_t)acc[mi][nj][v];
                 }
             }
@@ -189,18 +189,16 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     const int mval = min(4, (B.M - it.m0 + 15) / 16), nval = min(4, (B.N - it.n0 + 15) / 16);
     const int vm = clamp2(mval - 2 * wm), vn = clamp2(nval - 2 * wn);
 
-    // loader roles: wave w brings row panel w of Acat (the lane's packed piece); thread t brings
-    // column t / 4 of the tile, K quarter t % 4 (KPL values), as the fragment of lane
-    // (t % 4, t / 4 % 16) of column panel t / 64
+    // loader roles: wave w brings row panel w of Acat (the lane's packed piece) and column panel w
+    // of the data (lane (g, r): column r, the KPL values of lane group g)
     const bool a_on = wave < mval;
     const op_t* __restrict__ pa = static_cast<const op_t*>(P_.Lops) + B.Aoff * P::PER +
                                   (int64_t)(it.m0 / kPanel + wave) * B.nch * chunk_elems<P>() +
                                   lane_off<P>(g, r);
-    const int bn = tid >> 2, bq = tid & 3;
+    const int bn = 16 * wave + r, bq = g;
     const int ncol = min(it.n0 + bn, B.N - 1);
     const int bpl = ncol >= split;
     const int bcol = ncol - bpl * split;
-    const int bp = bn >> 4, bl = bq * 16 + (bn & 15);
 
     // pass 1: chunks of segment 0 (the diagonal H_S term, read from the input vector, clamped
     // to the block and scaled like the workspace); pass 2: the workspace chunks, addressed
@@ -208,15 +206,15 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     const Segment s0 = segs[B.seg0];
     const int x_end = min(it.kc1, (s0.K + P::CK - 1) / P::CK);
     const int t_beg = max(it.kc0, x_end);
-    __shared__ int64_t ctab[kLSlice][3];   // per workspace chunk: off - ch0 CK, poff, ld
+    __shared__ int64_t ctab[kLSlice][3];   // per workspace chunk: off, poff, (col0, ld)
     if (tid < it.kc1 - t_beg) {
         const int c = t_beg + tid;
         int si = 1;
         Segment sg = segs[B.seg0 + 1];
         while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-        ctab[tid][0] = sg.B.off - (int64_t)sg.ch0 * P::CK;
+        ctab[tid][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
         ctab[tid][1] = sg.B.poff;
-        ctab[tid][2] = sg.B.ld;
+        ctab[tid][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
     }
     __syncthreads();
 
@@ -234,21 +232,21 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     };
     auto store_x = [&](int d) {
         if (a_on) sm.A[d][wave][lane] = ra[d];
-        sm.B[d][bp][bl] = P::from(xb[d]);
+        sm.B[d][wave][lane] = P::from(xb[d]);
     };
     auto load_t = [&](int c, int d) {
         load_a(c, d);
         const int64_t* e = ctab[c - t_beg];
-        const int64_t base = e[0] + bpl * e[1] + (int64_t)bcol * e[2] + c * P::CK;
-#pragma unroll
-        for (int t = 0; t < P::KPL; ++t) tb[d][t] = ldg(Tws, base + koff<P>(bq, t));
+        const int64_t base = e[0] + (bpl ? e[1] : 0) +
+                             tpos<ws_t>((int)e[2], (int)(e[2] >> 32) + bcol, 0);
+        load_units<P>(Tws, base, bq, tb[d]);
     };
     auto store_t = [&](int d) {
         if (a_on) sm.A[d][wave][lane] = ra[d];
         double v[P::KPL];
 #pragma unroll
         for (int t = 0; t < P::KPL; ++t) v[t] = (double)tb[d][t];
-        sm.B[d][bp][bl] = P::from(v);
+        sm.B[d][wave][lane] = P::from(v);
     };
 
     acc_t acc[2][2];
@@ -274,7 +272,7 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
                 for (int v = 0; v < 4; ++v) {
                     const int m = it.m0 + 32 * wm + 16 * mi + P::row(g, v);
                     if (m < B.M) {
-                        const double init = (double)Tws[t0.off + p * t0.poff + (int64_t)cc * t0.ld + m];
+                        const double init = (double)Tws[t0.off + p * t0.poff + tpos<ws_t>(t0.ld, cc, m)];
                         Y[yv.off + p * yv.poff + (int64_t)cc * yv.ld + m] = init + (double)acc[mi][nj][v];
                     }
                 }
@@ -319,7 +317,7 @@ __global__ __launch_bounds__(256) void stage2_reduce(const S2Block* __restrict__
         if (m < B.M && n < B.N) {
             const int p = n >= split;
             const int cc = n - p * split;
-            double s = (double)Tws[t0.off + p * t0.poff + (int64_t)cc * t0.ld + m];
+            double s = (double)Tws[t0.off + p * t0.poff + tpos<ws_t>(t0.ld, cc, m)];
             for (int sl = 0; sl < rd.nslice; ++sl)
                 s += part[(int64_t)(rd.slot0 + sl) * (kLTile * kLTile) + e];
             Y[yv.off + p * yv.poff + (int64_t)cc * yv.ld + m] = s;

@@ -264,11 +264,11 @@ __global__ __launch_bounds__(kXT, 2) void stage1x(const S1Block* __restrict__ bl
         const int m = tl.m0 + 16 * s + 4 * b + t;
         if (m >= B.M) continue;
         const int pl = m >= tv.split;
-        const int64_t rbase = tv.off + pl * tv.poff + (m - pl * tv.split);
+        const int64_t pbase = tv.off + pl * tv.poff;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             const int n = tl.n0 + 16 * wave + 4 * cb + j;
-            if (n < B.N) T[rbase + (int64_t)n * tv.ld] = acc[s][cb];
+            if (n < B.N) T[pbase + tpos<double>(tv.ld, n, m - pl * tv.split)] = acc[s][cb];
         }
     }
 }
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
     if (P_.skip && *P_.skip) return;
     __shared__ XStage<4, 2> sm[2];
     __shared__ int64_t s_off[kXMaxItemChunks], s_poff[kXMaxItemChunks];
-    __shared__ int32_t s_ld[kXMaxItemChunks];
+    __shared__ int32_t s_ld[kXMaxItemChunks], s_col[kXMaxItemChunks];
     const int tid = threadIdx.x, lane = tid & 63;
     // the item's chunk sources (at most kXMaxItemChunks, planner's guarantee) into LDS first
     for (int t = tid; t < it.kc1 - it.kc0; t += kXT) {
@@ -296,6 +296,7 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
         s_off[t] = e.off;
         s_poff[t] = e.poff;
         s_ld[t] = e.ld;
+        s_col[t] = e.col0;
     }
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -305,10 +306,10 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
     const int apanel = tid >> 6;
     const double* ap = static_cast<const double*>(P_.Lops) + B.Aoff +
                        (int64_t)(it.m0 / kPanel + apanel) * B.nch * 256 + lane * 2;
-    // B loader: column j of the tile, k = 2 q, 2 q + 1 of the chunk -> half q / 4 of lane
-    // (q mod 4, j mod 16) of column panel j / 16 (eight consecutive lanes read one column's 128
-    // bytes)
-    const int jc = tid >> 3, q = tid & 7, kq = 2 * q;
+    // B loader: column j of the tile, k = 2 q, 2 q + 1 of the chunk (one unit of the workspace) ->
+    // half q / 4 of lane (q mod 4, j mod 16) of column panel j / 16 (16 consecutive lanes read the
+    // unit's 256 bytes)
+    const int jc = (tid & 15) + ((tid >> 7) << 4), q = (tid >> 4) & 7, kq = 2 * q;
     const int n = min(it.n0 + jc, B.N - 1);    // columns beyond N: any valid column, not stored
     const int pl = n >= split, col = n - pl * split;
     const int bpanel = jc >> 4, bslot = (q >> 2) * kBHalf + bpos((q & 3) * 16 + (jc & 15));
@@ -325,11 +326,12 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
         r.ahi = ldgv<u4>(qa + 128);
         const int t = c - it.kc0;
         const int k = c * PF64::CK + kq;
-        const int64_t base = s_off[t] + pl * s_poff[t] + (int64_t)col * s_ld[t];
+        const int64_t base = s_off[t] + pl * s_poff[t];
         if (c < nch0) {     // input vector: rows beyond K0 clamped (their factors are zero)
-            r.bv = pack2(ldg(xin, base + min(k, K0 - 1)), ldg(xin, base + min(k + 1, K0 - 1)));
-        } else {            // workspace: zero-padded whole chunks, 16-byte aligned pairs
-            r.bv = ldgv<u4>(tws + base + k);
+            const int64_t bc = base + (int64_t)col * s_ld[t];
+            r.bv = pack2(ldg(xin, bc + min(k, K0 - 1)), ldg(xin, bc + min(k + 1, K0 - 1)));
+        } else {            // workspace: whole chunks of 16-byte units
+            r.bv = ldgv<u4>(tws + base + tpos<double>(s_ld[t], s_col[t] + col, kq));
         }
     };
     auto store = [&](int buf, const Regs& r) {
@@ -375,13 +377,13 @@ __global__ __launch_bounds__(kXT, 2) void stage2x(const S2Block* __restrict__ bl
         if (nn >= B.N) continue;
         const int p2 = nn >= split, c2 = nn - p2 * split;
         const int64_t ybase = yv.off + p2 * yv.poff + (int64_t)c2 * yv.ld;
-        const int64_t tbase = t0.off + p2 * t0.poff + (int64_t)c2 * t0.ld;
+        const int64_t tbase = t0.off + p2 * t0.poff;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int m = it.m0 + 32 * wm + 16 * s + 4 * b + t;
             if (m >= B.M) continue;
             double val = acc[s][cb];
-            if (it.mode != 2) val = tws[tbase + m] + val;
+            if (it.mode != 2) val = tws[tbase + tpos<double>(t0.ld, c2, m)] + val;
             if (it.mode == 0)
                 Y[ybase + m] = val;
             else

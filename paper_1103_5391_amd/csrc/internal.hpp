@@ -8,8 +8,9 @@ namespace dmrg {
 
 constexpr int kMaxKrylov = 64;      // largest kdim accepted
 constexpr int kTile = 32;           // output tile edge of the block-product kernels
-constexpr int kTile1N = 64;         // stage-1 tiles are kTile x kTile1N (one per wavefront),
-constexpr int kTile1NN = 32;        // or kTile x kTile1NN (narrow: twice the tiles, each shorter)
+constexpr int kTile1M = 16;         // stage-1 tiles are kTile1M rows of both planes x kTile1N (one
+constexpr int kTile1N = 64;         // per wavefront), or
+constexpr int kTile1NN = 32;        // x kTile1NN (narrow: twice the tiles, each shorter)
 constexpr int kTile2NN = 16;        // narrow stage-2 tiles are kTile x kTile2NN
 constexpr int kChunk = 16;          // K depth of one FP64/FP32 chunk (4 MFMA K-steps of 4)
 constexpr int kChunkMax = 32;       // K depth of one BF16 chunk (one 16x16x32 MFMA)
@@ -55,9 +56,12 @@ constexpr int kPanel = 16;                        // rows (columns) per packed p
 // Stage 1 (right products) of one source block b:  T_b = X_b * R_b
 //   X_b: 2d x e, rows 0..d-1 = real plane of Psi_b, rows d..2d-1 = imaginary plane
 //   R_b: e x N, [H_E(q)^T | right factors of every term leaving b], packed (column panels)
-//   T_b: workspace, column-major with both planes padded to dpad = d rounded up to a whole
-//        K chunk (ld 2 dpad); the padding rows are zeroed once and never written, so the left
-//        products read whole chunks of a column without bounds checks
+//   T_b: workspace, one matrix per plane in the order stage 2's lanes read it: panels of 16
+//        columns (N rounded up), in a panel 16-deep K chunks (rows, d rounded up) of
+//        [unit][16 columns][16 / element size]: a 16-byte unit holds consecutive rows of one
+//        column (tpos in mfma.hpp).  View: ld = elements of a panel, poff = of a plane.  The
+//        padding rows are read, times zero factors, and hold zeros: from the workspace's start,
+//        and again from every register-tiled stage 1
 struct S1Block {
     int32_t M, K, N, prob;
     int32_t nch, pad;   // K chunks of the packed factor
@@ -83,12 +87,13 @@ struct S2Block {
 struct Segment {
     int32_t K, ch0;
     int32_t src;        // 0: the input vector (diagonal H_S term), 1: the workspace
-    int32_t pad;
+    int32_t col0;       // first column of the source (workspace)
     View B;
 };
 
-// One output tile of a register-tiled stage: rows m0.., columns n0.. of block blk; half: the
-// tile has 16 rows instead of 32 (the last rows of a block, 16 or fewer).
+// One output tile of a register-tiled stage: columns n0.. of block blk and, in stage 1, rows
+// m0 .. m0 + 15 of both planes, in stage 2 rows m0.. (half: 16 rows instead of 32, the last rows of
+// a block, 16 or fewer).
 struct Tile {
     int32_t blk, m0, n0, half;
 };
@@ -126,14 +131,16 @@ constexpr int kXTile2N = 32;        // stage-2 tile columns
 constexpr int kXSplitChunks = 40;   // stage-2 tiles with more 16-deep K chunks run as two slices
 constexpr int kXMaxItemChunks = 256;   // most chunks of one stage-2 item (its table in LDS); a
                                        // plan with longer items does not offer the family
-// Source of one 16-deep K chunk of a stage-2 block: element (k, column n of plane p) of the
-// chunk's segment at off + p poff + col ld + k, k counted from the block's first chunk (the
-// segment's own start subtracted); src 0: the input vector (rows < K0 valid), 1: the workspace.
+// Source of one 16-deep K chunk of a stage-2 block.  src 0, the input vector (rows < K0 valid):
+// element (k, column n of plane p) at off + p poff + n ld + k, k counted from the block's first
+// chunk; src 1, the workspace: the chunk at off + p poff of the panels (stride ld) from column
+// col0 on.
 struct XChunk {
     int64_t off;
     int64_t poff;
     int32_t ld;
     int32_t src;
+    int32_t col0, pad;
 };
 // One stage-2 work group: output tile (m0, n0) of block blk, K chunks [kc0, kc1); mode 0: the
 // whole K, y = T0 + product; 1: first slice, y += T0 + product (atomic); 2: second slice,

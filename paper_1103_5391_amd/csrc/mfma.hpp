@@ -27,14 +27,16 @@ __device__ __forceinline__ T ldg(const T* p, int64_t i) {
     return ((const __attribute__((address_space(1))) T*)p)[i];
 }
 template <typename V>
+__device__ __forceinline__ void stgv(void* p, const V& v) {
+    *((__attribute__((address_space(1))) V*)p) = v;
+}
+template <typename V>
 __device__ __forceinline__ V ldgv(const void* p) {
     return *((const __attribute__((address_space(1))) V*)p);
 }
 
 // ---------------------------------------------------------------------------------------
-// arithmetic traits.  mma: c += A B with the result's rows in the lane's four values (row(g, v))
-// and its columns across the lanes; mma_t: the transposed result, c^T += (A B)^T, the same
-// products in the same order, with the rows of A B across the lanes.
+// arithmetic traits
 // ---------------------------------------------------------------------------------------
 struct PF64 {
     static constexpr int CK = 16, KPL = 4, PER = 1;   // PER: packed pieces per value
@@ -53,7 +55,6 @@ struct PF64 {
         for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[t], c, 0, 0, 0);
         return c;
     }
-    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) { return mma(b, a, c); }
     __device__ static int row(int g, int v) { return g + 4 * v; }   // result lane layout
 };
 
@@ -73,7 +74,6 @@ struct PF32 {
         for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0);
         return c;
     }
-    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) { return mma(b, a, c); }
     __device__ static int row(int g, int v) { return 4 * g + v; }
 };
 
@@ -117,14 +117,6 @@ struct PSplit {
                 c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[i], b.p[o - i], c, 0, 0, 0);
         return c;
     }
-    __device__ static acc_t mma_t(const frag_t& a, const frag_t& b, acc_t c) {
-#pragma unroll
-        for (int o = 0; o < NP; ++o)
-#pragma unroll
-            for (int i = 0; i <= o; ++i)
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.p[o - i], a.p[i], c, 0, 0, 0);
-        return c;
-    }
     __device__ static int row(int g, int v) { return 4 * g + v; }
 };
 using PBF3 = PSplit<2>;
@@ -157,12 +149,34 @@ __device__ __forceinline__ int lane_off(int g, int r) {
     return (kPanel * g + r) * (P::KP * P::PER);
 }
 
-// The lane's data values v[t] = src[base + koff(g, t)] (workspace, zero-padded chunks; base at
-// the chunk's first index)
+// Element (k, col) of a plane of the stage-1 workspace (S1Block::T), ld = elements of a panel.
+template <typename T>
+__device__ __forceinline__ int64_t tpos(int ld, int col, int k) {
+    constexpr int U = 16 / sizeof(T);
+    return (int64_t)(col >> 4) * ld + k / U * (16 * U) + (col & 15) * U + (k & (U - 1));
+}
+
+// The lane's data values k = koff(g, t) of a chunk of the workspace, base at the lane's column in
+// the chunk's first unit: 16-byte units, so that 16 lanes read 256 contiguous bytes.  (From a
+// column-major intermediate every lane of a load was in a line of its own; the L1's data return
+// then took four times the cycles and bounded stage 2, see gemm.hip.)
+template <class P, typename T>
+__device__ __forceinline__ void load_units(const T* src, int64_t base, int g, T (&v)[P::KPL]) {
+    constexpr int U = 16 / sizeof(T);
+    typedef T unit_t __attribute__((ext_vector_type(U)));
+#pragma unroll
+    for (int t = 0; t < P::KPL; t += U) {
+        const unit_t u = ldgv<unit_t>(src + base + koff<P>(g, t) / U * (16 * U));
+#pragma unroll
+        for (int q = 0; q < U; ++q) v[t + q] = u[q];
+    }
+}
 template <class P, typename T>
 __device__ __forceinline__ void load_run(const T* src, int64_t base, int g, double (&v)[P::KPL]) {
+    T u[P::KPL];
+    load_units<P>(src, base, g, u);
 #pragma unroll
-    for (int t = 0; t < P::KPL; ++t) v[t] = (double)ldg(src, base + koff<P>(g, t));
+    for (int t = 0; t < P::KPL; ++t) v[t] = (double)u[t];
 }
 // The lane's values src[base + min(k0 + koff(g, t), K - 1) * stride] (input vector, clamped)
 template <class P>

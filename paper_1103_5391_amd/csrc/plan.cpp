@@ -162,7 +162,7 @@ std::vector<T> xcd_order(const std::vector<T>& tiles, const std::vector<double>&
 }
 
 // Tiles of tm x tn over an M x N block; a last row of tiles with tm / 2 rows or fewer is marked
-// half-height (the kernels then run half the row fragments).
+// half-height (stage 2 then runs half the row fragments).
 void tile_list(std::vector<Tile>& out, int blk, int M, int N, int tm, int tn) {
     for (int m0 = 0; m0 < M; m0 += tm)
         for (int n0 = 0; n0 < N; n0 += tn) out.push_back(Tile{blk, m0, n0, M - m0 <= tm / 2});
@@ -276,10 +276,9 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
         }
     }
 
-    // stage-1 columns, workspace views (planes padded to whole 32-deep chunks), flops, tiles
+    // stage-1 columns, workspace views, flops, tiles
     P.N1.assign(nb, 0);
-    P.Tview.assign(nb, View{});
-    int64_t toff = 0;
+    int64_t tsize[2] = {0, 0};
     for (int bi = 0; bi < nb; ++bi) {
         const auto& B = P.blocks[bi];
         int N = B.e;
@@ -288,14 +287,21 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
             N += P.blocks[P.edges[ei].dst].e;
         }
         P.N1[bi] = N;
-        const int dpad = round_up(B.d, kChunkMax);
-        P.Tview[bi] = View{toff, dpad, 2 * dpad, B.d};
-        toff += (int64_t)2 * dpad * N;
+        // both chunk depths share the sizes; a panel's rows are whole chunks of the deeper one
+        // only in its own layout (FP32 elements: half the bytes of the FP64 one's)
+        const int np = round_up(N, 16);
+        for (int k = 0; k < 2; ++k) {
+            const int dpad = round_up(B.d, k ? kChunkMax : kChunk);
+            P.Tview[k].push_back(View{tsize[k], (int64_t)dpad * np, dpad * 16, B.d});
+            tsize[k] += (int64_t)2 * dpad * np;
+        }
+        P.T_need += (int64_t)2 * round_up(B.d, kChunkMax) * N;
         P.flops1 += 2.0 * (2 * B.d) * (double)B.e * N;
-        tile_list(P.tiles1, bi, 2 * B.d, N, kTile, kTile1N);
-        tile_list(P.tiles1n, bi, 2 * B.d, N, kTile, kTile1NN);
+        tile_list(P.tiles1, bi, B.d, N, kTile1M, kTile1N);
+        tile_list(P.tiles1n, bi, B.d, N, kTile1M, kTile1NN);
     }
-    P.T_size = toff;
+    static_assert(sizeof(float) * 2 <= sizeof(double), "the deeper layout fits the FP64 one");
+    P.T_size = std::max(tsize[0], (tsize[1] + 1) / 2);
     std::vector<int> kcat(nb);
     for (int bi = 0; bi < nb; ++bi) {
         const auto& B = P.blocks[bi];
@@ -333,7 +339,7 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
             s.pad = 0;
             s.X = View{B.off, P.n, B.d, B.d};
             s.Roff = roff;
-            s.T = P.Tview[bi];
+            s.T = P.Tview[ck == kChunk ? 0 : 1][bi];
             roff += (int64_t)round_up(s.N, kTile1N) * s.nch * ck;
             pk->s1.push_back(s);
         }
@@ -345,7 +351,8 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
             s.prob = 0;
             s.seg0 = (int)pk->segs.size();
             s.Aoff = aoff;
-            s.T0 = View{P.Tview[bi].off, P.Tview[bi].poff, P.Tview[bi].ld, B.e};
+            const std::vector<View>& tv = P.Tview[ck == kChunk ? 0 : 1];
+            s.T0 = View{tv[bi].off, tv[bi].poff, tv[bi].ld, B.e};
             s.Y = View{B.off, P.n, B.d, B.e};
             int nch = 0;
             // the diagonal H_S term reads the block itself from the input vector
@@ -354,9 +361,8 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
             for (int ei : P.into[bi]) {
                 const Edge& ed = P.edges[ei];
                 const auto& Bs = P.blocks[ed.src];
-                const View& ts = P.Tview[ed.src];
-                pk->segs.push_back(Segment{Bs.d, nch, 1, 0,
-                                           View{ts.off + (int64_t)ed.col * ts.ld, ts.poff, ts.ld, B.e}});
+                const View& ts = tv[ed.src];
+                pk->segs.push_back(Segment{Bs.d, nch, 1, ed.col, View{ts.off, ts.poff, ts.ld, B.e}});
                 nch += (Bs.d + ck - 1) / ck;
             }
             s.nseg = (int)pk->segs.size() - s.seg0;
@@ -374,7 +380,7 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
     std::vector<double> w1(nb), w2(nb);
     for (int bi = 0; bi < nb; ++bi) {
         const auto& B = P.blocks[bi];
-        const double nt1 = (double)((2 * B.d + kTile - 1) / kTile) * ((P.N1[bi] + kTile1N - 1) / kTile1N);
+        const double nt1 = (double)((B.d + kTile1M - 1) / kTile1M) * ((P.N1[bi] + kTile1N - 1) / kTile1N);
         const double nt2 = (double)((B.d + kTile - 1) / kTile) * ((2 * B.e + kTile - 1) / kTile);
         w1[bi] = nt1 * ((B.e + 15) / 16 + 1);
         w2[bi] = nt2 * ((kcat[bi] + 15) / 16 + 2);
@@ -542,7 +548,8 @@ void x_lists(Plan& P) {
             const Segment& sg = pk.segs[s.seg0 + si];
             const int nc = (sg.K + pk.ck - 1) / pk.ck;
             for (int c = 0; c < nc; ++c)
-                pk.xch.push_back(XChunk{sg.B.off - (int64_t)sg.ch0 * pk.ck, sg.B.poff, sg.B.ld, sg.src});
+                pk.xch.push_back(XChunk{sg.B.off + (sg.src ? (int64_t)c * 256 : 0), sg.B.poff, sg.B.ld,
+                                        sg.src, sg.col0, 0});
         }
     }
     auto panels = [](int v) { return (v + kPanel - 1) / kPanel; };

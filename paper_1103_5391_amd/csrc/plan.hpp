@@ -112,10 +112,11 @@ struct Plan {
     std::vector<Edge> edges;
     std::vector<std::vector<int>> out_of, into;
     std::vector<int> N1;                       // stage-1 columns per source block
-    std::vector<View> Tview;                   // stage-1 workspace view per block
+    std::vector<View> Tview[2];                // stage-1 workspace view per block (chunk depth)
     int64_t T_size = 0;                        // workspace elements (every family)
     int64_t T_base = 0;                        // of them, what the families other than the
                                                // K-split one use
+    int64_t T_need = 0;                        // what dmrg_matvec_noalloc counts against its limit
     std::vector<Tile> tiles1, tiles1n, tiles2, tiles2n;   // register-tiled lists (wide, narrow)
     std::vector<LItem1> l1;                    // LDS-tiled stage-1 tiles (both packings)
     std::vector<double> w1, w2;                // per-block work estimates of the two stages

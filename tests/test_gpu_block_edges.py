@@ -1,0 +1,79 @@
+"""Block products at the sizes where a tile, a K chunk or a column panel ends: superblocks with
+hand-picked sector dimensions, every kernel family and arithmetic, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import matvec as M
+from paper_1103_5391_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+QN = np.array([[0, 0], [0, 1], [1, 0], [1, 1]], dtype=np.int32)
+# sector dimensions of the two halves: 16 rows and columns make a panel and an FP64 chunk, 32 a
+# tile and a bf16 chunk, 64 the widest tile
+DIMS = [((1, 1, 1, 1), (1, 1, 1, 1)), ((15, 16, 17, 2), (17, 15, 1, 16)),
+        ((31, 32, 33, 48), (3, 33, 32, 31)), ((64, 65, 1, 47), (49, 1, 64, 65))]
+VARIANTS = [0, 1, 2, 3, 4, 6, 8, 9, 12, 16, 32]
+# relative 2-norm bounds: K <= 5 * 65 terms of relative error 2^-53, 2^-24 (twice: the intermediate
+# is rounded too), and 2^-16 for two bf16 pieces
+BOUND = {0: 1e-13, 1: 2e-6, 2: 1e-4, 3: 2e-6}
+
+
+def _half(dims, rng):
+    sp = I.Space(QN.copy(), np.array(dims, dtype=np.int32))
+    H = []
+    for d in dims:
+        a = rng.standard_normal((d, d))
+        H.append(a + a.T)
+    ops = []
+    for dq in I.E_SIGMA:
+        op = I.BlockOp(dq)
+        for p in range(4):
+            p2 = sp.shift(p, dq)
+            if p2 is not None:
+                op.blocks[p] = rng.standard_normal((dims[p2], dims[p]))
+        ops.append(op)
+    return I.Half(sp, H, ops, [(0, 0), (0, 1)], [0])
+
+
+def _problem(dims, seed=5):
+    rng = np.random.default_rng(I.SEED_BASE + seed)
+    S, E = _half(dims[0], rng), _half(dims[1], rng)
+    return I.Problem(S, E, (1, 1), [I.Bond((0, 1), (0, 1), 1.0, (0, 1))])
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_1103_5391_amd import lib as L
+    return torch, L
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3], ids=["fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("dims", DIMS, ids=["1", "16", "32", "64"])
+def test_products_at_tile_edges(env, dims, prec):
+    torch, L = env
+    pb = _problem(dims)
+    h = L.dmrg_create(pb)
+    h.set_precision(prec)
+    x = I.random_psi(h.n, np.random.default_rng(I.SEED_BASE + 6))
+    ref = M.matvec_sector(pb, x)
+    xd = torch.from_numpy(x).to("cuda")
+    bad = torch.full_like(xd, float("nan"))
+    y = torch.empty_like(xd)
+    for v in VARIANTS:
+        h.set_gemm(v)
+        h.matvec(bad, y)          # nothing of a vector of NaN may stay behind in the workspace
+        for w in (v, 0) if v != 32 else (v,):
+            h.set_gemm(w)
+            y.fill_(0.0)
+            h.matvec(xd, y)
+            err = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
+            assert err < BOUND[prec], (v, w, err)
+    for v in (0, 12, 3):
+        h.set_gemm(v)
+        y.fill_(0.0)
+        h.matvec_noalloc(xd, y)
+        err = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
+        assert err < BOUND[prec], ("noalloc", v, err)
+    h.destroy()
