@@ -29,38 +29,35 @@
 // m = 2000: 186 / 187 -> 161 / 166; BF16x3 at m = 1000: 21.8 / 26.7 -> 21.6 / 23.4.
 #include "mfma.hpp"
 
+#include <type_traits>
+
 namespace dmrg {
 
 // ---------------------------------------------------------------------------------------
 // stage 1: one tile of 16 rows of both planes x 16 NJ columns (NJ = 4 wide, 2 narrow) per
 // single-wavefront work group
 // ---------------------------------------------------------------------------------------
-// One 16 x 16 fragment of T (rows row(g, v), column r of the lane) into a chunk of the workspace:
-// contiguous kilobytes of 16-byte units.  FP32 results hold a unit per lane already; in FP64 lane
-// groups 2 h and 2 h + 1 hold the two rows of a unit, and swapping rows of 16 lanes between the
-// accumulators of two row groups brings each pair to one lane.
+// One 16 x 16 fragment of T (the lane's values: rows a_row(row(g, v)) of column r) into a chunk of
+// the workspace, contiguous kilobytes of 16-byte units.  In FP64 a lane holds the two rows of two
+// units; in FP32 swapping two pairs of values between the wave's halves gives it the four of one.
 __device__ __forceinline__ void store_frag(double* t, const d4& c, int g, int r) {
-    // after the swap: lane groups 0..3 hold the rows of units 0, 2, 1, 3
-    const int unit = ((g & 1) << 1) | (g >> 1);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        union {
-            double d[2];
-            unsigned u[4];
-        } p;
-        p.d[0] = c[2 * h];
-        p.d[1] = c[2 * h + 1];
-        const auto lo = __builtin_amdgcn_permlane16_swap(p.u[0], p.u[2], false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap(p.u[1], p.u[3], false, false);
-        p.u[0] = lo[0];
-        p.u[2] = lo[1];
-        p.u[1] = hi[0];
-        p.u[3] = hi[1];
-        stgv(t + 128 * h + 32 * unit + 2 * r, (d2){p.d[0], p.d[1]});
-    }
+    stgv(t + 32 * g + 2 * r, (d2){c[0], c[2]});
+    stgv(t + 128 + 32 * g + 2 * r, (d2){c[1], c[3]});
 }
 __device__ __forceinline__ void store_frag(float* t, const f4& c, int g, int r) {
-    stgv(t + 64 * g + 4 * r, c);
+    union {
+        f4 f;
+        unsigned u[4];
+    } a, b;
+    a.f = c;
+    const auto p = __builtin_amdgcn_permlane32_swap(a.u[0], a.u[2], false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(a.u[1], a.u[3], false, false);
+    b.u[0] = p[0];
+    b.u[1] = p[1];
+    b.u[2] = q[0];
+    b.u[3] = q[1];
+    const int unit = ((g & 1) << 1) | (g >> 1);     // lane groups 0..3 hold units 0, 2, 1, 3
+    stgv(t + 64 * unit + 4 * r, b.f);
 }
 
 template <class P, int NJ>
@@ -75,9 +72,12 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
     const int K = B.K;
     const int nch = (K + P::CK - 1) / P::CK;
 
-    // the lane's row of either plane (rows past the block: its last one, in padding rows of T)
+    // The operand's rows are permuted (a_row).  A whole tile loads two rows per lane: a load of
+    // one row costs the L1 the same 14 cycles for half the bytes (stage 1 at m = 1000: 29.8 ->
+    // 28.3 us).  At the block's end rows past it are its last one, in padding rows of T.
+    const bool whole = tl.m0 + 16 <= B.X.split;       // the same in every lane
     int64_t arow[2];
-    arow[0] = B.X.off + min(tl.m0 + r, B.X.split - 1);
+    arow[0] = B.X.off + (whole ? tl.m0 + 2 * (r & 7) : min(tl.m0 + a_row(r), B.X.split - 1));
     arow[1] = arow[0] + B.X.poff;
     const op_t* pb = static_cast<const op_t*>(P_.Rops) + B.Roff * P::PER +
                      (int64_t)(tl.n0 / kPanel) * nch * chunk_elems<P>() + lane_off<P>(g, r);
@@ -88,39 +88,70 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
         for (int nj = 0; nj < NJ; ++nj) zero<P>(acc[mi][nj]);
-    frag_t a[2][2], b[2][NJ];
-    auto load = [&](int c, frag_t (&fa)[2], frag_t (&fb)[NJ]) {
+    auto run = [&](auto pairs) {
+        constexpr bool kPairs = decltype(pairs)::value;
+        struct Chunk {
+            double x[2][P::KPL];      // as loaded: exchanged and converted when it is multiplied
+                                      // (a conversion beside the load waits for it there: FP32
+                                      // 24.7 -> 21.2 us, BF16x3 21.6 -> 19.9)
+            frag_t b[NJ];
+        };
+        auto load = [&](int c, Chunk& k) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            double v[P::KPL];
-            load_clamped<P>(X, arow[i], c * P::CK, g, K, ldx, v);
-            fa[i] = P::from(v);
+            for (int i = 0; i < 2; ++i) {
+                if constexpr (kPairs) {
+#pragma unroll
+                    for (int t = 0; t < P::KPL; t += 2) {
+                        const int kk = min(c * P::CK + koff<P>(g, t) + (r >> 3), K - 1);
+                        const d2 p = ldg2(X, arow[i] + kk * ldx);
+                        k.x[i][t] = p[0];
+                        k.x[i][t + 1] = p[1];
+                    }
+                } else {
+                    load_clamped<P>(X, arow[i], c * P::CK, g, K, ldx, k.x[i]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                k.b[j] = P::load_op(pb + j * panel + (int64_t)c * chunk_elems<P>());
+        };
+        auto mma = [&](const Chunk& k) {
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) {
+                double v[P::KPL];
+#pragma unroll
+                for (int t = 0; t < P::KPL; t += 2) {
+                    v[t] = k.x[mi][t];
+                    v[t + 1] = k.x[mi][t + 1];
+                    if constexpr (kPairs) half_rows((d2){k.x[mi][t], k.x[mi][t + 1]}, v[t], v[t + 1]);
+                }
+                const frag_t fa = P::from(v);
+#pragma unroll
+                for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(fa, k.b[nj], acc[mi][nj]);
+            }
+        };
+        // two register buffers, the next chunk always in flight (as in the stage-2 loop)
+        Chunk k0, k1;
+        load(0, k0);
+        int c = 0;
+        for (; c + 1 < nch; c += 2) {
+            load(c + 1, k1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(k0);
+            load(min(c + 2, nch - 1), k0);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(k1);
         }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) fb[j] = P::load_op(pb + j * panel + (int64_t)c * chunk_elems<P>());
+        if (c < nch) mma(k0);
     };
-    auto mma = [&](const frag_t (&fa)[2], const frag_t (&fb)[NJ]) {
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(fa[mi], fb[nj], acc[mi][nj]);
-    };
-    // two register buffers, the next chunk always in flight (as in the stage-2 loop)
-    load(0, a[0], b[0]);
-    int c = 0;
-    for (; c + 1 < nch; c += 2) {
-        load(c + 1, a[1], b[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(a[0], b[0]);
-        load(min(c + 2, nch - 1), a[0], b[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(a[1], b[1]);
-    }
-    if (c < nch) mma(a[0], b[0]);
+    if (whole)
+        run(std::true_type{});
+    else
+        run(std::false_type{});
     // whole fragments, padding columns (never read) and rows (zero) included
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-        if (tl.m0 + P::row(g, v) >= B.X.split)
+        if (tl.m0 + a_row(P::row(g, v)) >= B.X.split)
 #pragma unroll
             for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -134,8 +165,10 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
                 store_frag(T + mi * B.T.poff + (int64_t)nj * B.T.ld, acc[mi][nj], g, r);
 }
 
+// Wide tiles take two wavefronts per SIMD: at three they spilled (FP64 at m = 2000: 174 -> 154 us,
+// BF16x6 at m = 1000: 48.7 -> 20.7).
 template <class P, int NJ>
-__global__ __launch_bounds__(64, 3) void stage1(const S1Block* __restrict__ blks,
+__global__ __launch_bounds__(64, NJ > 2 ? 2 : 3) void stage1(const S1Block* __restrict__ blks,
                                                  const Tile* __restrict__ tiles, int ntiles,
                                                  const ProbPtrs* __restrict__ probs,
                                                  ProbPtrs single) {
@@ -153,34 +186,49 @@ __global__ __launch_bounds__(64, 3) void stage1(const S1Block* __restrict__ blks
 // stage 2: one 32 x 32 (or 32 x 16) tile per work group, K chunks dealt round-robin to its waves
 // ---------------------------------------------------------------------------------------
 constexpr int kChunkTab = 256;   // workspace chunks of a block addressed through the LDS table
-template <class P, int MI, int NJ, class Load>
+// D: element type of the data operand as it is loaded; it is converted to the MFMA input type when
+// it is multiplied (a conversion beside the load would wait for it there).
+template <class P, int MI, int NJ, typename D>
+struct Chunk2 {
+    typename P::frag_t a[MI];
+    D b[NJ][P::KPL];
+    __device__ __forceinline__ typename P::frag_t right(int j) const {
+        double v[P::KPL];
+#pragma unroll
+        for (int t = 0; t < P::KPL; ++t) v[t] = (double)b[j][t];
+        return P::from(v);
+    }
+};
+template <class P, int MI, int NJ, typename D, class Load>
 __device__ __forceinline__ void kloop(typename P::acc_t (&acc)[MI][NJ], int c0, int step, int nch,
                                       Load load) {
-    using frag_t = typename P::frag_t;
     if (c0 >= nch) return;
     const int last = c0 + (nch - 1 - c0) / step * step;
-    frag_t a0[MI], b0[NJ], a1[MI], b1[NJ];
-    auto mma = [&](const frag_t (&fa)[MI], const frag_t (&fb)[NJ]) {
+    Chunk2<P, MI, NJ, D> k0, k1;
+    auto mma = [&](const Chunk2<P, MI, NJ, D>& k) {
+        typename P::frag_t fb[NJ];
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj) fb[nj] = k.right(nj);
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(fa[mi], fb[nj], acc[mi][nj]);
+            for (int nj = 0; nj < NJ; ++nj) acc[mi][nj] = P::mma(k.a[mi], fb[nj], acc[mi][nj]);
     };
     // Two register buffers, one exit test per pair of chunks: the chunk after the one being
     // multiplied is always in flight (the last prefetch is clamped and unused).  The
     // scheduling barriers keep each prefetch ahead of the products it overlaps; without them
     // the compiler moved the loads down to their products and waited for them there.
-    load(c0, a0, b0);
+    load(c0, k0);
     int c = c0;
     for (; c + step <= last; c += 2 * step) {
-        load(c + step, a1, b1);
+        load(c + step, k1);
         __builtin_amdgcn_sched_barrier(0);
-        mma(a0, b0);
-        load(min(c + 2 * step, last), a0, b0);
+        mma(k0);
+        load(min(c + 2 * step, last), k0);
         __builtin_amdgcn_sched_barrier(0);
-        mma(a1, b1);
+        mma(k1);
     }
-    if (c <= last) mma(a0, b0);   // odd count: chunk c is in a0
+    if (c <= last) mma(k0);   // odd count: chunk c is in k0
 }
 
 // One 16 MI x 16 NJ output tile (MI = 2, or 1 for a half-height tile) per work group of NW
@@ -228,18 +276,21 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             bcol[j] = s0.B.off + pl[j] * s0.B.poff + (int64_t)col[j] * s0.B.ld;
-        auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
+        auto load = [&](int c, Chunk2<P, MI, NJ, double>& k) {
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
+            for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
+            // a lane's values lie in a line of its own: half the loads where the chunk is whole
+            if ((c + 1) * P::CK <= s0.K) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                double v[P::KPL];
-                load_clamped<P>(P_.x, bcol[j], c * P::CK, g, s0.K, 1, v);
-                fb[j] = P::from(v);
+                for (int j = 0; j < NJ; ++j) load_pairs<P>(P_.x, bcol[j], c * P::CK, g, k.b[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    load_clamped<P>(P_.x, bcol[j], c * P::CK, g, s0.K, 1, k.b[j]);
             }
         };
-        kloop<P, MI, NJ>(acc, wave, NW, nch0, load);
+        kloop<P, MI, NJ, double>(acc, wave, NW, nch0, load);
     }
     // pass 2: every workspace chunk of segments 1.. in one pipelined stream per wave (global
     // chunk c goes to wave c mod NW), its source view read from a per-chunk table in LDS (built
@@ -257,22 +308,20 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
             ctab[t][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
         }
         __syncthreads();
-        auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
+        auto load = [&](int c, Chunk2<P, MI, NJ, ws_t>& k) {
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
+            for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
             const int64_t* e = ctab[c - nch0];
             const int ld = (int)e[2], col0 = (int)(e[2] >> 32);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                double v[P::KPL];
-                load_run<P>(Tws, e[0] + (pl[j] ? e[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g, v);
-                fb[j] = P::from(v);
-            }
+            for (int j = 0; j < NJ; ++j)
+                load_units<P>(Tws, e[0] + (pl[j] ? e[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g,
+                              k.b[j]);
         };
         // first chunk >= nch0 owned by this wave
         const int cw = nch0 + ((wave - nch0) % NW + NW) % NW;
-        kloop<P, MI, NJ>(acc, cw, NW, B.nch, load);
+        kloop<P, MI, NJ, ws_t>(acc, cw, NW, B.nch, load);
     } else {
         // very long K: one pipeline per segment
         for (int s = 1; s < B.nseg; ++s) {
@@ -283,18 +332,15 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
                 bcol[j] = sg.B.off + pl[j] * sg.B.poff + tpos<ws_t>(sg.B.ld, sg.col0 + col[j], 0);
             const int nch = (sg.K + P::CK - 1) / P::CK;
             const int c0 = ((wave - sg.ch0) % NW + NW) % NW;
-            auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NJ]) {
+            auto load = [&](int c, Chunk2<P, MI, NJ, ws_t>& k) {
                 const int64_t ga = (int64_t)(sg.ch0 + c) * chunk_elems<P>();
 #pragma unroll
-                for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-    #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    double v[P::KPL];
-                    load_run<P>(Tws, bcol[j] + (int64_t)c * (16 * P::CK), g, v);
-                    fb[j] = P::from(v);
-                }
+                for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    load_units<P>(Tws, bcol[j] + (int64_t)c * (16 * P::CK), g, k.b[j]);
             };
-            kloop<P, MI, NJ>(acc, c0, NW, nch, load);
+            kloop<P, MI, NJ, ws_t>(acc, c0, NW, nch, load);
         }
     }
 

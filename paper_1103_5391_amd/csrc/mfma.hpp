@@ -95,7 +95,9 @@ struct PSplit {
             float rest = (float)v[t];
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
-                const __bf16 h = (__bf16)rest;
+                // the first piece rounds the value itself (one rounding, not through FP32): the
+                // compiler took either for the other, by context
+                const __bf16 h = q == 0 ? (__bf16)v[t] : (__bf16)rest;
                 f.p[q][t] = h;
                 rest -= (float)h;
             }
@@ -185,6 +187,46 @@ __device__ __forceinline__ void load_clamped(const double* src, int64_t base, in
 #pragma unroll
     for (int t = 0; t < P::KPL; ++t)
         v[t] = ldg(src, base + (int64_t)min(k0 + koff<P>(g, t), K - 1) * stride);
+}
+// Two consecutive values as one 16-byte load (8-byte aligned).
+__device__ __forceinline__ d2 ldg2(const double* p, int64_t i) {
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    const d2u v = ldgv<d2u>(p + i);
+    return (d2){v[0], v[1]};
+}
+// The lane's values src[base + k0 + koff(g, t)] of a whole chunk (input vector, K contiguous)
+template <class P>
+__device__ __forceinline__ void load_pairs(const double* src, int64_t base, int k0, int g,
+                                           double (&v)[P::KPL]) {
+#pragma unroll
+    for (int t = 0; t < P::KPL; t += 2) {
+        const d2 p = ldg2(src, base + k0 + koff<P>(g, t));
+        v[t] = p[0];
+        v[t + 1] = p[1];
+    }
+}
+
+// Rows of a 16-row A operand whose row index is contiguous in memory, loaded two at a time: lane
+// (g, r) asks for rows 2 (r mod 8), 2 (r mod 8) + 1 at k = koff(g, t) + r / 8 (t even), 8 lanes per
+// column of 128 bytes.  Exchanging the lanes of each half row of 16 (DPP) then leaves lane (g, r)
+// with row a_row(r) at koff(g, t) and koff(g, t + 1): the operand with its rows permuted.
+__device__ __forceinline__ int a_row(int r) { return r < 8 ? 2 * r : 2 * r - 15; }
+__device__ __forceinline__ void half_rows(const d2& p, double& v0, double& v1) {
+    union {
+        double d;
+        int u[2];
+    } a, b, x, y;
+    a.d = p[0];
+    b.d = p[1];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        // lanes 8..15 of v0 from lanes 0..7 of the second row, lanes 0..7 of v1 from lanes 8..15 of
+        // the first
+        x.u[w] = __builtin_amdgcn_update_dpp(a.u[w], b.u[w], 0x118, 0xf, 0xc, false);   // row_shr:8
+        y.u[w] = __builtin_amdgcn_update_dpp(b.u[w], a.u[w], 0x108, 0xf, 0x3, false);   // row_shl:8
+    }
+    v0 = x.d;
+    v1 = y.d;
 }
 
 }  // namespace dmrg
