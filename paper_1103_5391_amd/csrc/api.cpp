@@ -23,13 +23,13 @@ namespace dmrg {
 
 hipError_t launch_stage1(int, int, const S1Block*, const Tile*, int, const ProbPtrs*, ProbPtrs,
                          hipStream_t);
-hipError_t launch_stage2(int, int, const S2Block*, const Segment*, const Tile*, int,
+hipError_t launch_stage2(int, int, const S2Block*, const XChunk*, const Tile*, int,
                          const ProbPtrs*, ProbPtrs, hipStream_t);
-hipError_t launch_stage2_mr(const S2Block*, const Segment*, const Tile*, int, const ProbPtrs*,
+hipError_t launch_stage2_mr(const S2Block*, const XChunk*, const Tile*, int, const ProbPtrs*,
                             hipStream_t);
 hipError_t launch_stage1_lds(int, const S1Block*, const LItem1*, int, const ProbPtrs*, ProbPtrs,
                              hipStream_t);
-hipError_t launch_stage2_lds(int, const S2Block*, const Segment*, const LItem2*, int, const LRed*,
+hipError_t launch_stage2_lds(int, const S2Block*, const XChunk*, const LItem2*, int, const LRed*,
                              int, const ProbPtrs*, ProbPtrs, double*, hipStream_t);
 hipError_t launch_stage1_x(const S1Block*, const LItem1*, int, const S2Block*, const XZero*, int,
                            const ProbPtrs*, ProbPtrs, hipStream_t);
@@ -140,8 +140,8 @@ struct HostBuf {
 // register-tiled kernels (gemm.hip), tile lists of the LDS-tiled kernels (gemm_lds.hip) and
 // their partial-tile workspace.
 struct Lists {
-    DevBuf dS1[2], dS2[2], dSeg[2], dT1, dT1n, dT2, dT2n, dL1, dL2[2], dLred[2], dPart;
-    DevBuf dXch, dX2, dXz;    // LDS-staged family: chunk tables, stage-2 items, zeroed regions
+    DevBuf dS1[2], dS2[2], dXch[2], dT1, dT1n, dT2, dT2n, dL1, dL2[2], dLred[2], dPart;
+    DevBuf dX2, dXz;          // LDS-staged family: stage-2 items, zeroed regions
     DevBuf dKX, dKP, dKS1, dKE, dKT1, dKS2, dKC, dKT2;   // K-split family
     int nt1 = 0, nt1n = 0, nt2 = 0, nt2n = 0, nl1 = 0, nl2[2] = {0, 0}, nred[2] = {0, 0};
     int nx2 = 0, nxz = 0;
@@ -165,18 +165,17 @@ hipError_t upload(DevBuf& b, const std::vector<T>& v, hipStream_t s) {
 
 // Uploads the work lists of one launch set; k indexes the chunk depth (0: 16, 1: 32).
 hipError_t upload_lists(Lists& W, const std::vector<S1Block>* s1, const std::vector<S2Block>* s2,
-                        const std::vector<Segment>* segs, const std::vector<Tile>& t1,
+                        const std::vector<XChunk>* xch, const std::vector<Tile>& t1,
                         const std::vector<Tile>& t1n, const std::vector<Tile>& t2,
                         const std::vector<Tile>& t2n, const std::vector<LItem1>& l1,
                         const std::vector<LItem2>* l2, const std::vector<LRed>* lred,
-                        const int* nslots, const std::vector<XChunk>& xch,
-                        const std::vector<XItem2>& x2, const std::vector<XZero>& xz,
+                        const int* nslots, const std::vector<XItem2>& x2, const std::vector<XZero>& xz,
                         const KLists& kf, hipStream_t st) {
     hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
         e = upload(W.dS1[k], s1[k], st);
         if (e == hipSuccess) e = upload(W.dS2[k], s2[k], st);
-        if (e == hipSuccess) e = upload(W.dSeg[k], segs[k], st);
+        if (e == hipSuccess) e = upload(W.dXch[k], xch[k], st);
         if (e == hipSuccess) e = upload(W.dL2[k], l2[k], st);
         if (e == hipSuccess) e = upload(W.dLred[k], lred[k], st);
     }
@@ -185,7 +184,6 @@ hipError_t upload_lists(Lists& W, const std::vector<S1Block>* s1, const std::vec
     if (e == hipSuccess) e = upload(W.dT2, t2, st);
     if (e == hipSuccess) e = upload(W.dT2n, t2n, st);
     if (e == hipSuccess) e = upload(W.dL1, l1, st);
-    if (e == hipSuccess) e = upload(W.dXch, xch, st);
     if (e == hipSuccess) e = upload(W.dX2, x2, st);
     if (e == hipSuccess) e = upload(W.dXz, xz, st);
     W.nx2 = (int)x2.size();
@@ -239,7 +237,7 @@ hipError_t run_stage(const Lists& W, int stage, int variant, int prec, const Pro
                 return launch_stage1_x(W.dS1[0].as<S1Block>(), W.dL1.as<LItem1>(), W.nl1,
                                        W.dS2[0].as<S2Block>(), W.dXz.as<XZero>(), W.nxz, probs,
                                        single, s);
-            return launch_stage2_x(W.dS2[0].as<S2Block>(), W.dXch.as<XChunk>(), W.dX2.as<XItem2>(),
+            return launch_stage2_x(W.dS2[0].as<S2Block>(), W.dXch[0].as<XChunk>(), W.dX2.as<XItem2>(),
                                    W.nx2, probs, single, s);
         }
         variant = 0;
@@ -255,13 +253,13 @@ hipError_t run_stage(const Lists& W, int stage, int variant, int prec, const Pro
                              single, s);
     }
     if (variant & DMRG_GEMM_STAGE2_LDS)
-        return launch_stage2_lds(prec, W.dS2[pk].as<S2Block>(), W.dSeg[pk].as<Segment>(),
+        return launch_stage2_lds(prec, W.dS2[pk].as<S2Block>(), W.dXch[pk].as<XChunk>(),
                                  W.dL2[pk].as<LItem2>(), W.nl2[pk], W.dLred[pk].as<LRed>(),
                                  W.nred[pk], probs, single, W.dPart.as<double>(), s);
     if (variant & DMRG_GEMM_STAGE2_NARROW)
-        return launch_stage2(prec, 1, W.dS2[pk].as<S2Block>(), W.dSeg[pk].as<Segment>(),
+        return launch_stage2(prec, 1, W.dS2[pk].as<S2Block>(), W.dXch[pk].as<XChunk>(),
                              W.dT2n.as<Tile>(), W.nt2n, probs, single, s);
-    return launch_stage2(prec, 0, W.dS2[pk].as<S2Block>(), W.dSeg[pk].as<Segment>(),
+    return launch_stage2(prec, 0, W.dS2[pk].as<S2Block>(), W.dXch[pk].as<XChunk>(),
                          W.dT2.as<Tile>(), W.nt2, probs, single, s);
 }
 
@@ -273,7 +271,7 @@ hipError_t run_stages(const Lists& W, int prec, const ProbPtrs* probs, ProbPtrs 
     if (W.mr && probs && prec == DMRG_FP64 &&
         W.variant == (DMRG_GEMM_STAGE1_NARROW | DMRG_GEMM_STAGE2_NARROW)) {
         const Lists& M = *W.mr;
-        return launch_stage2_mr(M.dS2[0].as<S2Block>(), M.dSeg[0].as<Segment>(),
+        return launch_stage2_mr(M.dS2[0].as<S2Block>(), M.dXch[0].as<XChunk>(),
                                 M.dT2n.as<Tile>(), M.nt2n, probs, s);
     }
     return run_stage(W, 2, W.variant, prec, probs, single, s);
@@ -368,6 +366,7 @@ struct Group {
     Lists* lists = nullptr;                    // the handle's own, or the batch's merged lists
     DevBuf dVP, dBmap, dBmapR, dProbs, dIO;    // VecProb, block maps (streaming, reduction passes),
                                                // ProbPtrs[kMaxKrylov][nprob], IO
+    std::vector<ProbPtrs> pp;                  // host copy of dProbs when there is one problem
     VecGroup vg{};
     int prec = -1;                             // precision the tables were built for
     std::vector<uint64_t> gens;                // member workspace generations of the tables
@@ -609,6 +608,7 @@ int group_prepare(Group& g, int kdim) {
     if (np > 1) HIP_TRY(h0, upload(g.dBmap, bmap, h0->stream));
     if (np > 1) HIP_TRY(h0, upload(g.dBmapR, bmapr, h0->stream));
     HIP_TRY(h0, upload(g.dProbs, pp, h0->stream));
+    g.pp = np == 1 ? pp : std::vector<ProbPtrs>();
     g.vg = VecGroup{g.dVP.as<VecProb>(), np > 1 ? g.dBmap.as<int>() : nullptr,
                     np > 1 ? g.dBmapR.as<int>() : nullptr, np, b0, b0r, 4,
                     np == 1 ? vp[0] : VecProb{}};
@@ -620,6 +620,11 @@ int group_prepare(Group& g, int kdim) {
 
 // Both block-product launches of Lanczos iteration j for every problem of the group.
 int group_matvec(Group& g, int j, hipStream_t s) {
+    // one problem: its pointers travel with the launch, saving the kernels a dependent load
+    if (g.hs.size() == 1) {
+        HIP_TRY(g.hs[0], run_stages(*g.lists, g.prec, nullptr, g.pp[j], s));
+        return DMRG_OK;
+    }
     const ProbPtrs* probs = g.dProbs.as<ProbPtrs>() + (size_t)j * g.hs.size();
     HIP_TRY(g.hs[0], run_stages(*g.lists, g.prec, probs, ProbPtrs{}, s));
     return DMRG_OK;
@@ -764,9 +769,9 @@ int chains_set(std::unique_ptr<dmrg_batch_ctx>& cs, const std::vector<dmrg_ctx*>
             }
         Merged M;
         merge_plans(plans, M);
-        hipError_t e = upload_lists(c->lists, M.s1, M.s2, M.segs, M.tiles1, M.tiles1n,
+        hipError_t e = upload_lists(c->lists, M.s1, M.s2, M.xch, M.tiles1, M.tiles1n,
                                     M.tiles2, M.tiles2n, M.l1, M.l2, M.lred, M.nslots,
-                                    M.xch, M.x2, M.xz, M.kf, h0->stream);
+                                    M.x2, M.xz, M.kf, h0->stream);
         if (e == hipSuccess) {
             // the owners' lists for the shared-operator stage 2 (problem i = owner i)
             static_assert(kChains == kMultiRhs, "chain c of owner i is problem kChains i + c");
@@ -774,8 +779,8 @@ int chains_set(std::unique_ptr<dmrg_batch_ctx>& cs, const std::vector<dmrg_ctx*>
             for (dmrg_ctx* h : owners) own.push_back(&h->plan);
             Merged O;
             merge_plans(own, O);
-            e = upload_lists(c->mrl, O.s1, O.s2, O.segs, O.tiles1, O.tiles1n, O.tiles2,
-                             O.tiles2n, O.l1, O.l2, O.lred, O.nslots, O.xch, O.x2, O.xz, O.kf,
+            e = upload_lists(c->mrl, O.s1, O.s2, O.xch, O.tiles1, O.tiles1n, O.tiles2,
+                             O.tiles2n, O.l1, O.l2, O.lred, O.nslots, O.x2, O.xz, O.kf,
                              h0->stream);
             c->lists.mr = &c->mrl;
         }
@@ -1372,12 +1377,12 @@ int dmrg_create(const dmrg_problem* problem, void* stream, dmrg_handle* out) {
     {
         const std::vector<S1Block> s1[2] = {P.pk16.s1, P.pk32.s1};
         const std::vector<S2Block> s2[2] = {P.pk16.s2, P.pk32.s2};
-        const std::vector<Segment> sg[2] = {P.pk16.segs, P.pk32.segs};
+        const std::vector<XChunk> xc[2] = {P.pk16.xch, P.pk32.xch};
         const std::vector<LItem2> l2[2] = {P.pk16.l2, P.pk32.l2};
         const std::vector<LRed> lr[2] = {P.pk16.lred, P.pk32.lred};
         const int ns[2] = {P.pk16.nslots, P.pk32.nslots};
-        e = upload_lists(h->lists, s1, s2, sg, P.tiles1, P.tiles1n, P.tiles2, P.tiles2n, P.l1, l2,
-                         lr, ns, P.pk16.xch, P.pk16.x2, P.pk16.xz, P.kf, h->stream);
+        e = upload_lists(h->lists, s1, s2, xc, P.tiles1, P.tiles1n, P.tiles2, P.tiles2n, P.l1, l2,
+                         lr, ns, P.pk16.x2, P.pk16.xz, P.kf, h->stream);
     }
     if (e == hipSuccess) e = h->ws[0].dT.alloc(sizeof(double) * (size_t)P.T_size);
     // the padding rows of the stage-1 workspace are read (times zero factors) but never
@@ -1463,7 +1468,7 @@ int dmrg_plan_stats(const dmrg_problem* problem, int32_t kdim, dmrg_plan_info* o
         for (const Packing* pk : {&P.pk16, &P.pk32}) {
             add(pk->s1.size() * sizeof(S1Block));
             add(pk->s2.size() * sizeof(S2Block));
-            add(pk->segs.size() * sizeof(Segment));
+            add(pk->xch.size() * sizeof(XChunk));
             add(pk->l2.size() * sizeof(LItem2));
             add(pk->lred.size() * sizeof(LRed));
         }
@@ -1472,7 +1477,6 @@ int dmrg_plan_stats(const dmrg_problem* problem, int32_t kdim, dmrg_plan_info* o
         add(P.tiles2.size() * sizeof(Tile));
         add(P.tiles2n.size() * sizeof(Tile));
         add(P.l1.size() * sizeof(LItem1));
-        add(P.pk16.xch.size() * sizeof(XChunk));
         add(P.pk16.x2.size() * sizeof(XItem2));
         add(P.pk16.xz.size() * sizeof(XZero));
         add(P.kf.xblk.size() * sizeof(KXBlock));
@@ -1973,8 +1977,8 @@ int dmrg_batch_create(const dmrg_handle* handles, int32_t count, dmrg_batch* out
         Merged M;
         merge_plans(plans, M);
         b->lists.variant = h0->lists.variant;
-        const hipError_t e = upload_lists(b->lists, M.s1, M.s2, M.segs, M.tiles1, M.tiles1n, M.tiles2,
-                                          M.tiles2n, M.l1, M.l2, M.lred, M.nslots, M.xch, M.x2,
+        const hipError_t e = upload_lists(b->lists, M.s1, M.s2, M.xch, M.tiles1, M.tiles1n, M.tiles2,
+                                          M.tiles2n, M.l1, M.l2, M.lred, M.nslots, M.x2,
                                           M.xz, M.kf, h0->stream);
         if (e != hipSuccess) {
             delete b;

@@ -33,6 +33,12 @@
 
 namespace dmrg {
 
+// Whether the problem's work is skipped (after a breakdown): a scalar load, tested after the first
+// operand loads have been issued.
+__device__ __forceinline__ int skip_of(const ProbPtrs& pp) {
+    return pp.skip ? *(const __attribute__((address_space(4))) int*)pp.skip : 0;
+}
+
 // ---------------------------------------------------------------------------------------
 // stage 1: one tile of 16 rows of both planes x 16 NJ columns (NJ = 4 wide, 2 narrow) per
 // single-wavefront work group
@@ -66,6 +72,7 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
     using ws_t = typename P::ws_t;
     using acc_t = typename P::acc_t;
     using frag_t = typename P::frag_t;
+    const int skip = skip_of(P_);
     const int lane = threadIdx.x;
     const int g = lane >> 4, r = lane & 15;
     const double* __restrict__ X = P_.x;
@@ -133,6 +140,7 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
         // two register buffers, the next chunk always in flight (as in the stage-2 loop)
         Chunk k0, k1;
         load(0, k0);
+        if (skip) return false;
         int c = 0;
         for (; c + 1 < nch; c += 2) {
             load(c + 1, k1);
@@ -143,11 +151,9 @@ __device__ __forceinline__ void stage1_tile(const Tile& tl, const S1Block& B, co
             mma(k1);
         }
         if (c < nch) mma(k0);
+        return true;
     };
-    if (whole)
-        run(std::true_type{});
-    else
-        run(std::false_type{});
+    if (!(whole ? run(std::true_type{}) : run(std::false_type{}))) return;
     // whole fragments, padding columns (never read) and rows (zero) included
 #pragma unroll
     for (int v = 0; v < 4; ++v)
@@ -178,14 +184,13 @@ __global__ __launch_bounds__(64, NJ > 2 ? 2 : 3) void stage1(const S1Block* __re
     if (tl.blk < 0) return;   // padding of the XCD-ordered list
     const S1Block B = blks[tl.blk];
     const ProbPtrs P_ = probs ? probs[B.prob] : single;
-    if (P_.skip && *P_.skip) return;
     stage1_tile<P, NJ>(tl, B, P_);
 }
 
 // ---------------------------------------------------------------------------------------
 // stage 2: one 32 x 32 (or 32 x 16) tile per work group, K chunks dealt round-robin to its waves
 // ---------------------------------------------------------------------------------------
-constexpr int kChunkTab = 256;   // workspace chunks of a block addressed through the LDS table
+constexpr int kChunkTab = 64 * kWaves;   // entries of the chunk table in LDS (one per thread)
 // D: element type of the data operand as it is loaded; it is converted to the MFMA input type when
 // it is multiplied (a conversion beside the load would wait for it there).
 template <class P, int MI, int NJ, typename D>
@@ -199,12 +204,17 @@ struct Chunk2 {
         return P::from(v);
     }
 };
-template <class P, int MI, int NJ, typename D, class Load>
-__device__ __forceinline__ void kloop(typename P::acc_t (&acc)[MI][NJ], int c0, int step, int nch,
-                                      Load load) {
-    if (c0 >= nch) return;
+// Chunks c0, c0 + step, ... below nch.  mid() runs once, after the first chunk's load where
+// `early` (that load does not depend on it), else before it; false from it ends the tile.
+template <class P, int MI, int NJ, typename D, class Load, class Mid>
+__device__ __forceinline__ bool kloop(typename P::acc_t (&acc)[MI][NJ], int c0, int step, int nch,
+                                      Load load, bool early, Mid mid) {
     const int last = c0 + (nch - 1 - c0) / step * step;
     Chunk2<P, MI, NJ, D> k0, k1;
+    if (early && c0 < nch) load(c0, k0);
+    if (!mid()) return false;
+    if (c0 >= nch) return true;
+    if (!early) load(c0, k0);
     auto mma = [&](const Chunk2<P, MI, NJ, D>& k) {
         typename P::frag_t fb[NJ];
 #pragma unroll
@@ -218,7 +228,6 @@ __device__ __forceinline__ void kloop(typename P::acc_t (&acc)[MI][NJ], int c0, 
     // multiplied is always in flight (the last prefetch is clamped and unused).  The
     // scheduling barriers keep each prefetch ahead of the products it overlaps; without them
     // the compiler moved the loads down to their products and waited for them there.
-    load(c0, k0);
     int c = c0;
     for (; c + step <= last; c += 2 * step) {
         load(c + step, k1);
@@ -229,13 +238,14 @@ __device__ __forceinline__ void kloop(typename P::acc_t (&acc)[MI][NJ], int c0, 
         mma(k1);
     }
     if (c <= last) mma(k0);   // odd count: chunk c is in k0
+    return true;
 }
 
 // One 16 MI x 16 NJ output tile (MI = 2, or 1 for a half-height tile) per work group of NW
 // wavefronts (K chunks dealt round-robin); ctab and red live in the kernel's LDS.
 template <class P, int MI, int NJ, int NW>
 __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
-                                            const Segment* __restrict__ segs, const ProbPtrs& P_,
+                                            const XChunk* __restrict__ xch, const ProbPtrs& P_,
                                             int64_t (&ctab)[kChunkTab][3],
                                             double (&red)[NW][16 * NJ][kTile + 1]) {
     using op_t = typename P::op_t;
@@ -243,6 +253,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
     using acc_t = typename P::acc_t;
     using frag_t = typename P::frag_t;
     constexpr int TN = 16 * NJ;
+    const int skip = skip_of(P_);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
     const int g = lane >> 4, r = lane & 15;
@@ -268,80 +279,76 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int nj = 0; nj < NJ; ++nj) zero<P>(acc[mi][nj]);
-    // pass 1: segment 0, the diagonal H_S term, reads the block itself from the input vector
-    const Segment s0 = segs[B.seg0];
-    const int nch0 = (s0.K + P::CK - 1) / P::CK;
-    {
-        int64_t bcol[NJ];
+    // segment 0, the diagonal H_S term, reads the block itself from the input vector; the other
+    // chunks read the workspace, their sources from the block's chunk table, kept in LDS (the
+    // first kChunkTab entries, the next ones when those are done)
+    const int K0 = B.M, nch0 = (K0 + P::CK - 1) / P::CK;
+    const int nT = B.nch - nch0;
+    const XChunk* __restrict__ tab = xch + B.ctab0 + nch0;
+    XChunk e{};
+    if ((int)threadIdx.x < min(nT, kChunkTab)) e = tab[threadIdx.x];
+    auto fill = [&] {
+        if (skip) return false;          // the same in every wave
+        ctab[threadIdx.x][0] = e.off;
+        ctab[threadIdx.x][1] = e.poff;
+        ctab[threadIdx.x][2] = ((int64_t)e.col0 << 32) | (uint32_t)e.ld;
+        __syncthreads();
+        return true;
+    };
+    int64_t bcol[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+        bcol[j] = B.Y.off + pl[j] * B.Y.poff + (int64_t)col[j] * B.Y.ld;
+    auto load_a = [&](int c, auto& k) {
+        const int64_t ga = (int64_t)c * chunk_elems<P>();
+#pragma unroll
+        for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
+    };
+    auto load_x = [&](int c, Chunk2<P, MI, NJ, double>& k) {
+        load_a(c, k);
+        // a lane's values lie in a line of its own: half the loads where the chunk is whole
+        if ((c + 1) * P::CK <= K0) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) load_pairs<P>(P_.x, bcol[j], c * P::CK, g, k.b[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                load_clamped<P>(P_.x, bcol[j], c * P::CK, g, K0, 1, k.b[j]);
+        }
+    };
+    int tc = nch0;      // chunk of the table's first entry
+    auto load_t = [&](int c, Chunk2<P, MI, NJ, ws_t>& k) {
+        load_a(c, k);
+        const int64_t* q = ctab[c - tc];
+        const int ld = (int)q[2], col0 = (int)(q[2] >> 32);
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            bcol[j] = s0.B.off + pl[j] * s0.B.poff + (int64_t)col[j] * s0.B.ld;
+            load_units<P>(Tws, q[0] + (pl[j] ? q[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g,
+                          k.b[j]);
+    };
+    const int end0 = min(B.nch, nch0 + kChunkTab);
+    if constexpr (std::is_same<ws_t, double>::value) {
+        // one stream of both kinds
         auto load = [&](int c, Chunk2<P, MI, NJ, double>& k) {
-            const int64_t ga = (int64_t)c * chunk_elems<P>();
-#pragma unroll
-            for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
-            // a lane's values lie in a line of its own: half the loads where the chunk is whole
-            if ((c + 1) * P::CK <= s0.K) {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) load_pairs<P>(P_.x, bcol[j], c * P::CK, g, k.b[j]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    load_clamped<P>(P_.x, bcol[j], c * P::CK, g, s0.K, 1, k.b[j]);
-            }
+            if (c < nch0)
+                load_x(c, k);
+            else
+                load_t(c, k);
         };
-        kloop<P, MI, NJ, double>(acc, wave, NW, nch0, load);
-    }
-    // pass 2: every workspace chunk of segments 1.. in one pipelined stream per wave (global
-    // chunk c goes to wave c mod NW), its source view read from a per-chunk table in LDS (built
-    // once per work group) instead of restarting the pipeline at every segment
-    // ctab: per workspace chunk off - ch0 CK, poff, ld
-    const int nT = B.nch - nch0;
-    if (nT > 0 && nT <= kChunkTab) {
-        for (int t = threadIdx.x; t < nT; t += blockDim.x) {
-            const int c = nch0 + t;
-            int si = 1;
-            Segment sg = segs[B.seg0 + 1];
-            while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-            ctab[t][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
-            ctab[t][1] = sg.B.poff;
-            ctab[t][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
-        }
-        __syncthreads();
-        auto load = [&](int c, Chunk2<P, MI, NJ, ws_t>& k) {
-            const int64_t ga = (int64_t)c * chunk_elems<P>();
-#pragma unroll
-            for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
-            const int64_t* e = ctab[c - nch0];
-            const int ld = (int)e[2], col0 = (int)(e[2] >> 32);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                load_units<P>(Tws, e[0] + (pl[j] ? e[1] : 0) + tpos<ws_t>(ld, col0 + col[j], 0), g,
-                              k.b[j]);
-        };
-        // first chunk >= nch0 owned by this wave
-        const int cw = nch0 + ((wave - nch0) % NW + NW) % NW;
-        kloop<P, MI, NJ, ws_t>(acc, cw, NW, B.nch, load);
+        if (!kloop<P, MI, NJ, double>(acc, wave, NW, end0, load, wave < nch0, fill)) return;
     } else {
-        // very long K: one pipeline per segment
-        for (int s = 1; s < B.nseg; ++s) {
-            const Segment sg = segs[B.seg0 + s];
-            int64_t bcol[NJ];
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                bcol[j] = sg.B.off + pl[j] * sg.B.poff + tpos<ws_t>(sg.B.ld, sg.col0 + col[j], 0);
-            const int nch = (sg.K + P::CK - 1) / P::CK;
-            const int c0 = ((wave - sg.ch0) % NW + NW) % NW;
-            auto load = [&](int c, Chunk2<P, MI, NJ, ws_t>& k) {
-                const int64_t ga = (int64_t)(sg.ch0 + c) * chunk_elems<P>();
-#pragma unroll
-                for (int i = 0; i < MI; ++i) k.a[i] = P::load_op(pa[i] + ga);
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    load_units<P>(Tws, bcol[j] + (int64_t)c * (16 * P::CK), g, k.b[j]);
-            };
-            kloop<P, MI, NJ, ws_t>(acc, c0, NW, nch, load);
-        }
+        if (!kloop<P, MI, NJ, double>(acc, wave, NW, nch0, load_x, true, fill)) return;
+        kloop<P, MI, NJ, ws_t>(acc, nch0 + ((wave - nch0) % NW + NW) % NW, NW, end0, load_t, true,
+                               [] { return true; });
+    }
+    for (int c1 = end0; c1 < B.nch; c1 += kChunkTab) {
+        __syncthreads();                 // every wave is done with the table
+        tc = c1;
+        if ((int)threadIdx.x < B.nch - c1) e = tab[c1 - nch0 + threadIdx.x];
+        fill();
+        kloop<P, MI, NJ, ws_t>(acc, c1 + ((wave - c1) % NW + NW) % NW, NW,
+                               min(B.nch, c1 + kChunkTab), load_t, true,
+                               [] { return true; });
     }
 
 #pragma unroll
@@ -374,7 +381,7 @@ __device__ __forceinline__ void stage2_tile(const Tile& tl, const S2Block& B,
 
 template <class P, int NJ, int NW>
 __global__ __launch_bounds__(64 * NW, 3) void stage2(const S2Block* __restrict__ blks,
-                                                     const Segment* __restrict__ segs,
+                                                     const XChunk* __restrict__ xch,
                                                      const Tile* __restrict__ tiles,
                                                      const ProbPtrs* __restrict__ probs,
                                                      ProbPtrs single) {
@@ -382,13 +389,12 @@ __global__ __launch_bounds__(64 * NW, 3) void stage2(const S2Block* __restrict__
     if (tl.blk < 0) return;   // padding of the XCD-ordered list
     const S2Block B = blks[tl.blk];
     const ProbPtrs P_ = probs ? probs[B.prob] : single;
-    if (P_.skip && *P_.skip) return;
     __shared__ int64_t ctab[kChunkTab][3];
     __shared__ double red[NW][16 * NJ][kTile + 1];
     if (tl.half)
-        stage2_tile<P, 1, NJ, NW>(tl, B, segs, P_, ctab, red);
+        stage2_tile<P, 1, NJ, NW>(tl, B, xch, P_, ctab, red);
     else
-        stage2_tile<P, 2, NJ, NW>(tl, B, segs, P_, ctab, red);
+        stage2_tile<P, 2, NJ, NW>(tl, B, xch, P_, ctab, red);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -444,7 +450,7 @@ __device__ __forceinline__ void kloop_mr(typename P::acc_t (&acc)[NR][MI][NJ], i
 
 template <class P, int MI, int NJ, int NW, int NR>
 __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
-                                               const Segment* __restrict__ segs,
+                                               const XChunk* __restrict__ xch,
                                                const ProbPtrs (&PP)[NR], const bool (&act)[NR],
                                                int64_t (&ctab)[kChunkTab][3],
                                                double (&red)[NW][16 * NJ][kTile + 1]) {
@@ -478,14 +484,24 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int nj = 0; nj < NJ; ++nj) zero<P>(acc[q][mi][nj]);
-    // pass 1: segment 0 (H_S) from each chain's input vector
-    const Segment s0 = segs[B.seg0];
-    const int nch0 = (s0.K + P::CK - 1) / P::CK;
+    // segment 0 (H_S) from each chain's input vector, then the workspace chunks from each chain's
+    // stage-1 intermediate (sources in the chunk table, as in the single-vector kernel)
+    const int K0 = B.M, nch0 = (K0 + P::CK - 1) / P::CK;
+    const XChunk* __restrict__ tab = xch + B.ctab0 + nch0;
+    auto fill = [&](int c1) {
+        if ((int)threadIdx.x < min(B.nch - c1, kChunkTab)) {
+            const XChunk e = tab[c1 - nch0 + threadIdx.x];
+            ctab[threadIdx.x][0] = e.off;
+            ctab[threadIdx.x][1] = e.poff;
+            ctab[threadIdx.x][2] = ((int64_t)e.col0 << 32) | (uint32_t)e.ld;
+        }
+        __syncthreads();
+    };
     {
         int64_t bcol[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            bcol[j] = s0.B.off + pl[j] * s0.B.poff + (int64_t)col[j] * s0.B.ld;
+            bcol[j] = B.Y.off + pl[j] * B.Y.poff + (int64_t)col[j] * B.Y.ld;
         auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NR][NJ]) {
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
@@ -495,30 +511,20 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     double v[P::KPL];
-                    load_clamped<P>(PP[q].x, bcol[j], c * P::CK, g, s0.K, 1, v);
+                    load_clamped<P>(PP[q].x, bcol[j], c * P::CK, g, K0, 1, v);
                     fb[q][j] = P::from(v);
                 }
         };
         kloop_mr<P, MI, NJ, NR>(acc, wave, NW, nch0, load);
     }
-    // pass 2: the workspace chunks of segments 1.. from each chain's stage-1 intermediate
-    const int nT = B.nch - nch0;
-    if (nT > 0 && nT <= kChunkTab) {
-        for (int t = threadIdx.x; t < nT; t += blockDim.x) {
-            const int c = nch0 + t;
-            int si = 1;
-            Segment sg = segs[B.seg0 + 1];
-            while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-            ctab[t][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
-            ctab[t][1] = sg.B.poff;
-            ctab[t][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
-        }
-        __syncthreads();
+    for (int c1 = nch0; c1 < B.nch; c1 += kChunkTab) {
+        if (c1 > nch0) __syncthreads();
+        fill(c1);
         auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NR][NJ]) {
             const int64_t ga = (int64_t)c * chunk_elems<P>();
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-            const int64_t* e = ctab[c - nch0];
+            const int64_t* e = ctab[c - c1];
             const int ld = (int)e[2], col0 = (int)(e[2] >> 32);
 #pragma unroll
             for (int q = 0; q < NR; ++q)
@@ -530,32 +536,8 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
                     fb[q][j] = P::from(v);
                 }
         };
-        const int cw = nch0 + ((wave - nch0) % NW + NW) % NW;
-        kloop_mr<P, MI, NJ, NR>(acc, cw, NW, B.nch, load);
-    } else {
-        for (int s = 1; s < B.nseg; ++s) {
-            const Segment sg = segs[B.seg0 + s];
-            int64_t bcol[NJ];
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                bcol[j] = sg.B.off + pl[j] * sg.B.poff + tpos<ws_t>(sg.B.ld, sg.col0 + col[j], 0);
-            const int nch = (sg.K + P::CK - 1) / P::CK;
-            const int c0 = ((wave - sg.ch0) % NW + NW) % NW;
-            auto load = [&](int c, frag_t (&fa)[MI], frag_t (&fb)[NR][NJ]) {
-                const int64_t ga = (int64_t)(sg.ch0 + c) * chunk_elems<P>();
-#pragma unroll
-                for (int i = 0; i < MI; ++i) fa[i] = P::load_op(pa[i] + ga);
-    #pragma unroll
-                for (int q = 0; q < NR; ++q)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        double v[P::KPL];
-                        load_run<P>(static_cast<const ws_t*>(PP[q].T), bcol[j] + (int64_t)c * (16 * P::CK), g, v);
-                        fb[q][j] = P::from(v);
-                    }
-            };
-            kloop_mr<P, MI, NJ, NR>(acc, c0, NW, nch, load);
-        }
+        kloop_mr<P, MI, NJ, NR>(acc, c1 + ((wave - c1) % NW + NW) % NW, NW,
+                                min(B.nch, c1 + kChunkTab), load);
     }
     // the waves' partial tiles summed in LDS in a fixed order, one chain after another
     const View t0 = B.T0, yv = B.Y;
@@ -594,7 +576,7 @@ __device__ __forceinline__ void stage2_tile_mr(const Tile& tl, const S2Block& B,
 
 template <class P, int NJ, int NW, int NR>
 __global__ __launch_bounds__(64 * NW, 2) void stage2_mr(const S2Block* __restrict__ blks,
-                                                        const Segment* __restrict__ segs,
+                                                        const XChunk* __restrict__ xch,
                                                         const Tile* __restrict__ tiles,
                                                         const ProbPtrs* __restrict__ probs) {
     const Tile tl = tiles[blockIdx.x];
@@ -606,9 +588,9 @@ __global__ __launch_bounds__(64 * NW, 2) void stage2_mr(const S2Block* __restric
     __shared__ int64_t ctab[kChunkTab][3];
     __shared__ double red[NW][16 * NJ][kTile + 1];
     if (tl.half)
-        stage2_tile_mr<P, 1, NJ, NW, NR>(tl, B, segs, PP, act, ctab, red);
+        stage2_tile_mr<P, 1, NJ, NW, NR>(tl, B, xch, PP, act, ctab, red);
     else
-        stage2_tile_mr<P, 2, NJ, NW, NR>(tl, B, segs, PP, act, ctab, red);
+        stage2_tile_mr<P, 2, NJ, NW, NR>(tl, B, xch, PP, act, ctab, red);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -630,15 +612,15 @@ hipError_t launch1(int narrow, const S1Block* blks, const Tile* tiles, int ntile
 }
 
 template <class P>
-hipError_t launch2(int narrow, const S2Block* blks, const Segment* segs, const Tile* tiles,
+hipError_t launch2(int narrow, const S2Block* blks, const XChunk* xch, const Tile* tiles,
                    int ntiles, const ProbPtrs* probs, ProbPtrs single, hipStream_t st) {
     if (ntiles == 0) return hipSuccess;
     if (narrow)
         hipLaunchKernelGGL((stage2<P, kTile2NN / 16, kWaves>), dim3(ntiles), dim3(64 * kWaves), 0,
-                           st, blks, segs, tiles, probs, single);
+                           st, blks, xch, tiles, probs, single);
     else
         hipLaunchKernelGGL((stage2<P, kTile / 16, kWaves>), dim3(ntiles), dim3(64 * kWaves), 0, st,
-                           blks, segs, tiles, probs, single);
+                           blks, xch, tiles, probs, single);
     return hipGetLastError();
 }
 
@@ -646,14 +628,14 @@ hipError_t launch2(int narrow, const S2Block* blks, const Segment* segs, const T
 
 // Stage 2 of the chains of the 4-RHS mode in one launch (FP64, narrow tiles): the owners' tile
 // list, chain c of problem p at probs[kMultiRhs p + c].
-hipError_t launch_stage2_mr(const S2Block* blks, const Segment* segs, const Tile* tiles,
+hipError_t launch_stage2_mr(const S2Block* blks, const XChunk* xch, const Tile* tiles,
                             int ntiles, const ProbPtrs* probs, hipStream_t st) {
     if (ntiles == 0) return hipSuccess;
     // all chains in one work group (two per work group, with a second grid row for the other
     // two, measured the same)
     constexpr int NR = kMultiRhs;
     hipLaunchKernelGGL((stage2_mr<PF64, kTile2NN / 16, kWaves, NR>), dim3(ntiles, kMultiRhs / NR),
-                       dim3(64 * kWaves), 0, st, blks, segs, tiles, probs);
+                       dim3(64 * kWaves), 0, st, blks, xch, tiles, probs);
     return hipGetLastError();
 }
 
@@ -670,14 +652,14 @@ hipError_t launch_stage1(int prec, int narrow, const S1Block* blks, const Tile* 
 }
 
 // narrow: the tiles are kTile x kTile2NN (else kTile x kTile)
-hipError_t launch_stage2(int prec, int narrow, const S2Block* blks, const Segment* segs,
+hipError_t launch_stage2(int prec, int narrow, const S2Block* blks, const XChunk* xch,
                          const Tile* tiles, int ntiles, const ProbPtrs* probs, ProbPtrs single,
                          hipStream_t st) {
     switch (prec) {
-        case 0: return launch2<PF64>(narrow, blks, segs, tiles, ntiles, probs, single, st);
-        case 1: return launch2<PF32>(narrow, blks, segs, tiles, ntiles, probs, single, st);
-        case 2: return launch2<PBF3>(narrow, blks, segs, tiles, ntiles, probs, single, st);
-        default: return launch2<PBF6>(narrow, blks, segs, tiles, ntiles, probs, single, st);
+        case 0: return launch2<PF64>(narrow, blks, xch, tiles, ntiles, probs, single, st);
+        case 1: return launch2<PF32>(narrow, blks, xch, tiles, ntiles, probs, single, st);
+        case 2: return launch2<PBF3>(narrow, blks, xch, tiles, ntiles, probs, single, st);
+        default: return launch2<PBF6>(narrow, blks, xch, tiles, ntiles, probs, single, st);
     }
 }
 

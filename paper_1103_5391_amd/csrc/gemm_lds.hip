@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256, 3) void stage1_lds(const S1Block* __restrict__
 // ---------------------------------------------------------------------------------------
 template <class P>
 __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__ blks,
-                                                     const Segment* __restrict__ segs,
+                                                     const XChunk* __restrict__ xch,
                                                      const LItem2* __restrict__ items,
                                                      const ProbPtrs* __restrict__ probs,
                                                      ProbPtrs single, double* __restrict__ part) {
@@ -203,18 +203,15 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     // pass 1: chunks of segment 0 (the diagonal H_S term, read from the input vector, clamped
     // to the block and scaled like the workspace); pass 2: the workspace chunks, addressed
     // through a per-chunk table of source views (a slice has at most kLSlice chunks)
-    const Segment s0 = segs[B.seg0];
-    const int x_end = min(it.kc1, (s0.K + P::CK - 1) / P::CK);
+    const int K0 = B.M;
+    const int x_end = min(it.kc1, (K0 + P::CK - 1) / P::CK);
     const int t_beg = max(it.kc0, x_end);
     __shared__ int64_t ctab[kLSlice][3];   // per workspace chunk: off, poff, (col0, ld)
     if (tid < it.kc1 - t_beg) {
-        const int c = t_beg + tid;
-        int si = 1;
-        Segment sg = segs[B.seg0 + 1];
-        while (c >= sg.ch0 + (sg.K + P::CK - 1) / P::CK) sg = segs[B.seg0 + ++si];
-        ctab[tid][0] = sg.B.off + (int64_t)(c - sg.ch0) * (16 * P::CK);
-        ctab[tid][1] = sg.B.poff;
-        ctab[tid][2] = ((int64_t)sg.col0 << 32) | (uint32_t)sg.B.ld;
+        const XChunk e = xch[B.ctab0 + t_beg + tid];
+        ctab[tid][0] = e.off;
+        ctab[tid][1] = e.poff;
+        ctab[tid][2] = ((int64_t)e.col0 << 32) | (uint32_t)e.ld;
     }
     __syncthreads();
 
@@ -225,10 +222,10 @@ __global__ __launch_bounds__(256, 3) void stage2_lds(const S2Block* __restrict__
     auto load_a = [&](int c, int d) {
         if (a_on) ra[d] = P::load_op(pa + (int64_t)c * chunk_elems<P>());
     };
-    const int64_t xbase = s0.B.off + bpl * s0.B.poff + (int64_t)bcol * s0.B.ld;
+    const int64_t xbase = B.Y.off + bpl * B.Y.poff + (int64_t)bcol * B.Y.ld;
     auto load_x = [&](int c, int d) {
         load_a(c, d);
-        load_clamped<P>(P_.x, xbase, c * P::CK, bq, s0.K, 1, xb[d]);
+        load_clamped<P>(P_.x, xbase, c * P::CK, bq, K0, 1, xb[d]);
     };
     auto store_x = [&](int d) {
         if (a_on) sm.A[d][wave][lane] = ra[d];
@@ -339,11 +336,11 @@ hipError_t launch1l(const S1Block* blks, const LItem1* items, int nitems, const 
 }
 
 template <class P>
-hipError_t launch2l(const S2Block* blks, const Segment* segs, const LItem2* items, int nitems,
+hipError_t launch2l(const S2Block* blks, const XChunk* xch, const LItem2* items, int nitems,
                     const LRed* reds, int nred, const ProbPtrs* probs, ProbPtrs single,
                     double* part, hipStream_t st) {
     if (nitems == 0) return hipSuccess;
-    hipLaunchKernelGGL(stage2_lds<P>, dim3(nitems), dim3(256), 0, st, blks, segs, items, probs,
+    hipLaunchKernelGGL(stage2_lds<P>, dim3(nitems), dim3(256), 0, st, blks, xch, items, probs,
                        single, part);
     if (nred > 0)
         hipLaunchKernelGGL(stage2_reduce<typename P::ws_t>, dim3(nred), dim3(256), 0, st, blks,
@@ -363,15 +360,15 @@ hipError_t launch_stage1_lds(int prec, const S1Block* blks, const LItem1* items,
     }
 }
 
-hipError_t launch_stage2_lds(int prec, const S2Block* blks, const Segment* segs,
+hipError_t launch_stage2_lds(int prec, const S2Block* blks, const XChunk* xch,
                              const LItem2* items, int nitems, const LRed* reds, int nred,
                              const ProbPtrs* probs, ProbPtrs single, double* part,
                              hipStream_t st) {
     switch (prec) {
-        case 0: return launch2l<PF64>(blks, segs, items, nitems, reds, nred, probs, single, part, st);
-        case 1: return launch2l<PF32>(blks, segs, items, nitems, reds, nred, probs, single, part, st);
-        case 2: return launch2l<PBF3>(blks, segs, items, nitems, reds, nred, probs, single, part, st);
-        default: return launch2l<PBF6>(blks, segs, items, nitems, reds, nred, probs, single, part, st);
+        case 0: return launch2l<PF64>(blks, xch, items, nitems, reds, nred, probs, single, part, st);
+        case 1: return launch2l<PF32>(blks, xch, items, nitems, reds, nred, probs, single, part, st);
+        case 2: return launch2l<PBF3>(blks, xch, items, nitems, reds, nred, probs, single, part, st);
+        default: return launch2l<PBF6>(blks, xch, items, nitems, reds, nred, probs, single, part, st);
     }
 }
 

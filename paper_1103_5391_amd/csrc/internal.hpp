@@ -76,19 +76,32 @@ struct S1Block {
 //         every segment padded to whole chunks)
 //   T0: the H_E columns of T_b'
 struct S2Block {
-    int32_t M, N, prob, nseg;
-    int32_t seg0, nch;  // first segment, total K chunks of the packed factor
+    int32_t M, N, prob, nch;   // nch: total K chunks of the packed factor
+    int32_t ctab0, pad;        // entry of the block's first chunk in the chunk table
     int64_t Aoff;       // packed left-factor buffer
     View T0;            // into the workspace
     View Y;             // into the output vector
 };
 
-// One K segment of a stage-2 block: chunks ch0.. of Acat times the source view B (K x N).
+// One K segment of a stage-2 block (host): chunks ch0.. of Acat times the source view B (K x N).
 struct Segment {
     int32_t K, ch0;
     int32_t src;        // 0: the input vector (diagonal H_S term), 1: the workspace
     int32_t col0;       // first column of the source (workspace)
     View B;
+};
+
+// Source of one K chunk of a stage-2 block, one entry per chunk.  src 0, the input vector (rows <
+// K0 valid): element (k, column n of plane p) at off + p poff + n ld + k, k counted from the block's
+// first chunk; src 1, the workspace: the chunk at off + p poff of the panels (stride ld) from column
+// col0 on.  The work groups read their block's entries with one load: finding a chunk's segment in
+// a segment list took a chain of up to nine dependent loads before the first operand.
+struct XChunk {
+    int64_t off;
+    int64_t poff;
+    int32_t ld;
+    int32_t src;
+    int32_t col0, pad;
 };
 
 // One output tile of a register-tiled stage: columns n0.. of block blk and, in stage 1, rows
@@ -131,17 +144,6 @@ constexpr int kXTile2N = 32;        // stage-2 tile columns
 constexpr int kXSplitChunks = 40;   // stage-2 tiles with more 16-deep K chunks run as two slices
 constexpr int kXMaxItemChunks = 256;   // most chunks of one stage-2 item (its table in LDS); a
                                        // plan with longer items does not offer the family
-// Source of one 16-deep K chunk of a stage-2 block.  src 0, the input vector (rows < K0 valid):
-// element (k, column n of plane p) at off + p poff + n ld + k, k counted from the block's first
-// chunk; src 1, the workspace: the chunk at off + p poff of the panels (stride ld) from column
-// col0 on.
-struct XChunk {
-    int64_t off;
-    int64_t poff;
-    int32_t ld;
-    int32_t src;
-    int32_t col0, pad;
-};
 // One stage-2 work group: output tile (m0, n0) of block blk, K chunks [kc0, kc1); mode 0: the
 // whole K, y = T0 + product; 1: first slice, y += T0 + product (atomic); 2: second slice,
 // y += product (atomic).  ctab0: first entry of the block's chunk table.

@@ -349,7 +349,8 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
             s.M = B.d;
             s.N = 2 * B.e;
             s.prob = 0;
-            s.seg0 = (int)pk->segs.size();
+            pk->seg0.push_back((int)pk->segs.size());
+            s.pad = 0;
             s.Aoff = aoff;
             const std::vector<View>& tv = P.Tview[ck == kChunk ? 0 : 1];
             s.T0 = View{tv[bi].off, tv[bi].poff, tv[bi].ld, B.e};
@@ -365,8 +366,14 @@ std::string build_plan(const dmrg_problem* pb, Plan& P) {
                 pk->segs.push_back(Segment{Bs.d, nch, 1, ed.col, View{ts.off, ts.poff, ts.ld, B.e}});
                 nch += (Bs.d + ck - 1) / ck;
             }
-            s.nseg = (int)pk->segs.size() - s.seg0;
             s.nch = nch;
+            s.ctab0 = (int)pk->xch.size();
+            for (size_t si = pk->seg0.back(); si < pk->segs.size(); ++si) {
+                const Segment& sg = pk->segs[si];
+                for (int c = 0; c * ck < sg.K; ++c)
+                    pk->xch.push_back(XChunk{sg.B.off + (sg.src ? (int64_t)c * (16 * ck) : 0),
+                                             sg.B.poff, sg.B.ld, sg.src, sg.col0, 0});
+            }
             aoff += (int64_t)round_up(B.d, kLTile) * nch * ck;   // whole 64-row tiles
             pk->s2.push_back(s);
         }
@@ -535,23 +542,10 @@ void k_lists(Plan& P) {
 // into two slices of about equal length, and the output regions of the cut tiles.
 void x_lists(Plan& P) {
     Packing& pk = P.pk16;
-    pk.xch.clear();
     pk.x2.clear();
     pk.xz.clear();
     const int nb = (int)P.blocks.size();
     std::vector<double> w(nb, 0.0);
-    std::vector<int> ctab0(nb, 0);
-    for (int bi = 0; bi < nb; ++bi) {
-        const S2Block& s = pk.s2[bi];
-        ctab0[bi] = (int)pk.xch.size();
-        for (int si = 0; si < s.nseg; ++si) {
-            const Segment& sg = pk.segs[s.seg0 + si];
-            const int nc = (sg.K + pk.ck - 1) / pk.ck;
-            for (int c = 0; c < nc; ++c)
-                pk.xch.push_back(XChunk{sg.B.off + (sg.src ? (int64_t)c * 256 : 0), sg.B.poff, sg.B.ld,
-                                        sg.src, sg.col0, 0});
-        }
-    }
     auto panels = [](int v) { return (v + kPanel - 1) / kPanel; };
     for (int bi = 0; bi < nb; ++bi) {
         const S2Block& s = pk.s2[bi];
@@ -562,11 +556,11 @@ void x_lists(Plan& P) {
                 const double area = (double)std::min(4, panels(s.M - m0)) *
                                     std::min(2, panels(s.N - n0));
                 if (split) {
-                    pk.x2.push_back(XItem2{bi, m0, n0, 0, half, 1, ctab0[bi], 0});
-                    pk.x2.push_back(XItem2{bi, m0, n0, half, s.nch, 2, ctab0[bi], 0});
+                    pk.x2.push_back(XItem2{bi, m0, n0, 0, half, 1, s.ctab0, 0});
+                    pk.x2.push_back(XItem2{bi, m0, n0, half, s.nch, 2, s.ctab0, 0});
                     pk.xz.push_back(XZero{bi, m0, n0, 0});
                 } else {
-                    pk.x2.push_back(XItem2{bi, m0, n0, 0, s.nch, 0, ctab0[bi], 0});
+                    pk.x2.push_back(XItem2{bi, m0, n0, 0, s.nch, 0, s.ctab0, 0});
                 }
                 w[bi] += area * (s.nch + 2);
             }
@@ -638,17 +632,24 @@ void merge_plans(const std::vector<const Plan*>& plans, Merged& out) {
         const Plan& P = *plans[i];
         const Packing* pks[2] = {&P.pk16, &P.pk32};
         for (int k = 0; k < 2; ++k) {
-            const int soff = (int)out.segs[k].size();
+            const int coff = (int)out.xch[k].size();
             for (S1Block b : pks[k]->s1) {
                 b.prob = (int)i;
                 out.s1[k].push_back(b);
             }
             for (S2Block b : pks[k]->s2) {
                 b.prob = (int)i;
-                b.seg0 += soff;
+                b.ctab0 += coff;
                 out.s2[k].push_back(b);
             }
-            out.segs[k].insert(out.segs[k].end(), pks[k]->segs.begin(), pks[k]->segs.end());
+            out.xch[k].insert(out.xch[k].end(), pks[k]->xch.begin(), pks[k]->xch.end());
+            if (k == 0)
+                for (XItem2 t : pks[k]->x2)
+                    if (t.blk >= 0) {
+                        t.blk += boff;
+                        t.ctab0 += coff;
+                        x2.push_back(t);
+                    }
         }
         for (Tile t : P.tiles1)
             if (t.blk >= 0) t1.push_back(Tile{t.blk + boff, t.m0, t.n0, t.half});
@@ -666,14 +667,6 @@ void merge_plans(const std::vector<const Plan*>& plans, Merged& out) {
                 l1.push_back(t);
             }
         {
-            const int coff = (int)out.xch.size();
-            out.xch.insert(out.xch.end(), P.pk16.xch.begin(), P.pk16.xch.end());
-            for (XItem2 t : P.pk16.x2)
-                if (t.blk >= 0) {
-                    t.blk += boff;
-                    t.ctab0 += coff;
-                    x2.push_back(t);
-                }
             for (XZero z : P.pk16.xz) {
                 z.blk += boff;
                 out.xz.push_back(z);
@@ -792,7 +785,7 @@ void pack_operators(const Plan& P, int kind, std::vector<uint8_t>& A, std::vecto
             const auto& Bs = P.blocks[ed.src];
             const auto& t = P.terms[ed.term];
             const double c = t.coef * (t.fermionic ? P.S.parity(Bs.p) : 1);
-            const int kbase = pk.segs[s2.seg0 + si].ch0 * pk.ck;
+            const int kbase = pk.segs[pk.seg0[bi] + si].ch0 * pk.ck;
             for (int k = 0; k < Bs.d; ++k)
                 for (int i = 0; i < B.d; ++i) wa.put(s2.Aoff, i, kbase + k, s2.nch, c * ed.a.at(i, k));
             ++si;

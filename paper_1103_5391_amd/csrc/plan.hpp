@@ -70,16 +70,17 @@ struct Packing {
     int ck = 0;
     std::vector<S1Block> s1;
     std::vector<S2Block> s2;
-    std::vector<Segment> segs;
+    std::vector<Segment> segs;                 // per stage-2 block: segments seg0[b] .. seg0[b + 1]
+    std::vector<int> seg0;
+    std::vector<XChunk> xch;                   // chunk table of stage 2
     int64_t A_elems = 0, R_elems = 0;          // packed operator values
     // LDS-tiled stage 2: slice length (chunks), tile slices, reductions of split tiles
     int slice = 0;
     std::vector<LItem2> l2;
     std::vector<LRed> lred;
     int nslots = 0;                            // partial tiles
-    // LDS-staged family (16-deep chunks only): per-block chunk tables, stage-2 items, and the
-    // output regions its split items add into
-    std::vector<XChunk> xch;
+    // LDS-staged family (16-deep chunks only): stage-2 items, and the output regions its split
+    // items add into
     std::vector<XItem2> x2;
     std::vector<XZero> xz;
 };
@@ -137,14 +138,13 @@ std::string build_plan(const dmrg_problem* pb, Plan& plan);
 struct Merged {
     std::vector<S1Block> s1[2];               // per chunk depth (0: 16, 1: 32)
     std::vector<S2Block> s2[2];
-    std::vector<Segment> segs[2];
+    std::vector<XChunk> xch[2];
     std::vector<Tile> tiles1, tiles1n, tiles2, tiles2n;
     std::vector<LItem1> l1;
     std::vector<LItem2> l2[2];
     std::vector<LRed> lred[2];
     int nslots[2] = {0, 0};
-    std::vector<XChunk> xch;                  // LDS-staged family (16-deep chunks)
-    std::vector<XItem2> x2;
+    std::vector<XItem2> x2;                   // LDS-staged family (16-deep chunks)
     std::vector<XZero> xz;
     KLists kf;                                // K-split family
 };

@@ -12,9 +12,11 @@ QN = np.array([[0, 0], [0, 1], [1, 0], [1, 1]], dtype=np.int32)
 # sector dimensions of the two halves: 16 rows and columns make a panel and an FP64 chunk, 32 a
 # tile and a bf16 chunk, 64 the widest tile
 DIMS = [((1, 1, 1, 1), (1, 1, 1, 1)), ((15, 16, 17, 2), (17, 15, 1, 16)),
-        ((31, 32, 33, 48), (3, 33, 32, 31)), ((64, 65, 1, 47), (49, 1, 64, 65))]
+        ((31, 32, 33, 48), (3, 33, 32, 31)), ((64, 65, 1, 47), (49, 1, 64, 65)),
+        # K = 7 x about 700 in stage 2: more chunks than its table in LDS holds at once
+        ((700, 650, 720, 680), (3, 5, 2, 4))]
 VARIANTS = [0, 1, 2, 3, 4, 6, 8, 9, 12, 16, 32]
-# relative 2-norm bounds: K <= 5 * 65 terms of relative error 2^-53, 2^-24 (twice: the intermediate
+# relative 2-norm bounds: K <= 5000 terms of relative error 2^-53, 2^-24 (twice: the intermediate
 # is rounded too), and 2^-16 for two bf16 pieces
 BOUND = {0: 1e-13, 1: 2e-6, 2: 1e-4, 3: 2e-6}
 
@@ -39,7 +41,8 @@ def _half(dims, rng):
 def _problem(dims, seed=5):
     rng = np.random.default_rng(I.SEED_BASE + seed)
     S, E = _half(dims[0], rng), _half(dims[1], rng)
-    return I.Problem(S, E, (1, 1), [I.Bond((0, 1), (0, 1), 1.0, (0, 1))])
+    bonds = [I.Bond((0, 1), (0, 1), t, (0, 1)) for t in ((1.0, 0.5, 0.25) if max(dims[0]) > 500 else (1.0,))]
+    return I.Problem(S, E, (1, 1), bonds)
 
 
 @pytest.fixture(scope="module")
@@ -50,7 +53,7 @@ def env():
 
 
 @pytest.mark.parametrize("prec", [0, 1, 2, 3], ids=["fp64", "fp32", "bf16x3", "bf16x6"])
-@pytest.mark.parametrize("dims", DIMS, ids=["1", "16", "32", "64"])
+@pytest.mark.parametrize("dims", DIMS, ids=["1", "16", "32", "64", "long"])
 def test_products_at_tile_edges(env, dims, prec):
     torch, L = env
     pb = _problem(dims)
