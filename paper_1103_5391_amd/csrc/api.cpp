@@ -584,7 +584,7 @@ int group_prepare(Group& g, int kdim) {
     std::vector<VecProb> vp(np);
     std::vector<int> bmap, bmapr;
     std::vector<ProbPtrs> pp((size_t)kMaxKrylov * np);
-    int b0 = 0, b0r = 0;
+    int b0 = 0, b0r = 0, max_nbr = 0;
     for (int i = 0; i < np; ++i) {
         dmrg_ctx* h = g.hs[i];
         const int r = g.rhs[i];
@@ -593,6 +593,7 @@ int group_prepare(Group& g, int kdim) {
         double* V = W.dV.as<double>();
         KState* st = W.dState.as<KState>();
         const int nb = vec_blocks(n), nbr = red_blocks(n);
+        max_nbr = std::max(max_nbr, nbr);
         vp[i] = VecProb{V, W.dW.as<double>(), W.dPart.as<double>(), st, n, 2 * n, nb, b0,
                         nbr, b0r};
         bmap.insert(bmap.end(), nb, i);
@@ -610,7 +611,7 @@ int group_prepare(Group& g, int kdim) {
     HIP_TRY(h0, upload(g.dProbs, pp, h0->stream));
     g.pp = np == 1 ? pp : std::vector<ProbPtrs>();
     g.vg = VecGroup{g.dVP.as<VecProb>(), np > 1 ? g.dBmap.as<int>() : nullptr,
-                    np > 1 ? g.dBmapR.as<int>() : nullptr, np, b0, b0r, 4,
+                    np > 1 ? g.dBmapR.as<int>() : nullptr, np, b0, b0r, max_nbr, 4,
                     np == 1 ? vp[0] : VecProb{}};
     g.prec = prec;
     g.gens.resize(np);

@@ -26,6 +26,12 @@ constexpr int kDMaxQ = (kMaxKrylov + kDSlots - 1) / kDSlots;   // reduction laun
 #define DMRG_RED_ELEMS 2
 #endif
 constexpr int kRedElems = DMRG_RED_ELEMS;  // complex elements per thread of a reduction pass
+// Most partial rows (blocks of the largest problem times launches) of one iteration that every block
+// of the update pass sums itself; k_dsum does it where there are more.  Measured per Lanczos basis,
+// own sums against k_dsum: chain8 (n = 4900, 10 to 30 rows) 2.53 against 2.65 ms for its 10 bases,
+// the 400-state chain (n = 48600, 96 rows) 422 against 431 us, two launches of it (192 rows) 933
+// against 922 us for its 30-vector ground-state basis; at 300 rows the two are equal.
+constexpr int kDirectRows = 128;
 constexpr int kMaxTimes = 4;        // time points evaluated from one Krylov basis
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;   // device scratch per GPU of the
                                     // allocation-free entry point (the public header's
@@ -258,6 +264,7 @@ struct VecGroup {
     const int* bmapr;     // the same for the reduction pass [nblkr]
     int nprob, nblk;      // problems, blocks of a pass (sum of nb)
     int nblkr;            // blocks of a reduction pass (sum of nbr)
+    int max_nbr;          // most partial rows of one problem
     int combine_mult;     // blocks per pass block of the non-chained combination
     VecProb one;          // host copy of the descriptor when nprob == 1
 };

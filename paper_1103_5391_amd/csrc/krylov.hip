@@ -84,6 +84,15 @@ __device__ __forceinline__ double wave_sum(double v) {
     return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
 }
 
+// The largest of the 64 lanes' values, returned in every lane.
+__device__ __forceinline__ double wave_fmax(double v) {
+    v = fmax(v, dpp<0xB1>(v));
+    v = fmax(v, dpp<0x4E>(v));
+    v = fmax(v, dpp<0x141>(v));
+    v = fmax(v, dpp<0x140>(v));
+    return fmax(fmax(lane_read(v, 0), lane_read(v, 16)), fmax(lane_read(v, 32), lane_read(v, 48)));
+}
+
 // Where block blockIdx.x of a pass works: problem bmap[blockIdx.x / mult] (0 without a map),
 // block lb of the nbt = nb * mult blocks that pass gives that problem.
 struct Where {
@@ -413,10 +422,23 @@ __global__ __launch_bounds__(kVecThreads) void k_dreduce(const VecProb* vp, cons
     block_partials_scatter<NV, kDVals>(acc, W.p.part + (int64_t)q * kVecMaxBlocks * kDVals, W.lb);
 }
 
-// Lanczos iteration j: totals of the reduction launches.  Wave w of block (x, problem) sums
-// value v = 4 x + w of the nq * kDVals values over the nbr partial rows (fixed order: lane l
-// adds rows l, l + 64, ... in turn, then the wavefront sum) into the state; many blocks, so the
-// partial rows are read in parallel across the chip rather than through one compute unit.
+// Totals of the reduction launches: every total is summed in the same order whichever kernel forms
+// it.  Lane l adds partial rows l, l + 64, ... in turn, then the lanes are added in the order of
+// the recursive halving (halve; tree_sum for one value).
+__device__ __forceinline__ double tree_sum(double v) {
+    v += partner<32>(v);
+    v += partner<16>(v);
+    v += partner<8>(v);
+    v += partner<4>(v);
+    v += partner<2>(v);
+    v += partner<1>(v);
+    return v;
+}
+
+// Lanczos iteration j: totals of the reduction launches in a launch of their own, for problems of
+// many partial rows (launch_lanczos_iter).  Wave w of block (x, problem) sums value v = 4 x + w of
+// the nq * kDVals values into the state; many blocks, so the partial rows are read in parallel
+// across the chip rather than through one compute unit.
 template <bool ONE>
 __global__ __launch_bounds__(kVecThreads) void k_dsum(const VecProb* vp, VecProb one) {
     const VecProb P = ONE ? one : vp[blockIdx.y];
@@ -435,140 +457,124 @@ __global__ __launch_bounds__(kVecThreads) void k_dsum(const VecProb* vp, VecProb
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < kVecMaxBlocks / 64; ++k) acc += x[k];
-    acc = wave_sum(acc);
+    acc = tree_sum(acc);
     if (lane == 0 && !broken) st->red[v] = acc;
 }
 
+// The same totals formed by every block of the update pass itself (kDVals values of each of nq
+// launches into LDS): each wavefront takes a quarter of a launch's values, one per register.
+__device__ __forceinline__ void sum_rows(const double* part, int nbr, int nq, double* tot) {
+    constexpr int P = kDVals / (kVecThreads / 64);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int q = 0; q < nq; ++q) {
+        const gcptr p = (gcptr)(part + (int64_t)q * kVecMaxBlocks * kDVals) +
+                        (int64_t)wave * P * kVecMaxBlocks;
+        double v[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) v[i] = 0.0;
+        for (int b0 = 0; b0 < nbr; b0 += 64) {
+            const int b = b0 + lane;
+            const double keep = b < nbr ? 1.0 : 0.0;
+            double x[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) x[i] = p[(int64_t)i * kVecMaxBlocks + (b < nbr ? b : nbr - 1)];
+#pragma unroll
+            for (int i = 0; i < P; ++i) v[i] += x[i] * keep;
+        }
+        halve<P>(v, lane);
+        constexpr int SPAN = 64 / P;
+        if ((lane & (SPAN - 1)) == 0) tot[q * kDVals + wave * P + lane / SPAN] = v[0];
+    }
+}
+
+// Coefficients of one update pass: co[x][c] (LDS, the wavefront's own) = {a_c, t_c, h_c} scale_c for
+// x = 0, 1, 2 (c < j, zero up to j8), and slot j's in registers.
+struct SlotJ {
+    double s, tr, ti, hr, hi;     // scale_j, t_j scale_j, h_j scale_j
+};
+
 // Lanczos iteration j: the small algebra of the iteration (see the top of this file), run by
-// every block of the update pass from the totals of the reduction launches (row layout as
+// every wavefront of the update pass from the totals of the reduction launches (row layout as
 // above; the first launch has nc0 = min(j, kDSlots) slots) and the Lanczos matrix so far, so
-// that no one-block launch sits between the reduction and the update.  Every block computes
-// the same values in the same order; block 0 of the problem (`writer`) stores alpha_j, beta_j,
-// scale_j, the breakdown flag and, on the last iteration, beta_{j+1} from ||w||^2 - |h|^2 for
-// the error estimate.  The other blocks read only entries < j of the state, which no block
-// writes here.  Result in LDS: co[0][c] = a_c scale_c, co[1][c] = t_c scale_c,
-// co[2][c] = h_c scale_c (c < j, zero up to j8), cj = {scale_j, t_j scale_j, h_j scale_j}.
-// Returns false (block-uniform) when the basis has broken down.
+// that no one-block launch sits between the reduction and the update.  Lane c holds slot c and
+// neighbours come by DPP, so a wavefront needs no barrier and no other's results (with the steps
+// split over a block between four barriers the pass of a 4900-state chain took 0.8 us longer).
+// Every wavefront computes the same values in the same order; the first of block 0 of the problem
+// (`writer`) stores alpha_j, beta_j, scale_j, the breakdown flag and, on the last iteration,
+// beta_{j+1} from ||w||^2 - |h|^2 for the error estimate.  The others read only entries < j of the
+// state, which nothing writes here.  Returns false (the same everywhere) when the basis has broken
+// down.  total(i): total i of the launches.
+template <class Total>
 __device__ __forceinline__ bool iteration_coefficients(KState* st, int j, int kdim, int nc0,
-                                                       bool writer, int j8,
-                                       int broken, double (&co)[3][2 * kMaxKrylov], double (&cj)[5]) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    __shared__ double al[kMaxKrylov], be[kMaxKrylov + 1];
-    __shared__ double A[2 * kMaxKrylov], Bv[2 * kMaxKrylov], T[2 * kMaxKrylov + 2], sc[kMaxKrylov];
-    __shared__ double cde[4], sh[4];
-    __shared__ int ok;
-    const gcptr red = (gcptr)st->red;
-    const double cdev = red[4 * nc0 + (tid & 3)];   // issued with the loads below
-    for (int c = tid; c < j; c += blockDim.x) {
-        const double s = ((gcptr)st->scale)[c];
-        al[c] = ((gcptr)st->alpha)[c];
-        be[c] = ((gcptr)st->beta)[c];
-        sc[c] = s;
-        const int base = (c / kDSlots) * kDVals + 4 * (c % kDSlots);
-        A[2 * c] = s * red[base];
-        A[2 * c + 1] = s * red[base + 1];
-        Bv[2 * c] = s * red[base + 2];
-        Bv[2 * c + 1] = s * red[base + 3];
-    }
-    if (tid < 4) cde[tid] = cdev;
-    __syncthreads();
+                                                       bool writer, int j8, int broken, Total total,
+                                                       double (&co)[3][2 * kMaxKrylov], SlotJ& cj) {
+    const int lane = threadIdx.x & 63;
+    const bool in = lane < j;
+    const int c = in ? lane : 0;
+    const int base = (c / kDSlots) * kDVals + 4 * (c % kDSlots);
+    const double sc = in ? ((gcptr)st->scale)[c] : 0.0, al = in ? ((gcptr)st->alpha)[c] : 0.0;
+    double be = in ? ((gcptr)st->beta)[c] : 0.0;
+    const double beta0 = ((gcptr)st->beta)[0];
+    double cde[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cde[k] = total(4 * nc0 + k);
+    const double Ar = in ? sc * total(base) : 0.0, Ai = in ? sc * total(base + 1) : 0.0;
+    const double Br = in ? sc * total(base + 2) : 0.0, Bi = in ? sc * total(base + 3) : 0.0;
     if (broken) return false;   // an earlier iteration broke down: nothing is written
-    if (tid < 64) {
-        // wave 0: |a|^2, u^H w_raw = c - a^H b, and the breakdown scale max(1, |alpha_c|, beta_c)
-        // over the iterations before j (lane c holds slot c; j <= kMaxKrylov = 64)
-        const bool in = lane < j;
-        const double ar = in ? A[2 * lane] : 0.0, ai = in ? A[2 * lane + 1] : 0.0;
-        const double br = in ? Bv[2 * lane] : 0.0, bi = in ? Bv[2 * lane + 1] : 0.0;
-        const double a2 = wave_sum(ar * ar + ai * ai);
-        const double abr = wave_sum(ar * br + ai * bi), abi = wave_sum(ar * bi - ai * br);
-        double m = in ? fabs(al[lane]) : 0.0;
-        if (in && lane >= 1) m = fmax(m, be[lane]);
-        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    // second sweep of u1: beta_j^2 = ||u1||^2 - |a|^2 (beta_0 = ||x|| from the start); breakdown
+    // against the scale max(1, |alpha_c|, beta_c) over the iterations before j
+    const double a2 = wave_sum(Ar * Ar + Ai * Ai);
+    const double m = wave_fmax(fmax(fabs(al), lane >= 1 ? be : 0.0));
+    double bj = beta0;
+    if (j > 0) {
+        bj = sqrt(fmax(cde[2] - a2, 0.0));
+        const bool good = bj > 1e-12 * fmax(1.0, m);
+        if (writer && lane == 0) {
+            st->beta[j] = bj;
+            if (good) {
+                st->scale[j] = 1.0 / bj;
+            } else {
+                st->broken = 1;
+                st->keff = j;
+            }
+        }
+        if (!good) return false;
+    }
+    const double ib = 1.0 / bj;
+    // u^H w_raw = c - a^H b
+    const double ur = cde[0] - wave_sum(Ar * Br + Ai * Bi), ui = cde[1] - wave_sum(Ar * Bi - Ai * Br);
+    // t = T a (lanes 0 .. j): T[m][m] = alpha_m, T[m][m-1] = beta_m, T[m][m+1] = beta_{m+1}
+    if (lane == j) be = bj;
+    const double bup = dpp<0x130>(be);                          // wave_shl: from lane + 1
+    const double lo = lane >= 1 && lane <= j ? be : 0.0;
+    const double Tr = al * Ar + lo * dpp<0x138>(Ar) + bup * dpp<0x130>(Ar);   // wave_shr: lane - 1
+    const double Ti = al * Ai + lo * dpp<0x138>(Ai) + bup * dpp<0x130>(Ai);
+    const double xr = (Br - Tr) * ib, xi = (Bi - Ti) * ib;      // h_c for c < j
+    if (lane < j8) {
+        co[0][2 * lane] = Ar * sc;
+        co[0][2 * lane + 1] = Ai * sc;
+        co[1][2 * lane] = Tr * sc;
+        co[1][2 * lane + 1] = Ti * sc;
+        co[2][2 * lane] = xr * sc;
+        co[2][2 * lane + 1] = xi * sc;
+    }
+    const double tjr = lane_read(Tr, j), tji = lane_read(Ti, j);
+    const double hr = ur * ib * ib - tjr * ib, hi = ui * ib * ib - tji * ib;
+    if (writer && lane == 0) st->alpha[j] = hr;
+    if (writer && j == kdim - 1) {
+        // ||w||^2 = (e - 2 Re(t^H V^H w_raw) + |t|^2) / beta_j^2, V^H w_raw = (b, (u^H w_raw) / beta_j)
+        const double tr = in ? Tr : 0.0, ti = in ? Ti : 0.0;
+        const double yr = in ? xr : 0.0, yi = in ? xi : 0.0;
+        const double tw = wave_sum(tr * Br + ti * Bi) + tjr * ur * ib + tji * ui * ib;
+        const double t2 = wave_sum(tr * tr + ti * ti) + tjr * tjr + tji * tji;
+        const double h2 = wave_sum(yr * yr + yi * yi) + hr * hr + hi * hi;
+        const double w2 = (cde[3] - 2.0 * tw + t2) * ib * ib;
         if (lane == 0) {
-            const double bscale = fmax(1.0, m);
-            // second sweep of u1: beta_j^2 = ||u1||^2 - |a|^2 (beta_0 = ||x|| from the start)
-            double bj = ((gcptr)st->beta)[0];
-            int good = 1;
-            if (j > 0) {
-                bj = sqrt(fmax(cde[2] - a2, 0.0));
-                if (bj <= 1e-12 * bscale) good = 0;
-            }
-            if (writer && j > 0) {
-                st->beta[j] = bj;
-                if (good) {
-                    st->scale[j] = 1.0 / bj;
-                } else {
-                    st->broken = 1;
-                    st->keff = j;
-                }
-            }
-            be[j] = bj;
-            sh[0] = bj;
-            sh[1] = cde[0] - abr;   // u^H w_raw
-            sh[2] = cde[1] - abi;
-            ok = good;
+            st->beta[j + 1] = sqrt(fmax(w2 - h2, 0.0));
+            st->keff = kdim;
         }
     }
-    __syncthreads();
-    if (!ok) return false;
-    const double bj = sh[0], ib = 1.0 / bj;
-    // t = T a (m = 0 .. j): T[m][m] = alpha_m, T[m][m-1] = beta_m, T[m][m+1] = beta_{m+1}
-    for (int m = tid; m <= j; m += blockDim.x) {
-        double tr = 0.0, ti = 0.0;
-        if (m < j) {
-            tr += al[m] * A[2 * m];
-            ti += al[m] * A[2 * m + 1];
-        }
-        if (m >= 1) {
-            tr += be[m] * A[2 * (m - 1)];
-            ti += be[m] * A[2 * (m - 1) + 1];
-        }
-        if (m + 1 < j) {
-            tr += be[m + 1] * A[2 * (m + 1)];
-            ti += be[m + 1] * A[2 * (m + 1) + 1];
-        }
-        T[2 * m] = tr;
-        T[2 * m + 1] = ti;
-    }
-    __syncthreads();
-    for (int c = tid; c < j8; c += blockDim.x) {
-        const bool in = c < j;
-        const double s = in ? sc[c] : 0.0;
-        co[0][2 * c] = in ? A[2 * c] * s : 0.0;
-        co[0][2 * c + 1] = in ? A[2 * c + 1] * s : 0.0;
-        co[1][2 * c] = in ? T[2 * c] * s : 0.0;
-        co[1][2 * c + 1] = in ? T[2 * c + 1] * s : 0.0;
-        co[2][2 * c] = in ? (Bv[2 * c] - T[2 * c]) * ib * s : 0.0;
-        co[2][2 * c + 1] = in ? (Bv[2 * c + 1] - T[2 * c + 1]) * ib * s : 0.0;
-    }
-    if (tid < 64) {
-        const double ur = sh[1], ui = sh[2];
-        const double hr = ur * ib * ib - T[2 * j] * ib, hi = ui * ib * ib - T[2 * j + 1] * ib;
-        if (j == kdim - 1) {
-            // ||w||^2 = (e - 2 Re(t^H V^H w_raw) + |t|^2) / beta_j^2, V^H w_raw = (b, (u^H w_raw) / beta_j)
-            const bool in = lane < j;
-            const double tr = in ? T[2 * lane] : 0.0, ti = in ? T[2 * lane + 1] : 0.0;
-            const double br = in ? Bv[2 * lane] : 0.0, bi = in ? Bv[2 * lane + 1] : 0.0;
-            const double xr = (br - tr) * ib, xi = (bi - ti) * ib;
-            const double tw = wave_sum(tr * br + ti * bi) + T[2 * j] * ur * ib + T[2 * j + 1] * ui * ib;
-            const double t2 = wave_sum(tr * tr + ti * ti) + T[2 * j] * T[2 * j] + T[2 * j + 1] * T[2 * j + 1];
-            const double h2 = wave_sum(xr * xr + xi * xi) + hr * hr + hi * hi;
-            const double w2 = (cde[3] - 2.0 * tw + t2) * ib * ib;
-            if (writer && lane == 0) {
-                st->beta[j + 1] = sqrt(fmax(w2 - h2, 0.0));
-                st->keff = kdim;
-            }
-        }
-        if (lane == 0) {
-            if (writer) st->alpha[j] = hr;
-            cj[0] = ib;
-            cj[1] = T[2 * j] * ib;
-            cj[2] = T[2 * j + 1] * ib;
-            cj[3] = hr * ib;
-            cj[4] = hi * ib;
-        }
-    }
-    __syncthreads();
+    cj = SlotJ{ib, tjr * ib, tji * ib, hr * ib, hi * ib};
     return true;
 }
 
@@ -577,14 +583,16 @@ __device__ __forceinline__ bool iteration_coefficients(KState* st, int j, int kd
 // (skipped after the last iteration).
 template <bool ONE>
 __global__ __launch_bounds__(kVecThreads) void k_dupdate(const VecProb* vp, const int* bmap, int j,
-                                                         int kdim, int nc0, VecProb one) {
+                                                         int kdim, int nc0, int nq_direct,
+                                                         VecProb one) {
     const Where W = locate1<ONE>(vp, bmap, one);
     KState* st = W.p.st;
     const int broken = ((const int __attribute__((address_space(1)))*)&st->broken)[0];
     constexpr int G = 8;                       // basis slots loaded per round trip
     const int j8 = (j + G - 1) / G * G;
-    __shared__ double co[3][2 * kMaxKrylov];
-    __shared__ double cj[5];
+    __shared__ double cos[kVecThreads / 64][3][2 * kMaxKrylov];
+    double (&co)[3][2 * kMaxKrylov] = cos[threadIdx.x >> 6];
+    SlotJ cj;
     double* __restrict__ uj = W.p.V + (int64_t)j * W.p.vstride;
     double* __restrict__ un = W.p.V + (int64_t)(j + 1) * W.p.vstride;
     const double* __restrict__ V = W.p.V;
@@ -609,9 +617,20 @@ __global__ __launch_bounds__(kVecThreads) void k_dupdate(const VecProb* vp, cons
         }
     };
     if (even && i0 < n) head(i0);
-    if (!iteration_coefficients(st, j, kdim, nc0, W.lb == 0, j8, broken, co, cj)) return;
+    __shared__ double tot[kDMaxQ * kDVals];
+    const bool writer = W.lb == 0 && threadIdx.x < 64;
+    if (nq_direct > 0) {
+        sum_rows(W.p.part, W.p.nbr, nq_direct, tot);
+        __syncthreads();
+        if (!iteration_coefficients(st, j, kdim, nc0, writer, j8, broken,
+                                    [&](int i) { return tot[i]; }, co, cj))
+            return;
+    } else if (!iteration_coefficients(st, j, kdim, nc0, writer, j8, broken,
+                                       [&](int i) { return ((gcptr)st->red)[i]; }, co, cj)) {
+        return;
+    }
     const bool last = j == kdim - 1;
-    const double sj = cj[0], tjr = cj[1], tji = cj[2], hjr = cj[3], hji = cj[4];
+    const double sj = cj.s, tjr = cj.tr, tji = cj.ti, hjr = cj.hr, hji = cj.hi;
     if (even) {
         for (int64_t i = i0; i < n; i += 2 * stride) {
             if (i != i0) head(i);
@@ -1053,13 +1072,15 @@ hipError_t launch_lanczos_iter(const VecGroup& g, int j, int kdim, hipStream_t s
         hipLaunchKernelGGL(kRedMore[one][nc], gridr, blk, 0, s, vp, g.bmapr, j, q * kDSlots, q,
                            g.one);
     }
+    // few partial rows: every block of the update pass sums them itself
+    const int direct = nq * g.max_nbr <= kDirectRows ? nq : 0;
     const dim3 grids(nq * kDVals / (kVecThreads / 64), g.nprob);
     if (one) {
-        hipLaunchKernelGGL(k_dsum<true>, grids, blk, 0, s, vp, g.one);
-        hipLaunchKernelGGL(k_dupdate<true>, grid, blk, 0, s, vp, g.bmap, j, kdim, nc0, g.one);
+        if (!direct) hipLaunchKernelGGL(k_dsum<true>, grids, blk, 0, s, vp, g.one);
+        hipLaunchKernelGGL(k_dupdate<true>, grid, blk, 0, s, vp, g.bmap, j, kdim, nc0, direct, g.one);
     } else {
-        hipLaunchKernelGGL(k_dsum<false>, grids, blk, 0, s, vp, g.one);
-        hipLaunchKernelGGL(k_dupdate<false>, grid, blk, 0, s, vp, g.bmap, j, kdim, nc0, g.one);
+        if (!direct) hipLaunchKernelGGL(k_dsum<false>, grids, blk, 0, s, vp, g.one);
+        hipLaunchKernelGGL(k_dupdate<false>, grid, blk, 0, s, vp, g.bmap, j, kdim, nc0, direct, g.one);
     }
     return hipGetLastError();
 }

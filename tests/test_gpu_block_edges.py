@@ -3,6 +3,7 @@ hand-picked sector dimensions, every kernel family and arithmetic, against the o
 import numpy as np
 import pytest
 
+from oracle import krylov as K
 from oracle import matvec as M
 from paper_1103_5391_amd import inputs as I
 
@@ -79,4 +80,23 @@ def test_products_at_tile_edges(env, dims, prec):
         h.matvec_noalloc(xd, y)
         err = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
         assert err < BOUND[prec], ("noalloc", v, err)
+    h.destroy()
+
+
+@pytest.mark.parametrize("d,extra,rows", [(5, 0, 1), (64, 0, 32), (64, 1, 33), (128, 0, 128), (128, 1, 129)])
+def test_lanczos_totals_at_row_limits(env, d, extra, rows):
+    """64 Lanczos vectors (1 to 5 reduction launches) on either side of 128 partial rows, up to
+    which the update pass sums them itself; one row of sums per 512 states."""
+    torch, L = env
+    pb = _problem(((d,) * 4, (d, d, d, d + extra)))
+    h = L.dmrg_create(pb)
+    assert -(-h.n // 512) == rows
+    x = I.random_psi(h.n, np.random.default_rng(I.SEED_BASE + 9))
+    xd = torch.from_numpy(x).to("cuda")
+    y = torch.empty_like(xd)
+    tau = 0.2 / d                       # of the order of 1 / ||H||: converged with 64 vectors
+    info = h.krylov_expm(xd, y, tau, 64, 1)
+    yref, oinfo = K.krylov_expm(lambda v: M.matvec_sector(pb, v), x, tau, 64, 1)
+    assert info["k_eff"] == oinfo.k_eff[-1]
+    assert np.linalg.norm(y.cpu().numpy() - yref) <= 1e-10 * np.linalg.norm(yref)
     h.destroy()
