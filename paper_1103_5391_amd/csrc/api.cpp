@@ -912,11 +912,15 @@ int plan_wft(dmrg_handle h, const dmrg_wft_desc& D, std::vector<ZTile>& tA, std:
     for (int b = 0; b < nb; ++b) uoff[b + 1] = uoff[b] + 2 * (int64_t)P.blocks[b].d * P.blocks[b].d;
     std::vector<int64_t> phi_rows(D.ns_new, 0);
     double flops = 0.0;
-    auto tiles = [](std::vector<ZTile>& out, ZTile t) {
-        for (int m0 = 0; m0 < std::max(t.M, 1); m0 += kZTile)
-            for (int n0 = 0; n0 < t.N; n0 += kZTile) {
-                t.m0 = m0;
-                t.n0 = n0;
+    // tiles that share their part of the vector (its columns in stage A, its rows in stage B) are
+    // neighbours in the list: they run in one work group
+    auto tiles = [&](std::vector<ZTile>& out, ZTile t) {
+        const bool cols = &out == &tA;
+        const int no = cols ? t.N : t.M, ni = cols ? t.M : t.N;
+        for (int o = 0; o < no; o += kZTile)
+            for (int i = 0; i < ni; i += kZTile) {
+                t.m0 = cols ? i : o;
+                t.n0 = cols ? o : i;
                 out.push_back(t);
             }
     };
@@ -986,6 +990,9 @@ int plan_wft(dmrg_handle h, const dmrg_wft_desc& D, std::vector<ZTile>& tA, std:
         if (t.M > 0 && t.N > 0) tiles(tB, t);
         flops += 8.0 * t.M * t.N * t.K;
     }
+    // the longest tiles first: the last wave of work groups is then made of short ones
+    for (std::vector<ZTile>* l : {&tA, &tB})
+        std::stable_sort(l->begin(), l->end(), [](const ZTile& a, const ZTile& b) { return a.K > b.K; });
     w.nphi = nphi;
     w.n_new = n_new;
     w.phi_zero = zero;

@@ -326,7 +326,7 @@ struct ZTile {
     double alpha;
     int64_t aoff, aim, boff, bim, coff, cim;
 };
-constexpr int kZTile = 32;
+constexpr int kZTile = 16;          // rows and columns of a tile
 constexpr int kWftMaxVec = 16;      // vectors of one wave-function transformation call
 struct ZPtrs {                      // per vector: the A, B and C buffers of one launch
     const double* a[kWftMaxVec];

@@ -9,9 +9,9 @@
 //             address, with no sign since the bases are normal-ordered)
 //   stage B   psi'[(alpha', a), gamma] = sum_beta Phi[(alpha', a), beta] W[gamma, beta]
 //             (W_r: the states of R sector r in the product basis of s3 x R'')
-// Both stages are one launch over a list of 32 x 32 output tiles, one wavefront per tile, every
-// vector of the call in the second grid dimension.  A tile runs 2 x 2 MFMA 16x16x4 blocks, each
-// with two accumulators: Re C += Re A Re B - Im A Im B and Im C += Re A Im B + Im A Re B.
+// Both stages are one launch over a list of 16 x 16 output tiles for every vector of the call, one
+// wavefront per tile and vector, with two accumulators: Re C += Re A Re B - Im A Im B and
+// Im C += Re A Im B + Im A Re B.
 #include <algorithm>
 #include <cstdint>
 
@@ -22,57 +22,28 @@ namespace dmrg {
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
-typedef double d4u __attribute__((ext_vector_type(4), aligned(8)));   // 8-byte aligned
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // 8-byte aligned
+typedef const double __attribute__((address_space(1)))* gcptr;
 
-// Four consecutive doubles from global memory at an 8-byte aligned address.
-__device__ __forceinline__ d4 ld4u(const double* p) {
-    return *((const __attribute__((address_space(1))) d4u*)p);
+// The K index of MFMA u of a chunk of 16 in lane group g: pairs, so that a row's four lane groups
+// read 64 consecutive bytes with one 16-byte load each.
+__device__ __forceinline__ int koff(int g, int u) { return 8 * (u >> 1) + 2 * g + (u & 1); }
+// The four values of one lane from a row that starts at p and runs along K (8-byte aligned).
+__device__ __forceinline__ d4 ld4u(gcptr p, int g) {
+    const d2u a = *((const __attribute__((address_space(1))) d2u*)(p + 2 * g));
+    const d2u b = *((const __attribute__((address_space(1))) d2u*)(p + 8 + 2 * g));
+    return (d4){a[0], a[1], b[0], b[1]};
 }
 
-// Both planes of one operand element (zero outside the matrix; imaginary part zero for real
-// operands); the access mode is a template parameter.
+// Offset of operand element (i, k) of A, (k, j) of B, and its step along K (modes of the planner;
+// the identity has no elements).
 template <int AM>
-__device__ __forceinline__ void load_a(const ZTile& t, const double* __restrict__ A, int i, int k,
-                                       double& re, double& im) {
-    re = 0.0;
-    im = 0.0;
-    if (i >= t.M || k >= t.K) return;
-    if constexpr (AM == ZM_COL) {
-        const int64_t at = t.aoff + (int64_t)k * t.lda + i;
-        re = A[at];
-        im = A[at + t.aim];
-    } else if constexpr (AM == ZM_CT) {
-        const int64_t at = t.aoff + (int64_t)i * t.lda + k;
-        re = A[at];
-        im = -A[at + t.aim];
-    } else if constexpr (AM == ZM_RCOL) {
-        re = A[t.aoff + (int64_t)k * t.lda + i];
-    } else if constexpr (AM == ZM_RT) {
-        re = A[t.aoff + (int64_t)i * t.lda + k];
-    } else {
-        re = i == k ? 1.0 : 0.0;
-    }
+__device__ __forceinline__ int64_t at_a(const ZTile& t, int i, int k) {
+    return t.aoff + (AM == ZM_COL || AM == ZM_RCOL ? (int64_t)k * t.lda + i : (int64_t)i * t.lda + k);
 }
-
 template <int BM>
-__device__ __forceinline__ void load_b(const ZTile& t, const double* __restrict__ B, int k, int j,
-                                       double& re, double& im) {
-    re = 0.0;
-    im = 0.0;
-    if (j >= t.N || k >= t.K) return;
-    if constexpr (BM == ZM_COL) {
-        const int64_t at = t.boff + (int64_t)j * t.ldb + k;
-        re = B[at];
-        im = B[at + t.bim];
-    } else if constexpr (BM == ZM_CT) {      // transpose (no conjugate) of a complex matrix
-        const int64_t at = t.boff + (int64_t)k * t.ldb + j;
-        re = B[at];
-        im = B[at + t.bim];
-    } else if constexpr (BM == ZM_RCOL) {
-        re = B[t.boff + (int64_t)j * t.ldb + k];
-    } else {
-        re = B[t.boff + (int64_t)k * t.ldb + j];
-    }
+__device__ __forceinline__ int64_t at_b(const ZTile& t, int k, int j) {
+    return t.boff + (BM == ZM_COL || BM == ZM_RCOL ? (int64_t)j * t.ldb + k : (int64_t)k * t.ldb + j);
 }
 
 __device__ __forceinline__ d4 mma4(const double (&a)[4], const double (&b)[4], d4 c) {
@@ -83,121 +54,151 @@ __device__ __forceinline__ d4 mma4(const double (&a)[4], const double (&b)[4], d
 
 }  // namespace
 
-// One wavefront per output tile; vector v = blockIdx.y.  Lane (g, r) = (lane / 16, lane % 16)
-// supplies rows (columns) r of the 16-row (16-column) blocks and the K indices 4 g + u of a
-// chunk of 16 (the u-th MFMA of the chunk takes index 4 g + u from lane group g, the same for
-// A and B); result element (g + 4 v, r) of a 16 x 16 block is accumulator component v.  The
-// operands of the next chunk are loaded while the MFMAs of the current one run.
+constexpr int kZWaves = 4;          // tiles (wavefronts) of a work group
+constexpr int kZBuf = 2;            // chunks held by a wavefront
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// One wavefront per 16 x 16 output tile, four neighbours of the list in a work group, work groups
+// tile-major over the vectors.  Lane (g, r) = (lane / 16, lane % 16) supplies rows (columns) r and
+// the K indices koff(g, u) of a chunk of 16; B goes in as the MFMA's first operand, so that result
+// element (row r, column g + 4 q) is accumulator component q and 16 lanes store consecutive rows.
+// Rows and columns outside the matrix read the last one (they only enter results that are not
+// stored); K indices beyond K are zero in both operands.
+// Bound by load latency: five vectors of the 1000-state ladder's move are 0.6 GFLOP (13 us of
+// padded MFMAs if spread evenly) and 60 MB, but the longest tiles run 10 chunks in turn.  So the
+// tiles are small (they end sooner, and 3800 of them fill 1024 SIMDs more evenly than 2300 of
+// 32 x 32, whose operands also left no room beside the accumulators: the compiler moved these to
+// accumulation registers and back around every chunk), the planner lists the longest K first, and
+// a tile's neighbours share its part of the vector in the CU's L1.  Stage A 47.0 -> 21.0 us, stage
+// B 25.5 -> 17.3 us; three or four chunks in flight measured the same.
 template <int AM, int BM>
-__global__ __launch_bounds__(64) void k_zgemm(const ZTile* __restrict__ tiles, ZPtrs ptr) {
-    const ZTile t = tiles[blockIdx.x];
-    const int v = blockIdx.y;
-    const double* __restrict__ A = ptr.a[v];
-    const double* __restrict__ B = ptr.b[v];
+__global__ __launch_bounds__(64 * kZWaves, 3) void k_zgemm(const ZTile* __restrict__ tiles, int n,
+                                                           ZPtrs ptr, int nvec) {
+    const int ti = (int)(blockIdx.x / nvec) * kZWaves + wave_id();
+    if (ti >= n) return;
+    const ZTile t = tiles[ti];
+    const int v = blockIdx.x % nvec;
+    const gcptr A = (gcptr)ptr.a[v];
+    const gcptr B = (gcptr)ptr.b[v];
     double* __restrict__ C = ptr.c[v];
-    const int lane = threadIdx.x, g = lane >> 4, r = lane & 15;
-    d4 cre[2][2], cim[2][2];
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int nj = 0; nj < 2; ++nj) {
-            cre[mi][nj] = (d4){0.0, 0.0, 0.0, 0.0};
-            cim[mi][nj] = (d4){0.0, 0.0, 0.0, 0.0};
-        }
-    double ar[2][2][4], ai[2][2][4], br[2][2][4], bi[2][2][4];   // [buffer][half][u]
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+    const int i = min(t.m0 + r, t.M - 1), j = min(t.n0 + r, t.N - 1);
+    d4 cre = (d4){0.0, 0.0, 0.0, 0.0}, cim = cre;
+    double ar[kZBuf + 1][4], ai[kZBuf + 1][4], br[kZBuf + 1][4], bi[kZBuf + 1][4];   // [buffer][u]; last: the tail
     auto load = [&](int buf, int k0) {
-        if constexpr (AM == ZM_CT && BM == ZM_COL) {
-            // both operands run along K in memory: a chunk inside K is four consecutive values
-            // per lane and plane, one vector load each (rows and columns outside the matrix
-            // read row or column 0 and are zeroed)
-            if (k0 + 16 <= t.K) {
-                const int kk = k0 + 4 * g;
+        if (buf < kZBuf) {                     // a whole chunk: no tests
+            if constexpr (AM == ZM_CT) {               // four consecutive values per plane
+                const gcptr p = A + at_a<AM>(t, i, k0);
+                const d4 re = ld4u(p, g), im = ld4u(p + t.aim, g);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int i = t.m0 + 16 * h + r, j = t.n0 + 16 * h + r;
-                    const bool oi = i < t.M, oj = j < t.N;
-                    const int64_t at = t.aoff + (int64_t)(oi ? i : 0) * t.lda + kk;
-                    const int64_t bt = t.boff + (int64_t)(oj ? j : 0) * t.ldb + kk;
-                    const d4 are = ld4u(A + at), aim = ld4u(A + at + t.aim);
-                    const d4 bre = ld4u(B + bt), bim = ld4u(B + bt + t.bim);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        ar[buf][h][u] = oi ? are[u] : 0.0;
-                        ai[buf][h][u] = oi ? -aim[u] : 0.0;   // conjugate transpose
-                        br[buf][h][u] = oj ? bre[u] : 0.0;
-                        bi[buf][h][u] = oj ? bim[u] : 0.0;
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    ar[buf][u] = re[u];
+                    ai[buf][u] = -im[u];               // conjugate transpose
                 }
-                return;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = k0 + koff(g, u);
+                    const int64_t at = at_a<AM>(t, i, k);
+                    ar[buf][u] = AM == ZM_ID ? (t.m0 + r == k ? 1.0 : 0.0) : A[at];
+                    ai[buf][u] = AM == ZM_COL ? A[at + t.aim] : 0.0;
+                }
             }
+            if constexpr (BM == ZM_COL) {
+                const gcptr p = B + at_b<BM>(t, k0, j);
+                const d4 re = ld4u(p, g), im = ld4u(p + t.bim, g);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    br[buf][u] = re[u];
+                    bi[buf][u] = im[u];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t at = at_b<BM>(t, k0 + koff(g, u), j);
+                    br[buf][u] = B[at];
+                    bi[buf][u] = BM == ZM_CT ? B[at + t.bim] : 0.0;   // transpose only
+                }
+            }
+            return;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int k = k0 + 4 * g + u;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                load_a<AM>(t, A, t.m0 + 16 * h + r, k, ar[buf][h][u], ai[buf][h][u]);
-                load_b<BM>(t, B, k, t.n0 + 16 * h + r, br[buf][h][u], bi[buf][h][u]);
+            const int ku = k0 + koff(g, u), k = min(ku, t.K - 1);
+            const bool ok = ku < t.K;
+            double xr, xi = 0.0;
+            if constexpr (AM == ZM_ID) {
+                xr = t.m0 + r == ku ? 1.0 : 0.0;
+            } else {
+                const int64_t at = at_a<AM>(t, i, k);
+                xr = A[at];
+                if constexpr (AM == ZM_COL || AM == ZM_CT) xi = A[at + t.aim];
             }
+            const int64_t bt = at_b<BM>(t, k, j);
+            const double yr = B[bt], yi = BM == ZM_COL || BM == ZM_CT ? B[bt + t.bim] : 0.0;
+            ar[buf][u] = ok ? xr : 0.0;
+            ai[buf][u] = ok ? (AM == ZM_CT ? -xi : xi) : 0.0;
+            br[buf][u] = ok ? yr : 0.0;
+            bi[buf][u] = ok ? yi : 0.0;
         }
     };
     auto mma = [&](int buf) {
-        double an[2][4];
+        double an[4];
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) an[h][u] = -ai[buf][h][u];
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int nj = 0; nj < 2; ++nj) {
-                cre[mi][nj] = mma4(ar[buf][mi], br[buf][nj], cre[mi][nj]);
-                cre[mi][nj] = mma4(an[mi], bi[buf][nj], cre[mi][nj]);
-                cim[mi][nj] = mma4(ar[buf][mi], bi[buf][nj], cim[mi][nj]);
-                cim[mi][nj] = mma4(ai[buf][mi], br[buf][nj], cim[mi][nj]);
-            }
+        for (int u = 0; u < 4; ++u) an[u] = -ai[buf][u];
+        // B first: the result block then has its rows along the lanes
+        cre = mma4(br[buf], ar[buf], cre);
+        cim = mma4(bi[buf], ar[buf], cim);
+        cre = mma4(bi[buf], an, cre);
+        cim = mma4(br[buf], ai[buf], cim);
     };
-    if (t.K > 0) {
-        load(0, 0);
-        for (int k0 = 0;; k0 += 32) {
-            if (k0 + 16 < t.K) load(1, k0 + 16);
-            mma(0);
-            if (k0 + 16 >= t.K) break;
-            if (k0 + 32 < t.K) load(0, k0 + 32);
-            mma(1);
-            if (k0 + 32 >= t.K) break;
-        }
-    }
+    // The rest of K first, then whole chunks, chunks c + 1 .. c + kZBuf - 1 on their way while chunk c
+    // is multiplied.  The loads in the loop are unconditional (the last ones repeat the last
+    // chunk): a load that may be left out would make every wait one for all loads in flight.
+    const int nfull = t.K >> 4;
+    const bool tail = (t.K & 15) != 0;
+    if (tail) load(kZBuf, 16 * nfull);
+    if (nfull > 0) {
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+        for (int b = 0; b + 1 < kZBuf; ++b) load(b, 16 * min(b, nfull - 1));
+        int c = 0;
+        for (; c + kZBuf <= nfull; c += kZBuf) {
 #pragma unroll
-        for (int nj = 0; nj < 2; ++nj) {
-            const int j = t.n0 + 16 * nj + r;
-            if (j >= t.N) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = t.m0 + 16 * mi + g + 4 * q;
-                if (i >= t.M) continue;
-                const int64_t at = t.coff + (int64_t)j * t.ldc + i;
-                double vr = t.alpha * cre[mi][nj][q], vi = t.alpha * cim[mi][nj][q];
-                if (t.acc) {
-                    vr += C[at];
-                    vi += C[at + t.cim];
-                }
-                C[at] = vr;
-                C[at + t.cim] = vi;
+            for (int b = 0; b < kZBuf; ++b) {
+                load((b + kZBuf - 1) % kZBuf, 16 * min(c + b + kZBuf - 1, nfull - 1));
+                mma(b);
             }
         }
+#pragma unroll
+        for (int b = 0; b + 1 < kZBuf; ++b)
+            if (c + b < nfull) mma(b);
+    }
+    if (tail) mma(kZBuf);
+    const int ic = t.m0 + r;
+    if (ic >= t.M) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int jc = t.n0 + g + 4 * q;
+        if (jc >= t.N) continue;
+        const int64_t at = t.coff + (int64_t)jc * t.ldc + ic;
+        double vr = t.alpha * cre[q], vi = t.alpha * cim[q];
+        if (t.acc) {
+            vr += C[at];
+            vi += C[at + t.cim];
+        }
+        C[at] = vr;
+        C[at + t.cim] = vi;
+    }
 }
 
 // Launch of one tile list whose tiles share the operand modes (am, bm).
 hipError_t launch_zgemm_modes(const ZTile* t, int n, const ZPtrs& p, int nvec, int am, int bm,
                               hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const dim3 grid(n, nvec);
+    const dim3 grid((unsigned)((n + kZWaves - 1) / kZWaves) * nvec);
 #define DMRG_ZGEMM_CASE(A_, B_)                                                            \
     if (am == A_ && bm == B_) {                                                            \
-        hipLaunchKernelGGL((k_zgemm<A_, B_>), grid, dim3(64), 0, s, t, p);                 \
+        hipLaunchKernelGGL((k_zgemm<A_, B_>), grid, dim3(64 * kZWaves), 0, s, t, n, p, nvec);                \
         return hipGetLastError();                                                          \
     }
     DMRG_ZGEMM_CASE(ZM_CT, ZM_COL)        // wave-function transformation, stage A

@@ -100,3 +100,30 @@ def test_lanczos_totals_at_row_limits(env, d, extra, rows):
     assert info["k_eff"] == oinfo.k_eff[-1]
     assert np.linalg.norm(y.cpu().numpy() - yref) <= 1e-10 * np.linalg.norm(yref)
     h.destroy()
+
+
+@pytest.mark.parametrize("m", [100, 400])
+def test_move_at_tile_edges(env, m):
+    """Moves of the centre that keep 1, 15, 16, 17, 31, 32, 33 ... states of sectors of 1 to 60 (rows,
+    columns and inner dimensions around the 16 of a tile and a chunk), against the oracle: sums of
+    at most 60 products in each of two stages."""
+    from oracle import wft as Wo
+    torch, L = env
+    pb = I.synthetic_problem(24, m, 4.0, I.chain_bonds(24), I.SEED_BASE + 11)
+    rng = np.random.default_rng(I.SEED_BASE + 12)
+    blk = I.psi_blocks(pb)
+    kept = [min((1, 15, 16, 17, 31, 32, 33, 60)[b % 8], r) for b, (_, _, r, _) in enumerate(blk)]
+    mv = I.wft_move(pb, kept, seed=3)
+    evecs = [rng.standard_normal((r, r)) + 1j * rng.standard_normal((r, r)) for (_, _, r, _) in blk]
+    planes = lambda a: np.concatenate([a.real.ravel(order="F"), a.imag.ravel(order="F")])
+    cuda = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    h = L.dmrg_create(pb)
+    w = h.wft_create(mv, [cuda(planes(m)) for m in mv.W])
+    xs = [I.random_psi(h.n, rng) for _ in range(3)]
+    ys = [torch.full((2 * w.n_new,), float("nan"), dtype=torch.float64, device="cuda") for _ in xs]
+    w.apply(cuda(np.concatenate([planes(u) for u in evecs])), [cuda(x) for x in xs], ys)
+    for x, y in zip(xs, ys):
+        ref = Wo.wft_right(pb, mv, evecs, x)
+        assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-13 * np.linalg.norm(ref)
+    w.destroy()
+    h.destroy()
