@@ -55,10 +55,12 @@ hipError_t launch_wft(const ZTile*, int, const ZPtrs&, const ZTile*, int, const 
 hipError_t launch_zgemm(const ZTile*, int, const ZPtrs&, int, int, int, hipStream_t);
 hipError_t launch_zero(double*, int64_t, hipStream_t);
 hipError_t noalloc_scratch(double**);
-hipError_t launch_local_mono(const SJob*, int, int64_t, const int*, const double*, const int*,
-                             const double*, const double*, int64_t, double*, int64_t, hipStream_t);
+hipError_t launch_local_mono(const LocalItem*, int, const LocalSrc*, const int*, const double*,
+                             const int*, const double*, const double*, int64_t, double*, int64_t,
+                             double*, int, hipStream_t);
 hipError_t launch_zdot(const double*, const double*, int64_t, double*, int, hipStream_t);
-constexpr int kDotBlocks = 256;     // partial sums of one inner product
+constexpr int kDotBlocks = 2048;    // partial sums of one inner product
+constexpr size_t kLocalPlans = 8;   // planned lists of local terms a handle keeps
 int vec_blocks(int64_t n);
 int red_blocks(int64_t n);
 
@@ -419,6 +421,20 @@ struct dmrg_batch_ctx {
     std::unique_ptr<dmrg_batch_ctx> chains;   // the 4-RHS mode: every member's four chains
 };
 
+// The device lists of one list of local terms into one destination: tiles of the products, and the
+// gathering of the terms with monomial factors (one buffer).
+struct LocalPlan {
+    std::vector<dmrg_term> terms;
+    uint64_t dst = 0;                   // serial of the destination handle
+    std::vector<std::array<int, 5>> launches;
+    int64_t tsize = 0;
+    int nitems = 0;
+    DevBuf buf;
+    size_t at_tiles = 0, at_src = 0, at_items = 0;   // byte offsets
+    template <typename T>
+    const T* at(size_t off) const { return reinterpret_cast<const T*>(buf.as<char>() + off); }
+};
+
 struct dmrg_ctx {
     Budget budget;      // first member: destroyed after every buffer charged to it
     Plan plan;
@@ -444,21 +460,18 @@ struct dmrg_ctx {
     int64_t dens_nmat = 0;
     std::unique_ptr<dmrg_batch_ctx> chains;   // the handle's four chains of the 4-RHS mode
     // local operators (built on first use): raw operator blocks of both halves, the product
-    // intermediate, the tile list and the inner-product partials
-    DevBuf dOpS, dOpE, dLocT, dLocZ, dLocTiles, dLocPart, dLocJobs;
+    // intermediate, the image of an expectation and its partial sums (written by the kernel)
+    DevBuf dOpS, dOpE, dLocT, dLocZ;
+    HostBuf hLocPart;
     std::vector<int64_t> opS_base, opE_base;
     // monomial operator blocks (at most one nonzero per row and column): per half the maps
     // (input index -> output index) and values, and per operator and source sector the offsets
     // of the map of the block (fwd) and of its transpose (bwd), -1 if the block is not monomial
     DevBuf dMonoMap[2], dMonoVal[2];
     std::vector<std::vector<int>> mono_fwd[2], mono_bwd[2];
-    // the last planned call (terms and destination), whose device lists are reused when the
-    // next call repeats it
-    std::vector<dmrg_term> loc_terms;
-    uint64_t loc_dst = 0;               // serial of the destination handle (0: none)
+    // planned lists of local terms, the last used first: a program alternates between a few
+    std::vector<std::unique_ptr<LocalPlan>> loc;
     uint64_t serial = 0;                // unique per handle in the process (never reused)
-    std::vector<std::array<int, 5>> loc_launches;
-    int64_t loc_tsize = 0;
 };
 
 // A planned move of the centre (wave-function transformation): tile lists of its two stages,
@@ -1085,11 +1098,12 @@ bool factor_of(const HalfTable& T, const std::vector<int64_t>& base, int op, int
     return true;
 }
 
-// Tile lists of y = sum_t coef_t (A_t P_S^f_t (x) B_t) x (src layout -> dst layout): per term,
-// the right products T = X B^T (terms with an environment factor) then the left products
+// Lists of y = sum_t coef_t (A_t P_S^f_t (x) B_t) x (src layout -> dst layout).  Terms with
+// monomial factors are gathered by destination block (items, srcs); of the others, per term, the
+// right products T = X B^T (terms with an environment factor) then the left products
 // y += alpha A T; launches[i] = (first tile, count, which product).
 int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms,
-               std::vector<ZTile>& tiles, std::vector<SJob>& jobs,
+               std::vector<ZTile>& tiles, std::vector<LocalItem>& items, std::vector<LocalSrc>& srcs,
                std::vector<std::array<int, 5>>& launches, int64_t& tsize) {
     const Plan& S = hs->plan;
     const Plan& D = hd->plan;
@@ -1100,6 +1114,7 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
         if (a.nup != b.nup || a.ndn != b.ndn || a.dim != b.dim) return bad("the handles have different halves");
     }
     tsize = 0;
+    std::vector<std::vector<LocalSrc>> into(D.blocks.size());
     for (int t = 0; t < nterm; ++t) {
         const dmrg_term& tm = terms[t];
         if (tm.opS < -1 || tm.opS >= (int)S.S.ops.size() || tm.opE < -1 || tm.opE >= (int)S.E.ops.size())
@@ -1112,16 +1127,17 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
             for (int k = 0; k < 2; ++k) dq[k] += (tm.transE ? -1 : 1) * S.E.ops[tm.opE].dq[k];
         if (S.target[0] + dq[0] != D.target[0] || S.target[1] + dq[1] != D.target[1])
             return bad("the term does not map the source sector to the destination sector");
-        // monomial factors: every block this term uses maps one element to one element
+        // monomial factors: every block this term uses maps one element to one element (the maps
+        // of the inverse: of the transposed operator, from the destination)
         auto mono_of = [&](int side, int op, int trans, int p) -> int {
             if (op < 0) return -2;                              // identity
             const HalfTable& T = side == 0 ? S.S : S.E;
-            if (!trans) return hs->mono_fwd[side][op][p];
+            if (!trans) return hs->mono_bwd[side][op][p];
             const int src = T.find(T.nup[p] - T.ops[op].dq[0], T.ndn[p] - T.ops[op].dq[1]);
-            return src < 0 ? -1 : hs->mono_bwd[side][op][src];
+            return src < 0 ? -1 : hs->mono_fwd[side][op][src];
         };
         bool mono = true;
-        std::vector<SJob> tj;
+        std::vector<std::pair<int, LocalSrc>> part;
         for (const PsiBlock& B : S.blocks) {
             Factor fa, fb;
             if (!factor_of(S.S, hs->opS_base, tm.opS, tm.transS, B.p, fa)) continue;
@@ -1134,16 +1150,10 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
                 break;
             }
             const double sign = (tm.fermionic && ((S.S.nup[B.p] + S.S.ndn[B.p]) & 1)) ? -1.0 : 1.0;
-            tj.push_back(SJob{B.off, D.blocks[ob].off, B.d, B.e, D.blocks[ob].d, ma < 0 ? -1 : ma,
-                              mb < 0 ? -1 : mb, 0, tm.coef * sign});
+            part.push_back({ob, LocalSrc{B.off, B.d, ma < 0 ? -1 : ma, mb < 0 ? -1 : mb, 0, tm.coef * sign}});
         }
         if (mono) {
-            if (!tj.empty()) {
-                int64_t mx = 0;
-                for (const SJob& j : tj) mx = std::max<int64_t>(mx, (int64_t)j.d * j.e);
-                launches.push_back({(int)jobs.size(), (int)tj.size(), 3, (int)mx, 0});
-                jobs.insert(jobs.end(), tj.begin(), tj.end());
-            }
+            for (const auto& q : part) into[q.first].push_back(q.second);
             continue;
         }
         std::vector<ZTile> right, left;
@@ -1220,51 +1230,93 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
             tiles.insert(tiles.end(), left.begin(), left.end());
         }
     }
+    for (size_t b = 0; b < D.blocks.size(); ++b) {
+        const PsiBlock& O = D.blocks[b];
+        const int64_t cnt = (int64_t)O.d * O.e;
+        for (int64_t c = 0; c < cnt; c += kLocalChunk)
+            items.push_back(LocalItem{O.off + c, O.d, (int)(c % O.d), (int)(c / O.d),
+                                      (int)std::min<int64_t>(cnt - c, kLocalChunk), (int)srcs.size(),
+                                      (int)into[b].size()});
+        srcs.insert(srcs.end(), into[b].begin(), into[b].end());
+    }
     return DMRG_OK;
 }
 
-// y (dst layout) = sum of the terms applied to x (src layout); asynchronous.  launches[i] =
-// (first tile, tiles, kind, A mode, B mode), kind 0 right products, 1 left products of the
-// intermediate, 2 left products of x (the tiles of a launch share their operand modes), 3 a
-// term with monomial factors (first job, jobs, kind, largest block's element count).
-int run_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms, const double* x,
-              double* y) {
+// The lists of the terms into hd's sector: kept from an earlier call with the same terms, or
+// planned and uploaded now.
+int find_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms,
+               LocalPlan** out) try {
     int rc = ensure_local_ops(hs);
     if (rc) return rc;
-    hipStream_t s = hs->stream;
     auto same = [](const dmrg_term& a, const dmrg_term& b) {
         return a.coef == b.coef && a.opS == b.opS && a.transS == b.transS && a.opE == b.opE &&
                a.transE == b.transE && a.fermionic == b.fermionic;
     };
-    bool repeat = hs->loc_dst == hd->serial && (int)hs->loc_terms.size() == nterm;
-    for (int t = 0; repeat && t < nterm; ++t) repeat = same(hs->loc_terms[t], terms[t]);
-    if (!repeat) {
-        std::vector<ZTile> tiles;
-        std::vector<SJob> jobs;
-        std::vector<std::array<int, 5>> launches;
-        int64_t tsize = 0;
-        hs->loc_dst = 0;
-        rc = plan_local(hs, hd, nterm, terms, tiles, jobs, launches, tsize);
-        if (rc) return rc;
-        if ((int64_t)hs->dLocT.bytes < (int64_t)sizeof(double) * 2 * std::max<int64_t>(tsize, 1)) {
-            HIP_TRY(hs, hipStreamSynchronize(s));
-            HIP_TRY(hs, hs->dLocT.alloc(sizeof(double) * 2 * (size_t)std::max<int64_t>(tsize, 1)));
-        }
-        HIP_TRY(hs, upload(hs->dLocTiles, tiles, s));
-        HIP_TRY(hs, upload(hs->dLocJobs, jobs, s));
-        hs->loc_terms.assign(terms, terms + nterm);
-        hs->loc_launches = launches;
-        hs->loc_tsize = tsize;
-        hs->loc_dst = hd->serial;
+    for (size_t i = 0; i < hs->loc.size(); ++i) {
+        LocalPlan& L = *hs->loc[i];
+        bool repeat = L.dst == hd->serial && (int)L.terms.size() == nterm;
+        for (int t = 0; repeat && t < nterm; ++t) repeat = same(L.terms[t], terms[t]);
+        if (!repeat) continue;
+        std::rotate(hs->loc.begin(), hs->loc.begin() + i, hs->loc.begin() + i + 1);
+        *out = hs->loc.front().get();
+        return DMRG_OK;
     }
-    HIP_TRY(hs, launch_zero(y, 2 * hd->plan.n, s));
-    for (const auto& L : hs->loc_launches) {
-        if (L[2] == 3) {            // monomial factors: one element to one element
-            HIP_TRY(hs, launch_local_mono(hs->dLocJobs.as<SJob>() + L[0], L[1], L[3], hs->dMonoMap[0].as<int>(),
-                                          hs->dMonoVal[0].as<double>(), hs->dMonoMap[1].as<int>(),
-                                          hs->dMonoVal[1].as<double>(), x, hs->plan.n, y, hd->plan.n, s));
-            continue;
+    std::unique_ptr<LocalPlan> L(new LocalPlan());
+    std::vector<ZTile> tiles;
+    std::vector<LocalItem> items;
+    std::vector<LocalSrc> srcs;
+    rc = plan_local(hs, hd, nterm, terms, tiles, items, srcs, L->launches, L->tsize);
+    if (rc) return rc;
+    std::vector<char> all;
+    auto put = [&](const void* p, size_t bytes) {
+        const size_t at = all.size();
+        all.insert(all.end(), static_cast<const char*>(p), static_cast<const char*>(p) + bytes);
+        all.resize((all.size() + 63) / 64 * 64);
+        return at;
+    };
+    L->at_tiles = put(tiles.data(), tiles.size() * sizeof(ZTile));
+    L->at_src = put(srcs.data(), srcs.size() * sizeof(LocalSrc));
+    L->at_items = put(items.data(), items.size() * sizeof(LocalItem));
+    L->nitems = (int)items.size();
+    L->terms.assign(terms, terms + nterm);
+    L->dst = hd->serial;
+    // no more lists than kLocalPlans, and none but this one where the memory would not do
+    if (hs->loc.size() >= kLocalPlans) hs->loc.pop_back();
+    const int64_t need = (int64_t)sizeof(double) * 2 * L->tsize;
+    auto place = [&]() -> hipError_t {
+        if ((int64_t)hs->dLocT.bytes < need) {
+            hipError_t e = hipStreamSynchronize(hs->stream);
+            if (e == hipSuccess) e = hs->dLocT.alloc((size_t)need);
+            if (e != hipSuccess) return e;
         }
+        return upload(L->buf, all, hs->stream);
+    };
+    hipError_t e = place();
+    if (e == hipErrorOutOfMemory && !hs->loc.empty()) {
+        (void)hipGetLastError();
+        hs->loc.clear();
+        e = place();
+    }
+    HIP_TRY(hs, e);
+    hs->loc.insert(hs->loc.begin(), std::move(L));
+    *out = hs->loc.front().get();
+    return DMRG_OK;
+} catch (const std::bad_alloc&) {
+    return fail(hs, DMRG_ENOMEM, "local operator: out of host memory");
+}
+
+// y (dst layout) = sum of the terms applied to x (src layout); asynchronous.  launches[i] =
+// (first tile, tiles, kind, A mode, B mode), kind 0 right products, 1 left products of the
+// intermediate, 2 left products of x (the tiles of a launch share their operand modes).
+int run_local(dmrg_handle hs, dmrg_handle hd, const LocalPlan& P, const double* x, double* y,
+              double* part) {
+    hipStream_t s = hs->stream;
+    HIP_TRY(hs, launch_local_mono(P.at<LocalItem>(P.at_items), P.nitems,
+                                  P.at<LocalSrc>(P.at_src), hs->dMonoMap[0].as<int>(),
+                                  hs->dMonoVal[0].as<double>(), hs->dMonoMap[1].as<int>(),
+                                  hs->dMonoVal[1].as<double>(), x, hs->plan.n, y, hd->plan.n, part,
+                                  kDotBlocks, s));
+    for (const auto& L : P.launches) {
         ZPtrs p{};
         if (L[2] == 0) {            // right products: x, environment blocks -> intermediate
             p.a[0] = x;
@@ -1275,7 +1327,7 @@ int run_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms,
             p.b[0] = L[2] == 1 ? hs->dLocT.as<double>() : x;
             p.c[0] = y;
         }
-        HIP_TRY(hs, launch_zgemm(hs->dLocTiles.as<ZTile>() + L[0], L[1], p, 1, L[3], L[4], s));
+        HIP_TRY(hs, launch_zgemm(P.at<ZTile>(P.at_tiles) + L[0], L[1], p, 1, L[3], L[4], s));
     }
     return DMRG_OK;
 }
@@ -1902,7 +1954,9 @@ int dmrg_apply_local(dmrg_handle src, dmrg_handle dst, int32_t nterm, const dmrg
     if (nterm < 1 || !terms || !x || !y) return fail(src, DMRG_EINVAL, "local operator: NULL or empty argument");
     if (x == y) return fail(src, DMRG_EINVAL, "local operator: y must not be x");
     BudgetScope bs(&src->budget);
-    return run_local(src, dst, nterm, terms, x, y);
+    LocalPlan* P = nullptr;
+    const int rc = find_local(src, dst, nterm, terms, &P);
+    return rc ? rc : run_local(src, dst, *P, x, y, nullptr);
 }
 
 int dmrg_expect_local(dmrg_handle h, int32_t nterm, const dmrg_term* terms, const double* x,
@@ -1911,20 +1965,26 @@ int dmrg_expect_local(dmrg_handle h, int32_t nterm, const dmrg_term* terms, cons
     if (nterm < 1 || !terms || !x) return fail(h, DMRG_EINVAL, "local operator: NULL or empty argument");
     BudgetScope bs(&h->budget);
     hipStream_t s = h->stream;
-    if (!h->dLocZ.p) HIP_TRY(h, h->dLocZ.alloc(sizeof(double) * 2 * (size_t)h->plan.n));
-    if (!h->dLocPart.p) HIP_TRY(h, h->dLocPart.alloc(sizeof(double) * 2 * kDotBlocks));
-    int rc = run_local(h, h, nterm, terms, x, h->dLocZ.as<double>());
+    LocalPlan* P = nullptr;
+    int rc = find_local(h, h, nterm, terms, &P);
     if (rc) return rc;
-    HIP_TRY(h, launch_zdot(x, h->dLocZ.as<double>(), h->plan.n, h->dLocPart.as<double>(), kDotBlocks, s));
-    std::vector<double> part(2 * kDotBlocks);
-    HIP_TRY(h, hipMemcpyAsync(part.data(), h->dLocPart.p, sizeof(double) * part.size(),
-                              hipMemcpyDeviceToHost, s));
-    HIP_TRY(h, hipStreamSynchronize(s));
-    double ar = 0.0, ai = 0.0;
-    for (int b = 0; b < kDotBlocks; ++b) {
-        ar += part[2 * b];
-        ai += part[2 * b + 1];
+    if (!h->hLocPart.p) HIP_TRY(h, h->hLocPart.alloc(sizeof(double) * 2 * kDotBlocks));
+    double* part = h->hLocPart.as<double>();
+    if (P->launches.empty()) {          // monomial factors only: no image is stored
+        rc = run_local(h, h, *P, x, nullptr, part);
+        if (rc) return rc;
+    } else {
+        if (!h->dLocZ.p) HIP_TRY(h, h->dLocZ.alloc(sizeof(double) * 2 * (size_t)h->plan.n));
+        rc = run_local(h, h, *P, x, h->dLocZ.as<double>(), nullptr);
+        if (rc) return rc;
+        HIP_TRY(h, launch_zdot(x, h->dLocZ.as<double>(), h->plan.n, part, kDotBlocks, s));
     }
+    HIP_TRY(h, hipStreamSynchronize(s));
+    // in pairs: 2048 terms one after another would add up to 4 times the rounding of 256
+    static_assert((kDotBlocks & (kDotBlocks - 1)) == 0, "summed in halves");
+    for (int w = kDotBlocks; w >= 2; w /= 2)      // (Re, Im) pairs
+        for (int b = 0; b < w; ++b) part[b] += part[w + b];
+    const double ar = part[0], ai = part[1];
     if (re) *re = ar;
     if (im) *im = ai;
     return DMRG_OK;

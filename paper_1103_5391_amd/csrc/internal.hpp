@@ -334,15 +334,22 @@ struct ZPtrs {                      // per vector: the A, B and C buffers of one
     double* c[kWftMaxVec];
 };
 
-// One source block of a local term whose factors have at most one nonzero per row and per
-// column (site operators on exact blocks and at the central sites): every element of the block
-// goes to one element of the destination, scaled.  amap / bmap: offsets of the factors' maps
-// (input index -> output index, -1 for none, with the value) in the system / environment
-// tables, -1 for the identity.
-struct SJob {
-    int64_t src, dst;       // block offsets in x and y (complex elements)
-    int32_t d, e, dout;     // source rows and columns, destination rows
-    int32_t amap, bmap, pad;
+// Local terms whose factors have at most one nonzero per row and per column (site operators on
+// exact blocks and at the central sites): an element of the destination is the sum of one element
+// per term that reaches its block.  Work item: m <= kLocalChunk consecutive elements of a
+// destination block of d rows, from element (i0, j0) on.
+constexpr int kLocalChunk = 512;    // (2048: 5.3 and 8.6 us where 512 takes 4.7 and 6.6)
+struct LocalItem {
+    int64_t to;             // first element in y (complex elements)
+    int32_t d, i0, j0, m;
+    int32_t t0, nt;         // the block's sources t0 .. t0 + nt - 1
+};
+// Source block of one term.  amap / bmap: offsets of the factors' maps (destination row or column
+// -> source row or column, -1 for none, with the value) in the system / environment tables, -1
+// for the identity.
+struct LocalSrc {
+    int64_t off;            // in x (complex elements)
+    int32_t d, amap, bmap, pad;
     double alpha;
 };
 

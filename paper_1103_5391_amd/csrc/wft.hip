@@ -243,40 +243,113 @@ hipError_t launch_zgemm(const ZTile* t, int n, const ZPtrs& p, int nvec, int am,
     return launch_zgemm_modes(t, n, p, nvec, am, bm, s);
 }
 
-// Local term with monomial factors, work group (b, c) taking elements c kMonoChunk ... of source
-// block b (blocks in the first grid dimension, chunks in the second): element (i, j) goes to
-// (amap(i), bmap(j)) times alpha and the two factor values; the maps are one-to-one, so no two
-// elements of a term meet.  Real and imaginary planes at +nx / +ny.
-constexpr int64_t kMonoChunk = 2048;    // elements of a source block per work group
-__global__ __launch_bounds__(256) void k_local_mono(const SJob* __restrict__ jobs,
+// Sum of (ar, ai) over the work group's four wavefronts into part[0], part[1].
+__device__ __forceinline__ void store_group_sum(double ar, double ai, double* __restrict__ part) {
+    __shared__ double sr[4], si[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        ar += __shfl_xor(ar, o, 64);
+        ai += __shfl_xor(ai, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sr[threadIdx.x >> 6] = ar;
+        si[threadIdx.x >> 6] = ai;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        part[0] = (sr[0] + sr[1]) + (sr[2] + sr[3]);
+        part[1] = (si[0] + si[1]) + (si[2] + si[3]);
+    }
+}
+
+// Local terms with monomial factors, by destination: every element of y is the sum over the terms
+// of alpha times the two factor values times one element of x (0 where no term reaches it), in the
+// order of the terms.  DOT: nothing is stored; <x|y> goes to the work group's partial sums instead
+// (source and destination then share their layout).  Real and imaginary planes at +nx / +ny.
+// Bound by memory traffic (x and y once; 9.6 MB, 2 us for the 1000-state ladder) and, per term, the
+// chain source, map, element, of which a thread has two elements in flight: 4.7 us for a pair of
+// operators, 6.6 us for the expectation of two densities.  By source block the same work was a
+// clearing pass (3 us), a pass per term that read and wrote y (10 us each, with 64-bit divisions)
+// and for an expectation a pass over x and y (5 us).
+template <bool DOT>
+__global__ __launch_bounds__(256) void k_local_mono(const LocalItem* __restrict__ items, int nitems,
+                                                    const LocalSrc* __restrict__ srcs,
                                                     const int* __restrict__ mapS,
                                                     const double* __restrict__ valS,
                                                     const int* __restrict__ mapE,
                                                     const double* __restrict__ valE,
                                                     const double* __restrict__ x, int64_t nx,
                                                     double* __restrict__ y, int64_t ny) {
-    const SJob J = jobs[blockIdx.x];
-    const int64_t cnt = (int64_t)J.d * J.e;
-    const int64_t t0 = (int64_t)blockIdx.y * kMonoChunk;
-    const int64_t t1 = t0 + kMonoChunk < cnt ? t0 + kMonoChunk : cnt;
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
-        const int i = (int)(t % J.d), j = (int)(t / J.d);
-        const int io = J.amap < 0 ? i : mapS[J.amap + i];
-        const int jo = J.bmap < 0 ? j : mapE[J.bmap + j];
-        if (io < 0 || jo < 0) continue;
-        const double sc = J.alpha * (J.amap < 0 ? 1.0 : valS[J.amap + i]) * (J.bmap < 0 ? 1.0 : valE[J.bmap + j]);
-        const int64_t src = J.src + t, dst = J.dst + (int64_t)jo * J.dout + io;
-        y[dst] += sc * x[src];
-        y[ny + dst] += sc * x[nx + src];
+    constexpr int kPer = kLocalChunk / 256;
+    double ar = 0.0, ai = 0.0;
+    for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+        const LocalItem I = items[it];
+        // a thread's elements together, term by term: their loads are in flight at once
+        int i[kPer], j[kPer];
+        double zr[kPer], zi[kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int o = min((int)threadIdx.x + 256 * e, I.m - 1);
+            const unsigned u = (unsigned)I.i0 + (unsigned)o, dj = u / (unsigned)I.d;
+            i[e] = (int)(u - dj * (unsigned)I.d);
+            j[e] = I.j0 + (int)dj;
+            zr[e] = 0.0;
+            zi[e] = 0.0;
+        }
+        for (int k = I.t0; k < I.t0 + I.nt; ++k) {
+            const LocalSrc S = srcs[k];
+            int is[kPer], js[kPer];
+            double sc[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                is[e] = S.amap < 0 ? i[e] : mapS[S.amap + i[e]];
+                js[e] = S.bmap < 0 ? j[e] : mapE[S.bmap + j[e]];
+                sc[e] = S.alpha * (S.amap < 0 ? 1.0 : valS[S.amap + i[e]]) *
+                        (S.bmap < 0 ? 1.0 : valE[S.bmap + j[e]]);
+            }
+            double xr[kPer], xi[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                const int64_t at = S.off + (int64_t)max(js[e], 0) * S.d + max(is[e], 0);
+                xr[e] = x[at];
+                xi[e] = x[nx + at];
+            }
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                const bool ok = is[e] >= 0 && js[e] >= 0;
+                zr[e] = ok ? fma(sc[e], xr[e], zr[e]) : zr[e];
+                zi[e] = ok ? fma(sc[e], xi[e], zi[e]) : zi[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int o = (int)threadIdx.x + 256 * e;
+            if (o >= I.m) break;
+            const int64_t to = I.to + o;
+            if constexpr (DOT) {
+                const double xr = x[to], xi = x[nx + to];
+                ar += xr * zr[e] + xi * zi[e];
+                ai += xr * zi[e] - xi * zr[e];
+            } else {
+                y[to] = zr[e];
+                y[ny + to] = zi[e];
+            }
+        }
     }
+    if constexpr (DOT) store_group_sum(ar, ai, y + 2 * blockIdx.x);
 }
 
-hipError_t launch_local_mono(const SJob* jobs, int njobs, int64_t maxcnt, const int* mapS,
-                             const double* valS, const int* mapE, const double* valE,
-                             const double* x, int64_t nx, double* y, int64_t ny, hipStream_t s) {
-    if (njobs > 0 && maxcnt > 0)
-        hipLaunchKernelGGL(k_local_mono, dim3(njobs, (int)((maxcnt + kMonoChunk - 1) / kMonoChunk)), dim3(256),
-                           0, s, jobs, mapS, valS, mapE, valE, x, nx, y, ny);
+// part != nullptr: <x|y> in nblocks partial sums instead of y.
+hipError_t launch_local_mono(const LocalItem* items, int nitems, const LocalSrc* srcs,
+                             const int* mapS, const double* valS, const int* mapE,
+                             const double* valE, const double* x, int64_t nx, double* y, int64_t ny,
+                             double* part, int nblocks, hipStream_t s) {
+    if (part)
+        hipLaunchKernelGGL((k_local_mono<true>), dim3(nblocks), dim3(256), 0, s, items, nitems, srcs,
+                           mapS, valS, mapE, valE, x, nx, part, ny);
+    else if (nitems > 0)
+        hipLaunchKernelGGL((k_local_mono<false>), dim3(nitems), dim3(256), 0, s, items, nitems, srcs,
+                           mapS, valS, mapE, valE, x, nx, y, ny);
     return hipGetLastError();
 }
 
@@ -293,27 +366,13 @@ hipError_t launch_zero(double* x, int64_t n, hipStream_t s) {
 // in order.
 __global__ __launch_bounds__(256) void k_zdot(const double* __restrict__ x, const double* __restrict__ z,
                                               int64_t n, double* __restrict__ part) {
-    __shared__ double sr[256], si[256];
     double ar = 0.0, ai = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const double xr = x[i], xi = x[n + i], zr = z[i], zi = z[n + i];
         ar += xr * zr + xi * zi;
         ai += xr * zi - xi * zr;
     }
-    sr[threadIdx.x] = ar;
-    si[threadIdx.x] = ai;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sr[threadIdx.x] += sr[threadIdx.x + s];
-            si[threadIdx.x] += si[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = sr[0];
-        part[2 * blockIdx.x + 1] = si[0];
-    }
+    store_group_sum(ar, ai, part + 2 * blockIdx.x);
 }
 
 hipError_t launch_zdot(const double* x, const double* z, int64_t n, double* part, int nblocks,

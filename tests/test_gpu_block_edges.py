@@ -127,3 +127,48 @@ def test_move_at_tile_edges(env, m):
         assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-13 * np.linalg.norm(ref)
     w.destroy()
     h.destroy()
+
+
+def test_local_terms_mixed_and_many(env):
+    """Lists of terms with monomial factors (gathered), dense factors (products) and both, more lists
+    than a handle keeps, each called twice in turn, into the same sector; and their expectations.
+    Sums of at most 33 products per element: 1e-13 of the largest."""
+    from oracle import observables as Ob
+    torch, L = env
+    pb = _problem(DIMS[2])
+    rng = np.random.default_rng(I.SEED_BASE + 14)
+
+    def op(space, mono):
+        o = I.BlockOp((0, 0))
+        for p, d in enumerate(space.dim):
+            a = rng.standard_normal((d, d))
+            if mono:                                    # a permutation with values, some rows empty
+                a = np.where(np.eye(d)[rng.permutation(d)] > 0, a, 0.0)
+                a[rng.random(d) < 0.2] = 0.0
+            o.blocks[p] = a
+        return o
+
+    sS = [op(pb.S.space, m) for m in (True, False)]
+    sE = [op(pb.E.space, m) for m in (True, False)]
+    pbx, iS, iE = I.with_ops(pb, sS, sE)
+    h = L.dmrg_create(pbx)
+    x = I.random_psi(h.n, rng)
+    xd = torch.from_numpy(x).to("cuda")
+    none = -1
+    lists = []
+    for k in range(4):
+        c = 0.5 + k
+        lists += [([(c, iS[0], 0, iE[0], 0, 1), (1.0, none, 0, iE[0], 1, 0)],
+                   [(c, sS[0], sE[0], 1), (1.0, None, I._transpose(sE[0], pb.E.space), 0)]),
+                  ([(c, iS[1], 0, none, 0, 0), (2.0, iS[0], 1, none, 0, 1)],
+                   [(c, sS[1], None, 0), (2.0, I._transpose(sS[0], pb.S.space), None, 1)]),
+                  ([(c, iS[0], 0, iE[1], 0, 0)], [(c, sS[0], sE[1], 0)])]
+    for g, o in lists + lists:
+        y = torch.full((2 * h.n,), float("nan"), dtype=torch.float64, device="cuda")
+        for _ in range(2):
+            h.apply_local(h, g, xd, y)
+        ref = Ob.apply_terms(pbx, pbx, o, x)
+        assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-13 * np.max(np.abs(ref)) * 33
+        e, want = h.expect_local(g, xd), Ob.expect(pbx, o, x)
+        assert abs(e - want) <= 1e-12 * max(1.0, abs(want))
+    h.destroy()
