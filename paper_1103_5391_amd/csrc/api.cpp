@@ -45,10 +45,11 @@ hipError_t launch_lanczos_iter(const VecGroup&, int, int, hipStream_t);
 hipError_t launch_tridiag(const VecGroup&, const double*, int, int*, int, hipStream_t);
 hipError_t launch_lowest(const VecGroup&, int*, int, hipStream_t);
 hipError_t launch_count_nonfinite(const double*, int64_t, int*, hipStream_t);
-hipError_t launch_density(const DBlock*, int, const int*, int, const DTile*, int, const DensIn&, int,
-                          int64_t, void*, void*, double*, double*, void*, int, int*,
-                          const DBackItem*, int, double*, int, int, int*, double*, double*, int*,
-                          double*, hipStream_t);
+hipError_t launch_density(const DBlock*, int, const int*, int, int, const DTile*, int, const DensIn&,
+                          int, int64_t, void*, void*, double*, double*, void*, int, int*,
+                          const DBackItem*, int, const DBackItem*, int, const DBackItem*, int,
+                          double*, double*, int, int, int*, double*, double*, int*, double*,
+                          hipStream_t);
 hipError_t launch_combine(const VecGroup&, double* const*, double* const*, int, int, hipStream_t);
 hipError_t launch_wft(const ZTile*, int, const ZPtrs&, const ZTile*, int, const ZPtrs&, int, int64_t,
                       hipStream_t);
@@ -454,9 +455,10 @@ struct dmrg_ctx {
     // density matrix and truncation (built on first use): sectors, tiles, matrices, results
     // the call's results in one device area (per sector: the two sums, the number kept, the
     // eigen-decomposition flags), copied at once into pinned host memory
-    DevBuf dDBlk, dDSel, dDTile, dDBack, dDA, dDV, dDZ, dDS, dDT, dDEv, dDKept, dDRes;
+    DevBuf dDBlk, dDSel, dDTile, dDBack, dDEval, dDVec, dDTri, dDA, dDV, dDZ, dDS, dDT, dDEv, dDKept, dDRes;
     HostBuf hDRes;
     int dens_ntiles = 0, dens_ntot = 0, dens_nreg = 0, dens_nbt = 0, dens_nback = 0;
+    int dens_neval = 0, dens_nvec = 0, dens_dmax = 0;
     int64_t dens_nmat = 0;
     std::unique_ptr<dmrg_batch_ctx> chains;   // the handle's four chains of the 4-RHS mode
     // local operators (built on first use): raw operator blocks of both halves, the product
@@ -1818,11 +1820,18 @@ int dmrg_density_truncate(dmrg_handle h, const double* const* vecs, const double
         for (int b = 0; b < nb; ++b) order[b] = b;
         std::stable_sort(order.begin(), order.end(),
                          [&](int x, int y) { return P.blocks[x].d > P.blocks[y].d; });
-        std::vector<DBackItem> back;
+        std::vector<DBackItem> back, eval, vecs;
+        for (int b : order) {
+            for (int j = 0; j < P.blocks[b].d; j += kEvalCols) eval.push_back(DBackItem{b, j});
+            for (int j = 0; j < P.blocks[b].d; j += vec_cols(P.blocks[b].d)) vecs.push_back(DBackItem{b, j});
+            h->dens_dmax = std::max(h->dens_dmax, (int)P.blocks[b].d);
+        }
         for (int b : order)
             for (int jb = 0; jb < P.blocks[b].d; jb += back_cols(P.blocks[b].d))
                 back.push_back(DBackItem{b, jb});
         h->dens_nback = (int)back.size();
+        h->dens_neval = (int)eval.size();
+        h->dens_nvec = (int)vecs.size();
         h->dens_ntiles = (int)tiles.size();
         h->dens_ntot = (int)eoff;
         h->dens_nmat = aoff;
@@ -1831,6 +1840,9 @@ int dmrg_density_truncate(dmrg_handle h, const double* const* vecs, const double
         HIP_TRY(h, upload(h->dDTile, tiles, s));
         HIP_TRY(h, upload(h->dDSel, sel, s));
         HIP_TRY(h, upload(h->dDBack, back, s));
+        HIP_TRY(h, upload(h->dDEval, eval, s));
+        HIP_TRY(h, upload(h->dDVec, vecs, s));
+        HIP_TRY(h, h->dDTri.alloc(sizeof(double) * dens_tri(eoff, nb)));
         HIP_TRY(h, h->dDA.alloc(2 * sizeof(double) * (size_t)aoff));
         HIP_TRY(h, h->dDV.alloc(2 * sizeof(double) * (size_t)aoff));
         HIP_TRY(h, h->dDZ.alloc(sizeof(double) * (size_t)aoff));
@@ -1852,10 +1864,12 @@ int dmrg_density_truncate(dmrg_handle h, const double* const* vecs, const double
     int* d_nk = reinterpret_cast<int*>(d_sums + 2 * (size_t)nb);
     int* d_flags = d_nk + nb;
     HIP_TRY(h, launch_density(h->dDBlk.as<DBlock>(), nb, h->dDSel.as<int>(), h->dens_nreg,
-                              h->dDTile.as<DTile>(), h->dens_ntiles, in, nvec, P.n, h->dDA.p,
+                              h->dens_dmax, h->dDTile.as<DTile>(), h->dens_ntiles, in, nvec, P.n, h->dDA.p,
                               h->dDV.p, h->dDZ.as<double>(), h->dDS.as<double>(), h->dDT.p,
                               h->dens_nbt, d_flags, h->dDBack.as<DBackItem>(), h->dens_nback,
-                              h->dDEv.as<double>(), h->dens_ntot, keep,
+                              h->dDEval.as<DBackItem>(), h->dens_neval, h->dDVec.as<DBackItem>(),
+                              h->dens_nvec, h->dDEv.as<double>(), h->dDTri.as<double>(),
+                              h->dens_ntot, keep,
                               h->dDKept.as<int>(), evals, evecs, d_nk, d_sums, s));
     HIP_TRY(h, hipMemcpyAsync(h->hDRes.p, h->dDRes.p, res_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));

@@ -8,14 +8,15 @@
 // with Psi_{l,p} the d_p x e_q block of target l.  Steps:
 //   k_density   rho_p in 16 x 16 tiles on or below the diagonal (one wavefront per tile on the
 //               FP64 matrix cores, K = e_q columns per target, every target in turn)
-//   k_heig      eigen-decomposition of every rho_p up to the back-transformation, one work
+//   k_heig      Householder reduction of every rho_p to a real tridiagonal matrix T, one work
 //               group per sector (k_heig_r for sectors of up to 160 states, with the matrix
-//               in registers during the reduction): Householder reduction to a real tridiagonal matrix T,
-//               eigenvalues of T by multisection on Sturm counts, eigenvectors of T by inverse
-//               iteration (no cluster of close eigenvalues larger than 8) or else by implicit QL
-//               with shifts (one lane lists the rotations of the next sweep while the other
-//               wavefronts apply the current one to their rows)
-//   k_back_t    the compact-WY factor T of every block of reflectors, all in parallel
+//               in registers)
+//   k_eval_t    eigenvalues of T by multisection on Sturm counts, eight per work group; and the
+//               compact-WY factor of every block of reflectors
+//   k_vectors   eigenvectors of T by inverse iteration, a few columns per work group (sectors
+//               without a cluster of close eigenvalues larger than 8)
+//   k_ql        the other sectors: implicit QL with shifts (one lane lists the rotations of the next
+//               sweep while the other wavefronts apply the current one to their rows)
 //   k_heig_back back-transformation by the reflectors in those blocks, several work groups per
 //               sector
 //   k_rank      global rank of every eigenvalue (larger first; equal values by sector, then by
@@ -91,75 +92,97 @@ __device__ __forceinline__ void handover_barrier() {
 // target in turn,
 //   Re rho = sum_l w_l (Re P_i Re P_j^T + Im P_i Im P_j^T),
 //   Im rho = sum_l w_l (Im P_i Re P_j^T - Re P_i Im P_j^T),
-// one wavefront per tile (i0, j0) with j0 <= i0: v_mfma_f64_16x16x4f64 with lane (g, r) =
-// (lane div 16, lane mod 16) supplying row r of each panel at column c0 + g, the weight folded
-// into P_i, and the result in lane (g, r) at row g + 4 v, column r.  A tile below the diagonal
-// is also written, conjugated, at (j, i) (rho is Hermitian).  Written to A (complex,
-// column-major d x d at blk.aoff).  Work group 0 also clears the per-sector flags of the
-// eigen-decomposition, and all work groups clear the rank counters of k_rank.
-__global__ __launch_bounds__(64) void k_density(const DBlock* __restrict__ blks,
-                                                const DTile* __restrict__ tiles, const DensIn in,
-                                                int nv, int64_t n, dv2* __restrict__ A,
-                                                int* __restrict__ fail, int nblk,
-                                                int* __restrict__ kept, int ntot) {
+// one work group of four wavefronts per tile (i0, j0) with j0 <= i0: v_mfma_f64_16x16x4f64 with lane
+// (g, r) = (lane div 16, lane mod 16) supplying row r of each panel at column c0 + g, the weight
+// folded into P_i, and the result in lane (g, r) at row g + 4 v, column r.  The wavefronts deal the
+// steps (16 columns of one target) among them and add their tiles in a fixed order, wavefront v
+// the rows g + 4 v.  A tile below the diagonal is also written, conjugated, at (j, i) (rho is
+// Hermitian).  Written to A (complex, column-major d x d at blk.aoff).  Work group 0 also clears the
+// per-sector flags of the eigen-decomposition, and all work groups clear the rank counters of k_rank.
+// Bound by the loads of a step (16 of 8 bytes a lane, four segments of 128 bytes each) and their latency:
+// 35 us for five targets of the 1000-state ladder, whose MFMAs are 12 us if spread evenly.  With one
+// wavefront per tile the 148-state sector's tiles were 50 steps of 1024 MFMA cycles, and the
+// accumulators, left in accumulation registers, were copied around every step: 47 us.
+constexpr int kDensWaves = 4;
+__global__ __launch_bounds__(64 * kDensWaves, 2) void k_density(
+    const DBlock* __restrict__ blks, const DTile* __restrict__ tiles, const DensIn in, int nv,
+    int64_t n, dv2* __restrict__ A, int* __restrict__ fail, int nblk, int* __restrict__ kept,
+    int ntot) {
     typedef double d4 __attribute__((ext_vector_type(4)));
     // the per-sector flags and the rank counters of this call start at zero
     if (blockIdx.x == 0)
         for (int t = threadIdx.x; t < nblk; t += blockDim.x) fail[t] = 0;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < ntot; t += gridDim.x * blockDim.x)
         kept[t] = 0;
+    __shared__ double part[kDensWaves][8][64];
     const DTile tl = tiles[blockIdx.x];
     const DBlock B = blks[tl.blk];
-    const int ln = threadIdx.x, g = ln >> 4, r = ln & 15;
+    const int ln = threadIdx.x & 63, g = ln >> 4, r = ln & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = B.d, e = B.e;
     const int ia = tl.i0 + r, jb = tl.j0 + r;
     const bool oka = ia < d, okb = jb < d;
     const int64_t ra = B.off + (oka ? ia : 0), rb = B.off + (okb ? jb : 0);
     d4 cre[2] = {(d4){0.0, 0.0, 0.0, 0.0}, (d4){0.0, 0.0, 0.0, 0.0}};
     d4 cim[2] = {(d4){0.0, 0.0, 0.0, 0.0}, (d4){0.0, 0.0, 0.0, 0.0}};
-    // one K chunk of 4 columns (c = c0 + g) into accumulator pair q
-    auto chunk = [&](double are, double aim, double bre, double bim, int q) {
-        cre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(are, bre, cre[q], 0, 0, 0);
-        cre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bim, cre[q], 0, 0, 0);
-        cim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bre, cim[q], 0, 0, 0);
-        cim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-are, bim, cim[q], 0, 0, 0);
-    };
-    for (int l = 0; l < nv; ++l) {
+    const int per = (e + 15) >> 4, steps = nv * per;
+    double v[2][4][4];
+    auto load = [&](int buf, int st) {                  // columns beyond e read the last one
+        const int l = st / per, c0 = 16 * (st - l * per);
         const double* __restrict__ x = in.v[l];
-        const double wa = oka ? in.w[l] : 0.0;          // rows beyond d: zero
-        const double mb = okb ? 1.0 : 0.0;
-        int c0 = 0;
-        for (; c0 + 16 <= e; c0 += 16) {                // four whole chunks, loads first
-            double v[4][4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t cc = (int64_t)(c0 + 4 * u + g) * d;
-                v[u][0] = x[ra + cc];
-                v[u][1] = x[n + ra + cc];
-                v[u][2] = x[rb + cc];
-                v[u][3] = x[n + rb + cc];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                chunk(wa * v[u][0], wa * v[u][1], mb * v[u][2], mb * v[u][3], u & 1);
+        for (int u = 0; u < 4; ++u) {
+            const int64_t cc = (int64_t)min(c0 + 4 * u + g, e - 1) * d;
+            v[buf][u][0] = x[ra + cc];
+            v[buf][u][1] = x[n + ra + cc];
+            v[buf][u][2] = x[rb + cc];
+            v[buf][u][3] = x[n + rb + cc];
         }
-        for (; c0 < e; c0 += 4) {                       // the rest, columns beyond e zero
-            const int c = c0 + g;
-            const bool okc = c < e;
-            const int64_t cc = (int64_t)(okc ? c : 0) * d;
-            const double sa = okc ? wa : 0.0, sb = okc ? mb : 0.0;
-            chunk(sa * x[ra + cc], sa * x[n + ra + cc], sb * x[rb + cc], sb * x[n + rb + cc], 0);
+    };
+    auto mma = [&](int buf, int st) {                   // rows beyond d and columns beyond e: zero
+        const int l = st / per, c0 = 16 * (st - l * per);
+        const double wl = in.w[l];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool okc = c0 + 4 * u + g < e;
+            const bool ka = oka && okc, kb = okb && okc;
+            const double are = ka ? wl * v[buf][u][0] : 0.0, aim = ka ? wl * v[buf][u][1] : 0.0;
+            const double bre = kb ? v[buf][u][2] : 0.0, bim = kb ? v[buf][u][3] : 0.0;
+            const int q = u & 1;
+            cre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(are, bre, cre[q], 0, 0, 0);
+            cim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bre, cim[q], 0, 0, 0);
+            cre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bim, cre[q], 0, 0, 0);
+            cim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-are, bim, cim[q], 0, 0, 0);
+        }
+    };
+    if (wv < steps) {
+        load(0, wv);
+        for (int st = wv; st < steps; st += 2 * kDensWaves) {
+            load(1, min(st + kDensWaves, steps - 1));
+            mma(0, st);
+            load(0, min(st + 2 * kDensWaves, steps - 1));
+            if (st + kDensWaves < steps) mma(1, st + kDensWaves);
         }
     }
     const d4 sre = cre[0] + cre[1], sim = cim[0] + cim[1];
-    dv2* __restrict__ a = A + B.aoff;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = tl.i0 + g + 4 * v, j = tl.j0 + r;
-        if (i < d && j < d) {
-            a[(int64_t)j * d + i] = (dv2){sre[v], sim[v]};
-            if (tl.i0 != tl.j0) a[(int64_t)i * d + j] = (dv2){sre[v], -sim[v]};
-        }
+    for (int q = 0; q < 4; ++q) {
+        part[wv][q][ln] = sre[q];
+        part[wv][4 + q][ln] = sim[q];
+    }
+    __syncthreads();
+    static_assert(kDensWaves == 4, "one wavefront per accumulator component");
+    double re = part[0][wv][ln], im = part[0][4 + wv][ln];
+#pragma unroll
+    for (int w = 1; w < kDensWaves; ++w) {
+        re += part[w][wv][ln];
+        im += part[w][4 + wv][ln];
+    }
+    dv2* __restrict__ a = A + B.aoff;
+    const int i = tl.i0 + g + 4 * wv, j = tl.j0 + r;
+    if (i < d && j < d) {
+        a[(int64_t)j * d + i] = (dv2){re, im};
+        if (tl.i0 != tl.j0) a[(int64_t)i * d + j] = (dv2){re, -im};
     }
 }
 
@@ -211,15 +234,13 @@ __device__ __forceinline__ dv2 wg_sum1c(dv2 v, double* red) {
     return s;
 }
 
-constexpr int kEigThreads = 512;    // threads of an eigen-decomposition work group
+constexpr int kEigThreads = 512;    // threads of a reduction or QL work group
+constexpr int kEvalThreads = 256;   // threads of an eigenvalue work group, 32 per eigenvalue
 constexpr int kQlMaxSweeps = 64;    // QL sweeps per eigenvalue at most
 constexpr int kClusterMax = 8;      // inverse iteration when no cluster of eigenvalues is larger
 constexpr double kClusterGap = 1e-5;  // eigenvalues closer than this times |T| form a cluster
-constexpr int kSturmPts = 1;        // Sturm sequences one lane evaluates together in bisection
-constexpr int kSturmRun = 8;        // Sturm steps whose LDS reads are issued together
 constexpr int kInvRun = 8;          // rows an inverse-iteration solve loads before storing
 constexpr int kInvSolves = 2;       // inverse-iteration solves per eigenvector
-constexpr int kWaveCluster = 4;     // clusters of at least this many members go to a wavefront
 constexpr int kHhLdsDim = 66;       // largest trailing matrix the Householder phase keeps in LDS
 constexpr int kQlRun = 8;           // QL rotations whose LDS reads are issued together
 constexpr int kEigChunk = 16;       // loads a thread issues together in the QL rotation pass
@@ -553,81 +574,92 @@ __device__ __forceinline__ void hh_regs(const int d, dv2* __restrict__ a, double
     }
 }
 
-// The Sturm count of T - x I (the number of negative pivots of its L D L^T, that is of the
-// eigenvalues below x), with the arithmetic of the multisection rounds in heig: the hardware
-// reciprocal with one Newton step, runs of kSturmRun steps without the tiny-pivot guard, a run
-// that ends in a NaN taken again with it.
-__device__ __forceinline__ int sturm_count(int d, const double* __restrict__ dg,
-                                           const double* __restrict__ e2, double x) {
-    double q = dg[0] - x;
-    int cnt = q < 0.0;
-    auto step = [&](double di, double ei, bool guard) {
-        if (guard && fabs(q) < 1e-300) q = -1e-300;
-        const double r0 = __builtin_amdgcn_rcp(q);
-        const double r = fma(fma(-q, r0, 1.0), r0, r0);
-        q = (di - x) - ei * r;
-        cnt += q < 0.0;
-    };
-    int i = 1;
-    for (; i + kSturmRun <= d; i += kSturmRun) {
-        double dr[kSturmRun], er[kSturmRun];
+// The Sturm count of T - x I (the number of its eigenvalues below 0) by the signs of its leading
+// principal minors, p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2} (Givens): a step is one dependent
+// fused multiply-add, where the ratios p_i / p_{i-1} cost a reciprocal and three (88 cycles a step).
+// Each step is exact for entries changed by an ulp or two, so the counts place every
+// eigenvalue within a few eps |T|.  |T| is scaled to [0.5, 1) by the caller, so a run of kSturmRun steps
+// grows by less than 2^24 and the two minors carried on are scaled between runs.  A zero counts by
+// its sign bit, whichever it is, as its neighbours have opposite signs; two zeros in turn (a
+// diagonal entry equal to x beside a zero e) would stay zeros, so a run that ends in them is taken
+// again with a tiny value of the opposite sign in place of a zero.
+// The entries are the same in every lane and come by scalar loads, a run ahead: broadcast reads from
+// LDS bound the pass (two per step and wavefront).  rec: per run of kSturmRun rows the diagonal entries
+// and the squares of the subdiagonal entries above them (the first 0), nrun runs, the last one
+// padded with rows that change no sign (diagonal 4, above every x; subdiagonal 0).
+__device__ __forceinline__ int sturm_count(int nrun, const double* __restrict__ rec, double x) {
+    static_assert(kSturmRun < 32, "the signs of a run in one word");
+    double p2 = 0.0, p1 = 1.0;
+    unsigned sg = 0;                                    // signs of the minors, the latest lowest
+    int cnt = 0;
+    double cur[2 * kSturmRun], nxt[2 * kSturmRun];
 #pragma unroll
-        for (int t = 0; t < kSturmRun; ++t) {
-            dr[t] = dg[i + t];
-            er[t] = e2[i - 1 + t];
+    for (int t = 0; t < 2 * kSturmRun; ++t) cur[t] = rec[t];
+    for (int k = 0; k < nrun; ++k) {
+        // this run's entries are here before the next one's loads go out (scalar loads return in any
+        // order, so a wait is one for all of them)
+        __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        const double* __restrict__ rn = rec + 2 * kSturmRun * min(k + 1, nrun - 1);
+#pragma unroll
+        for (int t = 0; t < 2 * kSturmRun; ++t) nxt[t] = rn[t];
+        auto run = [&](bool guard) {
+#pragma unroll
+            for (int t = 0; t < kSturmRun; ++t) {
+                double p = fma(cur[t] - x, p1, -(cur[kSturmRun + t] * p2));
+                if (guard && p == 0.0) p = -copysign(1e-200, p1);
+                sg = __builtin_amdgcn_alignbit(sg, (unsigned)__double2hiint(p), 31);
+                p2 = p1;
+                p1 = p;
+            }
+        };
+        const double p10 = p1, p20 = p2;
+        const unsigned s0 = sg;
+        run(false);
+        if (p1 == 0.0 && p2 == 0.0) {
+            p1 = p10 != 0.0 ? p10 : -copysign(1e-200, p20);
+            p2 = p20;
+            sg = s0;
+            run(true);
         }
-        const double q0 = q;
-        const int c0 = cnt;
+        cnt += __popc((sg ^ (sg >> 1)) & ((1u << kSturmRun) - 1));
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+        p1 = __builtin_amdgcn_ldexp(p1, -ex);
+        p2 = __builtin_amdgcn_ldexp(p2, -ex);
 #pragma unroll
-        for (int t = 0; t < kSturmRun; ++t) step(dr[t], er[t], false);
-        if (__builtin_isnan(q)) {
-            q = q0;
-            cnt = c0;
-#pragma unroll
-            for (int t = 0; t < kSturmRun; ++t) step(dr[t], er[t], true);
-        }
+        for (int t = 0; t < 2 * kSturmRun; ++t) cur[t] = nxt[t];
     }
-    for (; i < d; ++i) step(dg[i], e2[i - 1], true);
     return cnt;
 }
+// Doubles of a sector's runs before sector blk, eoff states in.
+__device__ __forceinline__ int64_t sturm_off(int64_t eoff, int blk) {
+    return 2 * (eoff + (int64_t)kSturmRun * blk);
+}
 
-// Eigen-decomposition of rho_p up to the back-transformation, one work group per sector
-// (LAPACK's path for Hermitian matrices):
-//   1. Householder reduction to a real tridiagonal matrix: step k takes the reflector
-//      H_k = I - tau_k v_k v_k^H that maps column k below the diagonal to beta_k e_1 (beta_k
-//      real) and updates the trailing matrix B <- H_k^H B H_k as B - v w^H - w v^H with
-//      w = tau B v - (tau / 2)(w0^H v) v, w0 = tau B v.  v_k (v_k[0] = 1) is kept below the
-//      subdiagonal of A and tau_k on its diagonal.
-//   2. Eigenvalues of the tridiagonal matrix by multisection on Sturm counts.
-//   3. Eigenvectors of the tridiagonal matrix into the real matrix Z: inverse iteration when no
-//      cluster of close eigenvalues has more than kClusterMax members (3a), else implicit QL
-//      with shifts (3b: one lane runs the scalar recurrence and lists the plane rotations of a
-//      sweep while the other wavefronts apply the previous sweep to their rows of Z).
-// Eigenvalues go to ev, eigenvectors to Z (row-major, or column-major after QL: bit 1 of
-// fail[blk]); k_heig_back applies the reflectors.  A QL sweep count above the limit sets bit 0
-// of fail[blk].
-// NT threads, sectors of at most MAXD states; REG: step 1 by hh_regs (NT = kEigThreadsR).
-// Bisection takes GB lanes per eigenvalue, the largest power of two up to 8 with 2 GB d <= SBT.
-template <int NT, int MAXD, bool REG, int SBT = NT>
-__device__ __forceinline__ void heig(const DBlock B, const int blk, dv2* __restrict__ A,
-                                     double* __restrict__ Zb, double* __restrict__ Sb,
-                                     double* __restrict__ ev, int* __restrict__ fail) {
+// Householder reduction of rho_p to a real tridiagonal matrix T, one work group per sector: step k
+// takes the reflector H_k = I - tau_k v_k v_k^H that maps column k below the diagonal to beta_k e_1
+// (beta_k real) and updates the trailing matrix B <- H_k^H B H_k as B - v w^H - w v^H with
+// w = tau B v - (tau / 2)(w0^H v) v, w0 = tau B v.  v_k (v_k[0] = 1) is kept below the subdiagonal
+// of A and tau_k on its diagonal, for the back-transformation; the diagonal of T goes to tri,
+// the subdiagonal (and a final 0) to tri + ntot, at blk.eoff; the matrix scaled by a power of two to
+// |T| in [0.5, 1) (Gershgorin's bound) to rec, as the Sturm counts read it; and |T| and the ends of the
+// Gershgorin interval to tnb.
+// NT threads, sectors of at most MAXD states; REG: by hh_regs (NT = kEigThreadsR).
+template <int NT, int MAXD, bool REG>
+__device__ __forceinline__ void heig(const DBlock B, dv2* __restrict__ A, double* __restrict__ tri,
+                                     int ntot, double* __restrict__ rec, double* __restrict__ tnb) {
     const int d = B.d, tid = threadIdx.x;
     dv2* __restrict__ a = A + B.aoff;
-    double* __restrict__ Z = Zb + B.aoff;
     __shared__ double dg[MAXD], e[MAXD];
     __shared__ dv2 vv[MAXD], ww[MAXD], vv1[MAXD], ww1[MAXD];
-    __shared__ dv2 pp[NT];
-    __shared__ double red[3 * NT / 64];
-    __shared__ int s_i0[2], s_cnt[2], s_done[2], s_path, s_nlarge;
-    __shared__ double s_lo, s_hi, s_tn;
-    // ---------------------------------------------------------------- 1. tridiagonal
     if constexpr (REG) {
         static_assert(NT == kEigThreadsR && MAXD % 32 == 0, "32 x 32 thread grid");
         __shared__ dv2 rp[2 * (NT / 64) * MAXD];        // row sums of the half-waves
         __shared__ dv2 ws[MAXD], s_tau;
         hh_regs<MAXD / 32>(d, a, dg, e, vv, vv1, ws, ww, ww1, rp, &s_tau);
     } else {
+    __shared__ dv2 pp[NT];
+    __shared__ double red[3 * NT / 64];
     __shared__ dv2 s_alpha;                             // alpha of the current reflector
     __shared__ dv2 tm[kHhLdsDim * kHhLdsDim];          // trailing matrix once it fits
     // The update of step k is applied lazily, inside step k + 1's pass over the trailing
@@ -760,394 +792,447 @@ __device__ __forceinline__ void heig(const DBlock B, const int blk, dv2* __restr
         }
     }
     }
+    __shared__ double s_lo[NT / 64], s_hi[NT / 64];
     __syncthreads();
-    // ---------------------------------------------------------------- 2. eigenvalues
-    // Bisection on Sturm counts (the signs of the pivots of T - x I = L D L^T), one thread per
-    // eigenvalue, from the Gershgorin interval to an absolute width of 2 eps |T| (|T| the
-    // Gershgorin bound): the reduction to T already moves the eigenvalues by about eps |T|, so
-    // narrower intervals around small eigenvalues would add rounds and no accuracy (LAPACK's
-    // bisection takes the same absolute tolerance by default).
-    double* e2 = reinterpret_cast<double*>(pp);         // squared subdiagonal (pp is free now)
-    double* lam = reinterpret_cast<double*>(ww);        // eigenvalues, ascending
-    for (int i = tid; i + 1 < d; i += NT) e2[i] = e[i] * e[i];
+    // rows beyond d repeat row 0
+    double lo = dg[0] - (d > 1 ? fabs(e[0]) : 0.0), hi = dg[0] + (d > 1 ? fabs(e[0]) : 0.0);
+    for (int i = tid; i < d; i += NT) {
+        const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < d ? fabs(e[i]) : 0.0);
+        lo = fmin(lo, dg[i] - r);
+        hi = fmax(hi, dg[i] + r);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+    }
+    if ((tid & 63) == 0) {
+        s_lo[tid >> 6] = lo;
+        s_hi[tid >> 6] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+        lo = fmin(lo, s_lo[w]);
+        hi = fmax(hi, s_hi[w]);
+    }
+    const double tn = fmax(fmax(fabs(lo), fabs(hi)), 1e-300);
+    const int ex = __builtin_amdgcn_frexp_exp(tn);
+    for (int i = tid; i < d; i += NT) {
+        tri[B.eoff + i] = dg[i];
+        tri[ntot + B.eoff + i] = e[i];
+    }
+    for (int i = tid; i < (d + kSturmRun - 1) / kSturmRun * kSturmRun; i += NT) {
+        const double es = i > 0 && i < d ? __builtin_amdgcn_ldexp(e[i - 1], -ex) : 0.0;
+        double* __restrict__ r = rec + 2 * kSturmRun * (i / kSturmRun) + i % kSturmRun;
+        r[0] = i < d ? __builtin_amdgcn_ldexp(dg[i], -ex) : 4.0;
+        r[kSturmRun] = es * es;
+    }
     if (tid == 0) {
-        double lo = dg[0], hi = dg[0], tn = 0.0;
-        for (int i = 0; i < d; ++i) {
-            const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < d ? fabs(e[i]) : 0.0);
-            lo = fmin(lo, dg[i] - r);
-            hi = fmax(hi, dg[i] + r);
+        tnb[0] = tn;
+        tnb[1] = lo;
+        tnb[2] = hi;
+    }
+}
+
+// sel: the sectors of the launch, one per work group
+__global__ __launch_bounds__(kEigThreads) void k_heig(const DBlock* __restrict__ blks,
+                                                      const int* __restrict__ sel,
+                                                      dv2* __restrict__ A,
+                                                      double* __restrict__ tri, int ntot,
+                                                      double* __restrict__ rec,
+                                                      double* __restrict__ tnorm) {
+    const int b = sel[blockIdx.x];
+    heig<kEigThreads, kDensMaxDim, false>(blks[b], A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
+         tnorm + 3 * b);
+}
+
+// The same for sectors of at most kRegMaxDim states, with the matrix in registers.
+__global__ __launch_bounds__(kEigThreadsR) void k_heig_r(const DBlock* __restrict__ blks,
+                                                         const int* __restrict__ sel,
+                                                         dv2* __restrict__ A,
+                                                         double* __restrict__ tri, int ntot,
+                                                         double* __restrict__ rec,
+                                                         double* __restrict__ tnorm) {
+    const int b = sel[blockIdx.x];
+    heig<kEigThreadsR, kRegMaxDim, true>(blks[b], A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
+         tnorm + 3 * b);
+}
+
+// Eigenvalues of T by multisection on Sturm counts, from the Gershgorin interval to an absolute width
+// of 2 eps |T| (|T| the Gershgorin bound): the reduction to T already moves the eigenvalues by about
+// eps |T|, so narrower intervals around small eigenvalues would add rounds and no accuracy
+// (LAPACK's bisection takes the same absolute tolerance by default).  32 lanes per eigenvalue: each
+// counts at one of 32 interior points, and the piece that holds the eigenvalue is kept (from
+// the point before the first whose count exceeds its index, to that one).  Eight eigenvalues j0 ..
+// per work group, in the scaled T.
+// Bound by the instructions of a Sturm pass (148 steps, 11 rounds): 32 lanes, since 64 would save two
+// rounds and double the wavefronts.  40 us for the 4000 eigenvalues of the 1000-state ladder (57 with
+// T in LDS, 71 with the ratios of the minors); in the reduction's work group, all eigenvalues of a
+// sector on one CU with four lanes each, this took 165 us for 148 states.
+__device__ __forceinline__ void eigenvalues(const DBlock B, int j0, const double* __restrict__ rec,
+                                            double* __restrict__ ev, const double* __restrict__ tnb) {
+    const int d = B.d, tid = threadIdx.x, nrun = (d + kSturmRun - 1) / kSturmRun;
+    const int ex = __builtin_amdgcn_frexp_exp(tnb[0]);
+    const double tns = __builtin_amdgcn_ldexp(tnb[0], -ex);
+    double lo = __builtin_amdgcn_ldexp(tnb[1], -ex) - 2.220446049250313e-16 * tns;
+    double hi = __builtin_amdgcn_ldexp(tnb[2], -ex) + 2.220446049250313e-16 * tns;
+    const int j = min(j0 + (tid >> 5), d - 1), q = tid & 31;
+    for (int it = 0; it < 64; ++it) {                   // the same in all lanes of an eigenvalue
+        if (hi - lo <= 4.440892098500626e-16 * tns) break;
+        const double step = (hi - lo) / 33.0;
+        const int cnt = sturm_count(nrun, rec, lo + step * (q + 1));
+        const unsigned hit = (unsigned)(__ballot(cnt > j) >> (tid & 32));
+        const int f = hit ? __builtin_ctz(hit) : 32;    // first point beyond eigenvalue j
+        const double nlo = f > 0 ? lo + step * f : lo, nhi = f < 32 ? lo + step * (f + 1) : hi;
+        if (!(nhi - nlo < hi - lo)) break;              // no progress at rounding level
+        lo = nlo;
+        hi = nhi;
+    }
+    if (q == 0 && j0 + (tid >> 5) < d) ev[B.eoff + j] = __builtin_amdgcn_ldexp(0.5 * (lo + hi), ex);
+}
+
+// Whether the sector's eigenvalues lam (ascending) hold a cluster of more than kClusterMax members
+// (neighbours closer than kClusterGap |T|): its eigenvectors are then taken by QL.  Called by whole
+// wavefronts; the same in every lane.
+__device__ __forceinline__ bool big_cluster(const double* __restrict__ lam, int d, double tn) {
+    const int lane = threadIdx.x & 63;
+    for (int b = 0; b + kClusterMax < d; b += 64) {
+        const int j = b + lane;
+        bool run = j + kClusterMax < d;
+#pragma unroll
+        for (int k = 0; k < kClusterMax; ++k) {
+            const int i = min(j + k, d - 2);
+            run &= lam[i + 1] - lam[i] <= kClusterGap * tn;
         }
-        tn = fmax(fabs(lo), fabs(hi));
-        s_lo = lo - 2.220446049250313e-16 * tn - 1e-300;
-        s_hi = hi + 2.220446049250313e-16 * tn + 1e-300;
-        s_tn = fmax(tn, 1e-300);
+        if (__ballot(run)) return true;
+    }
+    return false;
+}
+
+// Factors and vectors of an inverse iteration: row i of column l at offset at(i, l), the next row
+// `row` further on.  In LDS a record of six values (z, U: 1 / pivot, superdiagonals 1 and 2, L:
+// multiplier, swap flag: 1 where rows i, i + 1 were exchanged), so that a row needs one address and few
+// wide accesses; in global memory (bound by memory instructions) U and L packed and Z row-major.
+typedef double dv2u __attribute__((ext_vector_type(2), aligned(16)));
+struct InvLds {
+    double* p;                                          // 16-byte aligned
+    int nc, row;
+    __device__ __forceinline__ int at(int i, int l) const { return 6 * (i * nc + l); }
+    __device__ __forceinline__ double& z(int o) const { return p[o]; }
+    __device__ __forceinline__ void put_u(int o, double a, double b, double c) const {
+        p[o + 1] = a;
+        *reinterpret_cast<dv2u*>(p + o + 2) = (dv2u){b, c};
+    }
+    __device__ __forceinline__ void get_zu(int o, double& z, double& a, double& b, double& c) const {
+        const dv2u x = *reinterpret_cast<const dv2u*>(p + o), y = *reinterpret_cast<const dv2u*>(p + o + 2);
+        z = x[0];
+        a = x[1];
+        b = y[0];
+        c = y[1];
+    }
+    __device__ __forceinline__ void put_l(int o, double m, double s) const {
+        *reinterpret_cast<dv2u*>(p + o + 4) = (dv2u){m, s};
+    }
+    __device__ __forceinline__ void get_l(int o, double& m, double& s) const {
+        const dv2u x = *reinterpret_cast<const dv2u*>(p + o + 4);
+        m = x[0];
+        s = x[1];
+    }
+};
+struct InvGlobal {
+    typedef double f4u __attribute__((ext_vector_type(4), aligned(8)));
+    typedef double f2u __attribute__((ext_vector_type(2), aligned(8)));
+    double* zb;                                         // the sector's Z, from its column s on
+    f4u* fu;
+    f2u* fl;
+    int row;                                            // d <= 1024: offsets fit
+    __device__ __forceinline__ int at(int i, int l) const { return i * row + l; }
+    __device__ __forceinline__ double& z(int o) const { return zb[o]; }
+    __device__ __forceinline__ void put_u(int o, double a, double b, double c) const {
+        fu[o] = (f4u){a, b, c, 0.0};
+    }
+    __device__ __forceinline__ void get_zu(int o, double& z, double& a, double& b, double& c) const {
+        const f4u f = fu[o];
+        z = zb[o];
+        a = f[0];
+        b = f[1];
+        c = f[2];
+    }
+    __device__ __forceinline__ void put_l(int o, double m, double s) const { fl[o] = (f2u){m, s}; }
+    __device__ __forceinline__ void get_l(int o, double& m, double& s) const {
+        const f2u f = fl[o];
+        m = f[0];
+        s = f[1];
+    }
+};
+
+// Eigenvectors s .. s + nc - 1 of T by inverse iteration, one wavefront, lane l column l (nc <= 64;
+// the columns are whole clusters): T - lam I = P L U (partial pivoting, pivots floored at eps |T|),
+// the factorisation fused with the forward substitution of the fixed start vector, and the first
+// solve.  An eigenvalue apart from both neighbours takes its remaining solves (kInvSolves in
+// all, the vector rescaled between them).  Then every cluster takes its members in order, all
+// clusters in step: each vector is orthogonalised against the cluster's earlier vectors (modified
+// Gram-Schmidt, the lanes sharing the rows) before and after every further solve, and normalised.
+// sc: per column the factor its vector has still to be multiplied with.
+template <class M>
+__device__ __forceinline__ void inverse_iteration(const M& m, int d, int s, int nc,
+                                                  const double* __restrict__ dg,
+                                                  const double* __restrict__ e,
+                                                  const double* __restrict__ lam, double tn,
+                                                  double& sc) {
+    const int lane = threadIdx.x & 63, l = lane;
+    const double tiny = 2.220446049250313e-16 * tn;
+    auto sync = [] {                                    // the lanes' stores before the others' loads
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // backward substitution U^-1 of column l, rows loaded a run of kInvRun ahead of the arithmetic
+    // (the first d mod kInvRun rows one by one); returns |z|^2
+    auto backward = [&]() {
+        double y1 = 0.0, y2 = 0.0, nrm = 0.0;
+        int o = m.at(d - 1, l);
+        auto row = [&](int at, double zv, double a0, double a1, double a2) {
+            const double y = ((zv - a2 * y2) - a1 * y1) * a0;
+            m.z(at) = y;
+            nrm += y * y;
+            y2 = y1;
+            y1 = y;
+        };
+        int left = d;
+        for (; left % kInvRun != 0; --left, o -= m.row) {
+            double zv, a0, a1, a2;
+            m.get_zu(o, zv, a0, a1, a2);
+            row(o, zv, a0, a1, a2);
+        }
+        for (; left > 0; left -= kInvRun, o -= kInvRun * m.row) {
+            double zv[kInvRun], a0[kInvRun], a1[kInvRun], a2[kInvRun];
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) m.get_zu(o - t * m.row, zv[t], a0[t], a1[t], a2[t]);
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) row(o - t * m.row, zv[t], a0[t], a1[t], a2[t]);
+        }
+        return nrm;
+    };
+    // one solve of column l from Z (times scale): P and L^-1 (the current entry carried in a
+    // register; row i is stored only after row i + 1 is read), then U^-1
+    auto solve = [&](double scale) {
+        int o = m.at(0, l);
+        double cur = scale * m.z(o);
+        auto row = [&](int at, double zn, double lw, double pw) {
+            const double nxt = scale * zn;
+            const bool swap = pw != 0.0;
+            const double a = swap ? nxt : cur, b = swap ? cur : nxt;
+            m.z(at) = a;
+            cur = b - lw * a;
+        };
+        int left = d - 1;
+        for (; left % kInvRun != 0; --left, o += m.row) {
+            double lw, pw;
+            m.get_l(o, lw, pw);
+            row(o, m.z(o + m.row), lw, pw);
+        }
+        for (; left > 0; left -= kInvRun, o += kInvRun * m.row) {
+            double zn[kInvRun], pw[kInvRun], lw[kInvRun];
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) {
+                zn[t] = m.z(o + (t + 1) * m.row);
+                m.get_l(o + t * m.row, lw[t], pw[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) row(o + t * m.row, zn[t], lw[t], pw[t]);
+        }
+        m.z(o) = cur;
+        return backward();
+    };
+    auto first_of_cluster = [&](int j) { return j == 0 || !(lam[j] - lam[j - 1] <= kClusterGap * tn); };
+    const int j = s + min(l, nc - 1);
+    int rank = 0;                                       // place of this column in its cluster
+    while (rank < kClusterMax && !first_of_cluster(j - rank)) ++rank;
+    const bool alone = rank == 0 && (j + 1 >= d || first_of_cluster(j + 1));
+    sc = 1.0;
+    if (l < nc) {
+        const double x = lam[j];
+        // start vector cos(0.7 i + j), by the recurrence
+        // cos(a + (i + 1) b) = 2 cos(b) cos(a + i b) - cos(a + (i - 1) b) (any fixed,
+        // generic vector serves; this one costs no call per element)
+        const double c2 = 2.0 * cos(0.7);
+        double cm = cos(j - 0.7), c0 = cos((double)j);
+        auto next_start = [&]() {
+            const double v = c0, cn = c2 * c0 - cm;
+            cm = c0;
+            c0 = cn;
+            return v;
+        };
+        // factorisation, row by row ((dd, du) = the current row's diagonal and superdiagonal), with
+        // the forward substitution P, L^-1 of the start vector
+        double dd = dg[0] - x, du = d > 1 ? e[0] : 0.0;
+        double cur = next_start();
+        int o = m.at(0, l);
+        auto row = [&](double sub, double di, double nu) {
+            const double nd = di - x, nxt = next_start();
+            // without a swap: U row (1 / dd, du, 0); with one: (1 / sub, nd, nu)
+            const bool keep = fabs(dd) >= fabs(sub);
+            const double piv = fabs(dd) >= tiny ? dd : (dd < 0.0 ? -tiny : tiny);
+            const double ip = recip(keep ? piv : sub);
+            const double mu = (keep ? sub : dd) * ip;
+            m.put_u(o, ip, keep ? du : nd, keep ? 0.0 : nu);
+            m.put_l(o, mu, keep ? 0.0 : 1.0);
+            const double dn = keep ? nd - mu * du : du - mu * nd;
+            du = keep ? nu : -mu * nu;
+            dd = dn;
+            const double a = keep ? cur : nxt, b = keep ? nxt : cur;
+            m.z(o) = a;
+            cur = b - mu * a;
+            o += m.row;
+        };
+        int i = 0;
+        for (; i + kInvRun < d - 1; i += kInvRun) {
+            double er[kInvRun + 1], dr[kInvRun];
+#pragma unroll
+            for (int t = 0; t <= kInvRun; ++t) er[t] = e[i + t];
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) dr[t] = dg[i + 1 + t];
+#pragma unroll
+            for (int t = 0; t < kInvRun; ++t) row(er[t], dr[t], er[t + 1]);
+        }
+        for (; i + 1 < d; ++i) row(e[i], dg[i + 1], i + 2 < d ? e[i + 1] : 0.0);
+        const double piv = fabs(dd) >= tiny ? dd : (dd < 0.0 ? -tiny : tiny);
+        m.put_u(o, 1.0 / piv, 0.0, 0.0);
+        m.z(o) = cur;
+        sc = 1.0 / sqrt(fmax(backward(), 1e-300));
+        if (alone)
+            for (int rep = 1; rep < kInvSolves; ++rep) sc = 1.0 / sqrt(fmax(solve(sc), 1e-300));
+    }
+    // |z_c|^2 after the projection of column c against its cluster's earlier columns f .. c - 1
+    auto mgs = [&](int f, int c) {
+        double nrm = 0.0;
+        for (int k = f; k < c; ++k) {
+            double part = 0.0;
+            for (int i = lane; i < d; i += 64) part += m.z(m.at(i, k)) * m.z(m.at(i, c));
+            const double dot = wave_sum(part);
+            double pn = 0.0;
+            for (int i = lane; i < d; i += 64) {
+                const double y = m.z(m.at(i, c)) - dot * m.z(m.at(i, k));
+                m.z(m.at(i, c)) = y;
+                pn += y * y;
+            }
+            nrm = wave_sum(pn);
+        }
+        return nrm;
+    };
+    for (int k = 0; k < kClusterMax; ++k) {
+        const bool mine = l < nc && !alone && rank == k;
+        const unsigned long long who = __ballot(mine);
+        if (!who) break;                                // no member of this rank, so none of a later
+        double sq = 0.0;                                // |z|^2 of this lane's column
+        auto project = [&] {
+            sync();
+            for (unsigned long long w = who; w; w &= w - 1) {
+                const int c = __builtin_ctzll(w);
+                const double nrm = mgs(c - k, c);
+                if (c == l) sq = nrm;
+            }
+            sync();
+        };
+        if (k > 0) project();
+        double f = mine ? (k > 0 ? 1.0 / sqrt(fmax(sq, 1e-300)) : sc) : 0.0;
+        for (int rep = 1; rep < kInvSolves; ++rep) {
+            if (mine) sq = solve(f);
+            if (k > 0) project();
+            if (mine) f = 1.0 / sqrt(fmax(sq, 1e-300));
+        }
+        if (mine) {
+            for (int i = 0; i < d; ++i) m.z(m.at(i, l)) *= f;
+            sc = 1.0;
+        }
+    }
+    sync();
+}
+
+// Inverse iteration of one work item (blk, j0): the clusters (single eigenvalues mostly) that begin
+// at j0 .. j0 + vec_cols(d) - 1, in LDS where they fit, else in the sector's global scratch; nothing
+// for sectors that QL takes.  Z row-major.  cap: doubles of LDS for the columns.
+// Bound by the dependent chains of the factorisation (18 us for 148 states) and of the three
+// substitutions after it (9 us each): 55 us.  In the reduction's work group, a thread per eigenvalue of
+// a sector and everything in global memory, this took 150 us, bound by one CU's memory
+// instructions, and 340 us for a sector of 84 states in clusters of eight.
+__global__ __launch_bounds__(64) void k_vectors(const DBlock* __restrict__ blks,
+                                                const DBackItem* __restrict__ items,
+                                                const double* __restrict__ tri, int ntot,
+                                                const double* __restrict__ ev,
+                                                const double* __restrict__ tnorm, int dmax, int cap,
+                                                double* __restrict__ Zb, double* __restrict__ Sb) {
+    extern __shared__ double lds[];
+    const DBackItem it = items[blockIdx.x];
+    const DBlock B = blks[it.blk];
+    const int d = B.d, lane = threadIdx.x;
+    double* const lam = lds;
+    double* const dg = lds + dmax;
+    double* const e = lds + 2 * dmax;
+    for (int i = lane; i < d; i += 64) {
+        lam[i] = ev[B.eoff + i];
+        dg[i] = tri[B.eoff + i];
+        e[i] = tri[ntot + B.eoff + i];
     }
     __syncthreads();
-    // one shared round: the counts at NT equally spaced interior points of the interval (every
-    // thread one point, the arithmetic of the rounds below), from which each eigenvalue starts:
-    // the first point whose count exceeds its index and the point before it (a binary search
-    // for a change of the predicate count > j, which brackets eigenvalue j whatever the counts
-    // do in between)
-    __shared__ int s_cnt0[NT];
-    const double w0 = (s_hi - s_lo) / (NT + 1);
-    s_cnt0[tid] = sturm_count(d, dg, e2, s_lo + w0 * (tid + 1));
-    __syncthreads();
-    {
-        // GB lanes per eigenvalue (a power of two inside a wavefront), kSturmPts points per lane
-        // (independent Sturm sequences interleaved in one pass over T): the lanes count at
-        // GB kSturmPts interior points of the interval and keep the piece that holds the
-        // eigenvalue
-        // Only the whole wavefronts that hold eigenvalues take part (nact threads; lanes past
-        // the last eigenvalue repeat it, so that every lane of a wave runs the same rounds).
-        constexpr int P = kSturmPts;
-        int GB = 1;
-        while (GB < 8 && 2 * GB * d <= SBT) GB *= 2;
-        const int nact = GB * d >= NT ? NT : (GB * d + 63) / 64 * 64;
-        const int qb = tid % GB, jslots = nact / GB;
-        const int jend = (d + jslots - 1) / jslots * jslots;
-        for (int j0 = tid / GB; tid < nact && j0 < jend; j0 += jslots) {
-            const int j = j0 < d ? j0 : d - 1;
-            int a = -1, b = NT;                         // count(a) <= j < count(b) (virtual ends)
-            while (b - a > 1) {
-                const int m = (a + b) >> 1;
-                if (s_cnt0[m] > j) b = m; else a = m;
-            }
-            double lo = a < 0 ? s_lo : s_lo + w0 * (a + 1);
-            double hi = b >= NT ? s_hi : s_lo + w0 * (b + 1);
-            for (int it = 0; it < 256; ++it) {
-                if (hi - lo <= 4.440892098500626e-16 * s_tn) break;
-                const double step = (hi - lo) / (GB * P + 1);
-                double x[P], q[P];
-                int cnt[P];
-#pragma unroll
-                for (int u = 0; u < P; ++u) {
-                    x[u] = lo + step * (qb * P + u + 1);
-                    q[u] = dg[0] - x[u];
-                    cnt[u] = q[u] < 0.0;
-                }
-                // 1 / q: the hardware reciprocal and one Newton step (a few ulp; the counts then
-                // place each eigenvalue within a few eps |T|)
-                // a pivot q with |q| < 1e-300 is taken as -1e-300 (guarded); the unguarded step
-                // meets such a pivot as a NaN (1 / 0 or an overflow), after which its count is
-                // discarded and the run taken again with the guard
-                auto sturm = [&](double di, double ei, bool guard) {
-#pragma unroll
-                    for (int u = 0; u < P; ++u) {
-                        if (guard && fabs(q[u]) < 1e-300) q[u] = -1e-300;
-                        const double r0 = __builtin_amdgcn_rcp(q[u]);
-                        const double r = fma(fma(-q[u], r0, 1.0), r0, r0);
-                        q[u] = (di - x[u]) - ei * r;
-                        cnt[u] += q[u] < 0.0;
-                    }
-                };
-                int i = 1;
-                for (; i + kSturmRun <= d; i += kSturmRun) {   // LDS reads of a run issued first
-                    double dr[kSturmRun], er[kSturmRun];
-#pragma unroll
-                    for (int t = 0; t < kSturmRun; ++t) {
-                        dr[t] = dg[i + t];
-                        er[t] = e2[i - 1 + t];
-                    }
-                    double q0[P];
-                    int c0[P];
-#pragma unroll
-                    for (int u = 0; u < P; ++u) {
-                        q0[u] = q[u];
-                        c0[u] = cnt[u];
-                    }
-#pragma unroll
-                    for (int t = 0; t < kSturmRun; ++t) sturm(dr[t], er[t], false);
-                    bool bad = false;
-#pragma unroll
-                    for (int u = 0; u < P; ++u) bad |= __builtin_isnan(q[u]);
-                    if (bad) {
-#pragma unroll
-                        for (int u = 0; u < P; ++u) {
-                            q[u] = q0[u];
-                            cnt[u] = c0[u];
-                        }
-#pragma unroll
-                        for (int t = 0; t < kSturmRun; ++t) sturm(dr[t], er[t], true);
-                    }
-                }
-                for (; i < d; ++i) sturm(dg[i], e2[i - 1], true);
-                double nlo = lo, nhi = hi;
-                bool found = false;
-                for (int l = 0; l < GB; ++l) {
-#pragma unroll
-                    for (int u = 0; u < P; ++u) {
-                        const int cu = __shfl(cnt[u], (tid & 63) - qb + l, 64);
-                        const double xu = lo + step * (l * P + u + 1);
-                        if (!found) {
-                            if (cu > j) {
-                                nhi = xu;
-                                found = true;
-                            } else {
-                                nlo = xu;
-                            }
-                        }
-                    }
-                }
-                if (!(nhi - nlo < hi - lo)) break;      // no progress at rounding level
-                lo = nlo;
-                hi = nhi;
-            }
-            if (qb == 0 && j0 < d) lam[j] = 0.5 * (lo + hi);
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {                                     // largest cluster decides the path
-        int run = 1, big = 1;
-        for (int j = 1; j < d; ++j) {
-            run = lam[j] - lam[j - 1] <= kClusterGap * s_tn ? run + 1 : 1;
-            big = max(big, run);
-        }
-        s_path = big <= kClusterMax ? 0 : 1;
-    }
-    __syncthreads();
-    int zr = d, zc = 1;                                 // Z(i, j) at i zr + j zc
-    if (s_path == 0) {
-        // ------------------------------------------------------------ 3a. inverse iteration
-        // Every eigenvalue has its own thread: T - lam I = P L U (partial pivoting, pivots
-        // floored at eps |T|), the factorisation fused with the forward substitution of the
-        // fixed start vector, and the first solve; an eigenvalue apart from both neighbours
-        // takes its remaining solves (kInvSolves in all, the vector rescaled between them) on
-        // the same thread and leaves 1 / |z| in sc.  Then each cluster of close eigenvalues
-        // takes its members in order (the thread of its first eigenvalue, or a wavefront for a
-        // cluster of kWaveCluster or more): each vector is orthogonalised against the cluster's
-        // earlier vectors (modified Gram-Schmidt) after every solve, normalised, and its sc set
-        // to 1.  A last pass over all elements scales the
-        // columns.  Z and the factors are row-major [i][j] (consecutive threads, consecutive
-        // addresses).
-        // the factors of T - lam_j I, packed so that a row takes one or two wide accesses (the
-        // passes are bound by memory instructions): row i of U (1 / pivot, the superdiagonals
-        // 1 and 2, an unused slot) at fu[i d + j], row i of L and the swap flag (1 where rows
-        // i, i + 1 were exchanged) at fl[i d + j]; consecutive threads, consecutive records
-        typedef double f4u __attribute__((ext_vector_type(4), aligned(8)));
-        typedef double f2u __attribute__((ext_vector_type(2), aligned(8)));
-        f4u* fu = reinterpret_cast<f4u*>(Sb + 6 * B.aoff);
-        f2u* fl = reinterpret_cast<f2u*>(Sb + 6 * B.aoff + 4 * (int64_t)d * d);
-        double* sc = reinterpret_cast<double*>(vv1);    // per eigenvector: 1 / |z|
-        const double tiny = 2.220446049250313e-16 * s_tn;
-        auto first_of_cluster = [&](int j) { return j == 0 || lam[j] - lam[j - 1] > kClusterGap * s_tn; };
-        // a cluster of at least kWaveCluster members: its fourth member is close too
-        static_assert(kWaveCluster == 4, "large() tests three following members");
-        auto large = [&](int j0) {
-            return j0 + kWaveCluster - 1 < d && !first_of_cluster(j0 + 1) &&
-                   !first_of_cluster(j0 + 2) && !first_of_cluster(j0 + 3);
-        };
-        int* const largel = reinterpret_cast<int*>(pp);   // first members of large clusters
-        if (tid == 0) s_nlarge = 0;
-        __syncthreads();
-        // one solve of eigenvector j from Z (times scale): P, L^-1 then U^-1; returns |z|^2
-        auto backward = [&](int j) {
-            // backward: U^-1, runs of kInvRun rows loaded first
-            double y1 = 0.0, y2 = 0.0, nrm = 0.0;
-            for (int i0 = d - 1; i0 >= 0; i0 -= kInvRun) {
-                double zv[kInvRun], a0[kInvRun], a1[kInvRun], a2[kInvRun];
-#pragma unroll
-                for (int t = 0; t < kInvRun; ++t) {
-                    const int i = max(i0 - t, 0);
-                    const int64_t at = (int64_t)i * d + j;
-                    zv[t] = Z[at];
-                    const f4u f = fu[at];
-                    a0[t] = f[0];
-                    a1[t] = f[1];
-                    a2[t] = f[2];
-                }
-#pragma unroll
-                for (int t = 0; t < kInvRun; ++t) {
-                    if (i0 - t < 0) break;
-                    const double y = (zv[t] - a1[t] * y1 - a2[t] * y2) * a0[t];
-                    Z[(int64_t)(i0 - t) * d + j] = y;
-                    nrm += y * y;
-                    y2 = y1;
-                    y1 = y;
-                }
-            }
-            return nrm;
-        };
-        auto solve = [&](int j, double scale) {
-            // forward: P and L^-1 (the current entry carried in a register); a run of
-            // kInvRun rows is loaded before any of it is stored (row i is stored only
-            // after row i + 1 is read, so no load depends on the stores)
-            double cur = scale * Z[j];
-            for (int i0 = 0; i0 + 1 < d; i0 += kInvRun) {
-                double zn[kInvRun], pw[kInvRun], lw[kInvRun];
-#pragma unroll
-                for (int t = 0; t < kInvRun; ++t) {
-                    const int i = min(i0 + t, d - 2);
-                    const int64_t at = (int64_t)i * d + j;
-                    zn[t] = Z[at + d];
-                    const f2u f = fl[at];
-                    lw[t] = f[0];
-                    pw[t] = f[1];
-                }
-#pragma unroll
-                for (int t = 0; t < kInvRun; ++t) {
-                    if (i0 + t + 1 >= d) break;
-                    double nxt = scale * zn[t];
-                    if (pw[t] != 0.0) {
-                        const double tt = cur;
-                        cur = nxt;
-                        nxt = tt;
-                    }
-                    Z[(int64_t)(i0 + t) * d + j] = cur;
-                    cur = nxt - lw[t] * cur;
-                }
-            }
-            Z[(int64_t)(d - 1) * d + j] = cur;
-            return backward(j);
-        };
-        for (int j = tid; j < d; j += NT) {
-            const double x = lam[j];
-            // start vector cos(0.7 i + j), by the recurrence
-            // cos(a + (i + 1) b) = 2 cos(b) cos(a + i b) - cos(a + (i - 1) b) (any fixed,
-            // generic vector serves; this one costs no call per element)
-            const double c2 = 2.0 * cos(0.7);
-            double cm = cos(j - 0.7), c0 = cos((double)j);
-            auto next_start = [&]() {
-                const double v = c0, cn = c2 * c0 - cm;
-                cm = c0;
-                c0 = cn;
-                return v;
-            };
-            // factorisation, row by row ((dd, du) = the current row's diagonal and
-            // superdiagonal), with the forward substitution P, L^-1 of the start vector (the
-            // current entry carried in a register)
-            double dd = dg[0] - x, du = d > 1 ? e[0] : 0.0;
-            double cur = next_start();
-            for (int i = 0; i + 1 < d; ++i) {
-                const int64_t at = (int64_t)i * d + j;
-                const double sub = e[i], nd = dg[i + 1] - x, nu = i + 2 < d ? e[i + 1] : 0.0;
-                double nxt = next_start();
-                double m;
-                if (fabs(dd) >= fabs(sub)) {
-                    const double piv = fabs(dd) >= tiny ? dd : (dd < 0.0 ? -tiny : tiny);
-                    const double ip = recip(piv);
-                    m = sub * ip;
-                    fu[at] = (f4u){ip, du, 0.0, 0.0};
-                    fl[at] = (f2u){m, 0.0};
-                    dd = nd - m * du;
-                    du = nu;
-                } else {
-                    const double is = recip(sub);
-                    m = dd * is;
-                    fu[at] = (f4u){is, nd, nu, 0.0};
-                    fl[at] = (f2u){m, 1.0};
-                    dd = du - m * nd;
-                    du = -m * nu;
-                    const double tt = cur;
-                    cur = nxt;
-                    nxt = tt;
-                }
-                Z[at] = cur;
-                cur = nxt - m * cur;
-            }
-            {
-                const int64_t at = (int64_t)(d - 1) * d + j;
-                const double piv = fabs(dd) >= tiny ? dd : (dd < 0.0 ? -tiny : tiny);
-                fu[at] = (f4u){1.0 / piv, 0.0, 0.0, 0.0};
-                Z[at] = cur;
-            }
-            // the first solve: backward substitution U^-1
-            sc[j] = 1.0 / sqrt(fmax(backward(j), 1e-300));
-            if (first_of_cluster(j) && large(j)) largel[atomicAdd(&s_nlarge, 1)] = j;
-            // an eigenvalue apart from both neighbours: the remaining solves now
-            if (first_of_cluster(j) && (j + 1 >= d || first_of_cluster(j + 1)))
-                for (int rep = 1; rep < kInvSolves; ++rep) sc[j] = 1.0 / sqrt(fmax(solve(j, sc[j]), 1e-300));
-            ev[B.eoff + j] = x;
-        }
-        handover_barrier();
-        // clusters: the thread of the first member takes the members in order, each
-        // orthogonalised against the cluster's earlier vectors (modified Gram-Schmidt) after
-        // every solve, as the first solve was
-        auto mgs = [&](int j0, int j) {                 // returns |z_j|^2 after the projection
-            double nrm = 0.0;
-            for (int k = j0; k < j; ++k) {
-                double dot = 0.0;
-                for (int i = 0; i < d; ++i) dot += Z[(int64_t)i * d + k] * Z[(int64_t)i * d + j];
-                nrm = 0.0;
-                for (int i = 0; i < d; ++i) {
-                    const double y = Z[(int64_t)i * d + j] - dot * Z[(int64_t)i * d + k];
-                    Z[(int64_t)i * d + j] = y;
-                    nrm += y * y;
-                }
-            }
-            return nrm;
-        };
-        for (int j0 = tid; j0 < d; j0 += NT) {
-            if (!first_of_cluster(j0) || j0 + 1 >= d || first_of_cluster(j0 + 1)) continue;
-            if (large(j0)) continue;
-            for (int j = j0; j < d && (j == j0 || !first_of_cluster(j)); ++j) {
-                double s = sc[j];
-                if (j > j0) s = 1.0 / sqrt(fmax(mgs(j0, j), 1e-300));
-                for (int rep = 1; rep < kInvSolves; ++rep) {
-                    double nrm = solve(j, s);
-                    if (j > j0) nrm = mgs(j0, j);
-                    s = 1.0 / sqrt(fmax(nrm, 1e-300));
-                }
-                for (int i = 0; i < d; ++i) Z[(int64_t)i * d + j] *= s;
-                sc[j] = 1.0;
-            }
-        }
-        // large clusters (the Gram-Schmidt steps grow as the square of the size, listed in
-        // phase 1): one wavefront each, dealt from the last wavefront down.  Lane 0 runs the solves; the lanes share the
-        // Gram-Schmidt steps (rows i = lane mod 64, sums by wave_sum, the same in every lane);
-        // the fences order the lanes' global stores of Z before the other lanes' loads.
-        {
-            const int wv = tid >> 6, lane = tid & 63;
-            auto mgsw = [&](int j0, int j) {            // |z_j|^2 after the projection
-                double nrm = 0.0;
-                for (int k = j0; k < j; ++k) {
-                    double part = 0.0;
-                    for (int i = lane; i < d; i += 64)
-                        part += Z[(int64_t)i * d + k] * Z[(int64_t)i * d + j];
-                    const double dot = wave_sum(part);
-                    double pn = 0.0;
-                    for (int i = lane; i < d; i += 64) {
-                        const double y = Z[(int64_t)i * d + j] - dot * Z[(int64_t)i * d + k];
-                        Z[(int64_t)i * d + j] = y;
-                        pn += y * y;
-                    }
-                    nrm = wave_sum(pn);
-                }
-                return nrm;
-            };
-            // the list's order depends on the atomics, but every cluster takes the same
-            // arithmetic on whichever wavefront runs it
-            for (int q = NT / 64 - 1 - wv; q < s_nlarge; q += NT / 64) {
-                const int j0 = largel[q];
-                for (int j = j0; j < d && (j == j0 || !first_of_cluster(j)); ++j) {
-                    double s = sc[j];
-                    if (j > j0) s = 1.0 / sqrt(fmax(mgsw(j0, j), 1e-300));
-                    for (int rep = 1; rep < kInvSolves; ++rep) {
-                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-                        double nrm = 0.0;
-                        if (lane == 0) nrm = solve(j, s);
-                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-                        nrm = __shfl(nrm, 0, 64);
-                        if (j > j0) nrm = mgsw(j0, j);
-                        s = 1.0 / sqrt(fmax(nrm, 1e-300));
-                    }
-                    for (int i = lane; i < d; i += 64) Z[(int64_t)i * d + j] *= s;
-                    if (lane == 0) sc[j] = 1.0;
-                }
-            }
-        }
-        handover_barrier();
-        for (int t = tid; t < d * d; t += NT) Z[t] *= sc[t % d];
-        handover_barrier();
+    const double tn = tnorm[3 * it.blk];
+    if (big_cluster(lam, d, tn)) return;
+    auto start = [&](int j) {                           // the first cluster that begins at j or later
+        while (j > 0 && j < d && lam[j] - lam[j - 1] <= kClusterGap * tn) ++j;
+        return j;
+    };
+    const int j1 = min(it.jb + vec_cols(d), d);
+    const int s = start(it.jb);
+    if (s >= j1) return;
+    const int nc = start(j1) - s;
+    static_assert(kVecCols + kClusterMax <= 64, "a lane per column");
+    double* const Z = Zb + B.aoff;
+    double sc;
+    // the lanes share the rows of the final scaling: lane (ri, c) column c of rows ri, ri + per, ..
+    const int per = 64 / nc, ri = lane / nc, c = lane - ri * nc;
+    if (6 * d * nc <= cap) {
+        const InvLds m{lds + (3 * dmax + 1) / 2 * 2, nc, 6 * nc};
+        inverse_iteration(m, d, s, nc, dg, e, lam, tn, sc);
+        const double f = __shfl(sc, c, 64);
+        if (ri < per)
+            for (int i = ri; i < d; i += per) Z[(int64_t)i * d + s + c] = m.z(m.at(i, c)) * f;
     } else {
-    zr = 1;
-    zc = d;
+        const InvGlobal m{Z + s, reinterpret_cast<InvGlobal::f4u*>(Sb + 6 * B.aoff) + s,
+                          reinterpret_cast<InvGlobal::f2u*>(Sb + 6 * B.aoff + 4 * (int64_t)d * d) + s, d};
+        inverse_iteration(m, d, s, nc, dg, e, lam, tn, sc);
+        const double f = __shfl(sc, c, 64);
+        if (ri < per)
+            for (int i = ri; i < d; i += per) Z[(int64_t)i * d + s + c] *= f;
+    }
+}
+
+// Eigenvalues and eigenvectors (column-major in Z: bit 1 of fail[blk]) of T by implicit QL with shifts,
+// one work group per sector, for sectors with a cluster of more than kClusterMax eigenvalues (the
+// others return).  Wavefront 0 runs the sweep recurrence (its first lane) and lists the rotations of
+// the next sweep while the other wavefronts apply the current one to their rows (two rotation
+// lists in LDS).  A sweep count above the limit sets bit 0 of fail[blk].
+__global__ __launch_bounds__(kEigThreads) void k_ql(const DBlock* __restrict__ blks,
+                                                    const double* __restrict__ tri, int ntot,
+                                                    double* __restrict__ ev,
+                                                    const double* __restrict__ tnorm,
+                                                    double* __restrict__ Zb, int* __restrict__ fail) {
+    constexpr int NT = kEigThreads, MAXD = kDensMaxDim;
+    const int blk = blockIdx.x;
+    const DBlock B = blks[blk];
+    const int d = B.d, tid = threadIdx.x;
+    if (!big_cluster(ev + B.eoff, d, tnorm[3 * blk])) return;
+    double* __restrict__ Z = Zb + B.aoff;
+    __shared__ double dg[MAXD], e[MAXD], rot[4 * MAXD];
+    __shared__ int s_i0[2], s_cnt[2], s_done[2];
+    for (int i = tid; i < d; i += NT) {
+        dg[i] = tri[B.eoff + i];
+        e[i] = tri[ntot + B.eoff + i];
+    }
     for (int64_t it = tid; it < (int64_t)d * d; it += NT)
         Z[it] = (it % d == it / d) ? 1.0 : 0.0;
     handover_barrier();
-    // ---------------------------------------------------------------- 3b. implicit QL
-    // Wavefront 0 runs the sweep recurrence (its first lane) and lists the rotations of the next
-    // sweep while the other wavefronts apply the current one (two rotation lists in LDS).
-    auto rcl = [&](int buf) { return buf ? reinterpret_cast<double*>(ww) : reinterpret_cast<double*>(vv); };
+    auto rcl = [&](int buf) { return rot + 2 * MAXD * buf; };
     auto rsl = [&](int buf) { return rcl(buf) + MAXD; };
     int l = 0, sweeps = 0;                              // scalar state (the same in every lane of wave 0)
     // wave 0: the next sweep into list buf.  All its lanes look for the end m of the unreduced
@@ -1288,30 +1373,7 @@ __device__ __forceinline__ void heig(const DBlock B, const int blk, dv2* __restr
     }
     handover_barrier();                                 // rows of Z to the column owners
     for (int i = tid; i < d; i += NT) ev[B.eoff + i] = dg[i];
-    }
-    if (tid == 0 && zr == 1) atomicOr(&fail[blk], 2);   // Z column-major (QL path)
-}
-
-// sel: the sectors of the launch, one per work group
-__global__ __launch_bounds__(kEigThreads) void k_heig(const DBlock* __restrict__ blks,
-                                                      const int* __restrict__ sel,
-                                                      dv2* __restrict__ A, double* __restrict__ Zb,
-                                                      double* __restrict__ Sb,
-                                                      double* __restrict__ ev, int* __restrict__ fail) {
-    const int b = sel[blockIdx.x];
-    heig<kEigThreads, kDensMaxDim, false>(blks[b], b, A, Zb, Sb, ev, fail);
-}
-
-// The same for sectors of at most kRegMaxDim states, with the matrix in registers in step 1.
-__global__ __launch_bounds__(kEigThreadsR) void k_heig_r(const DBlock* __restrict__ blks,
-                                                         const int* __restrict__ sel,
-                                                         dv2* __restrict__ A,
-                                                         double* __restrict__ Zb,
-                                                         double* __restrict__ Sb,
-                                                         double* __restrict__ ev,
-                                                         int* __restrict__ fail) {
-    const int b = sel[blockIdx.x];
-    heig<kEigThreadsR, kRegMaxDim, true>(blks[b], b, A, Zb, Sb, ev, fail);
+    if (tid == 0) atomicOr(&fail[blk], 2);              // Z column-major
 }
 
 // Back-transformation Y = H_0 H_1 ... H_{d-2} Z of one sector's eigenvectors, BT reflectors
@@ -1320,8 +1382,8 @@ __global__ __launch_bounds__(kEigThreadsR) void k_heig_r(const DBlock* __restric
 // every block has BT of them.  The product H_k1 ... H_k2 of a block is I - V T V^H (V the
 // block's reflectors as columns, T upper triangular from the taus on the diagonal of A and the
 // Gram matrix V^H V, T[r][c] = -tau_c sum_{r <= u < c} T[r][u] G[u][c], T[c][c] = tau_c).
-//   k_back_t     the T of every block, in parallel (one work group per sector and block), into
-//                Tb at blk.toff (block bi, from the bottom: bi BT^2 elements on, T[r][c] at
+//   k_eval_t     the T of every block, in parallel (one work group per sector and block, beside
+//                those of the eigenvalues, which take longer), into Tb at blk.toff (block bi, from the bottom: bi BT^2 elements on, T[r][c] at
 //                r + BT c);
 //   k_heig_back  Y - V (T (V^H Y)) block after block, one work group per item of a host list
 //                (a sector and its range of back_cols(d) columns of Y; larger sectors first, so
@@ -1344,12 +1406,12 @@ __device__ __forceinline__ dv2 back_v(const dv2* __restrict__ a, int d, int k, i
     return i == k + 1 ? (dv2){1.0, 0.0} : a[(int64_t)k * d + i];
 }
 
-constexpr int kBackTThreads = 256;  // threads of k_back_t (8 per Gram entry, 28 entries)
+constexpr int kBackTThreads = kEvalThreads;   // 8 per Gram entry, 28 entries
 template <int BT>
 __device__ __forceinline__ void back_t(int d, int bi, const dv2* __restrict__ a,
-                                       dv2* __restrict__ tg) {
+                                       dv2* __restrict__ tg, dv2* __restrict__ Vl) {
     constexpr int NP = BT * (BT - 1) / 2, GL = 8;      // Gram pairs, lanes per pair
-    __shared__ dv2 Vl[kBackVs], Gm[BT * BT], taus[BT];
+    __shared__ dv2 Gm[BT * BT], taus[BT];
     const int ln = threadIdx.x;
     const int k2 = d - 2 - bi * BT, k1 = k2 - BT + 1;
     for (int c = 0; c < BT; ++c)
@@ -1397,19 +1459,34 @@ __device__ __forceinline__ void back_t(int d, int bi, const dv2* __restrict__ a,
     }
 }
 
-__global__ __launch_bounds__(kBackTThreads) void k_back_t(const DBlock* __restrict__ blks,
-                                               const dv2* __restrict__ A, dv2* __restrict__ Tb) {
-    const DBlock B = blks[blockIdx.x];
-    const int d = B.d, bi = blockIdx.y;
+// items: sectors and their first eigenvalues, larger sectors first (neval of them), then the blocks of
+// every sector.
+__global__ __launch_bounds__(kEvalThreads) void k_eval_t(const DBlock* __restrict__ blks, int nblk,
+                                                         const DBackItem* __restrict__ items, int neval,
+                                                         const double* __restrict__ rec,
+                                                         double* __restrict__ ev,
+                                                         const double* __restrict__ tnorm,
+                                                         const dv2* __restrict__ A,
+                                                         dv2* __restrict__ Tb) {
+    __shared__ dv2 buf[kBackVs];                        // a block's reflectors
+    if ((int)blockIdx.x < neval) {
+        const DBackItem it = items[blockIdx.x];
+        const DBlock B = blks[it.blk];
+        eigenvalues(B, it.jb, rec + sturm_off(B.eoff, it.blk), ev, tnorm + 3 * it.blk);
+        return;
+    }
+    const int t = (int)blockIdx.x - neval;
+    const DBlock B = blks[t % nblk];
+    const int d = B.d, bi = t / nblk;
     if (bi >= back_nblocks(d)) return;
     const dv2* __restrict__ a = A + B.aoff;
     dv2* __restrict__ tg = Tb + B.toff;
     if (back_bt(d) == 8)
-        back_t<8>(d, bi, a, tg);
+        back_t<8>(d, bi, a, tg, buf);
     else if (back_bt(d) == 4)
-        back_t<4>(d, bi, a, tg);
+        back_t<4>(d, bi, a, tg, buf);
     else
-        back_t<2>(d, bi, a, tg);
+        back_t<2>(d, bi, a, tg, buf);
 }
 
 template <int BT>
@@ -1603,24 +1680,30 @@ __global__ __launch_bounds__(256) void k_finish(const DBlock* __restrict__ blks,
     }
 }
 
-hipError_t launch_density(const DBlock* blks, int nblk, const int* sel, int nreg,
+hipError_t launch_density(const DBlock* blks, int nblk, const int* sel, int nreg, int dmax,
                           const DTile* tiles, int ntiles, const DensIn& in, int nv, int64_t n,
                           void* A, void* V, double* Z, double* S, void* Tb, int nbt, int* fail,
-                          const DBackItem* back, int nback, double* ev,
+                          const DBackItem* back, int nback, const DBackItem* evals_of, int neval,
+                          const DBackItem* vecs_of, int nvecs, double* ev, double* tri,
                           int ntot, int keep, int* kept, double* evals, double* evecs, int* nkept,
                           double* sums, hipStream_t s) {
-    hipLaunchKernelGGL(k_density, dim3(ntiles), dim3(64), 0, s, blks, tiles, in, nv, n,
+    hipLaunchKernelGGL(k_density, dim3(ntiles), dim3(64 * kDensWaves), 0, s, blks, tiles, in, nv, n,
                        static_cast<dv2*>(A), fail, nblk, kept, ntot);
+    double* const rec = tri + 2 * (int64_t)ntot;         // with room for every sector's padding
+    double* const tnorm = rec + 2 * ((int64_t)ntot + kSturmRun * nblk);
     // sel: first the nreg sectors of the register-resident kernel, then the others
     if (nreg > 0)
         hipLaunchKernelGGL(k_heig_r, dim3(nreg), dim3(kEigThreadsR), 0, s, blks, sel,
-                           static_cast<dv2*>(A), Z, S, ev, fail);
+                           static_cast<dv2*>(A), tri, ntot, rec, tnorm);
     if (nblk > nreg)
         hipLaunchKernelGGL(k_heig, dim3(nblk - nreg), dim3(kEigThreads), 0, s, blks, sel + nreg,
-                           static_cast<dv2*>(A), Z, S, ev, fail);
-    if (nbt > 0)
-        hipLaunchKernelGGL(k_back_t, dim3(nblk, nbt), dim3(kBackTThreads), 0, s, blks,
-                           static_cast<const dv2*>(A), static_cast<dv2*>(Tb));
+                           static_cast<dv2*>(A), tri, ntot, rec, tnorm);
+    hipLaunchKernelGGL(k_eval_t, dim3(neval + nblk * nbt), dim3(kEvalThreads), 0, s, blks, nblk,
+                       evals_of, neval, rec, ev, tnorm, static_cast<const dv2*>(A),
+                       static_cast<dv2*>(Tb));
+    hipLaunchKernelGGL(k_vectors, dim3(nvecs), dim3(64), kVecLds, s, blks, vecs_of, tri, ntot, ev,
+                       tnorm, dmax, (int)(kVecLds / sizeof(double)) - (3 * dmax + 1) / 2 * 2, Z, S);
+    hipLaunchKernelGGL(k_ql, dim3(nblk), dim3(kEigThreads), 0, s, blks, tri, ntot, ev, tnorm, Z, fail);
     hipLaunchKernelGGL(k_heig_back, dim3(nback), dim3(kBackThreads), 0, s, blks, back,
                        static_cast<const dv2*>(A), static_cast<const dv2*>(Tb), Z,
                        static_cast<dv2*>(V), fail);

@@ -308,6 +308,21 @@ struct DensIn {            // target vectors (device, 2n doubles each) and their
     const double* v[kDensMaxVec];
     double w[kDensMaxVec];
 };
+// Inverse iteration: LDS of a work group (3 values per row of the largest sector, then six per row
+// and column), and the columns whose clusters it takes: as many as fit beside a sector's own rows,
+// so that two work groups share a CU.
+constexpr int kVecLds = 64 << 10, kVecCols = 16;
+__host__ __device__ constexpr int vec_cols(int d) {
+    const int fit = (kVecLds / 8 - 3 * d - 1) / (6 * (d > 0 ? d : 1));
+    return fit < 1 ? 1 : (fit > kVecCols ? kVecCols : fit);
+}
+// The tridiagonal matrices of nb sectors with n states in all: diagonals and subdiagonals, the scaled
+// ones in runs of kSturmRun rows, and three values per sector.
+constexpr int kSturmRun = 8;        // Sturm steps whose entries are loaded together
+constexpr size_t dens_tri(int64_t n, int nb) {
+    return 4 * (size_t)n + 2 * (size_t)kSturmRun * nb + 3 * (size_t)nb;
+}
+constexpr int kEvalCols = 8;        // eigenvalues of a work group
 constexpr int kDensRegMaxDim = 160;   // sectors up to this size take the register-resident kernel
 
 // One 32 x 32 tile of a complex product C = alpha A B (+ C if acc) (FP64; complex operands

@@ -172,3 +172,44 @@ def test_local_terms_mixed_and_many(env):
         e, want = h.expect_local(g, xd), Ob.expect(pbx, o, x)
         assert abs(e - want) <= 1e-12 * max(1.0, abs(want))
     h.destroy()
+
+
+@pytest.mark.parametrize("dims", [(1, 15, 17, 33), (64, 84, 90, 161), (9, 160, 230, 341)],
+                         ids=["33", "161", "341"])
+@pytest.mark.parametrize("size", [1, 2, 5, 8, 9])
+def test_density_clusters(env, dims, size):
+    """Spectra in clusters of `size` eigenvalues 1e-8 apart (from 9 on QL takes the sector), with the
+    columns of a cluster on either side of a work group's range, in sectors whose columns fit in
+    LDS and in larger ones: eigenvalues, residuals and orthonormality, with the bounds of the
+    parity test (1e-12 of the largest eigenvalue; 1e-11 d)."""
+    torch, L = env
+    pb = _problem((dims, dims[::-1]))       # square blocks
+    rng = np.random.default_rng(I.SEED_BASE + 16)
+    blk = I.psi_blocks(pb)
+    re, im, rhos = [], [], []
+    for (_, _, r, c) in blk:
+        assert r == c
+        q = [np.linalg.qr(rng.standard_normal((r, r)) + 1j * rng.standard_normal((r, r)))[0] for _ in range(2)]
+        lam = (1.0 + np.arange(r) // size + 1e-8 * (np.arange(r) % size)) / r
+        m = (q[0] * np.sqrt(lam)) @ q[1]
+        re.append(m.real.ravel(order="F"))
+        im.append(m.imag.ravel(order="F"))
+        rhos.append((m @ m.conj().T, lam[::-1]))
+    x = np.concatenate(re + im)
+    h = L.dmrg_create(pb)
+    total = sum(r for (_, _, r, _) in blk)
+    ev = torch.zeros(total, dtype=torch.float64, device="cuda")
+    vc = torch.zeros(sum(2 * r * r for (_, _, r, _) in blk), dtype=torch.float64, device="cuda")
+    h.density_truncate([torch.from_numpy(x).to("cuda")], np.array([1.0]), total, ev, vc)
+    ev, vc = ev.cpu().numpy(), vc.cpu().numpy()
+    eo = vo = 0
+    for (rho, lam) in rhos:
+        d = len(lam)
+        w = ev[eo:eo + d]
+        U = (vc[vo:vo + d * d] + 1j * vc[vo + d * d:vo + 2 * d * d]).reshape(d, d).T
+        assert np.max(np.abs(w - lam)) <= 1e-12 * lam[0]
+        assert np.linalg.norm(U.conj().T @ U - np.eye(d)) <= 1e-11 * d
+        assert np.linalg.norm(rho @ U - U * w) <= 1e-11 * lam[0] * d
+        eo += d
+        vo += 2 * d * d
+    h.destroy()
