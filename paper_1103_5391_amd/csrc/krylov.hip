@@ -37,6 +37,7 @@
 #include <utility>
 
 #include "internal.hpp"
+#include "tridiag.hpp"
 
 namespace dmrg {
 
@@ -707,98 +708,96 @@ __global__ __launch_bounds__(kVecThreads) void k_dupdate(const VecProb* vp, cons
 
 // ---------------------------------------------------------------------------------------
 // Small exponential: c(t_x) = beta0 exp(-i T t_x) e_1 for the k x k Lanczos matrix T
-// (diagonal alpha, off-diagonal beta_1..beta_{k-1}), one wavefront per problem, lane r holding
-// component r.  This is the quantity Sec. II.A obtains from T = S D S^T; on the device it is
+// (diagonal alpha, off-diagonal beta_1..beta_{k-1}), one wavefront per time and problem, lane r
+// holding component r.  This is the quantity Sec. II.A obtains from T = S D S^T; on the device it is
 // evaluated without the eigen-decomposition (a serial QL chase keeps one wavefront busy for
 // ~1e5 cycles): T is shifted by the centre sigma of its Gershgorin interval (radius rho bounds
-// ||T - sigma||_2), the vector is advanced from one target time to the next in s substeps of
-// length h with rho |h| <= 2, each by the Taylor series of exp(-i h (T - sigma)) to order 30
-// (remainder below 2^31 / 31! e^2 ~ 2e-24 relative; the largest term is at most 2, so no
-// cancellation), and the phase exp(-i sigma t_x) is applied to the output.  Every term costs one
-// tridiagonal product: two neighbour exchanges and three multiply-adds per lane.
+// ||T - sigma||_2), the vector is advanced to the target time in s substeps of length h with
+// rho |h| <= 2, each by the Taylor series of exp(-i h (T - sigma)) to order 30, or fewer where rho |h| is
+// smaller (first left-out term below 2^31 / 31! ~ 3e-25 relative; the largest term is at most 2,
+// so no cancellation), and the phase exp(-i sigma t_x) is applied to the output.  Every term costs
+// one tridiagonal product: two neighbour exchanges and three multiply-adds per lane.
+// Bound by that dependent chain.  The four times of a step one after another, each from the last, with
+// the neighbours through LDS and a division per term, took 23.8 us for the 400-state chain; 12.9.
 // Also the error estimate beta_k |c_{k-1}(t_last)|.
 // ---------------------------------------------------------------------------------------
 namespace {
 
 constexpr int kTaylorOrder = 30;
 constexpr double kTaylorRadius = 2.0;
-
-__device__ __forceinline__ double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
+constexpr double kTaylorTail = 2.6e-25;     // 2^31 / 31!
 
 }  // namespace
 
-__global__ __launch_bounds__(64) void k_tridiag_expm(const VecProb* vp, double t0, double t1,
-                                                     double t2, double t3, int ntimes,
-                                                     int* klog, int step) {
+__global__ __launch_bounds__(64 * kMaxTimes) void k_tridiag_expm(const VecProb* vp, double t0,
+                                                                 double t1, double t2, double t3,
+                                                                 int ntimes, int* klog, int step) {
     KState* st = vp[blockIdx.x].st;
-    const int r = threadIdx.x;
+    const int r = threadIdx.x & 63;
+    const int x = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // this wavefront's time
     const int k = st->keff;
-    if (klog && r == 0) klog[step] = k > 0 ? k : 0;     // Lanczos vectors of this step
+    if (klog && threadIdx.x == 0) klog[step] = k > 0 ? k : 0;   // Lanczos vectors of this step
     if (k <= 0) {
-        for (int x = 0; x < ntimes; ++x) {
-            st->coef[x][2 * r] = 0.0;
-            st->coef[x][2 * r + 1] = 0.0;
-        }
-        if (r == 0) {
+        st->coef[x][2 * r] = 0.0;
+        st->coef[x][2 * r + 1] = 0.0;
+        if (threadIdx.x == 0) {
             st->err_est = 0.0;
             st->keff_min = 0;
             st->any_break = 1;
         }
         return;
     }
+    __shared__ int s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
     const bool in = r < k;
     const double a = in ? st->alpha[r] : 0.0;
     const double bl = (in && r >= 1) ? st->beta[r] : 0.0;     // couples r-1 and r
     const double bu = (r + 1 < k) ? st->beta[r + 1] : 0.0;    // couples r and r+1
+    const double beta0 = st->beta[0], bk = st->beta[k];
     const double reach = fabs(bl) + fabs(bu);
-    const double hi = wave_max(in ? a + reach : -INFINITY);
-    const double lo = -wave_max(in ? reach - a : -INFINITY);
+    const double hi = wave_fmax(in ? a + reach : -INFINITY);
+    const double lo = -wave_fmax(in ? reach - a : -INFINITY);
     const double sigma = 0.5 * (hi + lo), rho = 0.5 * (hi - lo);
     const double d = in ? a - sigma : 0.0;
-    const double times[kMaxTimes] = {t0, t1, t2, t3};
-    double vr = (r == 0) ? st->beta[0] : 0.0, vi = 0.0;
-    double tprev = 0.0, lastr = 0.0, lasti = 0.0;
-    int bad = 0;
-    for (int x = 0; x < ntimes; ++x) {
-        const double dt = times[x] - tprev;
-        const double need = rho * fabs(dt) / kTaylorRadius;
-        const int64_t nsub = dt == 0.0 ? 0 : (need <= 1.0 ? 1 : (int64_t)ceil(need));
-        const double h = nsub ? dt / (double)nsub : 0.0;
-        for (int64_t sub = 0; sub < nsub; ++sub) {
-            // sum_m (-i h (T - sigma))^m v / m!
-            double sr = vr, si = vi, tr = vr, ti = vi;
-            for (int m = 1; m <= kTaylorOrder; ++m) {
-                const double trm = __shfl_up(tr, 1, 64), tim = __shfl_up(ti, 1, 64);
-                const double trp = __shfl_down(tr, 1, 64), tip = __shfl_down(ti, 1, 64);
-                const double ur = d * tr + bl * trm + bu * trp;
-                const double ui = d * ti + bl * tim + bu * tip;
-                const double f = h / (double)m;
-                tr = f * ui;        // -i f (ur + i ui)
-                ti = -f * ur;
-                sr += tr;
-                si += ti;
-            }
-            vr = sr;
-            vi = si;
+    const double t = x == 0 ? t0 : x == 1 ? t1 : x == 2 ? t2 : t3;
+    const double need = rho * fabs(t) / kTaylorRadius;
+    const int64_t nsub = t == 0.0 ? 0 : (need <= 1.0 ? 1 : (int64_t)ceil(need));
+    const double h = nsub ? t / (double)nsub : 0.0;
+    const double hm = h / (double)max(r, 1);        // h / m in lane m
+    // the order whose first left-out term is at most 2^31 / 31! for this radius too
+    int order = 0;
+    for (double term = 1.0; order < kTaylorOrder && !(term <= kTaylorTail);)
+        term *= rho * fabs(lane_read(hm, ++order));
+    double vr = (r == 0) ? beta0 : 0.0, vi = 0.0;
+    for (int64_t sub = 0; sub < nsub; ++sub) {
+        // sum_m (-i h (T - sigma))^m v / m!
+        double sr = vr, si = vi, tr = vr, ti = vi;
+#pragma unroll 2
+        for (int m = 1; m <= order; ++m) {
+            const double ur = d * tr + bl * dpp<0x138>(tr) + bu * dpp<0x130>(tr);
+            const double ui = d * ti + bl * dpp<0x138>(ti) + bu * dpp<0x130>(ti);
+            const double f = lane_read(hm, m);
+            tr = f * ui;        // -i f (ur + i ui)
+            ti = -f * ur;
+            sr += tr;
+            si += ti;
         }
-        tprev = times[x];
-        double sn, cs;
-        sincos(sigma * times[x], &sn, &cs);     // exp(-i sigma t) = cs - i sn
-        const double cr = vr * cs + vi * sn, ci = vi * cs - vr * sn;
-        if (!isfinite(cr) || !isfinite(ci)) bad = 1;
-        st->coef[x][2 * r] = in ? cr : 0.0;
-        st->coef[x][2 * r + 1] = in ? ci : 0.0;
-        lastr = cr;
-        lasti = ci;
+        vr = sr;
+        vi = si;
     }
-    const int fail = __any(bad);
-    const double cr = lane_read(lastr, k - 1), ci = lane_read(lasti, k - 1);
+    double sn, cs;
+    sincos(sigma * t, &sn, &cs);                    // exp(-i sigma t) = cs - i sn
+    const double cr = vr * cs + vi * sn, ci = vi * cs - vr * sn;
+    st->coef[x][2 * r] = in ? cr : 0.0;
+    st->coef[x][2 * r + 1] = in ? ci : 0.0;
+    if (__any(!isfinite(cr) || !isfinite(ci)) && r == 0) atomicOr(&s_bad, 1);
+    __syncthreads();
+    if (x != ntimes - 1) return;
+    const double er = lane_read(cr, k - 1), ei = lane_read(ci, k - 1);
     if (r == 0) {
-        st->err_est = st->broken ? 0.0 : st->beta[k] * sqrt(cr * cr + ci * ci);
-        st->exp_fail = fail;
+        st->err_est = st->broken ? 0.0 : bk * sqrt(er * er + ei * ei);
+        st->exp_fail = s_bad;
         st->keff_min = min(st->keff_min, k);
         st->any_break = st->any_break | st->broken;
     }
@@ -808,12 +807,15 @@ __global__ __launch_bounds__(64) void k_tridiag_expm(const VecProb* vp, double t
 // Ground-state targeting (the same Lanczos basis, with the lowest eigenpair of T in place of
 // the exponential): one wavefront per problem.  The lowest eigenvalue lambda of the k x k
 // tridiagonal T is found by multisection of its Gershgorin interval: each round, lane l counts
-// the eigenvalues below the l-th of 64 interior points (Sturm sequence of the LDL^T pivots) and
+// the eigenvalues below the l-th of 64 interior points (signs of the leading minors) and
 // the interval shrinks to the first gap that holds lambda, 65 times narrower.  Its eigenvector z
 // then comes from three steps of inverse iteration on T - lambda, solved by Gaussian
-// elimination with partial pivoting (lane 0, O(k) per solve, tiny pivots replaced by a floor).
+// elimination with partial pivoting (every lane the same, rows loaded in runs; tiny pivots replaced by
+// a floor).
 // Output: coef[0] = z (real, unit norm; the combination gives the unit Ritz vector V z),
 // eig = lambda, err_est = beta_k |z_{k-1}| (the residual norm ||H V z - lambda V z||).
+// Bound by dependent arithmetic: 25 us for 40 vectors.  With a division per pivot of the counts, and the
+// solves on one lane that waited for LDS at every step, it was 78 us.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void k_tridiag_lowest(const VecProb* vp, int* klog, int step) {
     KState* st = vp[blockIdx.x].st;
@@ -831,29 +833,31 @@ __global__ __launch_bounds__(64) void k_tridiag_lowest(const VecProb* vp, int* k
         }
         return;
     }
-    __shared__ double al[kMaxKrylov], bt[kMaxKrylov];   // alpha_i; beta_i couples i - 1 and i
+    __shared__ double al[kMaxKrylov], bt[kMaxKrylov];   // alpha_i; beta_{i+1}, between i and i + 1
+    __shared__ double rec[2 * kMaxKrylov];              // T scaled, in runs (sturm_count)
+    __shared__ __align__(16) double inv[6 * kMaxKrylov];
+    static_assert(kMaxKrylov == 64 && kMaxKrylov % kSturmRun == 0, "a lane per row, whole runs");
     const bool in = r < k;
     const double a = in ? st->alpha[r] : 0.0;
     const double bl = (in && r >= 1) ? st->beta[r] : 0.0;
     const double bu = (r + 1 < k) ? st->beta[r + 1] : 0.0;
     al[r] = a;
-    bt[r] = bl;
+    bt[r] = bu;
     const double reach = fabs(bl) + fabs(bu);
-    double hi = wave_max(in ? a + reach : -INFINITY);
-    double lo = -wave_max(in ? reach - a : -INFINITY);
+    double hi = wave_fmax(in ? a + reach : -INFINITY);
+    double lo = -wave_fmax(in ? reach - a : -INFINITY);
     const double tnorm = fmax(fabs(hi), fabs(lo));
     const double pivmin = 1e-290 * fmax(1.0, tnorm * tnorm);
+    // the counts run on the matrix scaled by a power of two to |T| in [0.5, 1)
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(tnorm, 1e-300));
+    const double bs = __builtin_amdgcn_ldexp(bl, -ex);
+    rec[2 * kSturmRun * (r / kSturmRun) + r % kSturmRun] = in ? __builtin_amdgcn_ldexp(a, -ex) : 4.0;
+    rec[2 * kSturmRun * (r / kSturmRun) + kSturmRun + r % kSturmRun] = bs * bs;
     __syncthreads();
     // multisection: count(x) = number of eigenvalues below x
     for (int it = 0; it < 16; ++it) {
         const double x = lo + (hi - lo) * (double)(r + 1) / 65.0;
-        int cnt = 0;
-        double d = 1.0;
-        for (int i = 0; i < k; ++i) {
-            d = (al[i] - x) - (i ? bt[i] * bt[i] / d : 0.0);
-            if (fabs(d) < pivmin) d = -pivmin;
-            cnt += d < 0.0;
-        }
+        const int cnt = sturm_count((k + kSturmRun - 1) / kSturmRun, rec, __builtin_amdgcn_ldexp(x, -ex));
         const unsigned long long m = __ballot(cnt >= 1);
         const int f = m ? __ffsll(m) - 1 : 64;     // first point above lambda (64: the top end)
         const double nlo = f == 0 ? lo : lo + (hi - lo) * (double)f / 65.0;
@@ -863,77 +867,27 @@ __global__ __launch_bounds__(64) void k_tridiag_lowest(const VecProb* vp, int* k
         if (hi - lo <= 4.0 * 2.220446049250313e-16 * fmax(fabs(lo), fabs(hi)) + pivmin) break;
     }
     const double lam = 0.5 * (lo + hi);
-    // factors of T - lam and the iterate, in LDS (lane 0 works on them serially)
-    __shared__ double d[kMaxKrylov], du[kMaxKrylov], du2[kMaxKrylov], dl[kMaxKrylov], z[kMaxKrylov];
-    __shared__ bool piv[kMaxKrylov];
+    // inverse iteration from a vector of ones; every lane runs the same solves
+    const InvLds m{inv, 1, 6};
+    tri_factor<true>(m, k, 0, al, bt, lam, fmax(pivmin, 2.220446049250313e-16 * tnorm),
+                     [] { return 1.0; });
+    double z = 0.0, nrm = tri_backward(m, k, 0);
+    for (int it = 1; it < 3; ++it) nrm = tri_solve(m, k, 0, 1.0 / sqrt(nrm));
+    // unit norm, the first of the largest entries positive
+    z = in ? m.z(m.at(r, 0)) : 0.0;
+    const double big = wave_fmax(fabs(z));
+    const unsigned long long at = __ballot(in && fabs(z) == big);
+    const double sign = at && lane_read(z, __ffsll(at) - 1) < 0.0 ? -1.0 : 1.0;
+    z *= sign / sqrt(nrm);
+    const double zk = lane_read(z, k - 1);
     if (r == 0) {
-        // inverse iteration: (T - lam) z = b, elimination with partial pivoting (rows i, i + 1)
-        const double floor = fmax(pivmin, 2.220446049250313e-16 * tnorm);
-        for (int i = 0; i < k; ++i) {
-            d[i] = al[i] - lam;
-            du[i] = i + 1 < k ? bt[i + 1] : 0.0;
-            dl[i] = i + 1 < k ? bt[i + 1] : 0.0;
-            du2[i] = 0.0;
-            z[i] = 1.0;
-        }
-        for (int i = 0; i + 1 < k; ++i) {
-            if (fabs(d[i]) >= fabs(dl[i])) {
-                piv[i] = false;
-                if (fabs(d[i]) < floor) d[i] = floor;
-                const double f = dl[i] / d[i];
-                dl[i] = f;
-                d[i + 1] -= f * du[i];
-            } else {
-                piv[i] = true;
-                const double f = d[i] / dl[i];
-                d[i] = dl[i];
-                dl[i] = f;
-                const double t = du[i];
-                du[i] = d[i + 1];
-                d[i + 1] = t - f * d[i + 1];
-                if (i + 2 < k) {
-                    du2[i] = du[i + 1];
-                    du[i + 1] = -f * du[i + 1];
-                }
-            }
-        }
-        if (fabs(d[k - 1]) < floor) d[k - 1] = floor;
-        for (int it = 0; it < 3; ++it) {
-            for (int i = 0; i + 1 < k; ++i) {       // apply the row operations to z
-                if (piv[i]) {
-                    const double t = z[i];
-                    z[i] = z[i + 1];
-                    z[i + 1] = t - dl[i] * z[i + 1];
-                } else {
-                    z[i + 1] -= dl[i] * z[i];
-                }
-            }
-            for (int i = k - 1; i >= 0; --i) {     // back substitution with U (three diagonals)
-                double t = z[i];
-                if (i + 1 < k) t -= du[i] * z[i + 1];
-                if (i + 2 < k) t -= du2[i] * z[i + 2];
-                z[i] = t / d[i];
-            }
-            double nrm = 0.0, big = 0.0;
-            int ib = 0;
-            for (int i = 0; i < k; ++i) {
-                nrm += z[i] * z[i];
-                if (fabs(z[i]) > big) {
-                    big = fabs(z[i]);
-                    ib = i;
-                }
-            }
-            const double s = (z[ib] < 0.0 ? -1.0 : 1.0) / sqrt(nrm);   // largest entry positive
-            for (int i = 0; i < k; ++i) z[i] *= s;
-        }
         st->eig = lam;
-        st->err_est = st->broken ? 0.0 : fabs(st->beta[k] * z[k - 1]);
-        st->exp_fail = !isfinite(lam) || !isfinite(z[k - 1]);
+        st->err_est = st->broken ? 0.0 : fabs(st->beta[k] * zk);
+        st->exp_fail = !isfinite(lam) || !isfinite(zk);
         st->keff_min = min(st->keff_min, k);
         st->any_break = st->any_break | st->broken;
     }
-    __syncthreads();
-    st->coef[0][2 * r] = in ? z[r] : 0.0;
+    st->coef[0][2 * r] = in ? z : 0.0;
     st->coef[0][2 * r + 1] = 0.0;
 }
 
@@ -943,19 +897,42 @@ __global__ __launch_bounds__(64) void k_tridiag_lowest(const VecProb* vp, int* k
 // batch come from the table yst[problem * kMaxTimes + x].  Without chaining a pass may give
 // each problem mult blocks per block of the other passes (no partial sums to collect).
 // ---------------------------------------------------------------------------------------
+// X: the times of the launch (1, or up to kMaxTimes).  G slots' loads are in flight at once, the first
+// ones before the coefficients are there: with four at a time, after the coefficients, 30 slots of 4900
+// states took 11.5 us, now 6.2; 40 slots of 48600 states 27.4, now 11.2; many states are bound by
+// memory traffic either way (the 1000-state ladder 19.8, now 19.1; four chains of it 57.6 and 57.4, with
+// 16 slots at a time, whose registers leave fewer wavefronts, 67).
+template <int X>
 __global__ __launch_bounds__(kVecThreads) void k_combine(const VecProb* vp, const int* bmap,
                                                          int mult, double* y0, double* y1,
                                                          double* y2, double* y3,
                                                          double* const* yst, int ntimes,
                                                          int chain) {
+    constexpr int G = X == 1 ? 8 : 4;
     const Where W = locate(vp, bmap, mult);
     const KState* st = W.p.st;
-    __shared__ double cs[kMaxTimes][2 * kMaxKrylov];
-    const int k = st->keff;
-    for (int idx = threadIdx.x; idx < ntimes * k; idx += blockDim.x) {
-        const int x = idx / k, c = idx % k;
-        cs[x][2 * c] = st->coef[x][2 * c] * st->scale[c];
-        cs[x][2 * c + 1] = st->coef[x][2 * c + 1] * st->scale[c];
+    __shared__ double cs[X][2 * kMaxKrylov];
+    static_assert(kMaxKrylov % G == 0, "whole groups of slots");
+    const int k = st->keff, kg = (k + G - 1) / G * G;
+    const double* V = W.p.V;
+    const int64_t n = W.p.n, vstride = W.p.vstride;
+    const int64_t first = (int64_t)W.lb * blockDim.x + threadIdx.x;
+    double vr[G], vi[G];
+    auto load = [&](int64_t i, int c0) {                // slots from k on re-read slot k - 1
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const double* u = V + (int64_t)min(c0 + g, k - 1) * vstride;
+            vr[g] = ldv(u, i);
+            vi[g] = ldv(u, n + i);
+        }
+    };
+    if (k > 0 && first < n) load(first, 0);
+    for (int idx = threadIdx.x; idx < X * kg; idx += blockDim.x) {
+        const int x = idx / kg, c = idx % kg;
+        const bool ok = x < ntimes && c < k;            // the rest of a group: zero
+        const double s = ok ? st->scale[c] : 0.0;
+        cs[x][2 * c] = ok ? st->coef[x][2 * c] * s : 0.0;
+        cs[x][2 * c + 1] = ok ? st->coef[x][2 * c + 1] * s : 0.0;
     }
     __syncthreads();
     double* ys[kMaxTimes];
@@ -971,27 +948,31 @@ __global__ __launch_bounds__(kVecThreads) void k_combine(const VecProb* vp, cons
         ys[2] = y2;
         ys[3] = y3;
     }
-    const double* V = W.p.V;
-    const int64_t n = W.p.n, vstride = W.p.vstride;
     double acc[1] = {0.0};
     const int64_t stride = (int64_t)W.nbt * blockDim.x;
-    for (int64_t i = (int64_t)W.lb * blockDim.x + threadIdx.x; i < n; i += stride) {
-        double yr[kMaxTimes] = {0.0, 0.0, 0.0, 0.0}, yi[kMaxTimes] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-        for (int c = 0; c < k; ++c) {
-            const double* u = V + (int64_t)c * vstride;
-            const double ur = ldv(u, i), ui = ldv(u, n + i);
+    for (int64_t i = first; i < n; i += stride) {
+        double yr[X], yi[X];
 #pragma unroll
-            for (int x = 0; x < kMaxTimes; ++x) {
-                if (x < ntimes) {
+        for (int x = 0; x < X; ++x) {
+            yr[x] = 0.0;
+            yi[x] = 0.0;
+        }
+        for (int c0 = 0; c0 < k; c0 += G) {
+            if (c0 > 0 || i != first) load(i, c0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int c = c0 + g;
+#pragma unroll
+                for (int x = 0; x < X; ++x) {
                     const double cr = cs[x][2 * c], ci = cs[x][2 * c + 1];
-                    yr[x] += cr * ur - ci * ui;
-                    yi[x] += cr * ui + ci * ur;
+                    yr[x] += cr * vr[g] - ci * vi[g];
+                    yi[x] += cr * vi[g] + ci * vr[g];
                 }
             }
         }
 #pragma unroll
-        for (int x = 0; x < kMaxTimes; ++x) {
+        for (int x = 0; x < X; ++x) {
             if (x < ntimes) {
                 ys[x][i] = yr[x];
                 ys[x][n + i] = yi[x];
@@ -1096,8 +1077,8 @@ hipError_t launch_tridiag(const VecGroup& g, const double* times, int ntimes, in
                           hipStream_t s) {
     double t[kMaxTimes] = {0, 0, 0, 0};
     for (int i = 0; i < ntimes; ++i) t[i] = times[i];
-    hipLaunchKernelGGL(k_tridiag_expm, dim3(g.nprob), dim3(64), 0, s, g.vp, t[0], t[1], t[2], t[3],
-                       ntimes, klog, step);
+    hipLaunchKernelGGL(k_tridiag_expm, dim3(g.nprob), dim3(64 * ntimes), 0, s, g.vp, t[0], t[1], t[2],
+                       t[3], ntimes, klog, step);
     return hipGetLastError();
 }
 
@@ -1128,9 +1109,9 @@ hipError_t launch_combine(const VecGroup& g, double* const* ys, double* const* y
     if (ys)
         for (int i = 0; i < ntimes; ++i) y[i] = ys[i];
     const int mult = chain ? 1 : g.combine_mult;
-    hipLaunchKernelGGL(k_combine, dim3(g.nblk * mult), dim3(kVecThreads), 0, s, g.vp,
-                       g.bmap, mult, y[0], y[1], y[2], y[3], yst, ntimes,
-                       chain);
+    auto* const kern = ntimes == 1 ? &k_combine<1> : &k_combine<kMaxTimes>;
+    hipLaunchKernelGGL(kern, dim3(g.nblk * mult), dim3(kVecThreads), 0, s, g.vp, g.bmap, mult, y[0],
+                       y[1], y[2], y[3], yst, ntimes, chain);
     if (chain) hipLaunchKernelGGL(k_fin_chain, dim3(g.nprob), dim3(kVecThreads), 0, s, g.vp);
     return hipGetLastError();
 }
