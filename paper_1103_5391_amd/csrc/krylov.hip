@@ -34,6 +34,7 @@
 // them in a fixed order (the kernel boundary orders the two; no device-wide fences or atomics:
 // on this chip a device-scope release writes back the XCD's L2 and costs more than a launch).
 #include <array>
+#include <type_traits>
 #include <utility>
 
 #include "internal.hpp"
@@ -221,34 +222,6 @@ __device__ __forceinline__ void halve(double (&v)[P], int lane) {
     }
 }
 
-// Block-level sums of NV <= 64 per-thread values by wavefront reduce-scatter, written as a row
-// of ROW values (zeros past NV), value-major: part[v * kVecMaxBlocks + lb].
-template <int NV, int ROW>
-__device__ __forceinline__ void block_partials_scatter(const double (&vals)[NV > 0 ? NV : 1],
-                                                       double* part, int lb) {
-    static_assert(NV <= 64 && ROW <= 64, "one value per lane");
-    constexpr int P = NV <= 1 ? 1 : NV <= 2 ? 2 : NV <= 4 ? 4 : NV <= 8 ? 8 : NV <= 16 ? 16
-                                                         : NV <= 32 ? 32 : 64;
-    constexpr int SHIFT = P == 1 ? 6 : P == 2 ? 5 : P == 4 ? 4 : P == 8 ? 3 : P == 16 ? 2
-                                                   : P == 32 ? 1 : 0;
-    __shared__ double red[kVecThreads / 64][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double v[P];
-#pragma unroll
-    for (int i = 0; i < P; ++i) v[i] = i < NV ? vals[i] : 0.0;
-    halve<P>(v, lane);
-    if ((lane & ((1 << SHIFT) - 1)) == 0) red[wave][lane >> SHIFT] = v[0];
-    __syncthreads();
-    for (int i = threadIdx.x; i < ROW; i += blockDim.x) {
-        double s = 0.0;
-        if (i < NV) {
-#pragma unroll
-            for (int w = 0; w < kVecThreads / 64; ++w) s += red[w][i];
-        }
-        part[(int64_t)i * kVecMaxBlocks + lb] = s;
-    }
-}
-
 // Finalise kernels run one block of FT threads per problem: totals[v] = sum_b part[v][b] for
 // v < NV in a fixed order (thread t adds rows t, t + FT, ... in turn, then the block reduction
 // of block_partials; nb <= kVecMaxBlocks, value-major layout as written by block_partials).
@@ -350,77 +323,114 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_start(const VecProb* vp, in
 // the first launch also accumulates u1^H w_raw, ||u1||^2 and ||w_raw||^2.  Partial rows of
 // launch q: kDVals values (a_c, b_c per slot, then c, d, e), unused values zero.
 // ---------------------------------------------------------------------------------------
+// The inner products are one small matrix product, rows (Re v_c, Im v_c) of the slots by columns
+// (Re u1, Im u1, Re w, Im w), summed over the elements: v_mfma_f64_4x4x4 takes two slots' rows by the
+// four columns (no row or column unused) over 16 elements, lane (i, b, k) = (l mod 4, l div 4 mod 4,
+// l div 16) row or column i of element (b, k), and D[i][j] of block b in lane j + 4 b + 16 i.  A wave
+// reads 32 elements at a time (two per lane: 256 consecutive bytes of every row).
+// Bound by memory traffic where there is much (16 slots of the 1000-state ladder: 77 MB, 18.6 us before,
+// 16.2 now, 4.8 TB/s; twice or half as many groups in flight measured the same), by latency where there
+// is little: with a lane's own sums (60 values, 300 registers) and their reduction over 64 lanes
+// 15 slots of 48600 states took 7.5 us, now 5.8.
+typedef double d2m __attribute__((ext_vector_type(2), aligned(8)));    // any element
 template <int NC, bool FIRST, bool ONE>
 __global__ __launch_bounds__(kVecThreads) void k_dreduce(const VecProb* vp, const int* bmap, int j,
                                                          int c0, int q, VecProb one) {
-    constexpr int NV = 4 * NC + (FIRST ? 4 : 0);
+    constexpr int NV = 4 * NC + (FIRST ? 4 : 0), NW = kVecThreads / 64;
+    constexpr int T = (NC + 1) / 2, TT = T + (FIRST ? 1 : 0);          // tiles; the last: u1, w alone
+    constexpr int S = NC <= 7 ? 4 : 2;                     // groups of 32 elements in flight
     const Where W = locate_red<ONE>(vp, bmap, one);
     // No breakdown test: the pass writes only its partial rows, which the totals kernel ignores
     // after a breakdown (the slots stay allocated, so every load is in bounds); a test here
     // would put the flag's load before the first data load.
-    const double* __restrict__ V0 = W.p.V + (int64_t)c0 * W.p.vstride;
-    const double* __restrict__ u1 = W.p.V + (int64_t)j * W.p.vstride;
-    const double* __restrict__ w = W.p.w;
     const int64_t n = W.p.n, vstride = W.p.vstride;
-    double acc[NV > 0 ? NV : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 3, e = 2 * (lane >> 2);
+    // row i of tile t: slot c0 + 2 t + i / 2, plane i mod 2 (an odd NC's last rows are those of a
+    // slot <= j, whose products are not used); column i: u1, then w
+    typedef const d2m __attribute__((address_space(1)))* pairs;
+    const gcptr pv = (gcptr)W.p.V + (int64_t)(c0 + (i >> 1)) * vstride + (i & 1) * n;
+    const gcptr pb = (i < 2 ? (gcptr)W.p.V + (int64_t)j * vstride : (gcptr)W.p.w) + (i & 1) * n;
+    double acc[TT > 0 ? TT : 1];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    const int64_t stride = (int64_t)W.nbt * blockDim.x;
-    if ((n & 1) == 0) {
-        for (int64_t i = 2 * ((int64_t)W.lb * blockDim.x + threadIdx.x); i < n; i += 2 * stride) {
-            d2v vr[NC > 0 ? NC : 1], vi[NC > 0 ? NC : 1];
-            const d2v ur = ld2(u1, i), ui = ld2(u1, n + i), wr = ld2(w, i), wi = ld2(w, n + i);
+    for (int t = 0; t < TT; ++t) acc[t] = 0.0;
+    auto products = [&](double (&a)[T > 0 ? T : 1], double b) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const double* v = V0 + (int64_t)c * vstride;
-                vr[c] = ld2(v, i);
-                vi[c] = ld2(v, n + i);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[t], b, acc[t], 0, 0, 0);
+        if (FIRST) acc[TT - 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(b, b, acc[TT - 1], 0, 0, 0);
+    };
+    auto groups = [&](auto count, int64_t g, int64_t nw) {      // whole groups g, g + nw, ..
+        constexpr int N = decltype(count)::value;
+        d2m a[N][T > 0 ? T : 1], b[N];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+        for (int k = 0; k < N; ++k) {
+            const int64_t at = 32 * (g + k * nw) + e;
+            b[k] = *(pairs)(pb + at);
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    acc[4 * c] += vr[c][h] * ur[h] + vi[c][h] * ui[h];
-                    acc[4 * c + 1] += vr[c][h] * ui[h] - vi[c][h] * ur[h];
-                    acc[4 * c + 2] += vr[c][h] * wr[h] + vi[c][h] * wi[h];
-                    acc[4 * c + 3] += vr[c][h] * wi[h] - vi[c][h] * wr[h];
-                }
-                if (FIRST) {
-                    acc[4 * NC] += ur[h] * wr[h] + ui[h] * wi[h];
-                    acc[4 * NC + 1] += ur[h] * wi[h] - ui[h] * wr[h];
-                    acc[4 * NC + 2] += ur[h] * ur[h] + ui[h] * ui[h];
-                    acc[4 * NC + 3] += wr[h] * wr[h] + wi[h] * wi[h];
-                }
-            }
-        }
-    } else
-    for (int64_t i = (int64_t)W.lb * blockDim.x + threadIdx.x; i < n; i += stride) {
-        // every load of the element first, then the arithmetic (one memory round trip)
-        double vr[NC > 0 ? NC : 1], vi[NC > 0 ? NC : 1];
-        const double ur = ldv(u1, i), ui = ldv(u1, n + i), wr = ldv(w, i), wi = ldv(w, n + i);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double* v = V0 + (int64_t)c * vstride;
-            vr[c] = ldv(v, i);
-            vi[c] = ldv(v, n + i);
+            for (int t = 0; t < T; ++t) a[k][t] = *(pairs)(pv + 2 * t * vstride + at);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            acc[4 * c] += vr[c] * ur + vi[c] * ui;
-            acc[4 * c + 1] += vr[c] * ui - vi[c] * ur;
-            acc[4 * c + 2] += vr[c] * wr + vi[c] * wi;
-            acc[4 * c + 3] += vr[c] * wi - vi[c] * wr;
-        }
-        if (FIRST) {
-            acc[4 * NC] += ur * wr + ui * wi;
-            acc[4 * NC + 1] += ur * wi - ui * wr;
-            acc[4 * NC + 2] += ur * ur + ui * ui;
-            acc[4 * NC + 3] += wr * wr + wi * wi;
+        for (int k = 0; k < N; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                double x[T > 0 ? T : 1];
+#pragma unroll
+                for (int t = 0; t < T; ++t) x[t] = a[k][t][h];
+                products(x, b[k][h]);
+            }
+    };
+    const int64_t nfull = n / 32, nw = (int64_t)W.nbt * NW;
+    int64_t g = (int64_t)W.lb * NW + wave;
+    for (; g + (S - 1) * nw < nfull; g += S * nw) groups(std::integral_constant<int, S>{}, g, nw);
+    for (; g < nfull; g += nw) groups(std::integral_constant<int, 1>{}, g, nw);
+    if (g == nfull && n % 32 != 0) {                            // the rest: zeros beyond n
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t at = 32 * nfull + e + h, to = at < n ? at : n - 1;
+            double x[T > 0 ? T : 1];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const double v = pv[2 * t * vstride + to];
+                x[t] = at < n ? v : 0.0;
+            }
+            const double v = pb[to];
+            products(x, at < n ? v : 0.0);
         }
     }
-    block_partials_scatter<NV, kDVals>(acc, W.p.part + (int64_t)q * kVecMaxBlocks * kDVals, W.lb);
+    // the four blocks of a tile, then the wavefronts
+    __shared__ double red[NW][TT > 0 ? TT : 1][16];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+        double v = acc[t];
+        v += dpp<0x128>(v);                                     // row_ror:8
+        v += dpp<0x124>(v);                                     // row_ror:4
+        if ((lane & 12) == 0) red[wave][t][4 * (lane >> 4) + i] = v;
+    }
+    __syncthreads();
+    double* part = W.p.part + (int64_t)q * kVecMaxBlocks * kDVals;
+    for (int v = threadIdx.x; v < kDVals; v += kVecThreads) {
+        double sum = 0.0;
+        if (v < NV) {
+            // entries (row, column) of the tile that make up value v: + first, +- second
+            const int c = v >> 2, m = v & 3;
+            int t = c >> 1, p, r;
+            double sg;
+            if (c < NC) {                                       // conj(v_c) u1, conj(v_c) w
+                const int row = 8 * (c & 1), col = m & 2;
+                p = row + col + (m & 1);
+                r = row + 4 + col + 1 - (m & 1);
+                sg = (m & 1) ? -1.0 : 1.0;
+            } else {                                            // conj(u1) w, |u1|^2, |w|^2
+                t = TT - 1;
+                p = m == 0 ? 2 : m == 1 ? 3 : m == 2 ? 0 : 10;
+                r = m == 0 ? 7 : m == 1 ? 6 : m == 2 ? 5 : 15;
+                sg = m == 1 ? -1.0 : 1.0;
+            }
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += red[w][t][p] + sg * red[w][t][r];
+        }
+        part[(int64_t)v * kVecMaxBlocks + W.lb] = sum;
+    }
 }
 
 // Totals of the reduction launches: every total is summed in the same order whichever kernel forms

@@ -213,3 +213,25 @@ def test_density_clusters(env, dims, size):
         eo += d
         vo += 2 * d * d
     h.destroy()
+
+
+@pytest.mark.parametrize("dims,kdim", [(((1, 1, 1, 1), (1, 1, 1, 1)), 4), (((3, 2, 1, 3), (1, 3, 5, 2)), 15),
+                                       (((3, 2, 1, 3), (2, 3, 5, 5)), 18), (((5, 4, 3, 3), (5, 4, 3, 5)), 33),
+                                       (((9, 8, 7, 11), (7, 9, 8, 9)), 48)])
+@pytest.mark.parametrize("tau", [1e-7, 0.03, 2.0])
+def test_lanczos_small_and_odd(env, dims, kdim, tau):
+    """Spaces of 4 to some 290 states (odd numbers, less than one group of 32 and a few more), bases around
+    the 15 slots of a reduction launch, and times from far below to far above 1 / ||H||."""
+    torch, L = env
+    pb = _problem(dims)
+    h = L.dmrg_create(pb)
+    x = I.random_psi(h.n, np.random.default_rng(I.SEED_BASE + 17))
+    xd = torch.from_numpy(x).to("cuda")
+    y = torch.empty_like(xd)
+    kdim = min(kdim, h.n)
+    tau = tau / max(max(d) for d in dims)
+    info = h.krylov_expm(xd, y, tau, kdim, 2)
+    yref, oinfo = K.krylov_expm(lambda v: M.matvec_sector(pb, v), x, tau, kdim, 2)
+    assert info["k_eff"] == oinfo.k_eff[-1]
+    assert np.linalg.norm(y.cpu().numpy() - yref) <= 1e-10 * np.linalg.norm(yref)
+    h.destroy()
