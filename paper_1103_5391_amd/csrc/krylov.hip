@@ -599,7 +599,11 @@ __global__ __launch_bounds__(kVecThreads) void k_dupdate(const VecProb* vp, cons
     const Where W = locate1<ONE>(vp, bmap, one);
     KState* st = W.p.st;
     const int broken = ((const int __attribute__((address_space(1)))*)&st->broken)[0];
-    constexpr int G = 8;                       // basis slots loaded per round trip
+    // basis slots loaded per round trip; a last group is padded with loads of slot j - 1, and eight at a
+    // time padded more than they hid: 30-vector bases of the 8-site chain 2421 us and four chains of the
+    // 1000-state ladder 4585 us with eight, 2365 and 4537 with four, 2370 and 4532 with two (a
+    // 40-vector basis of 48600 states 4071, 4044 and 4197)
+    constexpr int G = 4;
     const int j8 = (j + G - 1) / G * G;
     __shared__ double cos[kVecThreads / 64][3][2 * kMaxKrylov];
     double (&co)[3][2 * kMaxKrylov] = cos[threadIdx.x >> 6];
