@@ -22,15 +22,14 @@ constexpr int kDSlots = 15;         // basis slots per Lanczos reduction launch 
                                     // plus 4: a row of 64, one per lane)
 constexpr int kDVals = 4 * kDSlots + 4;   // values per partial row of a reduction launch
 constexpr int kDMaxQ = (kMaxKrylov + kDSlots - 1) / kDSlots;   // reduction launches per iteration
-#ifndef DMRG_RED_ELEMS
-#define DMRG_RED_ELEMS 2
-#endif
-constexpr int kRedElems = DMRG_RED_ELEMS;  // complex elements per thread of a reduction pass
+constexpr int kRedThreads = 1024;   // threads of a reduction block
+constexpr int kRedRows = 256;       // most blocks of a reduction
 // Most partial rows (blocks of the largest problem times launches) of one iteration that every block
 // of the update pass sums itself; k_dsum does it where there are more.  Measured per Lanczos basis,
-// own sums against k_dsum: chain8 (n = 4900, 10 to 30 rows) 2.53 against 2.65 ms for its 10 bases,
-// the 400-state chain (n = 48600, 96 rows) 422 against 431 us, two launches of it (192 rows) 933
-// against 922 us for its 30-vector ground-state basis; at 300 rows the two are equal.
+// own sums against k_dsum: chain8 (n = 4900, 10 rows) 2.53 against 2.65 ms for its 10 bases,
+// the 400-state chain (n = 49500, 97 rows) 422 against 431 us, two launches of it (194 rows) 933
+// against 922 us for its 30-vector ground-state basis; the 1000-state ladder (118 rows then) 1272
+// against 1263 us for its 587 update blocks.
 constexpr int kDirectRows = 128;
 constexpr int kMaxTimes = 4;        // time points evaluated from one Krylov basis
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;   // device scratch per GPU of the

@@ -331,14 +331,14 @@ __global__ __launch_bounds__(kVecThreads) void k_fin_start(const VecProb* vp, in
 // Bound by memory traffic where there is much (16 slots of the 1000-state ladder: 77 MB, 18.6 us before,
 // 16.2 now, 4.8 TB/s; twice or half as many groups in flight measured the same), by latency where there
 // is little: with a lane's own sums (60 values, 300 registers) and their reduction over 64 lanes
-// 15 slots of 48600 states took 7.5 us, now 5.8.
+// 15 slots of 48600 states took 7.5 us, with these 5.8.
 typedef double d2m __attribute__((ext_vector_type(2), aligned(8)));    // any element
 template <int NC, bool FIRST, bool ONE>
-__global__ __launch_bounds__(kVecThreads) void k_dreduce(const VecProb* vp, const int* bmap, int j,
+__global__ __launch_bounds__(kRedThreads) void k_dreduce(const VecProb* vp, const int* bmap, int j,
                                                          int c0, int q, VecProb one) {
-    constexpr int NV = 4 * NC + (FIRST ? 4 : 0), NW = kVecThreads / 64;
+    constexpr int NV = 4 * NC + (FIRST ? 4 : 0), NW = kRedThreads / 64;
     constexpr int T = (NC + 1) / 2, TT = T + (FIRST ? 1 : 0);          // tiles; the last: u1, w alone
-    constexpr int S = NC <= 7 ? 4 : 2;                     // groups of 32 elements in flight
+    constexpr int S = 2;                                   // groups of 32 elements in flight
     const Where W = locate_red<ONE>(vp, bmap, one);
     // No breakdown test: the pass writes only its partial rows, which the totals kernel ignores
     // after a breakdown (the slots stay allocated, so every load is in bounds); a test here
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kVecThreads) void k_dreduce(const VecProb* vp, cons
     }
     __syncthreads();
     double* part = W.p.part + (int64_t)q * kVecMaxBlocks * kDVals;
-    for (int v = threadIdx.x; v < kDVals; v += kVecThreads) {
+    for (int v = threadIdx.x; v < kDVals; v += kRedThreads) {
         double sum = 0.0;
         if (v < NV) {
             // entries (row, column) of the tile that make up value v: + first, +- second
@@ -1018,14 +1018,20 @@ int vec_blocks(int64_t n) {
     return (int)nb;
 }
 
-// Blocks of the Lanczos reduction pass: kRedElems elements per thread, at most kVecMaxBlocks.
+// Blocks (partial rows) of the Lanczos reduction pass: a group of 32 elements per wavefront, or as many
+// groups each as keep the rows at most kRedRows, one block of 16 wavefronts per CU.  Blocks of four
+// wavefronts with 512 elements each (587 rows for 300000 states) took 1289 us for the targets of the
+// 1000-state ladder and 8329 for a 2000-state basis, these 1236 and 8251; with up to 128 rows 1272 and
+// 8605, with 512 1284 and 8276.  Four chains or 16 problems in common launches measure the same (4537
+// and 4545 us, 5862 and 5878), small ones less rounds per wavefront (10 bases of the 8-site chain
+// 2365 and 2331 us, a 400-state chain's ground state 4044 and 3950).
 int red_blocks(int64_t n) {
-    const int64_t per = (int64_t)kVecThreads * kRedElems;
-    int64_t nb = (n + per - 1) / per;
-    if (nb < 1) nb = 1;
-    if (nb > kVecMaxBlocks) nb = kVecMaxBlocks;
-    return (int)nb;
+    constexpr int64_t waves = kRedThreads / 64;
+    const int64_t groups = n > 32 ? (n + 31) / 32 : 1;
+    const int64_t rounds = (groups + waves * kRedRows - 1) / (waves * kRedRows);
+    return (int)((groups + waves * rounds - 1) / (waves * rounds));
 }
+static_assert(kRedRows <= kVecMaxBlocks, "rows of partial sums");
 
 hipError_t launch_start(const VecGroup& g, const double* x1, const double* const* xt, int kdim,
                         int first, hipStream_t s) {
@@ -1055,16 +1061,16 @@ const std::array<RedFn, kDSlots + 1> kRedMore[2] = {
 
 // Runs Lanczos iteration j (after the block products of slot j) on every problem of the group.
 hipError_t launch_lanczos_iter(const VecGroup& g, int j, int kdim, hipStream_t s) {
-    const dim3 grid(g.nblk), gridr(g.nblkr), blk(kVecThreads);
+    const dim3 grid(g.nblk), gridr(g.nblkr), blk(kVecThreads), blkr(kRedThreads);
     const int nq = j > kDSlots ? (j + kDSlots - 1) / kDSlots : 1;
     const int nc0 = min(j, kDSlots);
     // one problem (no block map): its descriptor travels by value
     const int one = g.nprob == 1 && g.bmap == nullptr && g.bmapr == nullptr;
     const VecProb* vp = g.vp;
-    hipLaunchKernelGGL(kRedFirst[one][nc0], gridr, blk, 0, s, vp, g.bmapr, j, 0, 0, g.one);
+    hipLaunchKernelGGL(kRedFirst[one][nc0], gridr, blkr, 0, s, vp, g.bmapr, j, 0, 0, g.one);
     for (int q = 1; q < nq; ++q) {
         const int nc = min(kDSlots, j - q * kDSlots);
-        hipLaunchKernelGGL(kRedMore[one][nc], gridr, blk, 0, s, vp, g.bmapr, j, q * kDSlots, q,
+        hipLaunchKernelGGL(kRedMore[one][nc], gridr, blkr, 0, s, vp, g.bmapr, j, q * kDSlots, q,
                            g.one);
     }
     // few partial rows: every block of the update pass sums them itself

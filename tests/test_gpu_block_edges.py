@@ -83,10 +83,12 @@ def test_products_at_tile_edges(env, dims, prec):
     h.destroy()
 
 
-@pytest.mark.parametrize("d,extra,rows", [(5, 0, 1), (64, 0, 32), (64, 1, 33), (128, 0, 128), (128, 1, 129)])
+@pytest.mark.parametrize("d,extra,rows", [(5, 0, 1), (64, 0, 32), (64, 1, 33), (128, 0, 128), (128, 1, 129),
+                                          (181, 0, 256), (181, 2, 257)])
 def test_lanczos_totals_at_row_limits(env, d, extra, rows):
     """64 Lanczos vectors (1 to 5 reduction launches) on either side of 128 partial rows, up to
-    which the update pass sums them itself; one row of sums per 512 states."""
+    which the update pass sums them itself, and 256, the most there are; `rows` counts 512 states
+    each (16 wavefronts of 32)."""
     torch, L = env
     pb = _problem(((d,) * 4, (d, d, d, d + extra)))
     h = L.dmrg_create(pb)
