@@ -24,6 +24,10 @@ constexpr int kDVals = 4 * kDSlots + 4;   // values per partial row of a reducti
 constexpr int kDMaxQ = (kMaxKrylov + kDSlots - 1) / kDSlots;   // reduction launches per iteration
 constexpr int kRedThreads = 1024;   // threads of a reduction block
 constexpr int kRedRows = 256;       // most blocks of a reduction
+constexpr int kRedStride = kRedRows + 16;   // between the values of the partial rows: an odd number of
+                                    // 128-byte lines, so that they spread over the channels (16
+                                    // problems 5864 us at 8 KB, 5851 so)
+static_assert(kRedStride <= kVecMaxBlocks, "the partial rows' allocation");
 // Most partial rows (blocks of the largest problem times launches) of one iteration that every block
 // of the update pass sums itself; k_dsum does it where there are more.  Measured per Lanczos basis,
 // own sums against k_dsum: chain8 (n = 4900, 10 rows) 2.53 against 2.65 ms for its 10 bases,

@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kRedThreads) void k_dreduce(const VecProb* vp, cons
         if ((lane & 12) == 0) red[wave][t][4 * (lane >> 4) + i] = v;
     }
     __syncthreads();
-    double* part = W.p.part + (int64_t)q * kVecMaxBlocks * kDVals;
+    double* part = W.p.part + (int64_t)q * kRedStride * kDVals;
     for (int v = threadIdx.x; v < kDVals; v += kRedThreads) {
         double sum = 0.0;
         if (v < NV) {
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kRedThreads) void k_dreduce(const VecProb* vp, cons
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += red[w][t][p] + sg * red[w][t][r];
         }
-        part[(int64_t)v * kVecMaxBlocks + W.lb] = sum;
+        part[(int64_t)v * kRedStride + W.lb] = sum;
     }
 }
 
@@ -457,17 +457,17 @@ __global__ __launch_bounds__(kVecThreads) void k_dsum(const VecProb* vp, VecProb
     const int broken = ((const int __attribute__((address_space(1)))*)&st->broken)[0];
     const int lane = threadIdx.x & 63;
     const int v = blockIdx.x * (kVecThreads / 64) + (threadIdx.x >> 6);
-    const gcptr row = (gcptr)(P.part + (int64_t)v * kVecMaxBlocks);
+    const gcptr row = (gcptr)(P.part + (int64_t)v * kRedStride);
     const int nbr = P.nbr;
-    double x[kVecMaxBlocks / 64];
+    double x[kRedRows / 64];
 #pragma unroll
-    for (int k = 0; k < kVecMaxBlocks / 64; ++k) {
+    for (int k = 0; k < kRedRows / 64; ++k) {
         const int b = lane + 64 * k;
         x[k] = row[b < nbr ? b : nbr - 1] * (b < nbr ? 1.0 : 0.0);
     }
     double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < kVecMaxBlocks / 64; ++k) acc += x[k];
+    for (int k = 0; k < kRedRows / 64; ++k) acc += x[k];
     acc = tree_sum(acc);
     if (lane == 0 && !broken) st->red[v] = acc;
 }
@@ -478,8 +478,8 @@ __device__ __forceinline__ void sum_rows(const double* part, int nbr, int nq, do
     constexpr int P = kDVals / (kVecThreads / 64);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int q = 0; q < nq; ++q) {
-        const gcptr p = (gcptr)(part + (int64_t)q * kVecMaxBlocks * kDVals) +
-                        (int64_t)wave * P * kVecMaxBlocks;
+        const gcptr p = (gcptr)(part + (int64_t)q * kRedStride * kDVals) +
+                        (int64_t)wave * P * kRedStride;
         double v[P];
 #pragma unroll
         for (int i = 0; i < P; ++i) v[i] = 0.0;
@@ -488,7 +488,7 @@ __device__ __forceinline__ void sum_rows(const double* part, int nbr, int nq, do
             const double keep = b < nbr ? 1.0 : 0.0;
             double x[P];
 #pragma unroll
-            for (int i = 0; i < P; ++i) x[i] = p[(int64_t)i * kVecMaxBlocks + (b < nbr ? b : nbr - 1)];
+            for (int i = 0; i < P; ++i) x[i] = p[(int64_t)i * kRedStride + (b < nbr ? b : nbr - 1)];
 #pragma unroll
             for (int i = 0; i < P; ++i) v[i] += x[i] * keep;
         }
