@@ -29,11 +29,15 @@ __device__ __forceinline__ double recip2(double x) {
 // grows by less than 2^24 and the two minors carried on are scaled between runs.  A zero counts by
 // its sign bit, whichever it is, as its neighbours have opposite signs; two zeros in turn (a
 // diagonal entry equal to x beside a zero e) would stay zeros, so a run that ends in them is taken
-// again with a tiny value of the opposite sign in place of a zero.
+// again with -kTinyMinor times the minor before it in place of a zero: the exact minor of an entry
+// changed by that much (whatever couples to it, the ratio has to be tiny, not the minor alone).  A
+// zero carried in from the run before has been counted by its sign bit there, so its replacement
+// takes that sign.
 // The entries are the same in every lane; from global memory they come by scalar loads, a run ahead
 // (many wavefronts' broadcast reads from LDS bound the pass: two per step and wavefront).  rec: per run of kSturmRun rows the diagonal entries
 // and the squares of the subdiagonal entries above them (the first 0), nrun runs, the last one
 // padded with rows that change no sign (diagonal 4, above every x; subdiagonal 0).
+constexpr double kTinyMinor = 1e-30;    // eight in turn stay far above the smallest double
 __device__ __forceinline__ int sturm_count(int nrun, const double* __restrict__ rec, double x) {
     static_assert(kSturmRun < 32, "the signs of a run in one word");
     double p2 = 0.0, p1 = 1.0;
@@ -54,7 +58,7 @@ __device__ __forceinline__ int sturm_count(int nrun, const double* __restrict__ 
 #pragma unroll
             for (int t = 0; t < kSturmRun; ++t) {
                 double p = fma(cur[t] - x, p1, -(cur[kSturmRun + t] * p2));
-                if (guard && p == 0.0) p = -copysign(1e-200, p1);
+                if (guard && p == 0.0) p = -kTinyMinor * p1;
                 sg = __builtin_amdgcn_alignbit(sg, (unsigned)__double2hiint(p), 31);
                 p2 = p1;
                 p1 = p;
@@ -64,7 +68,7 @@ __device__ __forceinline__ int sturm_count(int nrun, const double* __restrict__ 
         const unsigned s0 = sg;
         run(false);
         if (p1 == 0.0 && p2 == 0.0) {
-            p1 = p10 != 0.0 ? p10 : -copysign(1e-200, p20);
+            p1 = p10 != 0.0 ? p10 : (s0 & 1 ? -kTinyMinor : kTinyMinor);
             p2 = p20;
             sg = s0;
             run(true);

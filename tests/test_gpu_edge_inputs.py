@@ -1,0 +1,50 @@
+"""Inputs whose results depend on a rare branch or on what an earlier call left behind (needs an
+MI355X)."""
+import numpy as np
+import pytest
+
+from paper_1103_5391_amd import inputs as I
+from tests.test_gpu_block_edges import _problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_1103_5391_amd import lib as L
+    return torch, L
+
+
+@pytest.mark.parametrize("d,seed", [(16, 0), (40, 1), (64, 2), (170, 3)])
+def test_density_of_diagonal_matrices(env, d, seed):
+    """Diagonal density matrices with the entries 0 .. 33, the values in the last rows of the Sturm
+    counts' runs among the points of the first section (its 32 points lie at 1, 2, .. but for
+    rounding, which leaves those around the middle exact).  The entries are exact sums of the
+    weights 1, 2, 4, .. of six targets; eigenvalues within 1e-12 of the largest, orthonormality and
+    residuals within 1e-11 d, as in the parity tests."""
+    torch, L = env
+    pb = _problem(((d,) * 4, (d,) * 4))
+    rng = np.random.default_rng(seed)
+    vals = []
+    for _ in I.psi_blocks(pb):
+        a = rng.integers(0, 34, d)
+        a[0], a[1] = 33, 0
+        for r in range(7, d, 8):
+            a[r] = rng.integers(13, 22)
+        vals.append(a)
+    vecs = []
+    for bit in range(6):
+        re = [np.diag(((a >> bit) & 1).astype(float)).ravel() for a in vals]
+        vecs.append(torch.from_numpy(np.concatenate(re + [np.zeros(4 * d * d)])).to("cuda"))
+    h = L.dmrg_create(pb)
+    ev = torch.zeros(4 * d, dtype=torch.float64, device="cuda")
+    vc = torch.zeros(8 * d * d, dtype=torch.float64, device="cuda")
+    h.density_truncate(vecs, 2.0 ** np.arange(6), 4 * d, ev, vc)
+    ev, vc = ev.cpu().numpy().reshape(4, d), vc.cpu().numpy().reshape(4, 2, d, d)
+    for b, a in enumerate(vals):
+        assert np.max(np.abs(ev[b] - np.sort(a)[::-1])) <= 1e-12 * 33
+        U = (vc[b, 0] + 1j * vc[b, 1]).T
+        assert np.linalg.norm(U.conj().T @ U - np.eye(d)) <= 1e-11 * d
+        assert np.linalg.norm(a[:, None] * U - U * ev[b]) <= 1e-11 * 33 * d
+    h.destroy()
