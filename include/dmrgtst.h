@@ -313,14 +313,19 @@ int dmrg_matvec(dmrg_handle h, const double* x, double* y, int32_t nvec);
  * no device allocation and no free: the stage-1 intermediate, which dmrg_matvec keeps in the
  * handle, lives here in a library-owned array of DMRG_NOALLOC_SCRATCH_BYTES on each GPU (held
  * from the library's load on that GPU until the process ends; its address is resolved by
- * dmrg_create).  Each call first clears the part it uses, with a kernel on the handle's stream.
+ * dmrg_create).  Nothing that an earlier call left there is used: each call's kernels, all on the
+ * handle's stream, first write or clear what they read.
  *   Every call on one GPU, from any handle, shares that GPU's array: calls that overlap in time
  * on one GPU (other streams, other threads) race and give wrong results; order them on one
- * stream.  The optional non-finite check (dmrg_set_check_finite) is not run.
+ * stream.  (A problem within the limit below whose intermediate, in whole panels of 16 columns,
+ * is larger than the array has an array of its own for this call, allocated by dmrg_create; its
+ * calls race with each other only.)  dmrg_matvec's workspace is not touched.  The optional
+ * non-finite check (dmrg_set_check_finite) is not run.
  * Errors: DMRG_EINVAL for a null handle, negative nvec, null vectors with nvec > 0, or a
- * problem whose intermediate, in the layout of the handle's block-product family (the K-split
- * family pads it more), needs more than DMRG_NOALLOC_SCRATCH_BYTES (message via
- * dmrg_last_error; nothing is launched); DMRG_EHIP. */
+ * problem whose intermediate needs more than DMRG_NOALLOC_SCRATCH_BYTES, counted as 16 bytes for
+ * every column of it and every row of its system sector, rows rounded up to a multiple of 32 (in
+ * the K-split family: as that family pads it) (message via dmrg_last_error; nothing is
+ * launched); DMRG_EHIP. */
 int dmrg_matvec_noalloc(dmrg_handle h, const double* x, double* y, int32_t nvec);
 
 /* y = (exp(-i tau H_sb))^nsteps x: nsteps Krylov steps of size kdim (1 <= kdim <= 64), each

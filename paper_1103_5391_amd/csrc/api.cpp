@@ -474,7 +474,19 @@ struct dmrg_ctx {
     // planned lists of local terms, the last used first: a program alternates between a few
     std::vector<std::unique_ptr<LocalPlan>> loc;
     uint64_t serial = 0;                // unique per handle in the process (never reused)
+    // stage-1 intermediate of dmrg_matvec_noalloc where it does not fit the library's array although
+    // the problem is within the limit (own_scratch)
+    DevBuf dNoAlloc;
 };
+
+// Bytes of a handle's own intermediate for dmrg_matvec_noalloc.  The limit counts the intermediate with
+// its columns as they are (Plan::T_need); rounded up to whole column panels it can take more
+// than the library's array, and such a handle gets an array of its own when it is created: the call
+// neither allocates nor shares dmrg_matvec's workspace.
+static size_t own_scratch(const Plan& P) {
+    const size_t need = (size_t)P.T_need * sizeof(double), base = (size_t)P.T_base * sizeof(double);
+    return need <= kNoAllocScratchBytes && base > kNoAllocScratchBytes ? base : 0;
+}
 
 // A planned move of the centre (wave-function transformation): tile lists of its two stages,
 // the matrices W_r, and the intermediate.
@@ -1451,6 +1463,7 @@ int dmrg_create(const dmrg_problem* problem, void* stream, dmrg_handle* out) {
     // written: they must hold finite values, so the workspace starts zeroed
     if (e == hipSuccess)
         e = hipMemsetAsync(h->ws[0].dT.p, 0, sizeof(double) * (size_t)P.T_size, h->stream);
+    if (e == hipSuccess && own_scratch(P) > 0) e = h->dNoAlloc.alloc(own_scratch(P));
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
         g_create_error = e == hipErrorOutOfMemory
@@ -1551,6 +1564,7 @@ int dmrg_plan_stats(const dmrg_problem* problem, int32_t kdim, dmrg_plan_info* o
         add(P.kf.t2.size() * sizeof(KTile));
         add(sizeof(double) * (size_t)std::max(P.pk16.nslots, P.pk32.nslots) * kLTile * kLTile);
         add(sizeof(double) * (size_t)P.T_size);
+        if (own_scratch(P) > 0) add(own_scratch(P));
         add(A.size());
         add(R.size());
         out->create_bytes = bytes;
@@ -1641,17 +1655,14 @@ int dmrg_matvec_noalloc(dmrg_handle h, const double* x, double* y, int32_t nvec)
                                         " bytes of the allocation-free scratch");
     double* T = nullptr;
     HIP_TRY(h, noalloc_scratch(&T));
-    if ((size_t)tb * sizeof(double) > kNoAllocScratchBytes) {
-        // its column panels round a problem near the limit above it: the handle's own array
-        T = h->ws[0].dT.as<double>();
-    } else if (kfam || h->precision >= DMRG_BF16X3 ||
-               (h->lists.variant & (DMRG_GEMM_STAGE1_LDS | DMRG_GEMM_X))) {
-        // the array holds whatever the last call on this GPU left: the intermediate's padding
-        // rows meet zero factors and must be finite, so the used region starts from zeros (a fill
-        // kernel, so that a captured call clears it on every replay).  The register-tiled stage 1
-        // with 16-deep chunks writes every row that is read.
+    if ((size_t)tb * sizeof(double) > kNoAllocScratchBytes) T = h->dNoAlloc.as<double>();
+    // the array holds whatever the last call on this GPU left: the intermediate's padding rows meet
+    // zero factors and must be finite, so the used region starts from zeros (a fill kernel, so that
+    // a captured call clears it on every replay).  The register-tiled stage 1 with 16-deep chunks
+    // writes every row that is read.
+    if (kfam || h->precision >= DMRG_BF16X3 ||
+        (h->lists.variant & (DMRG_GEMM_STAGE1_LDS | DMRG_GEMM_X)))
         HIP_TRY(h, launch_zero(T, tb, h->stream));
-    }
     const int64_t vs = 2 * h->plan.n;
     for (int v = 0; v < nvec; ++v) {
         ProbPtrs pp = make_ptrs(h, h->precision, x + v * vs, y + v * vs, nullptr);

@@ -48,3 +48,30 @@ def test_density_of_diagonal_matrices(env, d, seed):
         assert np.linalg.norm(U.conj().T @ U - np.eye(d)) <= 1e-11 * d
         assert np.linalg.norm(a[:, None] * U - U * ev[b]) <= 1e-11 * 33 * d
     h.destroy()
+
+
+def test_noalloc_with_an_array_of_its_own(env):
+    """A problem within the limit of dmrg_matvec_noalloc (66.8 of 67.1 MB by its columns) whose column
+    panels take more (87.3 MB): the bits of dmrg_matvec in every family and arithmetic that clears or
+    does not clear the array, also after a call of another handle and from a vector of NaN."""
+    from tests.test_noalloc_memory import panel_problem
+    torch, L = env
+    h, small = L.dmrg_create(panel_problem()), L.dmrg_create(_problem(((17, 5, 3, 9), (4, 8, 7, 6))))
+    rng = np.random.default_rng(I.SEED_BASE + 21)
+    x = torch.from_numpy(I.random_psi(h.n, rng)).to("cuda")
+    xs = torch.from_numpy(I.random_psi(small.n, rng)).to("cuda")
+    bad, y, z = torch.full_like(x, float("nan")), torch.empty_like(x), torch.empty_like(x)
+    ys, zs = torch.empty_like(xs), torch.empty_like(xs)
+    small.matvec(xs, ys)
+    for prec, variants in ((0, (0, 12, 3, 16)), (1, (0, 3)), (2, (0, 3))):
+        h.set_precision(prec)
+        for v in variants:
+            h.set_gemm(v)
+            h.matvec_noalloc(bad, z)
+            h.matvec_noalloc(x, z)
+            small.matvec_noalloc(xs, zs)
+            h.matvec(x, y)
+            assert torch.equal(y, z), (prec, v)
+            assert torch.equal(ys, zs), (prec, v)
+    h.destroy()
+    small.destroy()
