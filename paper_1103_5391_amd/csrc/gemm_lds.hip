@@ -153,9 +153,10 @@ __global__ __launch_bounds__(256, 3) void stage1_lds(const S1Block* __restrict__
             for (int v = 0; v < 4; ++v) {
                 const int m = it.m0 + 32 * wm + 16 * mi + P::row(g, v);
                 if (m < B.M) {
-                    const int pl = m >= tv.split;
-                    T[tv.off + pl * tv.poff + tpos<ws_t>(tv.ld, n, m - pl * tv.split)] =
-                        (ws_t)acc[mi][nj][v];
+                    const int pl = m >= tv.split, k = m - pl * tv.split;
+                    ws_t* __restrict__ plane = T + tv.off + pl * tv.poff;
+                    plane[tpos<ws_t>(tv.ld, n, k)] = (ws_t)acc[mi][nj][v];
+                    if (k == tv.split - 1) pad_rows<P>(plane, tv, n);
                 }
             }
         }

@@ -158,6 +158,14 @@ __device__ __forceinline__ int64_t tpos(int ld, int col, int k) {
     return (int64_t)(col >> 4) * ld + k / U * (16 * U) + (col & 15) * U + (k & (U - 1));
 }
 
+// Zeros in the padding rows of one column of a plane, by the lane that stores the column's last row:
+// stage 2 multiplies them with zero factors, and what another family's layout, or a vector of NaN,
+// left there need not be finite.
+template <class P>
+__device__ __forceinline__ void pad_rows(typename P::ws_t* plane, const View& tv, int col) {
+    for (int k = tv.split; k % P::CK != 0; ++k) plane[tpos<typename P::ws_t>(tv.ld, col, k)] = 0;
+}
+
 // The lane's data values k = koff(g, t) of a chunk of the workspace, base at the lane's column in
 // the chunk's first unit: 16-byte units, so that 16 lanes read 256 contiguous bytes.  (From a
 // column-major intermediate every lane of a load was in a line of its own; the L1's data return

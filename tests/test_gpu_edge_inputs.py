@@ -3,8 +3,9 @@ MI355X)."""
 import numpy as np
 import pytest
 
+from oracle import matvec as M
 from paper_1103_5391_amd import inputs as I
-from tests.test_gpu_block_edges import _problem
+from tests.test_gpu_block_edges import BOUND, DIMS, _problem
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +76,24 @@ def test_noalloc_with_an_array_of_its_own(env):
             assert torch.equal(ys, zs), (prec, v)
     h.destroy()
     small.destroy()
+
+
+@pytest.mark.parametrize("dims", DIMS[:4], ids=["1", "16", "32", "64"])
+def test_families_after_nan_in_the_k_split_layout(env, dims):
+    """The K-split family lays the handle's workspace out in its own way: after it has run on a vector of
+    NaN, no value that another family reads may come from what it left (bounds: FP64 products at the
+    tile edges)."""
+    torch, L = env
+    pb = _problem(dims)
+    h = L.dmrg_create(pb)
+    x = I.random_psi(h.n, np.random.default_rng(I.SEED_BASE + 22))
+    ref = M.matvec_sector(pb, x)
+    xd = torch.from_numpy(x).to("cuda")
+    bad, y = torch.full_like(xd, float("nan")), torch.empty_like(xd)
+    for v in (0, 1, 2, 3, 12, 16, 32):
+        h.set_gemm(32)
+        h.matvec(bad, y)
+        h.set_gemm(v)
+        h.matvec(xd, y)
+        assert np.linalg.norm(y.cpu().numpy() - ref) < BOUND[0] * np.linalg.norm(ref), v
+    h.destroy()
