@@ -644,6 +644,10 @@ __global__ __launch_bounds__(kVecThreads) void k_dupdate(const VecProb* vp, cons
                                        [&](int i) { return ((gcptr)st->red)[i]; }, co, cj)) {
         return;
     }
+    // the lanes' coefficients before the others' reads of them: within a wavefront LDS accesses are
+    // in order, so this holds the compiler only (no wait for the loads in flight)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     const bool last = j == kdim - 1;
     const double sj = cj.s, tjr = cj.tr, tji = cj.ti, hjr = cj.hr, hji = cj.hi;
     if (even) {
