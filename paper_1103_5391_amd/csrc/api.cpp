@@ -1029,7 +1029,8 @@ int plan_wft(dmrg_handle h, const dmrg_wft_desc& D, std::vector<ZTile>& tA, std:
 
 // Device copy of the raw operator blocks of both halves (first use of local operators).
 int ensure_local_ops(dmrg_handle h) {
-    if (h->dOpS.p && h->dOpE.p) return DMRG_OK;
+    // the last buffer of the set: after a failed allocation the next call starts again
+    if (h->dMonoVal[1].p) return DMRG_OK;
     for (int side = 0; side < 2; ++side) {
         const HalfTable& T = side == 0 ? h->plan.S : h->plan.E;
         std::vector<double> all;

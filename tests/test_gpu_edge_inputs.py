@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import matvec as M
+from oracle import observables as Ob
 from paper_1103_5391_amd import inputs as I
 from tests.test_gpu_block_edges import BOUND, DIMS, _problem
 
@@ -97,3 +98,63 @@ def test_families_after_nan_in_the_k_split_layout(env, dims):
         h.matvec(xd, y)
         assert np.linalg.norm(y.cpu().numpy() - ref) < BOUND[0] * np.linalg.norm(ref), v
     h.destroy()
+
+
+def _local_problem():
+    """A superblock with an operator per half that has one value per row and column, and the lists of
+    a pair of them with the coefficient c (for the library and for the oracle)."""
+    pb = _problem(DIMS[2])
+    ops = []
+    for space in (pb.S.space, pb.E.space):
+        o = I.BlockOp((0, 0))
+        for p, d in enumerate(space.dim):
+            o.blocks[p] = np.diag(1.0 + np.arange(d))[::-1].copy()
+        ops.append(o)
+    pbx, iS, iE = I.with_ops(pb, [ops[0]], [ops[1]])
+    return pbx, (lambda c: [(c, iS[0], 0, iE[0], 0, 0)]), (lambda c: [(c, ops[0], ops[1], 0)])
+
+
+def _capped(L, pb, cap):
+    import os
+    os.environ["DMRG_MAX_WORKSPACE"] = str(cap)
+    try:
+        return L.dmrg_create(pb)
+    finally:
+        del os.environ["DMRG_MAX_WORKSPACE"]
+
+
+def test_local_terms_below_and_above_a_memory_cap(env):
+    """Caps on the handle's memory from far below what the local operators take to all of it, in steps
+    smaller than their last buffers: a call that does not fit fails, and fails again, and the first
+    that fits is right."""
+    torch, L = env
+    pb, terms, oterms = _local_problem()
+    base = L.plan_stats(pb)["create_bytes"]
+    x = I.random_psi(L.plan_stats(pb)["n"], np.random.default_rng(I.SEED_BASE + 23))
+    ref = Ob.apply_terms(pb, pb, oterms(1.0), x)
+    xd = torch.from_numpy(x).to("cuda")
+
+    def fits(extra):
+        h = _capped(L, pb, base + extra)
+        done = []
+        for _ in range(2):
+            y = torch.full_like(xd, float("nan"))
+            try:
+                h.apply_local(h, terms(1.0), xd, y)
+                assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-13 * np.max(np.abs(ref))
+                done.append(True)
+            except L.DmrgError as e:
+                assert e.status == L.STATUS_CODE["DMRG_ENOMEM"]
+                done.append(False)
+        h.destroy()
+        assert done[0] == done[1], extra
+        return done[0]
+
+    lo, hi = 8, 1 << 24
+    assert not fits(lo) and fits(hi)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid) else (mid, hi)
+    for below in list(range(1, 12000, 120)) + [hi - hi // 2, hi - hi // 8]:
+        if below < hi:
+            assert not fits(hi - below)
