@@ -72,10 +72,13 @@ constexpr int DMRG_GEMM_DEFAULT = 0;
 // Device memory of one handle: a cap (DMRG_MAX_WORKSPACE bytes, read by dmrg_create; no cap
 // without it) and the bytes its buffers hold.  The entry points make their handle's budget the
 // current one for the calling thread; DevBuf allocations are charged to the current budget and
-// refused (hipErrorOutOfMemory, reported as DMRG_ENOMEM) beyond its cap, before hipMalloc.
+// refused (hipErrorOutOfMemory, reported as DMRG_ENOMEM) beyond its cap, before hipMalloc.  What the
+// handle only keeps for later calls is given up first (trim).
 struct Budget {
     size_t cap = SIZE_MAX;
     size_t used = 0;
+    void (*trim)(dmrg_ctx*) = nullptr;
+    dmrg_ctx* of = nullptr;
 };
 thread_local Budget* g_budget = nullptr;
 struct BudgetScope {
@@ -100,8 +103,16 @@ struct DevBuf {
         release();
         if (b == 0) b = 8;
         Budget* bg = g_budget;
-        if (bg && (b > bg->cap || bg->used > bg->cap - b)) return hipErrorOutOfMemory;
-        hipError_t e = hipMalloc(&p, b);
+        auto get = [&] {
+            if (bg && (b > bg->cap || bg->used > bg->cap - b)) return hipErrorOutOfMemory;
+            return hipMalloc(&p, b);
+        };
+        hipError_t e = get();
+        if (e == hipErrorOutOfMemory && bg && bg->trim) {
+            (void)hipGetLastError();
+            bg->trim(bg->of);
+            e = get();
+        }
         if (e == hipSuccess) {
             bytes = b;
             owner = bg;
@@ -471,13 +482,18 @@ struct dmrg_ctx {
     // of the map of the block (fwd) and of its transpose (bwd), -1 if the block is not monomial
     DevBuf dMonoMap[2], dMonoVal[2];
     std::vector<std::vector<int>> mono_fwd[2], mono_bwd[2];
-    // planned lists of local terms, the last used first: a program alternates between a few
+    // planned lists of local terms, the last used first: a program alternates between a few.  Where
+    // memory is short all but the last used are given up (keep_last_plan)
     std::vector<std::unique_ptr<LocalPlan>> loc;
     uint64_t serial = 0;                // unique per handle in the process (never reused)
     // stage-1 intermediate of dmrg_matvec_noalloc where it does not fit the library's array although
     // the problem is within the limit (own_scratch)
     DevBuf dNoAlloc;
 };
+
+static void keep_last_plan(dmrg_ctx* h) {
+    if (h->loc.size() > 1) h->loc.resize(1);
+}
 
 // Bytes of a handle's own intermediate for dmrg_matvec_noalloc.  The limit counts the intermediate with
 // its columns as they are (Plan::T_need); rounded up to whole column panels it can take more
@@ -1444,6 +1460,8 @@ int dmrg_create(const dmrg_problem* problem, void* stream, dmrg_handle* out) {
         }
         h->budget.cap = (size_t)v;
     }
+    h->budget.trim = keep_last_plan;
+    h->budget.of = h;
     BudgetScope bs(&h->budget);
     const Plan& P = h->plan;
     hipError_t e = hipSuccess;

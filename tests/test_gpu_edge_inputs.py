@@ -158,3 +158,35 @@ def test_local_terms_below_and_above_a_memory_cap(env):
     for below in list(range(1, 12000, 120)) + [hi - hi // 2, hi - hi // 8]:
         if below < hi:
             assert not fits(hi - below)
+
+
+def test_kept_lists_give_way_to_other_buffers(env):
+    """A memory cap that holds the tables of one list of local terms and a Krylov workspace holds them
+    after eight lists too: the lists a handle keeps are no reason to refuse another call."""
+    torch, L = env
+    pb, terms, oterms = _local_problem()
+    base = L.plan_stats(pb)["create_bytes"]
+    x = torch.from_numpy(I.random_psi(L.plan_stats(pb)["n"], np.random.default_rng(I.SEED_BASE + 24))).to("cuda")
+    y, z = torch.empty_like(x), torch.empty_like(x)
+
+    def fits(extra, lists):
+        h = _capped(L, pb, base + extra)
+        try:
+            for c in range(lists):
+                h.apply_local(h, terms(1.0 + c), x, y)
+            h.krylov_expm(x, z, 0.01, 4, 1)
+            h.apply_local(h, terms(1.0), x, z)
+            return True
+        except L.DmrgError as e:
+            assert e.status == L.STATUS_CODE["DMRG_ENOMEM"]
+            return False
+        finally:
+            h.destroy()
+
+    lo, hi = 8, 1 << 24
+    assert not fits(lo, 1) and fits(hi, 1)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid, 1) else (mid, hi)
+    assert fits(hi, 8)
+    assert np.max(np.abs((y - 8.0 * z).cpu().numpy())) <= 1e-13 * float(y.abs().max())
