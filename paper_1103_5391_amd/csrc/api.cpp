@@ -477,10 +477,11 @@ struct dmrg_ctx {
     DevBuf dOpS, dOpE, dLocT, dLocZ;
     HostBuf hLocPart;
     std::vector<int64_t> opS_base, opE_base;
-    // monomial operator blocks (at most one nonzero per row and column): per half the maps
-    // (input index -> output index) and values, and per operator and source sector the offsets
-    // of the map of the block (fwd) and of its transpose (bwd), -1 if the block is not monomial
-    DevBuf dMonoMap[2], dMonoVal[2];
+    // monomial operator blocks (at most one nonzero per row and column): the values of both halves,
+    // then the maps (input index -> output index), and per half, operator and source sector the
+    // offsets of the map of the block (fwd) and of its transpose (bwd), -1 if it is not monomial
+    DevBuf dMono;
+    size_t mono_nval = 0;
     std::vector<std::vector<int>> mono_fwd[2], mono_bwd[2];
     // planned lists of local terms, the last used first: a program alternates between a few.  Where
     // memory is short all but the last used are given up (keep_last_plan)
@@ -1046,7 +1047,9 @@ int plan_wft(dmrg_handle h, const dmrg_wft_desc& D, std::vector<ZTile>& tA, std:
 // Device copy of the raw operator blocks of both halves (first use of local operators).
 int ensure_local_ops(dmrg_handle h) {
     // the last buffer of the set: after a failed allocation the next call starts again
-    if (h->dMonoVal[1].p) return DMRG_OK;
+    if (h->dMono.p) return DMRG_OK;
+    std::vector<int> maps;
+    std::vector<double> vals;
     for (int side = 0; side < 2; ++side) {
         const HalfTable& T = side == 0 ? h->plan.S : h->plan.E;
         std::vector<double> all;
@@ -1058,8 +1061,6 @@ int ensure_local_ops(dmrg_handle h) {
         }
         HIP_TRY(h, upload(side == 0 ? h->dOpS : h->dOpE, all, h->stream));
         // monomial blocks: maps of the block and of its transpose
-        std::vector<int> maps;
-        std::vector<double> vals;
         h->mono_fwd[side].assign(T.ops.size(), std::vector<int>(T.nsec, -1));
         h->mono_bwd[side].assign(T.ops.size(), std::vector<int>(T.nsec, -1));
         for (size_t o = 0; o < T.ops.size(); ++o) {
@@ -1094,9 +1095,13 @@ int ensure_local_ops(dmrg_handle h) {
                 vals.insert(vals.end(), bv.begin(), bv.end());
             }
         }
-        HIP_TRY(h, upload(h->dMonoMap[side], maps, h->stream));
-        HIP_TRY(h, upload(h->dMonoVal[side], vals, h->stream));
     }
+    // values and maps of both halves in one upload: each costs a copy and a wait, most of what a
+    // handle's first local term takes on a small superblock
+    h->mono_nval = vals.size();
+    vals.resize(vals.size() + (maps.size() + 1) / 2);
+    if (!maps.empty()) std::memcpy(vals.data() + h->mono_nval, maps.data(), maps.size() * sizeof(int));
+    HIP_TRY(h, upload(h->dMono, vals, h->stream));
     return DMRG_OK;
 }
 
@@ -1342,11 +1347,10 @@ int find_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
 int run_local(dmrg_handle hs, dmrg_handle hd, const LocalPlan& P, const double* x, double* y,
               double* part) {
     hipStream_t s = hs->stream;
-    HIP_TRY(hs, launch_local_mono(P.at<LocalItem>(P.at_items), P.nitems,
-                                  P.at<LocalSrc>(P.at_src), hs->dMonoMap[0].as<int>(),
-                                  hs->dMonoVal[0].as<double>(), hs->dMonoMap[1].as<int>(),
-                                  hs->dMonoVal[1].as<double>(), x, hs->plan.n, y, hd->plan.n, part,
-                                  kDotBlocks, s));
+    const double* vals = hs->dMono.as<double>();
+    const int* maps = reinterpret_cast<const int*>(vals + hs->mono_nval);
+    HIP_TRY(hs, launch_local_mono(P.at<LocalItem>(P.at_items), P.nitems, P.at<LocalSrc>(P.at_src), maps,
+                                  vals, maps, vals, x, hs->plan.n, y, hd->plan.n, part, kDotBlocks, s));
     for (const auto& L : P.launches) {
         ZPtrs p{};
         if (L[2] == 0) {            // right products: x, environment blocks -> intermediate
