@@ -467,15 +467,14 @@ struct dmrg_ctx {
     // the call's results in one device area (per sector: the two sums, the number kept, the
     // eigen-decomposition flags), copied at once into pinned host memory
     DevBuf dDBlk, dDSel, dDTile, dDBack, dDEval, dDVec, dDTri, dDA, dDV, dDZ, dDS, dDT, dDEv, dDKept, dDRes;
-    HostBuf hDRes;
+    HostBuf hRes;       // pinned: what the host reads at the end of a call (host_results)
     int dens_ntiles = 0, dens_ntot = 0, dens_nreg = 0, dens_nbt = 0, dens_nback = 0;
     int dens_neval = 0, dens_nvec = 0, dens_dmax = 0;
     int64_t dens_nmat = 0;
     std::unique_ptr<dmrg_batch_ctx> chains;   // the handle's four chains of the 4-RHS mode
     // local operators (built on first use): raw operator blocks of both halves, the product
-    // intermediate, the image of an expectation and its partial sums (written by the kernel)
+    // intermediate, the image of an expectation (its partial sums go to hRes, by the kernel)
     DevBuf dOpS, dOpE, dLocT, dLocZ;
-    HostBuf hLocPart;
     std::vector<int64_t> opS_base, opE_base;
     // monomial operator blocks (at most one nonzero per row and column): the values of both halves,
     // then the maps (input index -> output index), and per half, operator and source sector the
@@ -1044,6 +1043,14 @@ int plan_wft(dmrg_handle h, const dmrg_wft_desc& D, std::vector<ZTile>& tA, std:
     return DMRG_OK;
 }
 
+// The handle's pinned area, of at least b bytes.  Its users (density matrices, expectations) wait for
+// the stream before they return, so that they can share it: a sweep truncates before it measures, and
+// the allocation (30 to 100 us) is paid once.
+hipError_t host_results(dmrg_handle h, size_t b) {
+    if (h->hRes.bytes >= b) return hipSuccess;
+    return h->hRes.alloc(std::max(b, sizeof(double) * 2 * kDotBlocks));
+}
+
 // Device copy of the raw operator blocks of both halves (first use of local operators).
 int ensure_local_ops(dmrg_handle h) {
     // the last buffer of the set: after a failed allocation the next call starts again
@@ -1150,7 +1157,8 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
         if (a.nup != b.nup || a.ndn != b.ndn || a.dim != b.dim) return bad("the handles have different halves");
     }
     tsize = 0;
-    std::vector<std::vector<LocalSrc>> into(D.blocks.size());
+    std::vector<std::pair<int, LocalSrc>> part;     // (destination block, source), term by term
+    part.reserve(S.blocks.size());
     for (int t = 0; t < nterm; ++t) {
         const dmrg_term& tm = terms[t];
         if (tm.opS < -1 || tm.opS >= (int)S.S.ops.size() || tm.opE < -1 || tm.opE >= (int)S.E.ops.size())
@@ -1173,7 +1181,7 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
             return src < 0 ? -1 : hs->mono_fwd[side][op][src];
         };
         bool mono = true;
-        std::vector<std::pair<int, LocalSrc>> part;
+        const size_t part0 = part.size();
         for (const PsiBlock& B : S.blocks) {
             Factor fa, fb;
             if (!factor_of(S.S, hs->opS_base, tm.opS, tm.transS, B.p, fa)) continue;
@@ -1188,10 +1196,8 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
             const double sign = (tm.fermionic && ((S.S.nup[B.p] + S.S.ndn[B.p]) & 1)) ? -1.0 : 1.0;
             part.push_back({ob, LocalSrc{B.off, B.d, ma < 0 ? -1 : ma, mb < 0 ? -1 : mb, 0, tm.coef * sign}});
         }
-        if (mono) {
-            for (const auto& q : part) into[q.first].push_back(q.second);
-            continue;
-        }
+        if (mono) continue;
+        part.resize(part0);
         std::vector<ZTile> right, left;
         int64_t toff = 0;
         for (const PsiBlock& B : S.blocks) {
@@ -1266,15 +1272,25 @@ int plan_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
             tiles.insert(tiles.end(), left.begin(), left.end());
         }
     }
+    // the sources by destination block, the terms of a block in their order
+    std::vector<int> at(D.blocks.size() + 1, 0);
+    size_t total = 0;
+    for (const auto& q : part) ++at[q.first + 1];
+    for (size_t b = 0; b < D.blocks.size(); ++b) {
+        at[b + 1] += at[b];
+        total += ((int64_t)D.blocks[b].d * D.blocks[b].e + kLocalChunk - 1) / kLocalChunk;
+    }
+    items.reserve(total);
     for (size_t b = 0; b < D.blocks.size(); ++b) {
         const PsiBlock& O = D.blocks[b];
         const int64_t cnt = (int64_t)O.d * O.e;
         for (int64_t c = 0; c < cnt; c += kLocalChunk)
             items.push_back(LocalItem{O.off + c, O.d, (int)(c % O.d), (int)(c / O.d),
-                                      (int)std::min<int64_t>(cnt - c, kLocalChunk), (int)srcs.size(),
-                                      (int)into[b].size()});
-        srcs.insert(srcs.end(), into[b].begin(), into[b].end());
+                                      (int)std::min<int64_t>(cnt - c, kLocalChunk), at[b],
+                                      at[b + 1] - at[b]});
     }
+    srcs.resize(part.size());
+    for (const auto& q : part) srcs[at[q.first]++] = q.second;
     return DMRG_OK;
 }
 
@@ -1303,16 +1319,15 @@ int find_local(dmrg_handle hs, dmrg_handle hd, int nterm, const dmrg_term* terms
     std::vector<LocalSrc> srcs;
     rc = plan_local(hs, hd, nterm, terms, tiles, items, srcs, L->launches, L->tsize);
     if (rc) return rc;
-    std::vector<char> all;
-    auto put = [&](const void* p, size_t bytes) {
-        const size_t at = all.size();
-        all.insert(all.end(), static_cast<const char*>(p), static_cast<const char*>(p) + bytes);
-        all.resize((all.size() + 63) / 64 * 64);
-        return at;
-    };
-    L->at_tiles = put(tiles.data(), tiles.size() * sizeof(ZTile));
-    L->at_src = put(srcs.data(), srcs.size() * sizeof(LocalSrc));
-    L->at_items = put(items.data(), items.size() * sizeof(LocalItem));
+    auto pad = [](size_t b) { return (b + 63) / 64 * 64; };
+    const size_t nt = tiles.size() * sizeof(ZTile), ns = srcs.size() * sizeof(LocalSrc),
+                 ni = items.size() * sizeof(LocalItem);
+    L->at_src = pad(nt);
+    L->at_items = L->at_src + pad(ns);
+    std::vector<char> all(L->at_items + pad(ni));
+    if (nt) std::memcpy(all.data(), tiles.data(), nt);
+    if (ns) std::memcpy(all.data() + L->at_src, srcs.data(), ns);
+    if (ni) std::memcpy(all.data() + L->at_items, items.data(), ni);
     L->nitems = (int)items.size();
     L->terms.assign(terms, terms + nterm);
     L->dst = hd->serial;
@@ -1885,7 +1900,7 @@ int dmrg_density_truncate(dmrg_handle h, const double* const* vecs, const double
         HIP_TRY(h, h->dDEv.alloc(sizeof(double) * (size_t)eoff));
         HIP_TRY(h, h->dDKept.alloc(sizeof(int) * (size_t)eoff));
         HIP_TRY(h, h->dDRes.alloc(res_bytes));
-        HIP_TRY(h, h->hDRes.alloc(res_bytes));
+        HIP_TRY(h, host_results(h, res_bytes));
         HIP_TRY(h, upload(h->dDBlk, blks, s));
     }
     // per-call pointers and weights go by value in the launch
@@ -1905,9 +1920,9 @@ int dmrg_density_truncate(dmrg_handle h, const double* const* vecs, const double
                               h->dens_nvec, h->dDEv.as<double>(), h->dDTri.as<double>(),
                               h->dens_ntot, keep,
                               h->dDKept.as<int>(), evals, evecs, d_nk, d_sums, s));
-    HIP_TRY(h, hipMemcpyAsync(h->hDRes.p, h->dDRes.p, res_bytes, hipMemcpyDeviceToHost, s));
+    HIP_TRY(h, hipMemcpyAsync(h->hRes.p, h->dDRes.p, res_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
-    const double* sums = h->hDRes.as<double>();
+    const double* sums = h->hRes.as<double>();
     const int* nk = reinterpret_cast<const int*>(sums + 2 * (size_t)nb);
     const int* flags = nk + nb;
     for (int b = 0; b < nb; ++b)
@@ -2016,8 +2031,8 @@ int dmrg_expect_local(dmrg_handle h, int32_t nterm, const dmrg_term* terms, cons
     LocalPlan* P = nullptr;
     int rc = find_local(h, h, nterm, terms, &P);
     if (rc) return rc;
-    if (!h->hLocPart.p) HIP_TRY(h, h->hLocPart.alloc(sizeof(double) * 2 * kDotBlocks));
-    double* part = h->hLocPart.as<double>();
+    HIP_TRY(h, host_results(h, sizeof(double) * 2 * kDotBlocks));
+    double* part = h->hRes.as<double>();
     if (P->launches.empty()) {          // monomial factors only: no image is stored
         rc = run_local(h, h, *P, x, nullptr, part);
         if (rc) return rc;

@@ -190,3 +190,28 @@ def test_kept_lists_give_way_to_other_buffers(env):
         lo, hi = (lo, mid) if fits(mid, 1) else (mid, hi)
     assert fits(hi, 8)
     assert np.max(np.abs((y - 8.0 * z).cpu().numpy())) <= 1e-13 * float(y.abs().max())
+
+
+@pytest.mark.parametrize("first", ["density", "expectation"])
+def test_density_and_expectation_share_their_results_area(env, first):
+    """Truncations and expectations in turn on one handle, either of them first: the weights add up and
+    the expectation is the oracle's (1e-12), every time."""
+    torch, L = env
+    pb, terms, oterms = _local_problem()
+    h = L.dmrg_create(pb)
+    x = I.random_psi(h.n, np.random.default_rng(I.SEED_BASE + 25))
+    xd = torch.from_numpy(x).to("cuda")
+    rows = [r for (_, _, r, _) in I.psi_blocks(pb)]
+    ev = torch.zeros(sum(rows), dtype=torch.float64, device="cuda")
+    U = torch.zeros(2 * sum(r * r for r in rows), dtype=torch.float64, device="cuda")
+    want = Ob.expect(pb, oterms(1.0), x)
+    for k in range(6):
+        if (k % 2 == 0) == (first == "density"):
+            kept, err = h.density_truncate([xd], np.array([1.0]), 10, ev, U)
+            assert sum(kept) == 10
+            top = np.sort(ev.cpu().numpy())[::-1]
+            assert abs(float(top.sum()) - float(x @ x)) <= 1e-12 * float(x @ x)
+            assert abs(err - float(top[10:].sum())) <= 1e-12 * float(x @ x)
+        else:
+            assert abs(h.expect_local(terms(1.0), xd) - want) <= 1e-12 * max(1.0, abs(want))
+    h.destroy()
