@@ -116,7 +116,7 @@ constexpr int kInvRun = 8;          // rows a solve loads before storing
 
 // T - x I = P L U of column l (partial pivoting, pivots floored at tiny), row by row ((dd, du) = the
 // current row's diagonal and superdiagonal), with the forward substitution P, L^-1 of a start vector
-// whose entries start() gives in turn.  EXACT: reciprocals to about an ulp.
+// whose entries start() gives in turn.  EXACT: correctly rounded reciprocals.
 template <bool EXACT, class M, class Start>
 __device__ __forceinline__ void tri_factor(const M& m, int d, int l, const double* __restrict__ dg,
                                            const double* __restrict__ e, double x, double tiny,
@@ -130,7 +130,7 @@ __device__ __forceinline__ void tri_factor(const M& m, int d, int l, const doubl
         const bool keep = fabs(dd) >= fabs(sub);
         const double piv = fabs(dd) >= tiny ? dd : (dd < 0.0 ? -tiny : tiny);
         const double by = keep ? piv : sub;
-        const double ip = EXACT ? recip2(by) : recip(by);
+        const double ip = EXACT ? 1.0 / by : recip(by);
         const double mu = (keep ? sub : dd) * ip;
         m.put_u(o, ip, keep ? du : nd, keep ? 0.0 : nu);
         m.put_l(o, mu, keep ? 0.0 : 1.0);
