@@ -83,10 +83,10 @@ enum dmrg_precision {
 };
 
 /* Kernel families of the two block-product stages (bits of a variant).  Without the bits a stage
- * runs register-tiled (stage 1: a 32 x 64 tile per single-wavefront work group; stage 2: a
- * 32 x 32 tile per work group whose K chunks are dealt to its four wavefronts).  STAGE1_NARROW,
- * STAGE2_NARROW: register-tiled with tiles half as wide (stage 1: 32 x 32, stage 2: 32 x 16;
- * twice as many tiles, for balance on small problems).
+ * runs register-tiled (stage 1: a tile of 16 rows of both planes x 64 columns per single-wavefront
+ * work group; stage 2: a 32 x 32 tile per work group whose K chunks are dealt to its four
+ * wavefronts).  STAGE1_NARROW, STAGE2_NARROW: register-tiled with tiles half as wide (stage 1: 32
+ * columns, stage 2: 32 x 16; twice as many tiles, for balance on small problems).
  * STAGE1_LDS / STAGE2_LDS: LDS-tiled (64 x 64 tiles per work group, four wavefronts sharing
  * every K chunk through LDS; stage 2 splits long K into slices summed by a reduction launch).
  * The NARROW and LDS bits of one stage exclude each other.  Results agree to rounding. */

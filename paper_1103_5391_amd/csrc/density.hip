@@ -174,23 +174,9 @@ __global__ __launch_bounds__(64 * kDensWaves, 2) void k_density(
     }
 }
 
-// Sum over the work group (NT threads) of one double, returned to every thread: shuffles
-// inside each wavefront, then the wave sums in a fixed order.  red: NT / 64 doubles.
-template <int NT>
-__device__ __forceinline__ double wg_sum(double v, double* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += red[w];
-    __syncthreads();
-    return s;
-}
-
-// As wg_sum, with one barrier: the caller keeps `red` untouched until a further barrier has
-// passed (so every thread has read the previous sum).
+// Sum over the work group (NT threads) of one double, returned to every thread: shuffles inside each
+// wavefront, then the wave sums in a fixed order.  red: NT / 64 doubles, which the caller keeps
+// untouched until a further barrier has passed (so every thread has read the sum).
 template <int NT>
 __device__ __forceinline__ double wg_sum1(double v, double* red) {
 #pragma unroll
@@ -840,7 +826,8 @@ __device__ __forceinline__ bool big_cluster(const double* __restrict__ lam, int 
     return false;
 }
 
-// The same in global memory (bound by memory instructions): U and L packed, Z row-major.
+// Factors and vectors of an inverse iteration in global memory (as InvLds in LDS; bound by memory
+// instructions): U and L packed, Z row-major.
 struct InvGlobal {
     typedef double f4u __attribute__((ext_vector_type(4), aligned(8)));
     typedef double f2u __attribute__((ext_vector_type(2), aligned(8)));
@@ -961,8 +948,9 @@ __device__ __forceinline__ void inverse_iteration(const M& m, int d, int s, int 
 }
 
 // Inverse iteration of one work item (blk, j0): the clusters (single eigenvalues mostly) that begin
-// at j0 .. j0 + vec_cols(d) - 1, in LDS where they fit, else in the sector's global scratch; nothing
-// for sectors that QL takes.  Z row-major.  cap: doubles of LDS for the columns.
+// at j0 .. j0 + vec_cols(d) - 1, in LDS where they fit into cap doubles (what the rows of the handle's
+// largest sector leave), else in the sector's global scratch; nothing for sectors that QL takes.
+// Z row-major.
 // Bound by the dependent chains of the factorisation (18 us for 148 states) and of the three
 // substitutions after it (9 us each): 55 us.  In the reduction's work group, a thread per eigenvalue of
 // a sector and everything in global memory, this took 150 us, bound by one CU's memory

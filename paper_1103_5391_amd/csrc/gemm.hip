@@ -12,9 +12,9 @@
 // symmetry blocks in two stages, each one launch over a list of output tiles:
 //   stage 1  T_b  = X_b R_b        right products, X_b = [Re; Im] planes of the source block
 //   stage 2  Y_b' = T0 + Acat Bcat left products summed over all terms entering the block
-// Stage 1 gives each tile of 32 x 64 (or 32 x 32: twice the tiles, for better balance on small
-// problems) to a work group of one wavefront (single-wave work groups let the dispatcher
-// balance the compute units at the end of the launch).  In stage 2 a work group of four
+// Stage 1 gives each tile of 16 rows of both planes x 64 columns (or x 32: twice the tiles, for better
+// balance on small problems) to a work group of one wavefront (single-wave work groups let the
+// dispatcher balance the compute units at the end of the launch).  In stage 2 a work group of four
 // wavefronts owns one 32 x 32 tile (or 32 x 16, narrow) and deals its K chunks round-robin to the
 // waves; the four partial tiles are summed in LDS in a fixed order (deterministic, no atomics).
 //
@@ -640,7 +640,7 @@ hipError_t launch_stage2_mr(const S2Block* blks, const XChunk* xch, const Tile* 
 }
 
 // prec: 0 FP64, 1 FP32, 2 BF16x3, 3 BF16x6 (the operator buffers and workspace must match);
-// narrow: the tiles are kTile x kTile1NN (else kTile x kTile1N)
+// narrow: the tiles have kTile1NN columns (else kTile1N)
 hipError_t launch_stage1(int prec, int narrow, const S1Block* blks, const Tile* tiles, int ntiles,
                          const ProbPtrs* probs, ProbPtrs single, hipStream_t st) {
     switch (prec) {

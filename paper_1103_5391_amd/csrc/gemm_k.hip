@@ -1,8 +1,10 @@
 // K-split FP64 block products of H_sb.psi on gfx950 (the work lists and layouts are described
 // with KPack in internal.hpp).
 //
-// Why: measured on this part, v_mfma_f64_16x16x4f64 sustains about 44 TFLOP/s, while
-// v_mfma_f64_4x4x4_4b_f64 sustains about 69 TFLOP/s.  The 4x4x4 form (four blocks) takes, in
+// Why: an early probe gave v_mfma_f64_16x16x4f64 about 44 TFLOP/s and v_mfma_f64_4x4x4_4b_f64
+// about 69; it copied the first one's accumulators between register files at every step, and
+// without that they sustain 77.7 and 73, so what is left is the layout: no operand is broadcast, and
+// no LDS is needed.  The 4x4x4 form (four blocks) takes, in
 // lane l = 16 k' + 4 b + x, A(row x, k') and B(k', column x) of block b, and returns D(row t,
 // column j) of block b in lane 16 t + 4 b + j.  Taking the four blocks as four slices of a
 // 16-deep K chunk (k = 4 b + k'), one instruction multiplies a 4 x 16 piece of A by a 16 x 4

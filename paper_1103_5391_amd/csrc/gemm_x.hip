@@ -7,9 +7,9 @@
 //   stage 2  Y_b' = T0 + Acat Bcat   64 x 32 tiles, waves 2 x 2 of 32 x 16; tiles with long K
 //                                    run as two slices that add into a zeroed output
 //
-// Why this MFMA: on this part v_mfma_f64_16x16x4f64 sustains about 44 TFLOP/s (about 105
-// clocks per instruction per SIMD), while v_mfma_f64_4x4x4_4b_f64 sustains about 69 TFLOP/s
-// (measured with register operands and several independent accumulators per SIMD).  The 4x4x4
+// This MFMA was taken on an early probe (44 TFLOP/s for v_mfma_f64_16x16x4f64, 69 for
+// v_mfma_f64_4x4x4_4b_f64) that copied the first one's accumulators between register files at every
+// step; without that they sustain 77.7 and 73.  The 4x4x4
 // form needs more operand registers per flop, so the operands come from LDS: a work group's
 // tile is four waves' worth, and per 16-deep chunk the work group loads 16 KB (stage 1) or 12 KB
 // (stage 2) with 16-byte loads.

@@ -313,8 +313,11 @@ struct DensIn {            // target vectors (device, 2n doubles each) and their
     double w[kDensMaxVec];
 };
 // Inverse iteration: LDS of a work group (3 values per row of the largest sector, then six per row
-// and column), and the columns whose clusters it takes: as many as fit beside a sector's own rows,
-// so that two work groups share a CU.
+// and column; two work groups share a CU), and the columns whose clusters it takes: as many as
+// would fit beside a sector's own rows.  Where that is tight and the handle has a larger sector, or
+// a cluster runs past the range, the columns do not fit and work in global memory: all those of the
+// sectors of 94 and 118 states of the 1000-state ladder (848 of 4000), 71 us where the
+// kernel takes 55 with every column in LDS.
 constexpr int kVecLds = 64 << 10, kVecCols = 16;
 __host__ __device__ constexpr int vec_cols(int d) {
     const int fit = (kVecLds / 8 - 3 * d - 1) / (6 * (d > 0 ? d : 1));
@@ -329,7 +332,7 @@ constexpr size_t dens_tri(int64_t n, int nb) {
 constexpr int kEvalCols = 8;        // eigenvalues of a work group
 constexpr int kDensRegMaxDim = 160;   // sectors up to this size take the register-resident kernel
 
-// One 32 x 32 tile of a complex product C = alpha A B (+ C if acc) (FP64; complex operands
+// One kZTile x kZTile tile of a complex product C = alpha A B (+ C if acc) (FP64; complex operands
 // have real parts at off and imaginary parts at off + im).  A modes: 0 complex column-major,
 // A(i, k) at i + k lda; 1 conjugate transpose of a complex column-major X, A(i, k) =
 // conj(X(k, i)) at k + i lda; 2 real column-major; 3 real transpose, A(i, k) = X(k, i) at

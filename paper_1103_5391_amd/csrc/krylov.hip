@@ -8,7 +8,8 @@
 //
 // Orthogonalisation: full reorthogonalisation by two classical Gram-Schmidt sweeps against
 // the whole basis, with the second sweep of each new vector delayed into the next iteration so
-// that one iteration is one reduction pass, a small totals kernel and one update pass.  Slot j
+// that one iteration is one reduction pass, a small totals kernel where there are many partial
+// rows (kDirectRows) and one update pass.  Slot j
 // holds u1, the new vector after its first sweep, when iteration j starts; the block products
 // are applied to that slot as it is (w_raw = H u1).  Then
 //   reduce    a = V^H u1, b = V^H w_raw (slots c < j), c = u1^H w_raw, d = ||u1||^2,
@@ -160,25 +161,6 @@ __device__ __forceinline__ void block_partials(const double (&vals)[NV], double*
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kVecThreads / 64; ++w) s += red[v][w];
-        part[(int64_t)v * kVecMaxBlocks + lb] = s;
-    }
-}
-
-// As block_partials for NV values, then zeros for values NV .. ROW-1.
-template <int NV, int ROW>
-__device__ __forceinline__ void block_partials_row(const double (&vals)[NV > 0 ? NV : 1],
-                                                   double* part, int lb) {
-    __shared__ double red[NV > 0 ? NV : 1][kVecThreads / 64];
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) red[v][wave] = wave_sum(vals[v]);   // every lane holds the sum
-    __syncthreads();
-    for (int v = threadIdx.x; v < ROW; v += blockDim.x) {
-        double s = 0.0;
-        if (v < NV) {
-#pragma unroll
-            for (int w = 0; w < kVecThreads / 64; ++w) s += red[v][w];
-        }
         part[(int64_t)v * kVecMaxBlocks + lb] = s;
     }
 }
