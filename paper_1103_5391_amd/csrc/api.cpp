@@ -542,8 +542,7 @@ int hip_fail(dmrg_handle h, hipError_t e, const char* where) {
 
 // Workspace r of a handle sized for kdim basis vectors (the stage-1 intermediate of workspace 0
 // is allocated by dmrg_create; the padding rows of every intermediate are read, times zero factors:
-// stage 1 writes them to whole 16-deep chunks, not always to 32-deep ones, so intermediates start
-// zeroed).
+// not every stage 1 writes them in every arithmetic (S1Block), so intermediates start zeroed).
 int ensure_workspace(dmrg_handle h, int kdim, int r = 0) {
     BudgetScope bs(&h->budget);
     Workspace& W = h->ws[r];
@@ -1498,8 +1497,8 @@ int dmrg_create(const dmrg_problem* problem, void* stream, dmrg_handle* out) {
                          lr, ns, P.pk16.x2, P.pk16.xz, P.kf, h->stream);
     }
     if (e == hipSuccess) e = h->ws[0].dT.alloc(sizeof(double) * (size_t)P.T_size);
-    // padding rows of the stage-1 workspace are read, times zero factors, and not all are written
-    // by every stage 1 (32-deep chunks): they must be finite, so the workspace starts zeroed
+    // the padding rows of the stage-1 workspace are read, times zero factors, and not every stage 1
+    // writes them in every arithmetic: they must be finite, so the workspace starts zeroed
     if (e == hipSuccess)
         e = hipMemsetAsync(h->ws[0].dT.p, 0, sizeof(double) * (size_t)P.T_size, h->stream);
     if (e == hipSuccess && own_scratch(P) > 0) e = h->dNoAlloc.alloc(own_scratch(P));

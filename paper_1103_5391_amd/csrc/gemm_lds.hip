@@ -14,6 +14,8 @@
 // slices run by separate work groups: each slice writes a partial tile, and a reduction launch
 // adds T0 and the partial tiles of a tile in slice order (deterministic, no atomics).  Tiles
 // with a single slice write y directly.
+#include <type_traits>
+
 #include "mfma.hpp"
 
 namespace dmrg {
@@ -153,13 +155,14 @@ __global__ __launch_bounds__(256, 3) void stage1_lds(const S1Block* __restrict__
             for (int v = 0; v < 4; ++v) {
                 const int m = it.m0 + 32 * wm + 16 * mi + P::row(g, v);
                 if (m < B.M) {
-                    const int pl = m >= tv.split, k = m - pl * tv.split;
-                    ws_t* __restrict__ plane = T + tv.off + pl * tv.poff;
-                    plane[tpos<ws_t>(tv.ld, n, k)] = (ws_t)acc[mi][nj][v];
-                    if (k == tv.split - 1) pad_rows<P>(plane, tv, n);
+                    const int pl = m >= tv.split;
+                    T[tv.off + pl * tv.poff + tpos<ws_t>(tv.ld, n, m - pl * tv.split)] =
+                        (ws_t)acc[mi][nj][v];
                 }
             }
         }
+    static_assert(kLTile == 64, "the rows and columns that pad_rows takes");
+    if constexpr (std::is_same<P, PF64>::value) pad_rows<256>(T, tv, it.m0, it.n0, B.N);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -263,16 +263,15 @@ __global__ __launch_bounds__(kXT, 2) void stage1x(const S1Block* __restrict__ bl
     for (int s = 0; s < 4; ++s) {
         const int m = tl.m0 + 16 * s + 4 * b + t;
         if (m >= B.M) continue;
-        const int pl = m >= tv.split, k = m - pl * tv.split;
-        double* __restrict__ plane = T + tv.off + pl * tv.poff;
+        const int pl = m >= tv.split;
+        const int64_t pbase = tv.off + pl * tv.poff;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             const int n = tl.n0 + 16 * wave + 4 * cb + j;
-            if (n >= B.N) continue;
-            plane[tpos<double>(tv.ld, n, k)] = acc[s][cb];
-            if (k == tv.split - 1) pad_rows<PF64>(plane, tv, n);
+            if (n < B.N) T[pbase + tpos<double>(tv.ld, n, m - pl * tv.split)] = acc[s][cb];
         }
     }
+    pad_rows<kXT>(T, tv, tl.m0, tl.n0, B.N);
 }
 
 // ---------------------------------------------------------------------------------------

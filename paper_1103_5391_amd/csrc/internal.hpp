@@ -69,9 +69,9 @@ constexpr int kPanel = 16;                        // rows (columns) per packed p
 //        columns (N rounded up), in a panel 16-deep K chunks (rows, d rounded up) of
 //        [unit][16 columns][16 / element size]: a 16-byte unit holds consecutive rows of one
 //        column (tpos in mfma.hpp).  View: ld = elements of a panel, poff = of a plane.  The
-//        padding rows are read, times zero factors, and hold zeros: every stage 1 writes those
-//        up to whole 16-deep chunks, the LDS-tiled one also the rest of a 32-deep chunk, which
-//        for the register-tiled one stays as the workspace was cleared for the arithmetic
+//        padding rows are read, times zero factors, and hold zeros: in FP64, where the K-split
+//        family shares the workspace in a layout of its own, every stage 1 writes them; in the
+//        other arithmetics they may stay as the workspace was cleared for the arithmetic
 struct S1Block {
     int32_t M, K, N, prob;
     int32_t nch, pad;   // K chunks of the packed factor

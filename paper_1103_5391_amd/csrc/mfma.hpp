@@ -158,12 +158,23 @@ __device__ __forceinline__ int64_t tpos(int ld, int col, int k) {
     return (int64_t)(col >> 4) * ld + k / U * (16 * U) + (col & 15) * U + (k & (U - 1));
 }
 
-// Zeros in the padding rows of one column of a plane, by the lane that stores the column's last row:
-// stage 2 multiplies them with zero factors, and what another family's layout, or a vector of NaN,
-// left there need not be finite.
-template <class P>
-__device__ __forceinline__ void pad_rows(typename P::ws_t* plane, const View& tv, int col) {
-    for (int k = tv.split; k % P::CK != 0; ++k) plane[tpos<typename P::ws_t>(tv.ld, col, k)] = 0;
+// FP64: zeros in the padding rows of the columns n0 .. n0 + 63 (< N), by the work group (NT threads)
+// whose 64 rows m0 .. hold a plane's last one: stage 2 multiplies them with zero factors, and what the
+// K-split family's layout (FP64 only) or a vector of NaN left there need not be finite.  Stage 1
+// LDS-tiled and LDS-staged without and with it: 1000-state ladder 38.0 -> 38.6 and 35.1 -> 35.6 us,
+// 400-state chain 8.3 -> 8.6 and 7.8 -> 8.2; by the lanes that store a column's last row 40.8
+// and 40.5, 9.7 and 9.9.
+template <int NT>
+__device__ __forceinline__ void pad_rows(double* __restrict__ T, const View& tv, int m0, int n0, int N) {
+    const int pad = (kChunk - tv.split % kChunk) % kChunk;
+    for (int pl = 0; pl < 2; ++pl) {
+        const int last = (pl + 1) * tv.split - 1;
+        if (last < m0 || last >= m0 + 64) continue;
+        for (int t = threadIdx.x; t < 64 * pad; t += NT) {
+            const int n = n0 + (t & 63);
+            if (n < N) T[tv.off + pl * tv.poff + tpos<double>(tv.ld, n, tv.split + (t >> 6))] = 0;
+        }
+    }
 }
 
 // The lane's data values k = koff(g, t) of a chunk of the workspace, base at the lane's column in
