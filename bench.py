@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0
 MEASURED_TRAFFIC = {
     "workload": "ladder16_m1000",
     "source": "paper_1103_5391_amd/csrc/gemm.hip",
-    "source_sha256": "15a57827025a257a025bdf4d73d88b33fa01b7de3e6bc312809dde79b4d6993c",
-    "bytes": {"stage2<PF64, 1, 4>": 84.82e6 + 5.01e6, "stage1<PF64, 2>": 29.68e6 + 46.71e6},
+    "source_sha256": "b924798113809388f413356497ec3bfb72ce4afe0dcab91c4d1d17b43dff3eb0",
+    "bytes": {"stage2<PF64, 1, 4>": 84.82e6 + 5.02e6, "stage1<PF64, 2>": 29.68e6 + 46.71e6},
     "profile": "profiles/stage2_fp64_ladder16_m1000_kernel_stats.txt",
 }
 

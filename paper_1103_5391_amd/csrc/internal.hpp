@@ -315,9 +315,8 @@ struct DensIn {            // target vectors (device, 2n doubles each) and their
 // Inverse iteration: LDS of a work group (3 values per row of the largest sector, then six per row
 // and column; two work groups share a CU), and the columns whose clusters it takes: as many as
 // would fit beside a sector's own rows.  Where that is tight and the handle has a larger sector, or
-// a cluster runs past the range, the columns do not fit and work in global memory: all those of the
-// sectors of 94 and 118 states of the 1000-state ladder (848 of 4000), 71 us where the
-// kernel takes 55 with every column in LDS.
+// a cluster runs past the range, the columns do not fit and work in global memory: of the 1000-state
+// ladder all those of the sectors of 94 and 118 states (848 of 4000).
 constexpr int kVecLds = 64 << 10, kVecCols = 16;
 __host__ __device__ constexpr int vec_cols(int d) {
     const int fit = (kVecLds / 8 - 3 * d - 1) / (6 * (d > 0 ? d : 1));
