@@ -1397,6 +1397,10 @@ __global__ __launch_bounds__(kBackThreads) void k_heig_back(const DBlock* __rest
 // the values of chunk y (kRankChunk values through LDS) that rank before them, and adds the
 // count to rank[g] (integer atomics: the sum does not depend on their order).  rank starts at
 // zero (cleared by k_density).
+// rank_key: what an eigenvalue is ranked by, NaN as the smallest, so that the ranks are a permutation
+// whatever the values are (k_finish uses its own as indices).
+__device__ __forceinline__ double rank_key(double x) { return x != x ? -INFINITY : x; }
+
 constexpr int kRankChunk = 256;
 __global__ __launch_bounds__(256) void k_rank(const double* __restrict__ ev, int ntot,
                                               int* __restrict__ rank) {
@@ -1405,10 +1409,10 @@ __global__ __launch_bounds__(256) void k_rank(const double* __restrict__ ev, int
     const int h0 = blockIdx.y * kRankChunk;
     const int nh = ntot - h0 < kRankChunk ? ntot - h0 : kRankChunk;
     if (nh <= 0) return;
-    for (int t = threadIdx.x; t < nh; t += blockDim.x) sv[t] = ev[h0 + t];
+    for (int t = threadIdx.x; t < nh; t += blockDim.x) sv[t] = rank_key(ev[h0 + t]);
     __syncthreads();
     if (g >= ntot) return;
-    const double x = ev[g];
+    const double x = rank_key(ev[g]);
     int r = 0;
     for (int t = 0; t < nh; ++t) {
         const double y = sv[t];
@@ -1432,16 +1436,16 @@ __global__ __launch_bounds__(256) void k_finish(const DBlock* __restrict__ blks,
     const DBlock B = blks[blockIdx.x];
     const int d = B.d, tid = threadIdx.x;
     __shared__ double scratch[kVecThreads];
-    __shared__ double se[kDensMaxDim];                  // the sector's eigenvalues
+    __shared__ double se[kDensMaxDim];                  // what the sector's eigenvalues rank by
     __shared__ int src_of[kDensMaxDim];                 // output position r <- eigenvector i
-    for (int i = tid; i < d; i += blockDim.x) se[i] = ev[B.eoff + i];
+    for (int i = tid; i < d; i += blockDim.x) se[i] = rank_key(ev[B.eoff + i]);
     __syncthreads();
     double all = 0.0, ksum = 0.0, kc = 0.0;
     const int ys = blockIdx.y, ny = gridDim.y;          // this work group's share of the copy
     for (int i = tid; i < d; i += blockDim.x) {
-        const double x = se[i];
+        const double key = se[i], x = ev[B.eoff + i];
         int r = 0;
-        for (int h = 0; h < d; ++h) r += (se[h] > x) || (se[h] == x && h < i);
+        for (int h = 0; h < d; ++h) r += (se[h] > key) || (se[h] == key && h < i);
         if (ys == 0) evals[B.eoff + r] = x;
         src_of[r] = i;
         all += x;

@@ -215,3 +215,43 @@ def test_density_and_expectation_share_their_results_area(env, first):
         else:
             assert abs(h.expect_local(terms(1.0), xd) - want) <= 1e-12 * max(1.0, abs(want))
     h.destroy()
+
+
+def _truncate(torch, L, h, mats, weights, keep):
+    """density_truncate of the targets whose blocks are mats[l][b] (complex): per block the
+    eigenvalues and eigenvectors, and the states kept."""
+    planes = lambda M: np.concatenate([m.real.ravel(order="F") for m in M] + [m.imag.ravel(order="F") for m in M])
+    rows = [len(m) for m in mats[0]]
+    ev = torch.zeros(sum(rows), dtype=torch.float64, device="cuda")
+    vc = torch.zeros(sum(2 * r * r for r in rows), dtype=torch.float64, device="cuda")
+    vecs = [torch.from_numpy(planes(M)).to("cuda") for M in mats]
+    kept, err = h.density_truncate(vecs, np.array(weights), keep, ev, vc)
+    ev, vc, out, eo, vo = ev.cpu().numpy(), vc.cpu().numpy(), [], 0, 0
+    for r in rows:
+        out.append((ev[eo:eo + r], (vc[vo:vo + r * r] + 1j * vc[vo + r * r:vo + 2 * r * r]).reshape(r, r).T))
+        eo += r
+        vo += 2 * r * r
+    return out, kept, err
+
+
+def test_density_with_nan(env):
+    """NaN in one sector of a target, whose own results mean nothing: the other sectors' are right (1e-12
+    of their largest eigenvalue) and every state kept is counted once."""
+    torch, L = env
+    dims = (12, 40, 30, 170)
+    h = L.dmrg_create(_problem((dims, dims[::-1])))
+    rng = np.random.default_rng(I.SEED_BASE + 30)
+    mats = [rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)) for d in dims]
+    for nan in (0, 1, 3):
+        M = [m.copy() for m in mats]
+        M[nan][-1, 0] = np.nan
+        keep = 100 if nan == 3 else 200
+        out, kept, _ = _truncate(torch, L, h, [M], [1.0], keep)
+        assert sum(kept) == keep and all(0 <= k <= d for k, d in zip(kept, dims))
+        for b, (w, U) in enumerate(out):
+            if b == nan:
+                continue
+            lam = np.linalg.eigvalsh(mats[b] @ mats[b].conj().T)[::-1]
+            assert np.max(np.abs(w - lam)) <= 1e-12 * lam[0]
+            assert np.linalg.norm(U.conj().T @ U - np.eye(len(w))) <= 1e-11 * len(w)
+    h.destroy()
