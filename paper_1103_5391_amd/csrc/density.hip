@@ -862,15 +862,17 @@ struct InvGlobal {
 // all, the vector rescaled between them).  Then every cluster takes its members in order, all
 // clusters in step: each vector is orthogonalised against the cluster's earlier vectors (modified
 // Gram-Schmidt, the lanes sharing the rows) before and after every further solve, and normalised.
+// dg, e: T scaled by 2^-ex to |T| in [0.5, 1), so that neither a pivot's reciprocal nor the square
+// of a solution leaves the range (they did below |T| = 1e-138, and for T = 0); lam, tn: of T itself.
 // sc: per column the factor its vector has still to be multiplied with.
 template <class M>
 __device__ __forceinline__ void inverse_iteration(const M& m, int d, int s, int nc,
                                                   const double* __restrict__ dg,
                                                   const double* __restrict__ e,
-                                                  const double* __restrict__ lam, double tn,
+                                                  const double* __restrict__ lam, double tn, int ex,
                                                   double& sc) {
     const int lane = threadIdx.x & 63, l = lane;
-    const double tiny = 2.220446049250313e-16 * tn;
+    const double tiny = 2.220446049250313e-16 * __builtin_amdgcn_ldexp(tn, -ex);
     auto sync = [] {                                    // the lanes' stores before the others' loads
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         __builtin_amdgcn_wave_barrier();
@@ -884,7 +886,7 @@ __device__ __forceinline__ void inverse_iteration(const M& m, int d, int s, int 
     const bool alone = rank == 0 && (j + 1 >= d || first_of_cluster(j + 1));
     sc = 1.0;
     if (l < nc) {
-        const double x = lam[j];
+        const double x = __builtin_amdgcn_ldexp(lam[j], -ex);
         // start vector cos(0.7 i + j), by the recurrence
         // cos(a + (i + 1) b) = 2 cos(b) cos(a + i b) - cos(a + (i - 1) b) (any fixed,
         // generic vector serves; this one costs no call per element)
@@ -968,13 +970,14 @@ __global__ __launch_bounds__(64) void k_vectors(const DBlock* __restrict__ blks,
     double* const lam = lds;
     double* const dg = lds + dmax;
     double* const e = lds + 2 * dmax;
+    const double tn = tnorm[3 * it.blk];
+    const int ex = __builtin_amdgcn_frexp_exp(tn);
     for (int i = lane; i < d; i += 64) {
         lam[i] = ev[B.eoff + i];
-        dg[i] = tri[B.eoff + i];
-        e[i] = tri[ntot + B.eoff + i];
+        dg[i] = __builtin_amdgcn_ldexp(tri[B.eoff + i], -ex);
+        e[i] = __builtin_amdgcn_ldexp(tri[ntot + B.eoff + i], -ex);
     }
     __syncthreads();
-    const double tn = tnorm[3 * it.blk];
     if (big_cluster(lam, d, tn)) return;
     auto start = [&](int j) {                           // the first cluster that begins at j or later
         while (j > 0 && j < d && lam[j] - lam[j - 1] <= kClusterGap * tn) ++j;
@@ -991,14 +994,14 @@ __global__ __launch_bounds__(64) void k_vectors(const DBlock* __restrict__ blks,
     const int per = 64 / nc, ri = lane / nc, c = lane - ri * nc;
     if (6 * d * nc <= cap) {
         const InvLds m{lds + (3 * dmax + 1) / 2 * 2, nc, 6 * nc};
-        inverse_iteration(m, d, s, nc, dg, e, lam, tn, sc);
+        inverse_iteration(m, d, s, nc, dg, e, lam, tn, ex, sc);
         const double f = __shfl(sc, c, 64);
         if (ri < per)
             for (int i = ri; i < d; i += per) Z[(int64_t)i * d + s + c] = m.z(m.at(i, c)) * f;
     } else {
         const InvGlobal m{Z + s, reinterpret_cast<InvGlobal::f4u*>(Sb + 6 * B.aoff) + s,
                           reinterpret_cast<InvGlobal::f2u*>(Sb + 6 * B.aoff + 4 * (int64_t)d * d) + s, d};
-        inverse_iteration(m, d, s, nc, dg, e, lam, tn, sc);
+        inverse_iteration(m, d, s, nc, dg, e, lam, tn, ex, sc);
         const double f = __shfl(sc, c, 64);
         if (ri < per)
             for (int i = ri; i < d; i += per) Z[(int64_t)i * d + s + c] *= f;

@@ -255,3 +255,52 @@ def test_density_with_nan(env):
             assert np.max(np.abs(w - lam)) <= 1e-12 * lam[0]
             assert np.linalg.norm(U.conj().T @ U - np.eye(len(w))) <= 1e-11 * len(w)
     h.destroy()
+
+
+def _check_spectrum(out, rho):
+    """Eigenvalues (1e-12 of the largest), orthonormality and residuals (1e-11 d) of one block against
+    its density matrix, as in the parity tests."""
+    w, U = out
+    d, lam = len(w), np.linalg.eigvalsh(rho)[::-1]
+    top = max(abs(lam[0]), 1e-300)
+    assert np.max(np.abs(w - lam)) <= 1e-12 * top
+    assert np.linalg.norm(U.conj().T @ U - np.eye(d)) <= 1e-11 * d
+    assert np.linalg.norm(rho / top @ U - U * (w / top)) <= 1e-11 * d
+
+
+@pytest.mark.parametrize("dims", [(1, 2, 3, 8), (5, 4, 9, 30), (7, 6, 40, 170)])
+def test_density_with_empty_sectors(env, dims):
+    """Targets with no weight in some sectors: eigenvalues 0 with orthonormal vectors there."""
+    torch, L = env
+    h = L.dmrg_create(_problem((dims, dims[::-1])))
+    rng = np.random.default_rng(I.SEED_BASE + 31)
+    for empty in ((0,), (0, 1), (2,), (0, 1, 2, 3)):
+        M = [np.zeros((d, d), complex) if b in empty else rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))
+             for b, d in enumerate(dims)]
+        out, kept, err = _truncate(torch, L, h, [M], [1.0], sum(dims))
+        assert list(kept) == list(dims)
+        for b, m in enumerate(M):
+            _check_spectrum(out[b], m @ m.conj().T)
+    h.destroy()
+
+
+@pytest.mark.parametrize("size", [1, 4])
+@pytest.mark.parametrize("exponent", [-480, -430, 400])
+def test_density_scaled_by_powers_of_two(env, exponent, size):
+    """Density matrices of norm 2^exponent (isolated eigenvalues, and clusters of four): the eigenvectors'
+    squares and reciprocals stay in range."""
+    torch, L = env
+    dims = (3, 20, 60, 165)
+    h = L.dmrg_create(_problem((dims, dims[::-1])))
+    rng = np.random.default_rng(I.SEED_BASE + 32)
+    M = []
+    for d in dims:
+        q = [np.linalg.qr(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))[0] for _ in range(2)]
+        lam = (1.0 + np.arange(d) // size + 1e-8 * (np.arange(d) % size)) / d
+        M.append((q[0] * np.sqrt(lam)) @ q[1] * 2.0 ** (exponent // 2))
+    out, _, _ = _truncate(torch, L, h, [M], [1.0], 50)
+    for b, m in enumerate(M):
+        w, U = out[b]
+        s = 2.0 ** -(exponent // 2)
+        _check_spectrum((w * s * s, U), (m * s) @ (m * s).conj().T)
+    h.destroy()
