@@ -43,6 +43,9 @@ __device__ __forceinline__ dv2 cmul(dv2 a, dv2 b) {
     return (dv2){a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
 __device__ __forceinline__ dv2 cconj(dv2 a) { return (dv2){a.x, -a.y}; }
+__device__ __forceinline__ dv2 scale2(dv2 a, int ex) {
+    return (dv2){__builtin_amdgcn_ldexp(a.x, ex), __builtin_amdgcn_ldexp(a.y, ex)};
+}
 // 1 / sqrt(x), x > 0: the hardware reciprocal square root and two Newton steps
 __device__ __forceinline__ double rsqrt_nr(double x) {
     double y = __builtin_amdgcn_rsq(x);
@@ -208,6 +211,13 @@ __device__ __forceinline__ dv2 wg_sum1c(dv2 v, double* red) {
     return s;
 }
 
+// A column of the reduction whose squared norm is below kTinySquare (the smallest normal number) counts
+// as zero: its reciprocal would not be finite.  Where a density matrix has low rank and its rounding
+// errors have a structure (equal amplitudes), each step's column is rounding of the one before it,
+// and reaches such norms within ten steps.  A matrix whose own norm is beyond 2^+-kScaleFrom is
+// scaled by a power of two first, so that such columns are rounding in it.
+constexpr double kTinySquare = 2.2250738585072014e-308;
+constexpr int kScaleFrom = 300;
 constexpr int kEigThreads = 512;    // threads of a reduction or QL work group
 constexpr int kEvalThreads = 256;   // threads of an eigenvalue work group, 32 per eigenvalue
 constexpr int kQlMaxSweeps = 64;    // QL sweeps per eigenvalue at most
@@ -371,7 +381,7 @@ __device__ __forceinline__ dv2 cmsc(dv2 acc, dv2 a, dv2 b) {
 // columns wholly above k (those before (k + 1) div 32) are skipped, the column sums' DPP
 // additions included.
 template <int S>
-__device__ __forceinline__ void hh_regs(const int d, dv2* __restrict__ a, double* __restrict__ dg,
+__device__ __forceinline__ void hh_regs(const int d, const int ex0, dv2* __restrict__ a, double* __restrict__ dg,
                                         double* __restrict__ e, dv2* __restrict__ vs0,
                                         dv2* __restrict__ vs1, dv2* __restrict__ ws,
                                         dv2* __restrict__ ps, dv2* __restrict__ cs,
@@ -387,6 +397,7 @@ __device__ __forceinline__ void hh_regs(const int d, dv2* __restrict__ a, double
             const int i = 32 * I + r, j = 32 * J + c;
             dv2 x = z;
             if (i < d && (I > J || r >= c)) x = a[(int64_t)j * d + i];
+            if (ex0 != 0) x = scale2(x, -ex0);
             m[I * (I + 1) / 2 + J] = x;
         }
     for (int k = 0; k + 1 < d; ++k) {
@@ -420,10 +431,11 @@ __device__ __forceinline__ void hh_regs(const int d, dv2* __restrict__ a, double
             // |x below k + 1|^2 over the half-wave (into its lane 31), and alpha = x_{k+1}
             const double xn2 = readlane_d(half_sum(part), h + 31);
             const dv2 al = (dv2){readlane_d(x1.x, h + (i1 & 31)), readlane_d(x1.y, h + (i1 & 31))};
+            const double x2 = al.x * al.x + al.y * al.y + xn2;
             dv2 sc = z, tau = z;
             double beta = al.x;
-            if (!(xn2 == 0.0 && al.y == 0.0)) {
-                beta = -copysign(sqrt(al.x * al.x + al.y * al.y + xn2), al.x);
+            if (!(xn2 == 0.0 && al.y == 0.0) && !(x2 < kTinySquare)) {
+                beta = -copysign(sqrt(x2), al.x);
                 const double rb = recip2(beta);
                 tau = (dv2){(beta - al.x) * rb, -al.y * rb};
                 const dv2 den = (dv2){al.x - beta, al.y};               // 1 / (alpha - beta)
@@ -560,24 +572,43 @@ __device__ __forceinline__ int64_t sturm_off(int64_t eoff, int blk) {
 // the subdiagonal (and a final 0) to tri + ntot, at blk.eoff; the matrix scaled by a power of two to
 // |T| in [0.5, 1) (Gershgorin's bound) to rec, as the Sturm counts read it; and |T| and the ends of the
 // Gershgorin interval to tnb.
-// NT threads, sectors of at most MAXD states; REG: by hh_regs (NT = kEigThreadsR).
+// NT threads, sectors of at most MAXD states; REG: by hh_regs (NT = kEigThreadsR).  psd: rho is positive
+// semidefinite.
 template <int NT, int MAXD, bool REG>
-__device__ __forceinline__ void heig(const DBlock B, dv2* __restrict__ A, double* __restrict__ tri,
+__device__ __forceinline__ void heig(const DBlock B, const int psd, dv2* __restrict__ A, double* __restrict__ tri,
                                      int ntot, double* __restrict__ rec, double* __restrict__ tnb) {
     const int d = B.d, tid = threadIdx.x;
     dv2* __restrict__ a = A + B.aoff;
     __shared__ double dg[MAXD], e[MAXD];
     __shared__ dv2 vv[MAXD], ww[MAXD], vv1[MAXD], ww1[MAXD];
+    __shared__ double s_lo[NT / 64], s_hi[NT / 64];
+    // the scale, from the diagonal: no entry of a positive semidefinite matrix exceeds its largest
+    int ex0 = 0;
+    if (psd) {
+        double top = 0.0;
+        for (int i = tid; i < d; i += NT) top = fmax(top, a[(int64_t)i * d + i].x);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+        if ((tid & 63) == 0) s_lo[tid >> 6] = top;
+        __syncthreads();
+        for (int w = 0; w < NT / 64; ++w) top = fmax(top, s_lo[w]);
+        ex0 = __builtin_amdgcn_frexp_exp(top);
+        if (abs(ex0) < kScaleFrom) ex0 = 0;
+    }
     if constexpr (REG) {
         static_assert(NT == kEigThreadsR && MAXD % 32 == 0, "32 x 32 thread grid");
         __shared__ dv2 rp[2 * (NT / 64) * MAXD];        // row sums of the half-waves
         __shared__ dv2 ws[MAXD], s_tau;
-        hh_regs<MAXD / 32>(d, a, dg, e, vv, vv1, ws, ww, ww1, rp, &s_tau);
+        hh_regs<MAXD / 32>(d, ex0, a, dg, e, vv, vv1, ws, ww, ww1, rp, &s_tau);
     } else {
     __shared__ dv2 pp[NT];
     __shared__ double red[3 * NT / 64];
     __shared__ dv2 s_alpha;                             // alpha of the current reflector
     __shared__ dv2 tm[kHhLdsDim * kHhLdsDim];          // trailing matrix once it fits
+    if (ex0 != 0) {
+        for (int64_t t = tid; t < (int64_t)d * d; t += NT) a[t] = scale2(a[t], -ex0);
+        handover_barrier();
+    }
     // The update of step k is applied lazily, inside step k + 1's pass over the trailing
     // matrix, which also forms that step's product B v: one read and one write of the trailing
     // matrix per step.  The pending update is kept as (v, w0, al2) with w = w0 + al2 v, in one
@@ -623,10 +654,11 @@ __device__ __forceinline__ void heig(const DBlock B, dv2* __restrict__ A, double
         // this read after wave 0's store would otherwise form its reflector from alpha = 1.
         // s_alpha is next written in the following step, after the barriers below.
         const dv2 al = s_alpha;
+        const double x2 = al.x * al.x + al.y * al.y + xn2;
         dv2 tau = (dv2){0.0, 0.0}, sc = (dv2){0.0, 0.0};
         double beta = al.x;
-        if (!(xn2 == 0.0 && al.y == 0.0)) {
-            beta = -copysign(sqrt(al.x * al.x + al.y * al.y + xn2), al.x);
+        if (!(xn2 == 0.0 && al.y == 0.0) && !(x2 < kTinySquare)) {
+            beta = -copysign(sqrt(x2), al.x);
             tau = (dv2){(beta - al.x) / beta, -al.y / beta};
             const dv2 den = (dv2){al.x - beta, al.y};                   // 1 / (alpha - beta)
             const double q = den.x * den.x + den.y * den.y;
@@ -708,8 +740,14 @@ __device__ __forceinline__ void heig(const DBlock B, dv2* __restrict__ A, double
         }
     }
     }
-    __shared__ double s_lo[NT / 64], s_hi[NT / 64];
     __syncthreads();
+    if (ex0 != 0) {
+        for (int i = tid; i < d; i += NT) {
+            dg[i] = __builtin_amdgcn_ldexp(dg[i], ex0);
+            e[i] = __builtin_amdgcn_ldexp(e[i], ex0);
+        }
+        __syncthreads();
+    }
     // rows beyond d repeat row 0
     double lo = dg[0] - (d > 1 ? fabs(e[0]) : 0.0), hi = dg[0] + (d > 1 ? fabs(e[0]) : 0.0);
     for (int i = tid; i < d; i += NT) {
@@ -753,25 +791,25 @@ __device__ __forceinline__ void heig(const DBlock B, dv2* __restrict__ A, double
 
 // sel: the sectors of the launch, one per work group
 __global__ __launch_bounds__(kEigThreads) void k_heig(const DBlock* __restrict__ blks,
-                                                      const int* __restrict__ sel,
+                                                      const int* __restrict__ sel, int psd,
                                                       dv2* __restrict__ A,
                                                       double* __restrict__ tri, int ntot,
                                                       double* __restrict__ rec,
                                                       double* __restrict__ tnorm) {
     const int b = sel[blockIdx.x];
-    heig<kEigThreads, kDensMaxDim, false>(blks[b], A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
+    heig<kEigThreads, kDensMaxDim, false>(blks[b], psd, A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
          tnorm + 3 * b);
 }
 
 // The same for sectors of at most kRegMaxDim states, with the matrix in registers.
 __global__ __launch_bounds__(kEigThreadsR) void k_heig_r(const DBlock* __restrict__ blks,
-                                                         const int* __restrict__ sel,
+                                                         const int* __restrict__ sel, int psd,
                                                          dv2* __restrict__ A,
                                                          double* __restrict__ tri, int ntot,
                                                          double* __restrict__ rec,
                                                          double* __restrict__ tnorm) {
     const int b = sel[blockIdx.x];
-    heig<kEigThreadsR, kRegMaxDim, true>(blks[b], A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
+    heig<kEigThreadsR, kRegMaxDim, true>(blks[b], psd, A, tri, ntot, rec + sturm_off(blks[b].eoff, b),
          tnorm + 3 * b);
 }
 
@@ -1496,12 +1534,14 @@ hipError_t launch_density(const DBlock* blks, int nblk, const int* sel, int nreg
                        static_cast<dv2*>(A), fail, nblk, kept, ntot);
     double* const rec = tri + 2 * (int64_t)ntot;         // with room for every sector's padding
     double* const tnorm = rec + 2 * ((int64_t)ntot + kSturmRun * nblk);
+    int psd = 1;                                        // no negative weight
+    for (int l = 0; l < nv; ++l) psd &= in.w[l] >= 0.0;
     // sel: first the nreg sectors of the register-resident kernel, then the others
     if (nreg > 0)
         hipLaunchKernelGGL(k_heig_r, dim3(nreg), dim3(kEigThreadsR), 0, s, blks, sel,
-                           static_cast<dv2*>(A), tri, ntot, rec, tnorm);
+                           psd, static_cast<dv2*>(A), tri, ntot, rec, tnorm);
     if (nblk > nreg)
-        hipLaunchKernelGGL(k_heig, dim3(nblk - nreg), dim3(kEigThreads), 0, s, blks, sel + nreg,
+        hipLaunchKernelGGL(k_heig, dim3(nblk - nreg), dim3(kEigThreads), 0, s, blks, sel + nreg, psd,
                            static_cast<dv2*>(A), tri, ntot, rec, tnorm);
     hipLaunchKernelGGL(k_eval_t, dim3(neval + nblk * nbt), dim3(kEvalThreads), 0, s, blks, nblk,
                        evals_of, neval, rec, ev, tnorm, static_cast<const dv2*>(A),

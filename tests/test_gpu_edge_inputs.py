@@ -304,3 +304,20 @@ def test_density_scaled_by_powers_of_two(env, exponent, size):
         s = 2.0 ** -(exponent // 2)
         _check_spectrum((w * s * s, U), (m * s) @ (m * s).conj().T)
     h.destroy()
+
+
+@pytest.mark.parametrize("exponent", [-560, -500, 0])
+def test_density_of_tiny_norm(env, exponent):
+    """Density matrices of norm 2^exponent: the squares of a column leave the range of doubles (isolated
+    eigenvalues; sectors that the reduction holds in registers, and a larger one)."""
+    torch, L = env
+    dims = (2, 20, 60, 165)
+    h = L.dmrg_create(_problem((dims, dims[::-1])))
+    rng = np.random.default_rng(I.SEED_BASE + 33)
+    s = 2.0 ** (exponent // 2)
+    M = [(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d))) * s for d in dims]
+    out, _, _ = _truncate(torch, L, h, [M], [1.0], 50)
+    for b, m in enumerate(M):
+        w, U = out[b]
+        _check_spectrum((w / s / s, U), (m / s) @ (m / s).conj().T)
+    h.destroy()
