@@ -1051,6 +1051,11 @@ __global__ __launch_bounds__(64) void k_vectors(const DBlock* __restrict__ blks,
 // others return).  Wavefront 0 runs the sweep recurrence (its first lane) and lists the rotations of
 // the next sweep while the other wavefronts apply the current one to their rows (two rotation
 // lists in LDS).  A sweep count above the limit sets bit 0 of fail[blk].
+// T is scaled by a power of two to |T| in [0.5, 1), so that the squares of its entries stay in range.  An
+// off-diagonal entry is negligible beside its neighbours on the diagonal, or below eps |T|: the
+// reduction has moved the eigenvalues by as much, and where a block is all rounding (low rank,
+// spectra over many decades) sweeps through larger entries renew it at that size, so that the first
+// test alone was never met and finite matrices were refused.
 __global__ __launch_bounds__(kEigThreads) void k_ql(const DBlock* __restrict__ blks,
                                                     const double* __restrict__ tri, int ntot,
                                                     double* __restrict__ ev,
@@ -1060,13 +1065,16 @@ __global__ __launch_bounds__(kEigThreads) void k_ql(const DBlock* __restrict__ b
     const int blk = blockIdx.x;
     const DBlock B = blks[blk];
     const int d = B.d, tid = threadIdx.x;
-    if (!big_cluster(ev + B.eoff, d, tnorm[3 * blk])) return;
+    const double tn = tnorm[3 * blk];
+    if (!big_cluster(ev + B.eoff, d, tn)) return;
+    const int ex = __builtin_amdgcn_frexp_exp(tn);
+    const double small = 2.220446049250313e-16 * __builtin_amdgcn_ldexp(tn, -ex);
     double* __restrict__ Z = Zb + B.aoff;
     __shared__ double dg[MAXD], e[MAXD], rot[4 * MAXD];
     __shared__ int s_i0[2], s_cnt[2], s_done[2];
     for (int i = tid; i < d; i += NT) {
-        dg[i] = tri[B.eoff + i];
-        e[i] = tri[ntot + B.eoff + i];
+        dg[i] = __builtin_amdgcn_ldexp(tri[B.eoff + i], -ex);
+        e[i] = __builtin_amdgcn_ldexp(tri[ntot + B.eoff + i], -ex);
     }
     for (int64_t it = tid; it < (int64_t)d * d; it += NT)
         Z[it] = (it % d == it / d) ? 1.0 : 0.0;
@@ -1097,7 +1105,7 @@ __global__ __launch_bounds__(kEigThreads) void k_ql(const DBlock* __restrict__ b
             for (int base = l; m < 0; base += 64) {
                 const int i = base + lane;
                 const bool stop = i >= d - 1 ||
-                    !(fabs(e[i]) > 2.220446049250313e-16 * (fabs(dg[i]) + fabs(dg[i + 1])));
+                    !(fabs(e[i]) > fmax(2.220446049250313e-16 * (fabs(dg[i]) + fabs(dg[i + 1])), small));
                 const unsigned long long hit = __ballot(stop);
                 if (hit) m = base + __builtin_ctzll(hit);
             }
@@ -1211,7 +1219,7 @@ __global__ __launch_bounds__(kEigThreads) void k_ql(const DBlock* __restrict__ b
         __syncthreads();
     }
     handover_barrier();                                 // rows of Z to the column owners
-    for (int i = tid; i < d; i += NT) ev[B.eoff + i] = dg[i];
+    for (int i = tid; i < d; i += NT) ev[B.eoff + i] = __builtin_amdgcn_ldexp(dg[i], ex);
     if (tid == 0) atomicOr(&fail[blk], 2);              // Z column-major
 }
 

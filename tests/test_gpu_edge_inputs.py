@@ -321,3 +321,46 @@ def test_density_of_tiny_norm(env, exponent):
         w, U = out[b]
         _check_spectrum((w / s / s, U), (m / s) @ (m / s).conj().T)
     h.destroy()
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 3e-45])
+def test_density_of_equal_amplitudes(env, scale):
+    """Rank one with equal amplitudes: every column of the reduction after the first is rounding of
+    the one before it."""
+    torch, L = env
+    rng = np.random.default_rng(I.SEED_BASE + 34)
+    for dims in ((9, 14, 34, 21), (3, 8, 29, 45), (137, 12, 89, 20), (7, 170, 16, 60)):
+        h = L.dmrg_create(_problem((dims, dims[::-1])))
+        for phase in (1.0, np.exp(0.7j)):
+            M = [np.full((d, d), scale * phase * rng.uniform(0.1, 1.0)) for d in dims]
+            out, _, _ = _truncate(torch, L, h, [M, M], [0.5, 0.25], 50)
+            for b, m in enumerate(M):
+                rho = 0.75 * (m / scale) @ (m / scale).conj().T
+                w, U = out[b]
+                _check_spectrum((w / scale / scale, U), rho)
+        h.destroy()
+
+
+@pytest.mark.parametrize("decades", [3, 14, 30])
+def test_density_of_decaying_weights(env, decades):
+    """Weights that fall by that many decades over a sector, as those of a sweep's targets do, alone and
+    beside low-rank blocks; and norms from 2^-560 on."""
+    torch, L = env
+    rng = np.random.default_rng(I.SEED_BASE + 35)
+    cplx = lambda *s: rng.standard_normal(s) + 1j * rng.standard_normal(s)
+    for dims in ((12, 40, 85, 170), (59, 20, 150, 9)):
+        h = L.dmrg_create(_problem((dims, dims[::-1])))
+        for exponent in (0, -40, -560):
+            s = 2.0 ** (exponent // 2)
+            M = []
+            for b, d in enumerate(dims):
+                if (b + exponent) % 3 == 2:
+                    M.append(cplx(d, 2) @ cplx(2, d))
+                    continue
+                q, p = np.linalg.qr(cplx(d, d))[0], np.linalg.qr(cplx(d, d))[0]
+                M.append((q * 10.0 ** (-decades / 2 * np.arange(d) / (d - 1))) @ p)
+            out, _, _ = _truncate(torch, L, h, [[m * s for m in M]], [1.0], 50)
+            for b, m in enumerate(M):
+                w, U = out[b]
+                _check_spectrum((w / s / s, U), m @ m.conj().T)
+        h.destroy()
