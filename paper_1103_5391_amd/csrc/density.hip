@@ -974,7 +974,9 @@ __device__ __forceinline__ void inverse_iteration(const M& m, int d, int s, int 
         };
         if (k > 0) project();
         double f = mine ? (k > 0 ? 1.0 / sqrt(fmax(sq, 1e-300)) : sc) : 0.0;
-        for (int rep = 1; rep < kInvSolves; ++rep) {
+        // the third and later members once more: where their eigenvectors live in decoupled blocks the
+        // start vectors, which span two dimensions, leave them next to nothing after the first solve
+        for (int rep = 1; rep < kInvSolves + (k >= 2); ++rep) {
             if (mine) sq = solve(f);
             if (k > 0) project();
             if (mine) f = 1.0 / sqrt(fmax(sq, 1e-300));

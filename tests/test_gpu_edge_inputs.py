@@ -364,3 +364,23 @@ def test_density_of_decaying_weights(env, decades):
                 w, U = out[b]
                 _check_spectrum((w / s / s, U), m @ m.conj().T)
         h.destroy()
+
+
+@pytest.mark.parametrize("copies", [2, 3, 5, 8])
+def test_density_of_equal_blocks(env, copies):
+    """Density matrices made of equal blocks along the diagonal: every eigenvalue `copies` times, its
+    eigenvectors without common rows."""
+    torch, L = env
+    sizes = (3, 5, 8, 25)
+    dims = tuple(copies * s for s in sizes)
+    h = L.dmrg_create(_problem((dims, dims[::-1])))
+    for seed in range(4):
+        rng = np.random.default_rng([I.SEED_BASE, seed])
+        M = []
+        for s in sizes:
+            c = rng.standard_normal((s, s)) + 1j * rng.standard_normal((s, s))
+            M.append(np.kron(np.eye(copies), c))
+        out, _, _ = _truncate(torch, L, h, [M], [1.0], 50)
+        for b, m in enumerate(M):
+            _check_spectrum(out[b], m @ m.conj().T)
+    h.destroy()
