@@ -363,9 +363,9 @@ int dmrg_ground_state(dmrg_handle h, const double* x0, double* y, int32_t kdim,
  * the handle's sector, rho is block diagonal over the system sectors p,
  *   rho_p = sum_l weights[l] Psi_{l,p} Psi_{l,p}^H      (Psi_{l,p}: block p of vecs[l]),
  * and the keep eigenvectors with the largest eigenvalues over all sectors are kept (equal values
- * ranked by sector, then by position).  vecs: host array of nvec (1..16) device vectors;
- * weights: host array of nvec (the TST weights of dmrg_tst_targets for the ground state and the
- * four targets).  Outputs, per system sector in the order of dmrg_psi_layout (d = rows there):
+ * ranked by sector, then by position; NaN, of a target that holds NaN, last).  vecs: host array
+ * of nvec (1..16) device vectors; weights: host array of nvec (the TST weights of
+ * dmrg_tst_targets for the ground state and the four targets).  Outputs, per system sector in the order of dmrg_psi_layout (d = rows there):
  *   evals   device, sum of d doubles: eigenvalues of rho_p in descending order;
  *   evecs   device, sum of 2 d^2 doubles: per sector the d x d eigenvector matrix, column-major,
  *           real parts then imaginary parts, columns in the order of evals;
